@@ -158,7 +158,7 @@ def bench_prefill(args):
                       "algorithmic_MB": round(hbm_bytes / 1e6, 1),
                       "algorithmic_GBps": round(hbm_bytes / (ms * 1e-3) / 1e9, 1)},
            "roofline": {"bound": "mfma",
-                        "kernel": "bc::prefill_kernel<3, 128, %s>" % ("true" if use_ws else "false"),
+                        "kernel": "bc::prefill_kernel<128, %s, false>" % ("true" if use_ws else "false"),
                         "entry_point": "bc_prefill_attn_ws (conversion pass included)" if use_ws else "bc_prefill_attn",
                         "achieved": round(tflops, 2),
                         "peak": 2500.0, "unit": "TFLOP/s", "frac": round(tflops / 2500.0, 4),

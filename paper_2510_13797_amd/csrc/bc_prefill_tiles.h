@@ -1,0 +1,301 @@
+// What the kernels of the masked attention share: the compacted key list of a query tile, the
+// visibility of a tile's keys as bits, tiles of 32 rows staged in LDS in the order the matrix
+// operands are read, and the operand and result helpers of the 32x32x16 matrix instructions.
+#pragma once
+#include <type_traits>
+
+#include "bc_common.h"
+
+namespace bc {
+
+constexpr int kTileRows = 32;         // rows of a staged tile; query rows of a wave
+constexpr int kTileWaves = 4;         // waves of a workgroup
+constexpr int kTileStages = 3;        // tiles in LDS: one in use, two on their way
+
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+// ---------------------------------------------------------------------------
+// key list of a query tile
+// ---------------------------------------------------------------------------
+// The keys of a query tile as a list of entries in tiles of 32: the full tiles of run A and of run B
+// (nothing masked: tiles 0 .. dense-1), then the tail: what is left of A, what is left of B and the
+// band, back to back (each padded to whole tiles on its own: 7 % more matrix instructions on
+// trajectories of 8688 rows).
+struct KeyRuns {
+  WindowStride ws;
+  int P, band_start, FA, dense, tA, tAB, nT, NT;
+  __device__ __forceinline__ KeyRuns(const WindowStride& w, int prompt, int r0, int r1) : ws(w), P(prompt) {
+    int nA = 0, nB = 0;
+    band_start = 0;
+    if (ws.c > 0 && r0 >= P) {
+      const int m0 = (int)window_of(ws, (uint32_t)(r0 - P));
+      nA = P; nB = m0; band_start = P + m0 * ws.stride;
+    }
+    FA = nA / kTileRows;
+    dense = FA + nB / kTileRows;
+    tA = nA % kTileRows;
+    tAB = tA + nB % kTileRows;
+    nT = tAB + r1 - band_start + 1;
+    NT = dense + (nT + kTileRows - 1) / kTileRows;
+  }
+  // row of entry y of the tail
+  __device__ __forceinline__ int tail_row(int y) const {
+    if (y >= tAB) return band_start + y - tAB;
+    return y < tA ? FA * kTileRows + y : P + ((dense - FA) * kTileRows + y - tA) * ws.stride + ws.c;
+  }
+  // tiles that hold anything row `last` or an earlier one may see
+  __device__ __forceinline__ int tiles_up_to(int last) const {
+    return dense + (last - band_start + tAB) / kTileRows + 1;
+  }
+  // first row of the window row r lies in (prompt rows: of no use, every key they see is below P)
+  __device__ __forceinline__ int window_start(int r) const {
+    return ws.c > 0 && r >= P ? P + (int)window_of(ws, (uint32_t)(r - P)) * ws.stride : 0x7fffffff;
+  }
+  // Bit x: row r may see entry y0 + x of the tail (y0 a multiple of 32).  A key of the band is seen by
+  // every later row if it is a prompt row or a beacon (a property of the key alone: lane x works out
+  // key x, one vote gives the tile's word) and otherwise from its own window on, i.e. if it is not
+  // before r's window.  `own`: window_start(r).
+  __device__ __forceinline__ uint32_t visible(int y0, int r, int own, int lane) const {
+    const int y = y0 + (lane & 31), j = band_start + y - tAB;
+    bool everyone = y < tAB || j < P || ws.c <= 0;
+    if (!everyone) {
+      const uint32_t u = (uint32_t)(j - P);
+      everyone = (int)(u - window_of(ws, u) * (uint32_t)ws.stride) == ws.c;
+    }
+    const uint32_t dense_bits = (uint32_t)__builtin_amdgcn_ballot_w64(everyone);
+    const int base = band_start - tAB + y0;             // row of entry y0, were it of the band
+    const int from = own - base, upto = r - base;
+    const uint32_t mine = from >= 32 ? 0u : ~0u << max(from, 0);
+    const uint32_t past = upto < 0 ? 0u : upto >= 31 ? ~0u : (2u << upto) - 1u;
+    return (dense_bits | mine) & past;                  // (entries that do not exist lie behind r)
+  }
+};
+
+// What the loads of a tile need: byte offset of entry 0 from the (trajectory, KV head) base, bytes
+// from entry to entry, entries that exist (32 or more: all); or mixed >= 0: the tile holds the tail's
+// entries from that one on, rows of different runs, and off is 0 (they may lie before the band).
+struct TileLoad { int64_t off; int64_t step; int nvalid, mixed; };
+
+// The tiles of KeyRuns in order, as loads.  Kept as a cursor with constant increments inside a run:
+// working the offsets out anew from the tile number took some 70 scalar instructions and ten
+// branches per tile, which a wave issues one after the other between its matrix instructions.
+struct TileCursor {
+  int64_t row_bytes, off, step;
+  int left, seg, y;
+  __device__ __forceinline__ TileCursor(const KeyRuns& r, int64_t rb) : row_bytes(rb), seg(-1) { left = 1; next_segment(r); }
+  __device__ __forceinline__ void next_segment(const KeyRuns& r) {
+    do {
+      ++seg;
+      y = 0;
+      if (seg == 0) { left = r.FA; off = 0; step = row_bytes; }
+      else if (seg == 1) { left = r.dense - r.FA; off = (int64_t)(r.P + r.ws.c) * row_bytes; step = r.ws.stride * row_bytes; }
+      else { left = 0x7fffffff; off = ((int64_t)r.band_start - r.tAB) * row_bytes; step = row_bytes; }
+    } while (left == 0);
+  }
+  __device__ __forceinline__ TileLoad next(const KeyRuns& r) {
+    const bool mixed = seg == 2 && y < r.tAB;
+    const TileLoad t{mixed ? 0 : off, step, seg == 2 ? r.nT - y : kTileRows, mixed ? y : -1};
+    off += step * kTileRows;
+    y += kTileRows;
+    if (__builtin_expect(--left == 0, 0)) next_segment(r);
+    return t;
+  }
+};
+
+// Element e of a lane's 16 results of a 32x32 product is row 8*(e/4) + 4*(lane/32) + e%4 of the tile;
+// `see` is the visibility word shifted right by 4*(lane/32).
+__device__ __forceinline__ bool visible_bit(uint32_t see, int e) { return (see >> (8 * (e >> 2) + (e & 3))) & 1u; }
+__device__ __forceinline__ float keep_if_visible(float x, uint32_t see, int e) {
+  const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)see, 8 * (e >> 2) + (e & 3), 1);
+  return __uint_as_float(__float_as_uint(x) & m);
+}
+
+// ---------------------------------------------------------------------------
+// tiles in LDS
+// ---------------------------------------------------------------------------
+// A tile of 32 rows of D bf16 is staged as blocks of 8 rows x 8 units (16 bytes each): 1 KB, one
+// LDS-DMA instruction that reads 128 consecutive bytes of each of 8 rows.  Block (rg, uh) holds rows
+// 8*rg.. and units 8*uh..; it lies at (4*uh + rg) KB.  Inside a block the units stand in one of two
+// orders, chosen so that the addresses of all operands of a tile are one register per lane plus
+// constants, and that no read has a bank conflict (a 128-bit read is served in groups of 16 lanes -
+// {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} of each half wave - that must cover the 64 banks; a
+// transposing 64-bit read in half waves).
+//
+// Row order (operand "rows of the tile": lane l takes row l%32, head-dim elements 16*i + 8*(l/32)..):
+// unit u of row y at 16-byte slot (u%8/2)*16 + ((y%8)*2 + u%2 ^ rg/2).
+// Measured: 245 bytes per clock and CU, what linear addresses reach; the XOR swizzle of 256-byte rows
+// used before (rows {a + 8b} of one unit apart) ran at 126: its lanes 0-3, 12-15, 20-27 met in pairs.
+//
+// Column order (operand "tile transposed": lane l takes head-dim column 32*j + l%32 and the tile
+// rows its results e = 8*s.. of a product over the tile stand for): unit u of row y at slot
+// (u%8/4)*32 + (y%8)*4 + u%4.
+// What a lane of wave rg moves: the wave brings the blocks of row group rg, one instruction for each
+// 128 bytes of the row.
+struct TileLane { int row; uint32_t in_row; };       // row of the tile, byte offset inside the 128
+
+__device__ __forceinline__ TileLane rows_tile_lane(int lane, int rg) {
+  return TileLane{8 * rg + ((lane & 15) >> 1), (uint32_t)(2 * (lane >> 4) + ((lane & 1) ^ (rg >> 1))) << 4};
+}
+__device__ __forceinline__ TileLane cols_tile_lane(int lane, int rg) {
+  return TileLane{8 * rg + ((lane & 31) >> 2), (uint32_t)(4 * (lane >> 5) + (lane & 3)) << 4};
+}
+__device__ __forceinline__ int rows_read_offset(int lane) {
+  const int y = lane & 31, rg = y >> 3;
+  return rg * 1024 + ((((y & 7) * 2 + (lane >> 5)) ^ (rg >> 1)) << 4);
+}
+template <int D> constexpr int rows_read_imm(int i) { return (i >> 2) * 4096 + (i & 3) * 256; }
+__device__ __forceinline__ int cols_read_offset(int lane) {
+  const int rl = lane & 15;
+  return (((4 * (lane >> 5) + (rl >> 2)) * 4 + 2 * ((lane >> 4) & 1) + ((rl & 3) >> 1)) << 4) + ((rl & 1) << 3);
+}
+// base: tile + cols_read_offset(lane)
+template <int D>
+__device__ __forceinline__ bf16x8_t cols_operand(const char* base, int j, int s) {
+  const char* a = base + (j >> 1) * 4096 + (j & 1) * 512 + 2 * s * 1024;
+  const s16x4_t a0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)a);
+  const s16x4_t a1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(a + 1024));
+  return __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The lane's byte offset from the tile's base; entries that do not exist repeat the first one (what is
+// computed from them is masked).  WIDE: a trajectory's rows may span 4 GB or more.
+template <bool WIDE>
+__device__ __forceinline__ std::conditional_t<WIDE, int64_t, uint32_t> tile_lane_offset(const KeyRuns& runs, const TileLoad& t,
+                                                                                        const TileLane& ln, int64_t row_bytes) {
+  using OFF = std::conditional_t<WIDE, int64_t, uint32_t>;
+  const int e = ln.row < t.nvalid ? ln.row : 0;
+  if (t.mixed >= 0) return (OFF)runs.tail_row(t.mixed + e) * (OFF)row_bytes + ln.in_row;      // (t.off is 0)
+  return (OFF)e * (OFF)t.step + ln.in_row;
+}
+// HBM -> LDS: one block, 1 KB
+template <bool WIDE, typename OFF>
+__device__ __forceinline__ void issue_block(const char* tile_base, OFF lane_offset, uint32_t lds_addr) {
+  if constexpr (!WIDE) {       // scalar base, 32-bit offset per lane
+    lds_dma16_s<false>(lane_offset, (uint64_t)tile_base, lds_addr);
+  } else {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 : : "s"(lds_addr), "v"(tile_base + lane_offset) : "memory");
+  }
+}
+
+// The point by which operands loaded before a tile loop have landed: the compiler waits here and not
+// in front of their first use inside the loop, where the wait would cover the tiles' loads too.
+template <int N>
+__device__ __forceinline__ void landed_operands(bf16x8_t (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// Values that are to be worked out by here.
+__device__ __forceinline__ void pin8(float* x) {
+  asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
+}
+
+// Workgroup barrier for LDS traffic whose loads the compiler does not count: no implied wait.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Order of a stretch of straight-line code (a scheduling region of its own): AHEAD LDS reads first,
+// then NM matrix instructions with READS LDS reads and VALU vector instructions behind each.
+template <int NM, int AHEAD, int READS, int VALU, int ID>
+__device__ __forceinline__ void interleave() {
+  constexpr int kMfma = 0x8, kValu = 0x2, kDsRead = 0x100;
+  if constexpr (AHEAD > 0) __builtin_amdgcn_sched_group_barrier(kDsRead, AHEAD, ID);
+#pragma unroll
+  for (int n = 0; n < NM; ++n) {
+    __builtin_amdgcn_sched_group_barrier(kMfma, 1, ID);
+    __builtin_amdgcn_sched_group_barrier(kDsRead, READS, ID);
+    __builtin_amdgcn_sched_group_barrier(kValu, VALU, ID);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// ---------------------------------------------------------------------------
+// values
+// ---------------------------------------------------------------------------
+// all-reduce over the two halves of a wave (lane l with l ^ 32)
+__device__ __forceinline__ float halves_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float halves_sum(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
+// 8 floats (consecutive k indices) -> hi and lo bf16x8 operands with hi + lo ~ x to 16 bits
+__device__ __forceinline__ void split8(const float* x, bf16x8_t& hi, bf16x8_t& lo, const HalfSelectors& sel) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const uint32_t hp = pack2_bf16(x[e], x[e + 1]);
+    h[e >> 1] = hp;
+    l[e >> 1] = pack2_bf16(minus_half(x[e], hp, sel.low), minus_half(x[e + 1], hp, sel.high));
+  }
+  hi = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
+  lo = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
+}
+
+// Half the columns (pass 0 or 1) of a wave's 32 x D results (accumulator layout: lane l holds
+// columns 32*j + 8*i + 4*(l/32) .. +3 of row l%32) -> LDS -> bursts of D/2 floats per row.
+// row(t): destination of row t or nullptr.  Written once, not read again by the launch: streaming.
+template <int D, typename F>
+__device__ __forceinline__ void store_rows(float* my, const f32x16_t (&acc)[D / 32], float mul, int pass, int lane,
+                                           F row) {
+  constexpr int OW = D / 2, UW = OW / 4, RPP = 64 / UW;      // columns and units of a pass, rows per instruction
+  const int y = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int jb = 0; jb < D / 64; ++jb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x16_t& a = acc[(D / 64) * pass + jb];
+      *reinterpret_cast<f32x4_t*>(my + y * OW + (((8 * jb + 2 * i + half) ^ (y & (UW - 1))) << 2)) =
+          f32x4_t{a[4 * i] * mul, a[4 * i + 1] * mul, a[4 * i + 2] * mul, a[4 * i + 3] * mul};
+    }
+#pragma unroll
+  for (int n = 0; n < 32 / RPP; ++n) {
+    const int t = RPP * n + lane / UW, unit = lane & (UW - 1);
+    const f32x4_t val = *reinterpret_cast<const f32x4_t*>(my + t * OW + ((unit ^ (t & (UW - 1))) << 2));
+    float* dst = row(t);
+    if (dst) __builtin_nontemporal_store(val, reinterpret_cast<f32x4_t*>(dst + OW * pass + unit * 4));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// how the heads of a group are dealt to the waves of a workgroup (host)
+// ---------------------------------------------------------------------------
+struct HeadTiling {
+  int32_t heads;        // query heads per workgroup: 4, 2 or 1
+  int32_t splits;       // workgroups that share a group's heads
+  int32_t row_blocks;   // blocks of 32 query rows per workgroup: kTileWaves / heads
+};
+// Four waves, one per SIMD: three workgroups then fit a CU whatever SIMD each starts on (six waves
+// per workgroup, all heads of a group of six: 1.22 against 0.77 ms, the second workgroup found no
+// SIMD with room for two more waves).  As many heads as divide the group into fours or twos without a
+// remainder, since more rows per workgroup mean a longer masked band: groups of six with one head and
+// 128 rows took 0.75, with two heads and 64 rows 0.70 ms; groups of four with two heads 0.523, with
+// four heads and 32 rows 0.511 ms.
+inline HeadTiling head_tiling(int g) {
+  const int heads = g % 4 == 0 || g == 7 ? 4 : g % 2 == 0 ? 2 : 1;
+  return {heads, (g + heads - 1) / heads, kTileWaves / heads};
+}
+// Workgroups go to the 8 XCDs in turn.  With the pairs of a row tile (and its head splits) padded to a
+// multiple of 8, all tiles of a pair - which read the same prompt and beacon rows - share an L2; for
+// few pairs that would leave XCDs idle (three trajectories with two KV heads: six of eight XCDs at
+// work), and the tiles are dealt out evenly instead.
+inline int pair_stride(int npairs) { return npairs % 8 == 0 || npairs > 64 ? (npairs + 7) & ~7 : npairs; }
+
+// Whether byte offsets inside a trajectory's K or V rows may need more than 32 bits.
+inline bool rows_span_4gb(int32_t max_rows, const bc_shape* sh) {
+  return (uint64_t)max_rows * (uint64_t)sh->Hkv * (uint64_t)(sh->d * 2) >= 0x100000000ull;
+}
+
+}  // namespace bc

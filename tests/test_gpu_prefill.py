@@ -384,3 +384,43 @@ def test_gradients_from_the_half_form_forward(dev):
     assert np.isfinite(dq).all() and np.isfinite(dk).all() and np.isfinite(dv).all()
     for b in range(pw.B):
         _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
+
+
+@pytest.mark.parametrize("P", [31, 32, 33, 64, 65])
+@pytest.mark.parametrize("R", [62, 63, 64, 65, 129])
+def test_prefill_key_list_at_the_edges_of_its_tiles(dev, P, R, form):
+    # a query tile's keys are full tiles of prompt rows and of beacons, then a tail of what is left of
+    # both with the band behind it: prompt lengths and beacon counts (c = 1: one beacon per token) just
+    # below, at and above whole tiles, trajectories that end inside the first or second 32-row block
+    pw = W.PrefillWorkload("pf_edges", 69, 2, 2, 1, 128, "bf16", np.array([P, P], np.int32),
+                           np.array([R, R + 32], np.int32), np.array([1, 2], np.int32))
+    qkv, off, out, lse = _run(pw, dev)
+    assert np.isfinite(out).all()
+    for b in range(pw.B):
+        _check_rows(pw, qkv, off, out, lse, b, list(range(int(pw.S[b]))))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_addresses_beyond_32_bits(dev, d):
+    # max_rows is an upper bound the caller states; from 4 GB of K rows on the kernel with 64-bit
+    # offsets is launched, which must compute the same, bit for bit, as the one with 32-bit offsets
+    import ctypes as C
+    import torch
+    from paper_2510_13797_amd import bc
+    pw = W.PrefillWorkload("pf_wide", 70, 2, 16, 8, d, "bf16", np.array([37, 70], np.int32),
+                           np.array([300, 90], np.int32), np.array([4, 0], np.int32))
+    qkv = [pw.qkv(b) for b in range(pw.B)]
+    off = np.zeros(pw.B + 1, np.int64)
+    off[1:] = np.cumsum(pw.S)
+    q, k, v = (bc.to_device(np.concatenate([x[i] for x in qkv]), "bf16", dev) for i in range(3))
+    shape = bc.bc_shape(pw.B, pw.Hq, pw.Hkv, d, bc.BC_BF16, pw.scale)
+    tab = [torch.from_numpy(x).to(dev) for x in (off, pw.P, pw.c)]
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    most = (1 << 32) // (pw.Hkv * d * 2) + 7
+    got = []
+    for max_rows in (int(pw.S.max()), most):
+        out = torch.full((int(off[-1]), pw.Hq, d), float("nan"), device=dev)
+        assert bc.bc_prefill_attn(shape, ptr(q), ptr(k), ptr(v), *map(ptr, tab), max_rows, ptr(out), None, None) == 0
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy())
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
