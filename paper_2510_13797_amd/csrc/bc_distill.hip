@@ -3,14 +3,19 @@
 // respect to the student's logits.  Both are one streaming pass over the [T, V] logits: one
 // workgroup per token, 16-byte loads, a running (max, sum) per thread that is rescaled once per
 // batch of loads, and a workgroup reduction at the end.  HBM-bound by construction.
+//
+// A row may start at any element (V odd in bf16: every second row is 2 bytes off): the elements in
+// front of its first 16-byte boundary and behind its last one are taken one by one by the first
+// threads, everything between by 16-byte units (509 rows of 50,257 bf16, loss and gradient pass: 63 -> 13 and
+// 73 -> 23 us against one element per load).
 #include "bc_common.h"
 
 namespace bc {
 namespace {
 
-constexpr int kDistillThreads = 256;
-constexpr int kDistillWaves = kDistillThreads / 64;
-constexpr int kDistillBatch = 8;       // 16-byte loads in flight per thread
+constexpr int kDistillThreads = 256;       // threads of a workgroup: many tokens,
+constexpr int kDistillThreadsFew = 1024;   // and few (kFewTokens)
+constexpr int kMaxTeacher = 1024;          // largest k
 constexpr float kLn2 = 0.6931471805599453f;
 
 struct DistillParams {
@@ -35,7 +40,8 @@ __device__ __forceinline__ float wave_sum(float x) {
   for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
   return x;
 }
-// every thread gets the result; red: kDistillWaves floats of LDS, reusable after the call
+// every thread gets the result; red: NW floats of LDS, reusable after the call
+template <int NW>
 __device__ __forceinline__ float block_max(float x, float* red) {
   x = wave_max(x);
   __syncthreads();
@@ -43,9 +49,10 @@ __device__ __forceinline__ float block_max(float x, float* red) {
   __syncthreads();
   float r = red[0];
 #pragma unroll
-  for (int i = 1; i < kDistillWaves; ++i) r = fmaxf(r, red[i]);
+  for (int i = 1; i < NW; ++i) r = fmaxf(r, red[i]);
   return r;
 }
+template <int NW>
 __device__ __forceinline__ float block_sum(float x, float* red) {
   x = wave_sum(x);
   __syncthreads();
@@ -53,13 +60,16 @@ __device__ __forceinline__ float block_sum(float x, float* red) {
   __syncthreads();
   float r = red[0];
 #pragma unroll
-  for (int i = 1; i < kDistillWaves; ++i) r += red[i];   // fixed order: reproducible
+  for (int i = 1; i < NW; ++i) r += red[i];   // fixed order: reproducible
   return r;
 }
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-// 16 bytes read once: no reuse, so keep them out of the way of the caches
-__device__ __forceinline__ uint4 load16_stream(const uint4* p) {
+// 16 bytes of the logits.  KEEP: leave them in the Infinity Cache, where the gradient pass finds what the loss
+// pass read; otherwise out of the way of the caches (see logits_kept()).
+template <bool KEEP>
+__device__ __forceinline__ uint4 load16_logits(const uint4* p) {
+  if constexpr (KEEP) return *p;
   const u32x4_t r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
   return make_uint4(r.x, r.y, r.z, r.w);
 }
@@ -91,74 +101,94 @@ template <> __device__ __forceinline__ void store_elem<bf16_t>(void* p, int64_t 
   static_cast<uint16_t*>(p)[i] = static_cast<uint16_t>(bf16_rne(x));
 }
 
+// A row of V elements as what lies in front of its first 16-byte boundary, whole 16-byte units, and
+// the rest.
+struct RowSpan { int32_t head, units, tail; };
+template <typename T>
+__device__ __forceinline__ RowSpan row_span(const void* row, int32_t V) {
+  RowSpan r;
+  const int32_t off = static_cast<int32_t>(reinterpret_cast<uintptr_t>(row) & 15u);
+  r.head = min(((16 - off) & 15) / Elem<T>::size, V);
+  r.units = (V - r.head) / Elem<T>::per16;
+  r.tail = V - r.head - r.units * Elem<T>::per16;
+  return r;
+}
+
+// f(b, valid) for the B units base + b * NT + tid of a batch: no tests in a full batch, and in the
+// last one whole steps that do not exist are left out.
+template <int NT, int B, typename F>
+__device__ __forceinline__ void for_batch(int base, int units, const F& f) {
+  if (base + B * NT <= units) {
+#pragma unroll
+    for (int b = 0; b < B; ++b) f(b, true);
+  } else {
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+      if (base + b * NT < units) f(b, base + b * NT + static_cast<int>(threadIdx.x) < units);
+  }
+}
+
 // Running log-sum-exp of one row in the base-2 domain: returns (max, sum of 2^(x*log2e - max))
-// reduced over the workgroup.  VEC: rows are 16-byte aligned and V is a whole number of units.
-template <typename T, bool VEC>
+// reduced over the workgroup.
+template <typename T, int NT, int B, bool KEEP>
 __device__ __forceinline__ void row_lse(const void* zrow, int32_t V, float* red, float& m_out,
                                         float& s_out) {
   constexpr int EPU = Elem<T>::per16;
+  const RowSpan span = row_span<T>(zrow, V);
+  const uint4* row = reinterpret_cast<const uint4*>(static_cast<const char*>(zrow) + span.head * Elem<T>::size);
   float m = kNegBig, s = 0.f;
-  if (VEC) {
-    const uint4* row = static_cast<const uint4*>(zrow);
-    const int units = V / EPU;
-    for (int u0 = threadIdx.x; u0 < units; u0 += kDistillThreads * kDistillBatch) {
-      uint4 r[kDistillBatch] = {};
+  if (static_cast<int>(threadIdx.x) < span.head + span.tail) {     // (at most 14 elements)
+    const int i = threadIdx.x;
+    m = load_elem<T>(zrow, i < span.head ? i : V - span.tail + (i - span.head)) * kLog2e;
+    s = 1.f;
+  }
+  for (int base = 0; base < span.units; base += NT * B) {
+    uint4 r[B];
+    for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+      if (valid) r[b] = load16_logits<KEEP>(row + base + b * NT + threadIdx.x);
+    });
+    float bm = kNegBig;
+    for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+      float x[EPU];
+      unpack16(r[b], x, T{});
+      float um = kNegBig;
 #pragma unroll
-      for (int b = 0; b < kDistillBatch; ++b) {
-        const int u = u0 + b * kDistillThreads;
-        if (u < units) r[b] = load16_stream(row + u);
-      }
-      float x[kDistillBatch][EPU];
-      float bm = kNegBig;
-#pragma unroll
-      for (int b = 0; b < kDistillBatch; ++b) {
-        const int u = u0 + b * kDistillThreads;
-        unpack16(r[b], x[b], T{});
-#pragma unroll
-        for (int e = 0; e < EPU; ++e) {
-          x[b][e] = (u < units) ? x[b][e] * kLog2e : kNegBig;
-          bm = fmaxf(bm, x[b][e]);
-        }
-      }
-      const float mn = fmaxf(m, bm);
-      s *= fast_exp2(m - mn);
-      m = mn;
+      for (int e = 0; e < EPU; ++e) um = fmaxf(um, x[e]);
+      if (valid) bm = fmaxf(bm, um);
+    });
+    const float mn = fmaxf(m, bm * kLog2e);
+    s *= fast_exp2(m - mn);
+    m = mn;
+    for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+      float x[EPU];
+      unpack16(r[b], x, T{});
       float acc = 0.f;
 #pragma unroll
-      for (int b = 0; b < kDistillBatch; ++b)
-#pragma unroll
-        for (int e = 0; e < EPU; ++e) acc += fast_exp2(x[b][e] - m);
-      s += acc;
-    }
-  } else {
-    for (int v = threadIdx.x; v < V; v += kDistillThreads) {
-      const float x = load_elem<T>(zrow, v) * kLog2e;
-      const float mn = fmaxf(m, x);
-      s = s * fast_exp2(m - mn) + fast_exp2(x - mn);
-      m = mn;
-    }
+      for (int e = 0; e < EPU; ++e) acc += fast_exp2(fmaf(x[e], kLog2e, -m));
+      if (valid) s += acc;
+    });
   }
-  const float M = block_max(m, red);
-  s_out = block_sum(s * fast_exp2(m - M), red);
+  const float M = block_max<NT / 64>(m, red);
+  s_out = block_sum<NT / 64>(s * fast_exp2(m - M), red);
   m_out = M;
 }
 
 // Teacher side of one token: softmax over its k stored logits.  Each thread keeps the entries
-// i = tid, tid + 256, ... (at most kMaxPerThread of them).
-constexpr int kMaxPerThread = 4;   // k <= 1024
+// i = tid, tid + NT, ... (at most kMaxTeacher / NT of them).
 
-template <typename T, bool VEC>
-__global__ void __launch_bounds__(kDistillThreads)
+template <typename T, int NT, int B, bool KEEP>
+__global__ void __launch_bounds__(NT)
 topk_kl_fwd_kernel(DistillParams p) {
-  __shared__ float red[kDistillWaves];
+  constexpr int kPerThread = kMaxTeacher / NT;
+  __shared__ float red[NT / 64];
   const int64_t t = blockIdx.x;
   const void* zrow = static_cast<const char*>(p.z) + t * p.V * Elem<T>::size;
   // the k gathered student logits and the teacher row first: their latency hides behind the stream
-  float zs[kMaxPerThread], tl[kMaxPerThread];
+  float zs[kPerThread], tl[kPerThread];
   bool bad = false;
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) {
-    const int i = threadIdx.x + j * kDistillThreads;
+  for (int j = 0; j < kPerThread; ++j) {
+    const int i = threadIdx.x + j * NT;
     zs[j] = 0.f; tl[j] = kNegBig;
     if (i < p.k) {
       int32_t id = p.tidx[t * p.k + i];
@@ -168,28 +198,28 @@ topk_kl_fwd_kernel(DistillParams p) {
     }
   }
   float m2, s2;
-  row_lse<T, VEC>(zrow, p.V, red, m2, s2);
+  row_lse<T, NT, B, KEEP>(zrow, p.V, red, m2, s2);
   const float lse_s = (m2 + __log2f(s2)) * kLn2;
   float tm = kNegBig;
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) tm = fmaxf(tm, tl[j]);
-  tm = block_max(tm, red);
+  for (int j = 0; j < kPerThread; ++j) tm = fmaxf(tm, tl[j]);
+  tm = block_max<NT / 64>(tm, red);
   float ts = 0.f;
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) ts += fast_exp2((tl[j] - tm) * kLog2e);
-  ts = block_sum(ts, red);
+  for (int j = 0; j < kPerThread; ++j) ts += fast_exp2((tl[j] - tm) * kLog2e);
+  ts = block_sum<NT / 64>(ts, red);
   const float lse_t = tm + __log2f(ts) * kLn2;
   float kl = 0.f;
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) {
-    const int i = threadIdx.x + j * kDistillThreads;
+  for (int j = 0; j < kPerThread; ++j) {
+    const int i = threadIdx.x + j * NT;
     if (i < p.k) {
       const float lpt = tl[j] - lse_t;
       kl += fast_exp2(lpt * kLog2e) * (lpt - (zs[j] - lse_s));
     }
   }
   if (bad) kl = __builtin_nanf("");
-  kl = block_sum(kl, red);
+  kl = block_sum<NT / 64>(kl, red);
   if (threadIdx.x == 0) {
     p.loss[t] = kl;
     if (p.lse) p.lse[t] = lse_s;
@@ -210,10 +240,11 @@ __global__ void __launch_bounds__(1024) mean_kernel(const float* x, int64_t T, f
   if (threadIdx.x == 0) out[0] = static_cast<float>(part[0] / static_cast<double>(T));
 }
 
-template <typename T, bool VEC>
-__global__ void __launch_bounds__(kDistillThreads)
+template <typename T, bool VEC, int NT, int B, bool KEEP>
+__global__ void __launch_bounds__(NT)
 topk_kl_bwd_kernel(DistillParams p) {
-  __shared__ float red[kDistillWaves];
+  constexpr int kPerThread = kMaxTeacher / NT;
+  __shared__ float red[NT / 64];
   constexpr int EPU = Elem<T>::per16;
   const int64_t t = blockIdx.x;
   const void* zrow = static_cast<const char*>(p.z) + t * p.V * Elem<T>::size;
@@ -221,12 +252,12 @@ topk_kl_bwd_kernel(DistillParams p) {
   const float nl = -p.lse[t] * kLog2e;
   const float gs = p.grad_scale;
   // teacher probabilities of this token
-  float tl[kMaxPerThread];
-  int32_t id[kMaxPerThread];
+  float tl[kPerThread];
+  int32_t id[kPerThread];
   float tm = kNegBig;
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) {
-    const int i = threadIdx.x + j * kDistillThreads;
+  for (int j = 0; j < kPerThread; ++j) {
+    const int i = threadIdx.x + j * NT;
     tl[j] = kNegBig; id[j] = -1;
     if (i < p.k) {
       tl[j] = p.tl[t * p.k + i];
@@ -235,28 +266,28 @@ topk_kl_bwd_kernel(DistillParams p) {
     }
     tm = fmaxf(tm, tl[j]);
   }
-  tm = block_max(tm, red);
+  tm = block_max<NT / 64>(tm, red);
   float ts = 0.f;
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) ts += fast_exp2((tl[j] - tm) * kLog2e);
-  ts = block_sum(ts, red);
+  for (int j = 0; j < kPerThread; ++j) ts += fast_exp2((tl[j] - tm) * kLog2e);
+  ts = block_sum<NT / 64>(ts, red);
   const float inv_ts = 1.f / ts;
 
   if (VEC) {
-    const uint4* row = static_cast<const uint4*>(zrow);
-    uint4* out = static_cast<uint4*>(drow);
-    const int units = p.V / EPU;
-    for (int u0 = threadIdx.x; u0 < units; u0 += kDistillThreads * kDistillBatch) {
-      uint4 r[kDistillBatch] = {};
-#pragma unroll
-      for (int b = 0; b < kDistillBatch; ++b) {
-        const int u = u0 + b * kDistillThreads;
-        if (u < units) r[b] = load16_stream(row + u);
-      }
-#pragma unroll
-      for (int b = 0; b < kDistillBatch; ++b) {
-        const int u = u0 + b * kDistillThreads;
-        if (u >= units) continue;
+    const RowSpan span = row_span<T>(zrow, p.V);
+    const int off = span.head * Elem<T>::size;
+    const uint4* row = reinterpret_cast<const uint4*>(static_cast<const char*>(zrow) + off);
+    uint4* out = reinterpret_cast<uint4*>(static_cast<char*>(drow) + off);
+    if (static_cast<int>(threadIdx.x) < span.head + span.tail) {
+      const int i = threadIdx.x, v = i < span.head ? i : p.V - span.tail + (i - span.head);
+      store_elem<T>(drow, v, gs * fast_exp2(fmaf(load_elem<T>(zrow, v), kLog2e, nl)));
+    }
+    for (int base = 0; base < span.units; base += NT * B) {
+      uint4 r[B];
+      for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+        if (valid) r[b] = load16_logits<KEEP>(row + base + b * NT + threadIdx.x);
+      });
+      for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
         float x[EPU];
         unpack16(r[b], x, T{});
 #pragma unroll
@@ -269,11 +300,11 @@ topk_kl_bwd_kernel(DistillParams p) {
           w = make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]),
                          pack_bf16(x[6], x[7]));
         }
-        store16_stream(out + u, w);
-      }
+        if (valid) store16_stream(out + base + b * NT + threadIdx.x, w);
+      });
     }
   } else {
-    for (int v = threadIdx.x; v < p.V; v += kDistillThreads)
+    for (int v = threadIdx.x; v < p.V; v += NT)
       store_elem<T>(drow, v, gs * fast_exp2(fmaf(load_elem<T>(zrow, v), kLog2e, nl)));
   }
   // the k teacher ids: overwrite with softmax minus the teacher probability, computed afresh from
@@ -281,7 +312,7 @@ topk_kl_bwd_kernel(DistillParams p) {
   // same workgroup.
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kMaxPerThread; ++j) {
+  for (int j = 0; j < kPerThread; ++j) {
     if (id[j] >= 0) {
       const float ps = fast_exp2(fmaf(load_elem<T>(zrow, id[j]), kLog2e, nl));
       const float pt = fast_exp2((tl[j] - tm) * kLog2e) * inv_ts;
@@ -295,14 +326,51 @@ int32_t check_distill(int64_t T, int32_t V, int32_t k, const void* z, int32_t dt
   if (!z || !tl || !tidx) return BC_ERR_ARG;
   if (dtype != BC_F32 && dtype != BC_BF16) return BC_ERR_SHAPE;
   if (T < 0 || T > 0x7fffffffLL || V < 1 || k < 1 || k > V ||
-      k > kMaxPerThread * kDistillThreads)
+      k > kMaxTeacher)
     return BC_ERR_SHAPE;
   return BC_OK;
 }
 
-bool rows_vectorisable(const void* a, const void* b, int32_t V, int32_t dtype) {
-  return aligned16(a) && (!b || aligned16(b)) &&
-         (static_cast<int64_t>(V) * elem_size(dtype)) % 16 == 0;
+// The gradient's 16-byte units need rows of both tensors at the same place inside 16 bytes.
+bool rows_aligned_alike(const void* a, const void* b) {
+  return ((reinterpret_cast<uintptr_t>(a) ^ reinterpret_cast<uintptr_t>(b)) & 15u) == 0;
+}
+
+// A token has a workgroup to itself; few tokens leave waves unused, and get four times the threads (loss and
+// gradient pass of 64 tokens x 151,936 logits in bf16: 19.8 -> 14.4 and 20.9 -> 17.8 us, of one token 14.5 ->
+// 11.8 and 13.7 -> 10.2; 512 tokens: 28.6 -> 27.7 and 62.7 -> 60.6; with 2048 tokens there is nothing to gain).
+constexpr int64_t kFewTokens = 1024;
+
+// Logits that fit the 256 MB Infinity Cache are loaded with the default policy: the gradient pass, which
+// stores past the caches, then reads most of them from there (both passes, 600 x 151,936 in bf16 = 182 MB:
+// 110 -> 96 us; 243 MB: 145 -> 126; 304 MB: 164 -> 163).  Beyond that they are streamed (395 MB: 233
+// against 252 us, 622 MB: 343 against 376).
+bool logits_kept(const DistillParams& p, int32_t dtype) {
+  return p.T * p.V * elem_size(dtype) <= (int64_t(256) << 20);
+}
+
+template <typename T, bool KEEP>
+void launch_fwd(const DistillParams& p, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(p.T));
+  if (p.T <= kFewTokens) topk_kl_fwd_kernel<T, kDistillThreadsFew, 4, KEEP><<<grid, kDistillThreadsFew, 0, s>>>(p);
+  else topk_kl_fwd_kernel<T, kDistillThreads, 8, KEEP><<<grid, kDistillThreads, 0, s>>>(p);
+}
+template <typename T, bool VEC, bool KEEP>
+void launch_bwd(const DistillParams& p, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(p.T));
+  if (p.T <= kFewTokens) topk_kl_bwd_kernel<T, VEC, kDistillThreadsFew, 4, KEEP><<<grid, kDistillThreadsFew, 0, s>>>(p);
+  else topk_kl_bwd_kernel<T, VEC, kDistillThreads, 8, KEEP><<<grid, kDistillThreads, 0, s>>>(p);
+}
+template <typename T>
+void launch_bwd(const DistillParams& p, int32_t dtype, hipStream_t s) {
+  if (!rows_aligned_alike(p.z, p.dz)) launch_bwd<T, false, true>(p, s);
+  else if (logits_kept(p, dtype)) launch_bwd<T, true, true>(p, s);
+  else launch_bwd<T, true, false>(p, s);
+}
+template <typename T>
+void launch_fwd(const DistillParams& p, int32_t dtype, hipStream_t s) {
+  if (logits_kept(p, dtype)) launch_fwd<T, true>(p, s);
+  else launch_fwd<T, false>(p, s);
 }
 
 }  // namespace
@@ -320,16 +388,9 @@ extern "C" int32_t bc_topk_kl_loss(int64_t T, int32_t V, int32_t k, const void* 
   DistillParams p{};
   p.z = student_logits; p.tl = teacher_logits; p.tidx = teacher_idx;
   p.loss = loss_per_token; p.lse = lse; p.T = T; p.V = V; p.k = k;
-  const bool vec = rows_vectorisable(student_logits, nullptr, V, logits_dtype);
-  const dim3 grid(static_cast<unsigned>(T)), block(kDistillThreads);
   hipStream_t s = as_stream(stream);
-  if (logits_dtype == BC_BF16) {
-    if (vec) hipLaunchKernelGGL((topk_kl_fwd_kernel<bf16_t, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((topk_kl_fwd_kernel<bf16_t, false>), grid, block, 0, s, p);
-  } else {
-    if (vec) hipLaunchKernelGGL((topk_kl_fwd_kernel<float, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((topk_kl_fwd_kernel<float, false>), grid, block, 0, s, p);
-  }
+  if (logits_dtype == BC_BF16) launch_fwd<bf16_t>(p, logits_dtype, s);
+  else launch_fwd<float>(p, logits_dtype, s);
   if (loss_mean) hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(1024), 0, s, loss_per_token, T, loss_mean);
   return launch_status();
 }
@@ -348,15 +409,8 @@ extern "C" int32_t bc_topk_kl_loss_bwd(int64_t T, int32_t V, int32_t k,
   p.z = student_logits; p.tl = teacher_logits; p.tidx = teacher_idx;
   p.lse = const_cast<float*>(lse); p.dz = dlogits; p.T = T; p.V = V; p.k = k;
   p.grad_scale = grad_scale;
-  const bool vec = rows_vectorisable(student_logits, dlogits, V, logits_dtype);
-  const dim3 grid(static_cast<unsigned>(T)), block(kDistillThreads);
   hipStream_t s = as_stream(stream);
-  if (logits_dtype == BC_BF16) {
-    if (vec) hipLaunchKernelGGL((topk_kl_bwd_kernel<bf16_t, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((topk_kl_bwd_kernel<bf16_t, false>), grid, block, 0, s, p);
-  } else {
-    if (vec) hipLaunchKernelGGL((topk_kl_bwd_kernel<float, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((topk_kl_bwd_kernel<float, false>), grid, block, 0, s, p);
-  }
+  if (logits_dtype == BC_BF16) launch_bwd<bf16_t>(p, logits_dtype, s);
+  else launch_bwd<float>(p, logits_dtype, s);
   return launch_status();
 }

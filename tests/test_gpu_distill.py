@@ -56,6 +56,29 @@ def test_small_vocabularies(dev, dtype, V, k):
     _check(wl, range(37), dev, gs=0.25)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,V,k", [(5, 3, 2), (3, 31, 5), (9, 8200, 10), (7, 32771, 1000), (1024, 257, 20), (1025, 4099, 300)])
+def test_rows_that_start_anywhere(dev, dtype, T, V, k):
+    # rows shorter than the way to the first 16-byte boundary, one unit more than a batch of loads, several
+    # batches and a rest; both workgroup sizes; logits that start inside a 16-byte unit themselves, where the
+    # gradient's rows do not lie alike and its element-wise form runs
+    import torch
+    from paper_2510_13797_amd import bc
+    wl = W.DistillWorkload("rows", T, V, k, dtype)
+    z, tl, idx = wl.tokens(range(T))
+    zd, tld, idxd = _to_dev(z, tl, idx, dtype, dev)
+    room = torch.empty(T * V + 3, dtype=zd.dtype, device=dev)
+    for shift in (0, 1, 3):
+        zs = room[shift:shift + T * V].view(T, V)
+        zs.copy_(zd)
+        loss, lse, _ = bc.topk_kl_loss(zs, tld, idxd)
+        ref_loss, ref_lse = OD.topk_kl_loss(z, tl, idx)
+        assert np.abs(loss.cpu().numpy() - ref_loss).max() <= TOL
+        assert np.abs(lse.cpu().numpy() - ref_lse).max() <= TOL
+        dz = bc.topk_kl_loss_bwd(zs, tld, idxd, lse, 0.5).float().cpu().numpy()
+        _grad_close(dz, OD.topk_kl_loss_grad(z, tl, idx, 0.5), dtype, 0.5)
+
+
 def test_paper_vocabulary_all_rows(dev):
     wl = W.distill(T=24)
     _check(wl, range(24), dev)
