@@ -503,6 +503,21 @@ class Runtime:
         return out[0], out[1]
 
 
+def _trajectory_tables(row_offsets, P, c, device):
+    """row_offsets [B+1] int64, P, c [B] int32 in one device buffer: one copy instead of three (each a
+    round trip of some 12 us from pageable memory).  Returns (buffer, the three addresses)."""
+    import torch
+    B = len(row_offsets) - 1
+    host = np.empty(2 * B + 1, dtype=np.int64)
+    host[:B + 1] = row_offsets
+    tables = host[B + 1:].view(np.int32)
+    tables[:B] = np.asarray(P, dtype=np.int32).reshape(-1)[:B]
+    tables[B:] = np.asarray(c, dtype=np.int32).reshape(-1)[:B]
+    dev = torch.from_numpy(host).to(device)
+    at = dev.data_ptr()
+    return dev, at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B
+
+
 def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, workspace=False):
     """bc_prefill_attn (or, workspace=True, bc_prefill_attn_ws) on device tensors.
 
@@ -515,9 +530,7 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     row_offsets = np.asarray(row_offsets, dtype=np.int64)
     B = len(row_offsets) - 1
     shape = bc_shape(B, Hq, Hkv, d, BC_BF16, float(scale))
-    offd = torch.from_numpy(row_offsets).to(dev)
-    Pd = torch.from_numpy(np.asarray(P, dtype=np.int32)).to(dev)
-    cd = torch.from_numpy(np.asarray(c, dtype=np.int32)).to(dev)
+    tables, off_at, P_at, c_at = _trajectory_tables(row_offsets, P, c, dev)
     R = int(row_offsets[-1])
     out = torch.empty(R, Hq, d, dtype=torch.float32, device=dev)
     lse = torch.empty(R, Hq, dtype=torch.float32, device=dev) if want_lse else None
@@ -525,12 +538,12 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     if workspace:
         nbytes = int(bc_prefill_workspace_bytes(shape, R))
         ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-        _check(bc_prefill_attn_ws(shape, _ptr(q), _ptr(k), _ptr(v), _ptr(offd), _ptr(Pd), _ptr(cd), max_rows, R,
+        _check(bc_prefill_attn_ws(shape, _ptr(q), _ptr(k), _ptr(v), off_at, P_at, c_at, max_rows, R,
                                   _ptr(out), _ptr(lse), _ptr(ws), nbytes, _stream_ptr()))
     else:
-        _check(bc_prefill_attn(shape, _ptr(q), _ptr(k), _ptr(v), _ptr(offd), _ptr(Pd), _ptr(cd), max_rows,
+        _check(bc_prefill_attn(shape, _ptr(q), _ptr(k), _ptr(v), off_at, P_at, c_at, max_rows,
                                _ptr(out), _ptr(lse), _stream_ptr()))
-    torch.cuda.current_stream().synchronize()      # offd/Pd/cd (and the workspace) may be freed after this
+    torch.cuda.current_stream().synchronize()      # the tables (and the workspace) may be freed after this
     return out, lse
 
 
@@ -543,17 +556,19 @@ def prefill_attn_bwd(q, k, v, out, lse, dout, row_offsets, P, c, Hq, Hkv, d, sca
     B = len(row_offsets) - 1
     R = int(row_offsets[-1])
     shape = bc_shape(B, Hq, Hkv, d, BC_BF16, float(scale))
-    offd = torch.from_numpy(row_offsets).to(dev)
-    Pd = torch.from_numpy(np.asarray(P, dtype=np.int32)).to(dev)
-    cd = torch.from_numpy(np.asarray(c, dtype=np.int32)).to(dev)
-    dq = torch.full((R, Hq, d), float("nan"), dtype=torch.float32, device=dev)
-    dk = torch.full((R, Hkv, d), float("nan"), dtype=torch.float32, device=dev)
-    dv = torch.full((R, Hkv, d), float("nan"), dtype=torch.float32, device=dev)
+    tables, off_at, P_at, c_at = _trajectory_tables(row_offsets, P, c, dev)
+    # the kernels write every row of a trajectory (filling the gradients of 139,008 rows of 12/2 heads first
+    # took 0.165 ms); rows in front of the first one get NaN here
+    first = int(row_offsets[0])
+    dq, dk, dv = (torch.empty(R, h, d, dtype=torch.float32, device=dev) for h in (Hq, Hkv, Hkv))
+    if first:
+        for x in (dq, dk, dv):
+            x[:first] = float("nan")
     ws_bytes = int(bc_prefill_bwd_workspace_bytes(shape, R))
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
     max_rows = int(np.diff(row_offsets).max())
     _check(bc_prefill_attn_bwd(shape, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout),
-                               _ptr(offd), _ptr(Pd), _ptr(cd), max_rows, R, _ptr(dq), _ptr(dk), _ptr(dv),
+                               off_at, P_at, c_at, max_rows, R, _ptr(dq), _ptr(dk), _ptr(dv),
                                _ptr(ws), ws_bytes, _stream_ptr()))
     torch.cuda.current_stream().synchronize()
     return dq, dk, dv
@@ -576,9 +591,11 @@ def topk_kl_loss(student_logits, teacher_logits, teacher_idx):
     T, V = student_logits.shape
     k = teacher_logits.shape[1]
     dev = student_logits.device
-    loss = torch.full((T,), float("nan"), dtype=torch.float32, device=dev)
-    lse = torch.full((T,), float("nan"), dtype=torch.float32, device=dev)
-    mean = torch.full((1,), float("nan"), dtype=torch.float32, device=dev)
+    loss = torch.empty(T, dtype=torch.float32, device=dev)       # (all of it is written by the call)
+    lse = torch.empty(T, dtype=torch.float32, device=dev)
+    mean = torch.empty(1, dtype=torch.float32, device=dev)
+    if T == 0:
+        mean.fill_(float("nan"))
     _check(bc_topk_kl_loss(T, V, k, _ptr(student_logits), _logits_code(student_logits),
                            _ptr(teacher_logits), _ptr(teacher_idx), _ptr(loss), _ptr(lse), _ptr(mean),
                            _stream_ptr()))
@@ -592,7 +609,7 @@ def topk_kl_loss_bwd(student_logits, teacher_logits, teacher_idx, lse, grad_scal
     load()
     T, V = student_logits.shape
     k = teacher_logits.shape[1]
-    dz = torch.full_like(student_logits, float("nan"))
+    dz = torch.empty_like(student_logits)        # (written by the call; filling 1.2 GB first took 0.178 ms)
     _check(bc_topk_kl_loss_bwd(T, V, k, _ptr(student_logits), _logits_code(student_logits),
                                _ptr(teacher_logits), _ptr(teacher_idx), _ptr(lse), float(grad_scale),
                                _ptr(dz), _stream_ptr()))

@@ -424,3 +424,19 @@ def test_prefill_addresses_beyond_32_bits(dev, d):
         torch.cuda.synchronize()
         got.append(out.cpu().numpy())
     assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
+
+
+def test_rows_in_front_of_the_first_trajectory_have_no_gradient(dev):
+    # row_offsets[0] > 0: those rows belong to no trajectory; every other row is written
+    import torch
+    from paper_2510_13797_amd import bc
+    S, first, P = 70, 5, 20
+    g = torch.Generator(device=dev).manual_seed(3)
+    q, k, v, do = (torch.randn(first + S, h, 128, generator=g, device=dev).to(torch.bfloat16) for h in (4, 2, 2, 4))
+    args = (np.array([first, first + S]), [P], [4], 4, 2, 128, 128 ** -0.5)
+    out, lse = bc.prefill_attn(q, k, v, *args)
+    grads = bc.prefill_attn_bwd(q, k, v, out, lse, do, *args)
+    alone = bc.prefill_attn_bwd(q[first:].contiguous(), k[first:].contiguous(), v[first:].contiguous(), out[first:].contiguous(),
+                                lse[first:].contiguous(), do[first:].contiguous(), np.array([0, S]), *args[1:])
+    for x, y in zip(grads, alone):
+        assert torch.isnan(x[:first]).all() and torch.equal(x[first:], y)
