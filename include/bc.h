@@ -328,8 +328,7 @@ int32_t bc_prefill_attn_bwd(const bc_shape *shape, const void *q, const void *k,
  * loss_per_token: device [T] fp32.  lse (nullable): device [T] fp32, natural-log partition
  * function of the student row, the input of the backward call.  loss_mean (nullable): device
  * [1] fp32, the mean of loss_per_token (trajectories of equal weight per token), summed in a
- * fixed order.  1 <= k <= min(V, 1024).  Rows are read with 16-byte loads when V * element size
- * is a multiple of 16 and the pointer is aligned, element by element otherwise. */
+ * fixed order.  1 <= k <= min(V, 1024).  Rows may start at any element. */
 int32_t bc_topk_kl_loss(int64_t T, int32_t V, int32_t k, const void *student_logits,
                         int32_t logits_dtype, const float *teacher_logits,
                         const int32_t *teacher_idx, float *loss_per_token, float *lse,

@@ -159,6 +159,22 @@ __device__ __forceinline__ bf16x8_t cols_operand(const char* base, int j, int s)
   return __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// Either order (a tile read both ways, the backward's): unit u of row y at slot
+// (u%8/2)*16 + ((y%8)*2 + u%2 ^ rg/2 ^ 8*(u/2%2)): the row order with bit 3 flipped for every second pair of
+// units, so that the transposing reads of a half wave, 16 lanes in each of two neighbouring pairs, cover the
+// 64 banks once.
+__device__ __forceinline__ TileLane either_tile_lane(int lane, int rg) {
+  const int t = (lane & 15) ^ ((lane >> 1) & 8);
+  return TileLane{8 * rg + (t >> 1), (uint32_t)(2 * (lane >> 4) + ((t & 1) ^ (rg >> 1))) << 4};
+}
+// row operand i: tile + either_rows_offset(lane) ^ 128 * (i % 2), + rows_read_imm<D>(i)
+__device__ __forceinline__ int either_rows_offset(int lane) { return rows_read_offset(lane); }
+// column operand (j, s): tile + either_cols_offset(lane, s), as cols_operand takes it
+__device__ __forceinline__ int either_cols_offset(int lane, int s) {
+  const int rl = lane & 15, odd = (lane >> 4) & 1;
+  return odd * 256 + (((8 * (lane >> 5) + 2 * (rl >> 2) + ((rl & 3) >> 1)) ^ s ^ (8 * odd)) << 4) + ((rl & 1) << 3);
+}
+
 // The lane's byte offset from the tile's base; entries that do not exist repeat the first one (what is
 // computed from them is masked).  WIDE: a trajectory's rows may span 4 GB or more.
 template <bool WIDE>

@@ -440,3 +440,59 @@ def test_rows_in_front_of_the_first_trajectory_have_no_gradient(dev):
                                 lse[first:].contiguous(), do[first:].contiguous(), np.array([0, S]), *args[1:])
     for x, y in zip(grads, alone):
         assert torch.isnan(x[:first]).all() and torch.equal(x[first:], y)
+
+
+@pytest.mark.parametrize("P", [31, 33, 64, 65])
+@pytest.mark.parametrize("R,Hq,Hkv,d", [(62, 2, 1, 128), (65, 5, 1, 128), (129, 3, 3, 128), (700, 6, 1, 64)])
+def test_prefill_bwd_key_blocks_and_their_parts_at_the_edges(dev, P, R, Hq, Hkv, d):
+    # 64 keys per block, 32 per pair of waves, tiles of 32 rows, dense blocks whole and in two to eight
+    # parts, windows that end inside and behind a tile; results and workspace hold NaN before the call:
+    # what is not written, or read before it is written, shows
+    import torch
+    from paper_2510_13797_amd import bc
+    pw = W.PrefillWorkload("pfb_edges", 71, 3, Hq, Hkv, d, "bf16", np.array([P, P, 0], np.int32),
+                           np.array([R, R + 32, 33], np.int32), np.array([1, 6, 16], np.int32))
+    qkv = [pw.qkv(b) for b in range(pw.B)]
+    dos = [pw.dout(b) for b in range(pw.B)]
+    off = np.concatenate([[0], np.cumsum(pw.S)]).astype(np.int64)
+    q, k, v, do = (bc.to_device(np.concatenate(x), "bf16", dev) for x in (*zip(*qkv), dos))
+    out, lse = bc.prefill_attn(q, k, v, off, pw.P, pw.c, Hq, Hkv, d, pw.scale)
+    total, most = int(off[-1]), int(pw.S.max())
+    nan = lambda *shape: torch.full(shape, float("nan"), device=dev)
+    dq, dk, dv = nan(total, Hq, d), nan(total, Hkv, d), nan(total, Hkv, d)
+    shape = bc.bc_shape(pw.B, Hq, Hkv, d, bc.BC_BF16, pw.scale)
+    ws = nan(bc.bc_prefill_bwd_workspace_bytes(shape, total) // 4)
+    tables = [torch.from_numpy(x).to(dev) for x in (off, pw.P, pw.c)]
+    p = lambda t: t.data_ptr()
+    st = bc.bc_prefill_attn_bwd(shape, p(q), p(k), p(v), p(out), p(lse), p(do), *map(p, tables), most, total, p(dq), p(dk),
+                                p(dv), p(ws), ws.numel() * 4, None)
+    assert st == bc.BC_OK
+    torch.cuda.synchronize()
+    dq, dk, dv = (x.cpu().numpy() for x in (dq, dk, dv))
+    for b in range(pw.B):
+        _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_bwd_addresses_beyond_32_bits(dev, d):
+    # as above for the gradients: 512 heads make rows of 128 or 64 KB, so a stated 4 GB of K rows needs
+    # little workspace; the same bits as with 32-bit offsets
+    import torch
+    from paper_2510_13797_amd import bc
+    H, S = 512, 150
+    g = torch.Generator(device=dev).manual_seed(5)
+    q, k, v, do = (torch.randn(S, H, d, generator=g, device=dev).to(torch.bfloat16) for _ in range(4))
+    out, lse = bc.prefill_attn(q, k, v, [0, S], [37], [4], H, H, d, d ** -0.5)
+    shape = bc.bc_shape(1, H, H, d, bc.BC_BF16, d ** -0.5)
+    tab = [torch.from_numpy(x).to(dev) for x in (np.array([0, S]), np.array([37], np.int32), np.array([4], np.int32))]
+    p = lambda t: t.data_ptr()
+    got = []
+    for rows in (S, (1 << 32) // (H * d * 2) + 7):
+        grads = [torch.full((S, H, d), float("nan"), device=dev) for _ in range(3)]
+        ws = torch.empty(bc.bc_prefill_bwd_workspace_bytes(shape, rows), dtype=torch.uint8, device=dev)
+        assert bc.bc_prefill_attn_bwd(shape, p(q), p(k), p(v), p(out), p(lse), p(do), *map(p, tab), rows, rows,
+                                      *map(p, grads), p(ws), ws.numel(), None) == bc.BC_OK
+        torch.cuda.synchronize()
+        got.append(grads)
+    for x, y in zip(*got):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
