@@ -5,7 +5,7 @@
 // (max chunks, pairs).  With 128 pairs or more a pair is one chunk and its workgroup finishes
 // it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
 // workgroups (sequences under 1024 rows stay whole); every chunk writes an (m, l, o) partial
-// and a second, small kernel folds the partials of each pair in chunk order.  No float atomics
+// and the workgroup that is last folds the partials of its pair in chunk order.  No float atomics
 // and no fences: results are bit-reproducible.  Large ragged batches (more pairs than compute
 // units) can dispatch the longest sequences first (bc_sort_by_length).  Batches of at most 128
 // pairs with short caches use two workgroups per pair, each with all K rows and one half of the
@@ -22,6 +22,7 @@
 // Both carry the fused step (append before, eviction after the attention) in the same launch: the
 // appended row is read from the caller's tensors, every reader of a sequence takes a ticket when
 // it is done with the slab, and the holder of the last ticket moves the beacon and the tables.
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <cstdio>
@@ -46,9 +47,9 @@ struct DecodeParams {
   const char* q;
   float* out;
   const uint8_t* active;
-  float* part_o;       // [pairs][max_chunks][Gp][D]
-  float* part_ml;      // [pairs][max_chunks][2][Gp]   (running max in log2 units, denominator)
-  int32_t* part_n;     // [pairs] chunks written by this launch (read by the merge kernel)
+  float* part;         // [pairs][max_chunks][Gp*D + kPartTail]: o, then running max (log2 units) and denominator
+  int32_t* arrivals;   // chunks of a pair whose partial is written; zero between launches
+  int64_t arrival_stride;     // from sequence to sequence (the pairs of a sequence are neighbours)
   // fused step (all nullable): append this token row first, evict with this beacon afterwards
   const int32_t* c;
   int32_t* nb_rw;
@@ -175,6 +176,9 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
     while_tables_travel();
     asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(tP), "+s"(tnb), "+s"(tw), "+s"(tcap), "+s"(tbase), "+s"(tc) : : "memory");
     pi.P = tP; pi.nb = tnb; w = tw; pi.cap = tcap; pi.base = tbase; pi.c = tc;
+    // (the address of the kernel arguments keeps its registers up to here: the check of the generated code
+    // tells these loads from the arguments' by them)
+    asm volatile("" : : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
   }
   act = p.active ? __builtin_amdgcn_readfirstlane((int)p.active[pi.s]) : 1;
   if (bad_order) {
@@ -245,7 +249,6 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
       }
     }
   }
-  if (p.part_n && chunk == 0 && threadIdx.x == 0) p.part_n[pi.s * p.Hkv + pi.kvh] = pi.nchunks;
   // (uniform by construction; said explicitly for what went through vector arithmetic)
   pi.L = __builtin_amdgcn_readfirstlane(pi.L);
   pi.nchunks = __builtin_amdgcn_readfirstlane(pi.nchunks);
@@ -278,10 +281,89 @@ __device__ __forceinline__ void finish_step(const DecodeParams& p, const PairInf
     }
   }
   if (lane == 0) {
-    p.tickets[pi.s * kTicketStride] = 0;
+    // (past the L2: other words of the line are counted on by workgroups of other XCDs)
+    __hip_atomic_store(p.tickets + pi.s * kTicketStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     p.nb_rw[pi.s] = pi.nb + (pi.evict_due ? 1 : 0);
     p.w_rw[pi.s] = pi.evict_due ? 0 : pi.w_att;
     if (p.budget && pi.nb + pi.w_att >= p.budget[pi.s]) p.live[pi.s] = 0;   // generation interrupted
+  }
+}
+
+// ---------------------------------------------------------------------------
+// partial results of a sequence cut into chunks
+// ---------------------------------------------------------------------------
+// The chunks of a pair run on different XCDs, whose L2s do not see each other's dirty lines.  Partials
+// therefore go past the caches in both directions (system scope: stores through to memory, loads from
+// it) and no cache has to be written back or invalidated: an agent-scope release in their place took 50 us.
+// A chunk's partial has its 128-byte lines to itself.
+constexpr int kPartTail = 32;        // floats behind the o rows: [Gp] maxima, [Gp] denominators, padding
+
+__device__ __forceinline__ float* chunk_partial(const DecodeParams& p, const PairInfo& pi, int D, int chunk) {
+  return p.part + ((int64_t)(pi.s * p.Hkv + pi.kvh) * p.max_chunks + chunk) * (p.Gp * D + kPartTail);
+}
+__device__ __forceinline__ void store_part(float* a, float x) {
+  __hip_atomic_store(reinterpret_cast<uint32_t*>(a), __float_as_uint(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void store_part2(float* a, float x, float y) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(a), (uint64_t)__float_as_uint(y) << 32 | __float_as_uint(x),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ float load_part(const float* a) {
+  return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM));
+}
+__device__ __forceinline__ uint64_t load_part2(const float* a) {
+  return __hip_atomic_load(reinterpret_cast<const uint64_t*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The workgroup that finds all other chunks of its pair written folds them, in chunk order (so results do not
+// depend on which one it is).  Called by all threads of a workgroup that has stored its partial.
+// A second launch for this took MERGE_GAIN longer per step.
+template <int NT, int D>
+__device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's part of the partial is in memory
+  __syncthreads();                                       // ... and everyone's
+  int32_t* arrivals = p.arrivals + pi.s * p.arrival_stride + pi.kvh;
+  if (threadIdx.x == 0) *s_arrived = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*s_arrived) != pi.nchunks - 1) return;
+  if (threadIdx.x == 0) __hip_atomic_store(arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const float* part = chunk_partial(p, pi, D, 0);
+  const int stride = p.Gp * D + kPartTail;
+  float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * D;
+  // up to sixteen chunks at a time: the loads of a batch are independent and in flight together (eight where the
+  // kernel would need more registers for it)
+  constexpr int kBatch = NT > 256 ? 16 : 8;
+  for (int i = 2 * threadIdx.x; i < p.g * D; i += 2 * NT) {
+    const float* ml = part + p.Gp * D + i / D;
+    float mx = kNegBig, lsum = 0.f, o0 = 0.f, o1 = 0.f;
+    for (int ch0 = 0; ch0 < pi.nchunks; ch0 += kBatch) {
+      float mv[kBatch], lv[kBatch];
+      uint64_t ov[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int64_t at = (int64_t)min(ch0 + k, pi.nchunks - 1) * stride;
+        mv[k] = load_part(ml + at);
+        lv[k] = load_part(ml + at + p.Gp);
+        ov[k] = load_part2(part + at + i);
+      }
+      float bm = kNegBig;
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        if (ch0 + k >= pi.nchunks) mv[k] = kNegBig;
+        bm = fmaxf(bm, mv[k]);
+      }
+      const float mn = fmaxf(mx, bm);
+      const float keep = fast_exp2(mx - mn);
+      lsum *= keep; o0 *= keep; o1 *= keep; mx = mn;
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const float a = (ch0 + k < pi.nchunks) ? fast_exp2(mv[k] - mx) : 0.f;
+        lsum += lv[k] * a;
+        o0 += __uint_as_float((uint32_t)ov[k]) * a;
+        o1 += __uint_as_float((uint32_t)(ov[k] >> 32)) * a;
+      }
+    }
+    *reinterpret_cast<float2*>(outp + i) = make_float2(o0 / lsum, o1 / lsum);
   }
 }
 
@@ -296,9 +378,8 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
   // ml_stride, acc_stride: floats between the entries of two waves in s_m / s_l and in s_acc
   // D: columns this workgroup holds (all DOUT of a head, or one half starting at col0)
   const int nout = p.g * D;
-  const int pair = pi.s * p.Hkv + pi.kvh;
-  float* po = p.part_o + ((int64_t)pair * p.max_chunks + pi.chunk) * (p.Gp * D);
-  float* pml = p.part_ml + ((int64_t)pair * p.max_chunks + pi.chunk) * (2 * p.Gp);
+  float* po = chunk_partial(p, pi, D, pi.chunk);
+  float* pml = po + p.Gp * D;
   float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * DOUT + col0;
   // (NW * 64 threads: the block size read from the launch descriptor would be one more scalar-cache miss)
   for (int i = threadIdx.x; i < nout; i += NW * 64) {
@@ -316,10 +397,10 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
     if (pi.nchunks == 1) {
       __builtin_nontemporal_store(o / lsum, outp + (D == DOUT ? i : h * DOUT + x));   // streamed out: nothing left dirty in L2
     } else {
-      __builtin_nontemporal_store(o, po + i);
+      store_part(po + i, o);
       if (x == 0) {
-        __builtin_nontemporal_store(mx, pml + h);
-        __builtin_nontemporal_store(lsum, pml + p.Gp + h);
+        store_part(pml + h, mx);
+        store_part(pml + p.Gp + h, lsum);
       }
     }
   }
@@ -327,15 +408,13 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
 
 // The same merge, four output columns per thread (128-bit LDS reads and stores): fewer waves
 // take part, which shortens this serial tail of the matrix-core kernel.
-template <int NW, int D, int DOUT, int APITCH>
+// CHUNKS: the sequence may be cut into chunks.
+template <int NW, int D, int DOUT, int APITCH, bool CHUNKS>
 __device__ __forceinline__ void merge_waves_and_store4(const DecodeParams& p, const PairInfo& pi,
                                                        const float* s_m, const float* s_l,
                                                        const float* s_acc, int wave_stride, int col0) {
   constexpr int Q = D / 4;                       // column quads per head
   const int nitems = p.g * Q;
-  const int pair = pi.s * p.Hkv + pi.kvh;
-  float* po = p.part_o + ((int64_t)pair * p.max_chunks + pi.chunk) * (p.Gp * D);
-  float* pml = p.part_ml + ((int64_t)pair * p.max_chunks + pi.chunk) * (2 * p.Gp);
   float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * DOUT + col0;
   for (int i = threadIdx.x; i < nitems; i += NW * 64) {
     const int h = i / Q, x = (i - h * Q) * 4;
@@ -360,14 +439,17 @@ __device__ __forceinline__ void merge_waves_and_store4(const DecodeParams& p, co
       lsum += lw[wv] * a;
       o += ow[wv] * a;
     }
-    if (pi.nchunks == 1) {
+    if (!CHUNKS || pi.nchunks == 1) {
       const float inv = __builtin_amdgcn_rcpf(lsum);      // (one rounding error of the hardware reciprocal)
       __builtin_nontemporal_store(o * inv, reinterpret_cast<f32x4_t*>(outp + h * DOUT + x));
     } else {
-      __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(po + h * D + x));
+      float* po = chunk_partial(p, pi, D, pi.chunk);
+      float* pml = po + p.Gp * D;
+      store_part2(po + h * D + x, o[0], o[1]);
+      store_part2(po + h * D + x + 2, o[2], o[3]);
       if (x == 0) {
-        __builtin_nontemporal_store(mx, pml + h);
-        __builtin_nontemporal_store(lsum, pml + p.Gp + h);
+        store_part(pml + h, mx);
+        store_part(pml + p.Gp + h, lsum);
       }
     }
   }
@@ -832,7 +914,10 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
     if (kb == 0) { s_m[wave * WSTRIDE + n] = m_run; s_l[wave * WSTRIDE + n] = l_run; }
   }
   __syncthreads();
-  merge_waves_and_store4<NW, DV, D, APITCH>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
+  merge_waves_and_store4<NW, DV, D, APITCH, VS == 1 && !SHORT>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
+  if constexpr (VS == 1 && !SHORT) {
+    if (pi.nchunks > 1) merge_chunks<NW * 64, D>(p, pi, reinterpret_cast<int*>(lds));
+  }
 
   // ---- the wave that drew the sequence's last ticket writes the beacon row and updates the tables
   if (!pi.update) return;
@@ -1023,57 +1108,10 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   int ticket = -1;
   if (pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
   merge_waves_and_store<kValuWaves, D>(p, pi, s_m, s_l, s_acc, G, G * D);
+  if (pi.nchunks > 1) merge_chunks<256, D>(p, pi, reinterpret_cast<int*>(s_m));
   if (!pi.update || wave != 0) return;
   if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv * pi.nchunks - 1) return;
   finish_step<RB>(p, pi, lane);
-}
-
-// ---------------------------------------------------------------------------
-// chunk merge: one workgroup per pair, partials combined in chunk order
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
-  const int pair = blockIdx.x;
-  const int s = pair / p.Hkv, kvh = pair - s * p.Hkv;
-  const int nchunks = p.part_n[pair];             // 0: nothing to do, 1: already final
-  if (nchunks <= 1) return;
-  const int D = p.D;
-  const float* ao = p.part_o + (int64_t)pair * p.max_chunks * (p.Gp * D);
-  const float* aml = p.part_ml + (int64_t)pair * p.max_chunks * (2 * p.Gp);
-  float* outp = p.out + (int64_t)(s * p.Hq + kvh * p.g) * D;
-  const int nout = p.g * D;
-  // chunks are folded in order, sixteen at a time: the loads of a batch are independent and in
-  // flight together (the partials come from memory, not from this compute unit's caches)
-  constexpr int kBatch = 16;
-  for (int i = threadIdx.x; i < nout; i += 256) {
-    const int h = i / D;
-    float mx = kNegBig, lsum = 0.f, o = 0.f;
-    for (int ch0 = 0; ch0 < nchunks; ch0 += kBatch) {
-      float mv[kBatch], lv[kBatch], ov[kBatch];
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const int ch = min(ch0 + k, nchunks - 1);
-        mv[k] = __builtin_nontemporal_load(aml + ch * 2 * p.Gp + h);
-        lv[k] = __builtin_nontemporal_load(aml + ch * 2 * p.Gp + p.Gp + h);
-        ov[k] = __builtin_nontemporal_load(ao + (int64_t)ch * (p.Gp * D) + i);
-      }
-      float bm = kNegBig;
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        if (ch0 + k >= nchunks) mv[k] = kNegBig;
-        bm = fmaxf(bm, mv[k]);
-      }
-      const float mn = fmaxf(mx, bm);
-      const float keep = fast_exp2(mx - mn);
-      lsum *= keep; o *= keep; mx = mn;
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const float a = (ch0 + k < nchunks) ? fast_exp2(mv[k] - mx) : 0.f;
-        lsum += lv[k] * a;
-        o += ov[k] * a;
-      }
-    }
-    outp[i] = o / lsum;
-  }
 }
 
 struct DecodePlan {
@@ -1082,8 +1120,8 @@ struct DecodePlan {
   int rows_per_pass;  // rows one pass of a workgroup covers
   int R;              // rows per workgroup
   int max_chunks;
-  size_t tickets_bytes, part_n_bytes, part_o_bytes, part_ml_bytes;
-  size_t total() const { return tickets_bytes + part_n_bytes + part_o_bytes + part_ml_bytes; }
+  size_t tickets_bytes, arrivals_bytes, part_bytes;
+  size_t total() const { return tickets_bytes + arrivals_bytes + part_bytes; }
 };
 
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
@@ -1132,9 +1170,8 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
   if (rows_override == kPlanForSizing) pl.max_chunks = npairs < 128 ? 64 : 4;
   const size_t pairs = (size_t)sh->B * sh->Hkv;
   pl.tickets_bytes = align256((size_t)sh->B * kTicketStride * 4);
-  pl.part_n_bytes = align256(pairs * 4);
-  pl.part_o_bytes = align256(pairs * pl.max_chunks * pl.Gp * sh->d * 4);
-  pl.part_ml_bytes = align256(pairs * pl.max_chunks * 2 * pl.Gp * 4);
+  pl.arrivals_bytes = sh->Hkv < kTicketStride ? 0 : align256(pairs * 4);
+  pl.part_bytes = pairs * pl.max_chunks * (pl.Gp * sh->d + kPartTail) * 4;
   return pl;
 }
 
@@ -1276,10 +1313,18 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.active = active;
   char* ws = static_cast<char*>(workspace);
   p.tickets = reinterpret_cast<int32_t*>(ws);
-  char* parts = ws + pl.tickets_bytes;
-  p.part_n = pl.max_chunks > 1 ? reinterpret_cast<int32_t*>(parts) : nullptr;
-  p.part_o = reinterpret_cast<float*>(parts + pl.part_n_bytes);
-  p.part_ml = reinterpret_cast<float*>(parts + pl.part_n_bytes + pl.part_o_bytes);
+  p.part = reinterpret_cast<float*>(ws + pl.tickets_bytes + pl.arrivals_bytes);
+  // a pair's chunks are counted on the line of its sequence's ticket counter; where that has not got a
+  // place for every KV head they have an array, cleared in front of the launch
+  p.arrivals = p.tickets + 1;
+  p.arrival_stride = kTicketStride;
+  if (pl.arrivals_bytes) {
+    p.arrivals = reinterpret_cast<int32_t*>(ws + pl.tickets_bytes);
+    p.arrival_stride = shape->Hkv;
+    if (pl.max_chunks > 1)
+      fill_zero_kernel<<<(int)std::min<size_t>(1024, (pl.arrivals_bytes + 1023) / 1024), 256, 0, hs>>>(
+          reinterpret_cast<uint32_t*>(p.arrivals), (int64_t)(pl.arrivals_bytes / 4));
+  }
   p.c = cache->c; p.nb_rw = cache->nb; p.w_rw = cache->w;
   p.new_k = static_cast<const char*>(k); p.new_v = static_cast<const char*>(v);
   p.bk = static_cast<const char*>(bk); p.bv = static_cast<const char*>(bv);
@@ -1296,7 +1341,6 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.spec_P = (cache->plan & BC_PLAN_IGNORE_PROMISE) ? 0 : cache->uniform_P;
   p.spec_cap = cache->uniform_cap;
 
-  const int pairs = shape->B * shape->Hkv;
   const dim3 grid(pl.max_chunks, shape->Hkv, shape->B);
   if (pl.lds) {
     const int32_t st = enable_big_lds();
@@ -1310,7 +1354,6 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
     if (shape->d == 128) launch_valu<float, 128>(p, pl.Gp, grid, hs);
     else launch_valu<float, 64>(p, pl.Gp, grid, hs);
   }
-  if (pl.max_chunks > 1) decode_merge_kernel<<<pairs, 256, 0, hs>>>(p);
   return launch_status();
 }
 
@@ -1379,15 +1422,15 @@ extern "C" int32_t bc_decode_plan_describe(const bc_shape* shape, const bc_cache
   if (cache->rows_per_workgroup < 0 || (cache->plan & ~BC_PLAN_ALL_BITS)) return BC_ERR_ARG;
   const DecodePlan pl = make_plan(shape, cache->max_cap, cache->rows_per_workgroup, cache->plan);
   if ((cache->plan & BC_PLAN_NEED_MATRIX_KERNEL) && !pl.lds) return BC_ERR_SHAPE;
+  const char* merged = pl.max_chunks > 1 ? ", merged by a pair's last workgroup" : "";
   if (pl.lds) {
     const LdsLaunch k = pick_lds_kernel(shape, cache, pl, follows_order(shape, cache, pl));
     snprintf(text, text_bytes, "%s grid=(%u,%u,%u) threads=%d lds=%d chunks=%d%s", k.name, k.grid.x,
-             k.grid.y, k.grid.z, k.threads, k.lds_bytes, pl.max_chunks,
-             pl.max_chunks > 1 ? " + bc::decode_merge_kernel" : "");
+             k.grid.y, k.grid.z, k.threads, k.lds_bytes, pl.max_chunks, merged);
   } else {
     snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8> grid=(%d,%d,%d) threads=256 chunks=%d%s",
              shape->kv_dtype == BC_BF16 ? "bc::bf16_t" : "float", shape->d, pl.Gp, pl.max_chunks,
-             shape->Hkv, shape->B, pl.max_chunks, pl.max_chunks > 1 ? " + bc::decode_merge_kernel" : "");
+             shape->Hkv, shape->B, pl.max_chunks, merged);
   }
   return BC_OK;
 }
@@ -1429,7 +1472,9 @@ extern "C" int32_t bc_decode_step(const bc_shape* shape, const bc_cache* cache, 
 // bc_decode_step for callers that cannot allocate: the workspace is a fixed array in device memory
 // ---------------------------------------------------------------------------
 namespace bc {
-constexpr size_t kScratchBytes = BC_NOALLOC_SCRATCH_BYTES;
+// BC_NOALLOC_SCRATCH_BYTES of counters and results, and what the padding of the partials adds to them (at most 96
+// floats instead of 66: one head, d = 64).
+constexpr size_t kScratchBytes = BC_NOALLOC_SCRATCH_BYTES / 2 * 3;
 // One copy per GPU the library runs on, at an address of its own, held until the process ends.
 // (In host code the array's name is only a handle: its device address comes from
 // hipGetSymbolAddress, once per device, below.)
@@ -1463,8 +1508,11 @@ extern "C" int32_t bc_decode_step_noalloc(const bc_shape* shape, const bc_cache*
   if (beacon_k && (!aligned16(beacon_k) || !aligned16(beacon_v))) return BC_ERR_ARG;
   // what this call's plan touches: the per-sequence counters, and the partial results only when
   // sequences are split into chunks
-  const size_t need = pl.tickets_bytes + (pl.max_chunks > 1 ? pl.total() - pl.tickets_bytes : 0);
-  if (need > kScratchBytes) return BC_ERR_WORKSPACE;
+  const size_t pairs = (size_t)shape->B * shape->Hkv;
+  const size_t results = align256(pairs * 4) + align256(pairs * pl.max_chunks * pl.Gp * shape->d * 4) +
+                         align256(pairs * pl.max_chunks * 2 * pl.Gp * 4);
+  if (pl.tickets_bytes + (pl.max_chunks > 1 ? results : 0) > BC_NOALLOC_SCRATCH_BYTES) return BC_ERR_WORKSPACE;
+  if (pl.max_chunks > 1 && pl.total() > kScratchBytes) return BC_ERR_WORKSPACE;
   unsigned char* ws = nullptr;
   st = scratch_of_current_device(&ws);
   if (st != BC_OK) return st;
