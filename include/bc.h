@@ -98,7 +98,7 @@ typedef struct {
  * narrow that choice per call; no choice changes a result beyond the order of fp32 additions.
  *  rows_per_workgroup > 0: rows of one (sequence, KV head) stream handled by one workgroup (rounded
  *      up to the kernel's pass size and so that a sequence has at most 64 chunks); partial results
- *      are folded by a second launch.  On a batch with 128 or more (sequence, KV head) pairs the
+ *      are folded by the workgroup that finishes a pair.  On a batch with 128 or more (sequence, KV head) pairs the
  *      workspace of bc_decode_workspace_bytes() covers at most four chunks per sequence, beyond
  *      that the calls return BC_ERR_WORKSPACE.  < 0 is BC_ERR_ARG.
  *  plan: OR of the bits below; an unknown bit is BC_ERR_ARG. */
@@ -212,8 +212,8 @@ int32_t bc_compress_evict(const bc_shape *shape, const bc_cache *cache, const vo
                           int32_t require_full_window, void *stream);
 
 /* One decode step: append the token rows, attend, then evict where due (supplied-beacon
- * form); a single launch for every supported shape (a second one merges partial results when
- * a small batch's sequences are split into chunks).  Same semantics as bc_append_kv(TOKEN) +
+ * form); a single launch for every supported shape (with more than 31 KV heads a second one, in
+ * front of it, clears counters when a small batch's sequences are cut into chunks).  Same semantics as bc_append_kv(TOKEN) +
  * bc_decode_attn + bc_compress_evict(beacon_k, beacon_v, require_full_window = 1) in that order.
  * beacon_k/v may be NULL: then no eviction is attempted. */
 int32_t bc_decode_step(const bc_shape *shape, const bc_cache *cache, const void *k,
@@ -226,9 +226,9 @@ int32_t bc_decode_step(const bc_shape *shape, const bc_cache *cache, const void 
  * and semantics as bc_decode_step without the workspace: the counters and partial results live in
  * a fixed array of BC_NOALLOC_SCRATCH_BYTES in device memory that belongs to the library (one copy
  * per GPU it runs on, held until the process ends).  The call allocates and frees nothing.  Its
- * plan must fit the array: B * 128 bytes of counters, plus - only for batches of fewer than 128
- * (sequence, KV head) pairs whose sequences are split into chunks, or a forced chunk size - the
- * partial results of bc_decode_workspace_bytes(); a call that needs more returns BC_ERR_WORKSPACE
+ * plan must fit the array: B * 128 bytes of counters, plus - only for batches whose sequences are
+ * split into chunks, and only if that fits, or for a forced chunk size - the partial results of
+ * bc_decode_workspace_bytes(); a call that needs more returns BC_ERR_WORKSPACE
  * and launches nothing.  Every call on one GPU uses the same array (the counters are cleared at
  * the start of each call): calls that overlap in time on one GPU, on whatever streams, race -
  * serialise them, or give the overlapping ones a workspace of their own through bc_decode_step. */

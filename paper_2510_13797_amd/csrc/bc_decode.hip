@@ -3,8 +3,8 @@
 //
 // Split-K flash decoding.  Work item = (sequence, KV head) pair x chunk of rows; grid =
 // (max chunks, pairs).  With 128 pairs or more a pair is one chunk and its workgroup finishes
-// it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
-// workgroups (sequences under 1024 rows stay whole); every chunk writes an (m, l, o) partial
+// it.  With fewer pairs the resident rows of a sequence are spread evenly over up to sixteen
+// workgroups (short sequences stay whole, see make_plan); every chunk writes an (m, l, o) partial
 // and the workgroup that is last folds the partials of its pair in chunk order.  No float atomics
 // and no fences: results are bit-reproducible.  Large ragged batches (more pairs than compute
 // units) can dispatch the longest sequences first (bc_sort_by_length).  Batches of at most 128
@@ -71,6 +71,8 @@ struct DecodeParams {
   int32_t rows_per_wg; // R: rows per workgroup when a chunk size is forced; otherwise (0) the
                        // resident rows of a sequence are spread evenly over its chunks
   int32_t max_chunks;
+  int32_t chunk_rows;  // rows a chunk is cut down to, as long as there are chunks left
+  int32_t split_rows;  // shorter sequences stay whole
   float qscale;        // softmax scale * log2(e)
 };
 
@@ -88,8 +90,6 @@ struct PairInfo {
 // Common prologue: which rows does this workgroup own?  Uniform across the workgroup.  All
 // table loads are issued together.  With a fused append the state rules of bc_append_kv are
 // applied here, identically in every workgroup of the sequence.
-constexpr int kMinChunkRows = 128;   // a chunk smaller than this is not worth a workgroup
-constexpr int kMinSplitRows = 1024;  // sequences shorter than this are not split at all
 constexpr int kLptMaxB = 4096;       // sort key: length * 4096 + index
 constexpr int kLptMaxLen = 1 << 19;
 constexpr int kLptMinPairs = 256;    // compute units of the chip: below this every workgroup starts at once
@@ -225,7 +225,7 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
       if (herald) atomicOr(p.err, BC_ERRBIT_STATE);
     } else {
       // rows per chunk: the forced size, or the sequence's rows spread evenly over as many of
-      // the max_chunks workgroups as have at least kMinChunkRows rows to read
+      // the max_chunks workgroups as have chunk_rows rows to read
       int rpc = p.rows_per_wg;
       if (rpc <= 0 && p.max_chunks == 1) {
         rpc = (pi.L + 31) & ~31;              // one workgroup has the whole sequence
@@ -233,7 +233,7 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
       } else {
         if (rpc <= 0) {
           // (a short sequence stays whole: its partial would cost more than the split saves)
-          const int nc = pi.L < kMinSplitRows ? 1 : min(p.max_chunks, pi.L / kMinChunkRows);
+          const int nc = pi.L < p.split_rows ? 1 : min(p.max_chunks, (pi.L + p.chunk_rows - 1) / p.chunk_rows);
           rpc = (((pi.L + nc - 1) / nc) + 31) & ~31;
         }
         pi.nchunks = (pi.L + rpc - 1) / rpc;
@@ -315,18 +315,23 @@ __device__ __forceinline__ uint64_t load_part2(const float* a) {
   return __hip_atomic_load(reinterpret_cast<const uint64_t*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The workgroup that finds all other chunks of its pair written folds them, in chunk order (so results do not
-// depend on which one it is).  Called by all threads of a workgroup that has stored its partial.
-// A second launch for this took MERGE_GAIN longer per step.
-template <int NT, int D>
-__device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
+// Counts this workgroup's chunk as written (called by all of its threads, once it has stored its partial and
+// done all its reads of the slab).  True for the one that finds all other chunks of its pair written.
+__device__ __forceinline__ bool last_chunk(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's part of the partial is in memory
   __syncthreads();                                       // ... and everyone's
   int32_t* arrivals = p.arrivals + pi.s * p.arrival_stride + pi.kvh;
   if (threadIdx.x == 0) *s_arrived = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(*s_arrived) != pi.nchunks - 1) return;
+  if (__builtin_amdgcn_readfirstlane(*s_arrived) != pi.nchunks - 1) return false;
   if (threadIdx.x == 0) __hip_atomic_store(arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// The fold, in chunk order (so results do not depend on which workgroup it is).  A second launch for it cost
+// 4.5 us and the gap between two dependent launches.
+template <int NT, int D>
+__device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairInfo& pi) {
   const float* part = chunk_partial(p, pi, D, 0);
   const int stride = p.Gp * D + kPartTail;
   float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * D;
@@ -509,6 +514,7 @@ template <int STREAM, int D, int VS, int NW, bool SHORT = false>
 __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   constexpr bool KSTREAM = STREAM == 1, VSTREAM = STREAM >= 1;
+  constexpr bool CHUNKS = VS == 1 && !SHORT;         // the sequence may be cut into chunks
   constexpr int DV = D / VS;               // V (and output) columns of this workgroup
   constexpr int VROWB = DV * 2;            // bytes of its part of a V row, = row pitch of the V tile in LDS
   constexpr int VUPR = VROWB / 16;
@@ -704,9 +710,11 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   // load from the slab has landed (the tables were read at the start); whoever draws the last one
   // may write the beacon row and update the tables.  The answer is only looked at after the wave
   // merge, so the atomic's round trip (about a microsecond) hides behind the remaining compute.
+  // (Of a sequence cut into chunks the workgroup that folds a pair's takes one for the pair: a ticket for every wave
+  // of every chunk were 1472 atomics on one counter for 3000 rows of 8 KV heads, 23.7 us a step instead of 12.2.)
   int ticket = -1;
   auto take_ticket = [&]() {
-    if (pi.update && lane == 0) {
+    if (pi.update && lane == 0 && (!CHUNKS || pi.nchunks == 1)) {
       const int one_ = 1;
       asm volatile("global_atomic_add %0, %1, %2, off sc0"
                    : "=v"(ticket) : "v"(p.tickets + pi.s * kTicketStride), "v"(one_) : "memory");
@@ -723,14 +731,17 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   auto patch_v_row_and_store = [&](int trow0) {
     const int ra = pi.new_row - trow0;
     if (ra < 0 || ra >= kTileRows) return;
+    int lane_ = lane;
+    asm volatile("" : "+v"(lane_));       // addresses worked out here and not kept from before the tile loop (cut
+                                          // sequences, 48 pairs of 1100 rows: 19.9 us a step with, 14.1 without)
     if (lane >= UPR && lane < UPR + VUPR) {
-      const int u = lane - UPR;
+      const int u = lane_ - UPR;
       *reinterpret_cast<u32x4_t*>(wv + ra * VROWB + ((u ^ tile_swz<DV>(ra)) << 4)) = newrow_v;
       if (pi.store_new_row)
         *reinterpret_cast<u32x4_t*>(const_cast<char*>(vbase) + (int64_t)pi.new_row * ROWB + (u << 4)) = newrow_v;
     } else if (lane < UPR) {
       if (pi.store_new_row && vhalf == 0)
-        *reinterpret_cast<u32x4_t*>(const_cast<char*>(kbase) + (int64_t)pi.new_row * ROWB + (lane << 4)) = newrow_v;
+        *reinterpret_cast<u32x4_t*>(const_cast<char*>(kbase) + (int64_t)pi.new_row * ROWB + (lane_ << 4)) = newrow_v;
     }
     for (int rr = ra + 1 + r4v; rr < kTileRows; rr += VRPI)
       *reinterpret_cast<uint4*>(wv + rr * VROWB + (posv << 4)) = make_uint4(0u, 0u, 0u, 0u);
@@ -914,16 +925,24 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
     if (kb == 0) { s_m[wave * WSTRIDE + n] = m_run; s_l[wave * WSTRIDE + n] = l_run; }
   }
   __syncthreads();
-  merge_waves_and_store4<NW, DV, D, APITCH, VS == 1 && !SHORT>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
-  if constexpr (VS == 1 && !SHORT) {
-    if (pi.nchunks > 1) merge_chunks<NW * 64, D>(p, pi, reinterpret_cast<int*>(lds));
+  merge_waves_and_store4<NW, DV, D, APITCH, CHUNKS>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
+  if constexpr (CHUNKS) {
+    if (pi.nchunks > 1) {
+      if (!last_chunk(p, pi, reinterpret_cast<int*>(lds))) return;
+      int drawn = -1;
+      if (pi.update && tid == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+      merge_chunks<NW * 64, D>(p, pi);
+      if (!pi.update || wave != 0) return;
+      if (__builtin_amdgcn_readfirstlane(drawn) == p.Hkv - 1) finish_step<ROWB>(p, pi, lane);
+      return;
+    }
   }
 
   // ---- the wave that drew the sequence's last ticket writes the beacon row and updates the tables
   if (!pi.update) return;
   wait_vmcnt<0>();     // the ticket has arrived
   landed(ticket);
-  if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv * pi.nchunks * VS * NW - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv * VS * NW - 1) return;
   finish_step<ROWB>(p, pi, lane);
 }
 
@@ -1103,16 +1122,22 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   }
   __syncthreads();
   // Fused step: one ticket per workgroup, taken once all its waves have used the rows they read
-  // (the barrier above); the answer comes back under the merge.  The workgroup that draws the
-  // sequence's last one finishes the step.
+  // (the barrier above), or per pair, by the workgroup that folds its chunks; the answer comes back under the
+  // merge.  The workgroup that draws the sequence's last one finishes the step.
   int ticket = -1;
-  if (pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+  if (pi.nchunks == 1 && pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
   merge_waves_and_store<kValuWaves, D>(p, pi, s_m, s_l, s_acc, G, G * D);
-  if (pi.nchunks > 1) merge_chunks<256, D>(p, pi, reinterpret_cast<int*>(s_m));
+  if (pi.nchunks > 1) {
+    if (!last_chunk(p, pi, reinterpret_cast<int*>(s_m))) return;
+    if (pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+    merge_chunks<256, D>(p, pi);
+  }
   if (!pi.update || wave != 0) return;
-  if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv * pi.nchunks - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv - 1) return;
   finish_step<RB>(p, pi, lane);
 }
+
+static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct DecodePlan {
   bool lds;           // LDS/MFMA kernel (bf16, d = 128) or the VALU kernel
@@ -1120,13 +1145,21 @@ struct DecodePlan {
   int rows_per_pass;  // rows one pass of a workgroup covers
   int R;              // rows per workgroup
   int max_chunks;
+  int chunk_rows, split_rows;         // see DecodeParams
   size_t tickets_bytes, arrivals_bytes, part_bytes;
   size_t total() const { return tickets_bytes + arrivals_bytes + part_bytes; }
+  void size_for(const bc_shape* sh) {
+    const size_t pairs = (size_t)sh->B * sh->Hkv;
+    tickets_bytes = align256((size_t)sh->B * kTicketStride * 4);
+    arrivals_bytes = sh->Hkv < kTicketStride ? 0 : align256(pairs * 4);
+    part_bytes = pairs * max_chunks * (Gp * sh->d + kPartTail) * 4;
+  }
 };
 
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
-static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kEightWavePairs = 32;       // see make_plan
+constexpr long kMostChunks = 16;      // the fold reads that many partials at a time
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
 
 static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits) {
@@ -1142,6 +1175,8 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.rows_per_pass = kValuWaves * rpi * 8;
   }
   const long npairs = (long)sh->B * sh->Hkv;
+  pl.chunk_rows = pl.lds ? 2 * kTileRows : pl.rows_per_pass;
+  pl.split_rows = pl.lds ? kSplitMinRows : pl.rows_per_pass + 1;
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
     int R = ((rows_override + pl.rows_per_pass - 1) / pl.rows_per_pass) * pl.rows_per_pass;
@@ -1149,18 +1184,27 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.R = R;
     pl.max_chunks = (max_cap + R - 1) / R;
   } else {
-    // One workgroup per (sequence, KV head) pair when there are enough pairs: a long-running
-    // workgroup streams its rows at full rate and needs no merge launch.  With few pairs the
-    // rows of a sequence are spread over enough workgroups to fill the chip (256 compute units),
-    // at least kMinChunkRows rows each, at most 64 chunks - but only when the longest stream
-    // gets shorter by more than the merge launch costs (about 6 us, some 480 rows of one stream).
+    // One workgroup per (sequence, KV head) pair when there are enough pairs.  With fewer, the rows of a
+    // sequence are spread over as many workgroups as run at once, at most sixteen, whose partials are folded in
+    // one round of loads, and of at least two tiles or one pass of rows.  That many are 256 of the matrix kernel
+    // at d = 128 (128 KB of LDS each; at 48 pairs a step over 1500 rows takes 19.1 us with 288 workgroups, which
+    // make a second round, and 13.8 with 240), and 512 at d = 64 or with four waves (see pick_lds_kernel).  512 is
+    // the line from 33 pairs on: a ragged batch does not fill them, and its longest sequence sets the time (90 pairs
+    // of up to 2100 rows, cut in two by eight waves or in five by four: 31.5, 27.2 us; of equal length, 1500 rows:
+    // 19.0, 20.1); with up to 32 pairs eight waves and 256 are as fast or faster (16 pairs of 3000 rows: 12.0, 13.6;
+    // at 8 pairs 23 chunks take 12.2, sixteen 11.1).
+    // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster (d = 128, 8
+    // pairs, whole against cut: 700 rows 7.9, 9.2 us; 850: 8.9, 9.5; 1000: 9.4, 9.7; 2 pairs, 1000 rows: 9.25, 8.7);
+    // where the batch has longer sequences the shorter ones run in the tile loop, cut from 512 rows on (700 rows
+    // whole: 10.1 us).  The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of some 5 us: cut
+    // from the second pass on, with more pairs too (fp32, 64 sequences of 500 rows, 12/2 heads: 62.8 -> 28.2 us).
+    const long at_once = pl.lds && npairs <= kEightWavePairs ? 256 : 512, most_pairs = pl.lds ? 127 : 256;
     long chunks = 1;
-    if (npairs < 128) {
-      chunks = (256 + npairs - 1) / npairs;
-      const long by_rows = max_cap / kMinChunkRows;
+    if (npairs <= most_pairs && max_cap >= (pl.lds ? kSplitMinCap : pl.split_rows)) {
+      chunks = at_once / npairs;
+      const long by_rows = (max_cap + pl.chunk_rows - 1) / pl.chunk_rows, most = npairs < 128 ? kMostChunks : 4;
       if (chunks > by_rows) chunks = by_rows;
-      if (chunks > 64) chunks = 64;
-      if (chunks < 1 || max_cap - max_cap / chunks < 480) chunks = 1;
+      if (chunks > most) chunks = most;
     }
     pl.R = 0;                                        // spread evenly, decided per sequence
     pl.max_chunks = (int)chunks;
@@ -1168,10 +1212,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
   // Workspace sizing: the most chunks the automatic plan can choose (64 with few pairs, one
   // otherwise); a forced chunk size on a large batch may use up to four.
   if (rows_override == kPlanForSizing) pl.max_chunks = npairs < 128 ? 64 : 4;
-  const size_t pairs = (size_t)sh->B * sh->Hkv;
-  pl.tickets_bytes = align256((size_t)sh->B * kTicketStride * 4);
-  pl.arrivals_bytes = sh->Hkv < kTicketStride ? 0 : align256(pairs * 4);
-  pl.part_bytes = pairs * pl.max_chunks * (pl.Gp * sh->d + kPartTail) * 4;
+  pl.size_for(sh);
   return pl;
 }
 
@@ -1237,8 +1278,10 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
     // bytes, merge, store - overlap with the other's streaming.  Measured at 512 pairs of 512
     // rows: 28.2 -> 25.4 us; with long ragged sequences (512 pairs of up to 2700 rows) the longest
     // streams set the pace and eight waves are faster (54.5 against 62.5 us).
-    const bool four = pairs > kLptMinPairs && cache->max_cap <= kSplitWaves12MaxCap && stream &&
-                      !(cache->plan & BC_PLAN_NO_SMALL_WORKGROUPS);
+    // The same for sequences cut into chunks of more pairs than eight-wave workgroups serve well.
+    const bool four = (pl.max_chunks > 1 ? pl.R == 0 && pairs > kEightWavePairs
+                                         : pairs > kLptMinPairs && cache->max_cap <= kSplitWaves12MaxCap) &&
+                      stream && !(cache->plan & BC_PLAN_NO_SMALL_WORKGROUPS);
     if (four) return LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 4), grid, 4 * 64, kLdsBytes / 2};
     if (two8) return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes}
                             : LdsLaunch{BC_LDS_KERNEL(0, 128, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes};
@@ -1337,6 +1380,7 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.D = shape->d;
   p.rows_per_wg = pl.R;
   p.max_chunks = pl.max_chunks;
+  p.chunk_rows = pl.chunk_rows; p.split_rows = pl.split_rows;
   p.qscale = shape->scale * kLog2e;
   p.spec_P = (cache->plan & BC_PLAN_IGNORE_PROMISE) ? 0 : cache->uniform_P;
   p.spec_cap = cache->uniform_cap;
@@ -1422,7 +1466,7 @@ extern "C" int32_t bc_decode_plan_describe(const bc_shape* shape, const bc_cache
   if (cache->rows_per_workgroup < 0 || (cache->plan & ~BC_PLAN_ALL_BITS)) return BC_ERR_ARG;
   const DecodePlan pl = make_plan(shape, cache->max_cap, cache->rows_per_workgroup, cache->plan);
   if ((cache->plan & BC_PLAN_NEED_MATRIX_KERNEL) && !pl.lds) return BC_ERR_SHAPE;
-  const char* merged = pl.max_chunks > 1 ? ", merged by a pair's last workgroup" : "";
+  const char* merged = pl.max_chunks > 1 ? " + merge by a pair's last workgroup" : "";
   if (pl.lds) {
     const LdsLaunch k = pick_lds_kernel(shape, cache, pl, follows_order(shape, cache, pl));
     snprintf(text, text_bytes, "%s grid=(%u,%u,%u) threads=%d lds=%d chunks=%d%s", k.name, k.grid.x,
@@ -1509,9 +1553,15 @@ extern "C" int32_t bc_decode_step_noalloc(const bc_shape* shape, const bc_cache*
   // what this call's plan touches: the per-sequence counters, and the partial results only when
   // sequences are split into chunks
   const size_t pairs = (size_t)shape->B * shape->Hkv;
-  const size_t results = align256(pairs * 4) + align256(pairs * pl.max_chunks * pl.Gp * shape->d * 4) +
-                         align256(pairs * pl.max_chunks * 2 * pl.Gp * 4);
-  if (pl.tickets_bytes + (pl.max_chunks > 1 ? results : 0) > BC_NOALLOC_SCRATCH_BYTES) return BC_ERR_WORKSPACE;
+  auto results = [&]() {
+    return align256(pairs * 4) + align256(pairs * pl.max_chunks * pl.Gp * shape->d * 4) +
+           align256(pairs * pl.max_chunks * 2 * pl.Gp * 4);
+  };
+  if (pl.max_chunks > 1 && cache->rows_per_workgroup == 0 && pl.tickets_bytes + results() > BC_NOALLOC_SCRATCH_BYTES) {
+    pl.max_chunks = 1;            // (a cut that the array has no room for is left out)
+    pl.size_for(shape);
+  }
+  if (pl.tickets_bytes + (pl.max_chunks > 1 ? results() : 0) > BC_NOALLOC_SCRATCH_BYTES) return BC_ERR_WORKSPACE;
   if (pl.max_chunks > 1 && pl.total() > kScratchBytes) return BC_ERR_WORKSPACE;
   unsigned char* ws = nullptr;
   st = scratch_of_current_device(&ws);

@@ -848,3 +848,24 @@ def test_fused_steps_under_graph_replay(dev):
     q, ref = last_ref
     worst = max(float(np.abs(ref_out[-1][-1][s] - ref[s]).max()) for s in range(B))
     assert worst <= TOL[wl.dtype], worst
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,dtype,P,chunks", [
+    (2, 4, 2, 128, "bf16", (953, 940), 1),                  # one row of capacity short of being cut
+    (2, 4, 2, 128, "bf16", (954, 940), 15),                 # chunks of two tiles
+    (3, 6, 2, 128, "bf16", (507, 509, 1100), 16),           # sequences that come to be cut in the rollout
+    (1, 33, 33, 64, "bf16", (1000,), 15),                   # more KV heads than counters beside the ticket
+    (34, 2, 1, 128, "bf16", (1000, 30), 15),                # workgroups of four waves
+    (33, 3, 1, 64, "bf16", (1030, 500), 15),
+    (2, 8, 1, 128, "f32", (58, 59), 2),                     # one pass of rows and one row more
+    (65, 2, 2, 64, "f32", (130, 90), 2),                    # 130 pairs on the plain-ALU kernel
+])
+def test_sequences_cut_into_chunks(dev, B, Hq, Hkv, d, dtype, P, chunks):
+    # partials folded by a pair's last workgroup, one ticket per pair, evictions among the steps (c = 3)
+    G = 7
+    P = np.resize(np.array(P, np.int32), B)
+    wl = W.Workload("cut", 113, B, Hq, Hkv, d, dtype, P, np.full(B, G, np.int32), np.full(B, 3, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
+    rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
