@@ -3,7 +3,7 @@
 //
 // Split-K flash decoding.  Work item = (sequence, KV head) pair x chunk of rows; grid =
 // (max chunks, pairs).  With 128 pairs or more a pair is one chunk and its workgroup finishes
-// it.  With fewer pairs the resident rows of a sequence are spread evenly over up to sixteen
+// it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
 // workgroups (short sequences stay whole, see make_plan); every chunk writes an (m, l, o) partial
 // and the workgroup that is last folds the partials of its pair in chunk order.  No float atomics
 // and no fences: results are bit-reproducible.  Large ragged batches (more pairs than compute
@@ -1159,7 +1159,8 @@ struct DecodePlan {
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
 
 constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kEightWavePairs = 32;       // see make_plan
-constexpr long kMostChunks = 16;      // the fold reads that many partials at a time
+constexpr long kMostChunks = 64;
+constexpr int kChunkRowsMax = 512;    // rows a chunk of the matrix kernel need not go beyond: two passes of eight waves
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
 
 static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits) {
@@ -1175,7 +1176,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.rows_per_pass = kValuWaves * rpi * 8;
   }
   const long npairs = (long)sh->B * sh->Hkv;
-  pl.chunk_rows = pl.lds ? 2 * kTileRows : pl.rows_per_pass;
+  pl.chunk_rows = pl.lds ? std::min(kChunkRowsMax, std::max(2 * kTileRows, (max_cap + 15) / 16)) : pl.rows_per_pass;
   pl.split_rows = pl.lds ? kSplitMinRows : pl.rows_per_pass + 1;
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
@@ -1185,8 +1186,10 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.max_chunks = (max_cap + R - 1) / R;
   } else {
     // One workgroup per (sequence, KV head) pair when there are enough pairs.  With fewer, the rows of a
-    // sequence are spread over as many workgroups as run at once, at most sixteen, whose partials are folded in
-    // one round of loads, and of at least two tiles or one pass of rows.  That many are 256 of the matrix kernel
+    // sequence are spread over as many workgroups as run at once, of at least two tiles or one pass of rows, and at
+    // most sixteen, whose partials are folded in one round of loads, or one for every 512 rows (one sequence of
+    // 150,256 rows, one KV head: sixteen 94 us, 64 38; 16,900 rows: 17.1, 15.5; 6000 rows, 8 KV heads: a chunk for
+    // every 256 rows 15.7, every 512 14.8).  That many are 256 of the matrix kernel
     // at d = 128 (128 KB of LDS each; at 48 pairs a step over 1500 rows takes 19.1 us with 288 workgroups, which
     // make a second round, and 13.8 with 240), and 512 at d = 64 or with four waves (see pick_lds_kernel).  512 is
     // the line from 33 pairs on: a ragged batch does not fill them, and its longest sequence sets the time (90 pairs
