@@ -24,12 +24,13 @@
 // into LDS by 16-byte LDS-DMA loads, in the order that serves row and column operands alike
 // (bc_prefill_tiles.h).
 //
-// What bounds both: the matrix cores under the card's power limit; the dkv kernel issues 1560 GFLOP of MFMA
-// work in 1.55 ms on 16 trajectories of 8688 rows (12/2 heads, d = 128), 1.01 PFLOP/s, the dq kernel 970 in 1.09 ms
-// (a library product of 16384^3 runs at 1.34 PFLOP/s here).  The forms before, 16x16x32 MFMA with 16 rows
-// of two heads or 16 keys per wave and tiles read at half rate by bank conflicts, took 1.24 and 1.83 ms: the dkv
-// kernel read 128 KB of LDS per CU for every 768 matrix cycles of a SIMD.  The dq kernel needs 200
-// registers (Q, dO and dQ of 32 rows), two waves per SIMD; held to 168 it spilled in the tile loop.
+// What bounds both: matrix and vector issue of a SIMD that overlap only in part.  On 16 trajectories of 8688 rows
+// (12/2 heads, d = 128) the dkv kernel issues 1458 GFLOP of MFMA work in 1.60 ms (matrix pipe busy 48 % of the
+// cycles, a fifth of that together with vector work), the dq kernel 947 in 1.11 ms (44 %); a library product of
+// 16384^3 runs at 1.34 PFLOP/s here.  The forms before, 16x16x32 MFMA with 16 rows of two heads or 16 keys per wave
+// and tiles read at half rate by bank conflicts, took 1.24 and 1.83 ms: the dkv kernel read 128 KB of LDS per CU for
+// every 768 matrix cycles of a SIMD.  The dq kernel needs 200 registers (Q, dO and dQ of 32 rows), two waves per
+// SIMD; held to 168 it spilled in the tile loop.
 #include "bc_prefill_tiles.h"
 
 namespace bc {
