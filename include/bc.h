@@ -224,8 +224,8 @@ int32_t bc_decode_step(const bc_shape *shape, const bc_cache *cache, const void 
 /* bc_decode_step for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
  * and semantics as bc_decode_step without the workspace: the counters and partial results live in
- * a fixed array of BC_NOALLOC_SCRATCH_BYTES in device memory that belongs to the library (one copy
- * per GPU it runs on, held until the process ends).  The call allocates and frees nothing.  Its
+ * a fixed array in device memory that belongs to the library: BC_NOALLOC_SCRATCH_BYTES and half as
+ * much again for padding (one copy per GPU it runs on, held until the process ends).  The call allocates and frees nothing.  Its
  * plan must fit the array: B * 128 bytes of counters, plus - only for batches whose sequences are
  * split into chunks, and only if that fits, or for a forced chunk size - the partial results of
  * bc_decode_workspace_bytes(); a call that needs more returns BC_ERR_WORKSPACE
