@@ -28,6 +28,7 @@
 #include <cstdio>
 #include <type_traits>
 #include "bc_common.h"
+#include "bc_decode_count.h"
 
 namespace bc {
 
@@ -224,20 +225,9 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
     if (pi.L <= 0) {
       if (herald) atomicOr(p.err, BC_ERRBIT_STATE);
     } else {
-      // rows per chunk: the forced size, or the sequence's rows spread evenly over as many of
-      // the max_chunks workgroups as have chunk_rows rows to read
-      int rpc = p.rows_per_wg;
-      if (rpc <= 0 && p.max_chunks == 1) {
-        rpc = (pi.L + 31) & ~31;              // one workgroup has the whole sequence
-        pi.nchunks = 1;
-      } else {
-        if (rpc <= 0) {
-          // (a short sequence stays whole: its partial would cost more than the split saves)
-          const int nc = pi.L < p.split_rows ? 1 : min(p.max_chunks, (pi.L + p.chunk_rows - 1) / p.chunk_rows);
-          rpc = (((pi.L + nc - 1) / nc) + 31) & ~31;
-        }
-        pi.nchunks = (pi.L + rpc - 1) / rpc;
-      }
+      const SequenceCut cut = cut_sequence(pi.L, p.rows_per_wg, p.max_chunks, p.split_rows, p.chunk_rows);
+      const int rpc = cut.rows_per_chunk;
+      pi.nchunks = cut.nchunks;
       // the evaluation cap is tested on what this step's attention sees, whether or not the
       // append went through
       pi.update = append_ok || pi.evict_due ||
@@ -315,15 +305,16 @@ __device__ __forceinline__ uint64_t load_part2(const float* a) {
   return __hip_atomic_load(reinterpret_cast<const uint64_t*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Counts this workgroup's chunk as written (called by all of its threads, once it has stored its partial and
-// done all its reads of the slab).  True for the one that finds all other chunks of its pair written.
-__device__ __forceinline__ bool last_chunk(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
+// Counts this workgroup at its pair (called by all of its threads, once it has stored its partial and done all
+// its reads of the tables and the slab, or without a chunk).  True for the one that finds all others there: every
+// partial of the pair is then written, and every wave of the pair's workgroups has read the tables.
+__device__ __forceinline__ bool last_arrival(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's part of the partial is in memory
   __syncthreads();                                       // ... and everyone's
   int32_t* arrivals = p.arrivals + pi.s * p.arrival_stride + pi.kvh;
   if (threadIdx.x == 0) *s_arrived = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(*s_arrived) != pi.nchunks - 1) return false;
+  if (__builtin_amdgcn_readfirstlane(*s_arrived) != arrivals_due(pi.update, pi.nchunks, p.max_chunks) - 1) return false;
   if (threadIdx.x == 0) __hip_atomic_store(arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
 }
@@ -370,6 +361,31 @@ __device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairIn
     }
     *reinterpret_cast<float2*>(outp + i) = make_float2(o0 / lsum, o1 / lsum);
   }
+}
+
+// The end of a workgroup of a cut sequence.
+template <int NT, int D, int ROWB>
+__device__ __forceinline__ void close_pair(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
+  if (!last_arrival(p, pi, s_arrived)) return;
+  int drawn = -1;
+  if (pi.update && threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+  merge_chunks<NT, D>(p, pi);
+  if (!pi.update || threadIdx.x >= 64) return;
+  if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, 0, pi.nchunks, p.max_chunks) - 1)
+    finish_step<ROWB>(p, pi, threadIdx.x);
+}
+// The end of a workgroup without rows.  own: see tickets_due().
+template <int NT, int D, int ROWB>
+__device__ __forceinline__ void close_without_chunk(const DecodeParams& p, const PairInfo& pi, int own, int* s_arrived) {
+  const CloseBy move = closing_move(pi.update, false, pi.nchunks);
+  if (move == CloseBy::arrival) close_pair<NT, D, ROWB>(p, pi, s_arrived);
+  if (move != CloseBy::ticket) return;
+  __syncthreads();                 // every wave has read the tables
+  if (threadIdx.x >= 64) return;
+  int drawn = -1;
+  if (threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+  if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, own, pi.nchunks, p.max_chunks) - 1)
+    finish_step<ROWB>(p, pi, threadIdx.x);
 }
 
 // Epilogue shared by both kernels: s_m/s_l/s_acc hold one (m, l, o) per wave in LDS;
@@ -648,7 +664,11 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
       nothing_to_do = true;
     }
   }
-  if (nothing_to_do) { wait_vmcnt<0>(); return; }
+  if (nothing_to_do) {
+    wait_vmcnt<0>();
+    if constexpr (CHUNKS) close_without_chunk<NW * 64, D, ROWB>(p, pi, NW, reinterpret_cast<int*>(lds));
+    return;
+  }
   // rows the tile loads may touch: the resident rows that are already in the slab
   const int last_slab_row = max((pi.new_row >= 0 ? pi.new_row : pi.L) - 1, 0);
   if (early_tile && (pi.P != p.spec_P || pi.cap != p.spec_cap || pi.base != (int64_t)pi.s * p.spec_cap))
@@ -706,12 +726,12 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
     else request_tile_dma(std::true_type{}, kbase_s, vbase_s, trow0, last_slab_row);
   }
 
-  // Fused step: every wave of every workgroup of the sequence takes a ticket as soon as its last
-  // load from the slab has landed (the tables were read at the start); whoever draws the last one
-  // may write the beacon row and update the tables.  The answer is only looked at after the wave
-  // merge, so the atomic's round trip (about a microsecond) hides behind the remaining compute.
-  // (Of a sequence cut into chunks the workgroup that folds a pair's takes one for the pair: a ticket for every wave
-  // of every chunk were 1472 atomics on one counter for 3000 rows of 8 KV heads, 23.7 us a step instead of 12.2.)
+  // Fused step, whole sequence: every wave with rows takes a ticket as soon as its last load from the
+  // slab has landed (the tables were read at the start), a workgroup without rows takes one; whoever
+  // draws the last one may write the beacon row and update the tables.  The answer is only looked at
+  // after the wave merge, so the atomic's round trip (about a microsecond) hides behind the remaining
+  // compute.  (Of a sequence cut into chunks the workgroup that folds a pair's takes one for the pair: a ticket for
+  // every wave of every chunk were 1472 atomics on one counter for 3000 rows of 8 KV heads, 23.7 us a step instead of 12.2.)
   int ticket = -1;
   auto take_ticket = [&]() {
     if (pi.update && lane == 0 && (!CHUNKS || pi.nchunks == 1)) {
@@ -928,12 +948,7 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   merge_waves_and_store4<NW, DV, D, APITCH, CHUNKS>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
   if constexpr (CHUNKS) {
     if (pi.nchunks > 1) {
-      if (!last_chunk(p, pi, reinterpret_cast<int*>(lds))) return;
-      int drawn = -1;
-      if (pi.update && tid == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
-      merge_chunks<NW * 64, D>(p, pi);
-      if (!pi.update || wave != 0) return;
-      if (__builtin_amdgcn_readfirstlane(drawn) == p.Hkv - 1) finish_step<ROWB>(p, pi, lane);
+      close_pair<NW * 64, D, ROWB>(p, pi, reinterpret_cast<int*>(lds));
       return;
     }
   }
@@ -942,7 +957,7 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   if (!pi.update) return;
   wait_vmcnt<0>();     // the ticket has arrived
   landed(ticket);
-  if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv * VS * NW - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, VS * NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
   finish_step<ROWB>(p, pi, lane);
 }
 
@@ -962,8 +977,12 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
 
   touch_kernel_arguments();
   const PairInfo pi = pair_info(p, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x);
-  if (!pi.live) return;
-  const int L = pi.L, row_end = pi.row_end;
+  __shared__ int s_arrived;
+  if (!pi.live) {
+    close_without_chunk<256, D, RB>(p, pi, 1, &s_arrived);
+    return;
+  }
+  const int row_end = pi.row_end;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane / LPR, ls = lane - lr * LPR;
@@ -1121,19 +1140,18 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
     }
   }
   __syncthreads();
-  // Fused step: one ticket per workgroup, taken once all its waves have used the rows they read
-  // (the barrier above), or per pair, by the workgroup that folds its chunks; the answer comes back under the
-  // merge.  The workgroup that draws the sequence's last one finishes the step.
+  // Fused step, whole sequence: one ticket per workgroup, taken once all its waves have used the rows
+  // they read (the barrier above); the answer comes back under the merge.  The workgroup that draws the
+  // sequence's last one finishes the step.
   int ticket = -1;
   if (pi.nchunks == 1 && pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
   merge_waves_and_store<kValuWaves, D>(p, pi, s_m, s_l, s_acc, G, G * D);
   if (pi.nchunks > 1) {
-    if (!last_chunk(p, pi, reinterpret_cast<int*>(s_m))) return;
-    if (pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
-    merge_chunks<256, D>(p, pi);
+    close_pair<256, D, RB>(p, pi, &s_arrived);
+    return;
   }
   if (!pi.update || wave != 0) return;
-  if (__builtin_amdgcn_readfirstlane(ticket) != p.Hkv - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, 1, 1, p.max_chunks) - 1) return;
   finish_step<RB>(p, pi, lane);
 }
 

@@ -869,3 +869,21 @@ def test_sequences_cut_into_chunks(dev, B, Hq, Hkv, d, dtype, P, chunks):
     st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
     assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
     rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,dtype,P,rows", [
+    (100, 16, 2, 128, "f32", (59, 60, 61, 123, 20, 187), 64),      # one workgroup per compute unit, 600 of them
+    (70, 12, 2, 128, "bf16", (252, 253, 500, 509, 30, 760), 256),
+])
+def test_cut_plans_of_more_workgroups_than_run_at_once(dev, B, Hq, Hkv, d, dtype, P, rows):
+    # the later workgroups of a launch start when earlier ones are done; many of them have no rows, and the
+    # appended rows cross the lines where a sequence gets one chunk more
+    G = 9
+    P = np.resize(np.array(P, np.int32), B)
+    wl = W.Workload("rounds", 114, B, Hq, Hkv, d, dtype, P, np.full(B, G, np.int32),
+                    np.resize(np.array([4, 0, 7, 2, 0], np.int32), B))
+    rt, oc = make(wl, dev)
+    rt.cache.rows_per_workgroup = rows
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) >= 3, text
+    rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
