@@ -171,8 +171,8 @@ int32_t bc_append_kv(const bc_shape *shape, const bc_cache *cache, const void *k
  * (enough for the automatic plan; for a forced chunk size see bc_cache::rows_per_workgroup). */
 size_t bc_decode_workspace_bytes(const bc_shape *shape, int32_t max_cap);
 
-/* Zero a freshly allocated workspace (it holds per-sequence counters that the library
- * expects to find at zero and leaves at zero).  Call once after allocating it; a workspace
+/* Zero a freshly allocated workspace (it holds per-sequence counters that the step calls
+ * expect to find at zero and leave at zero).  Call once after allocating it; a workspace
  * allocated zero-filled needs no call.  Enqueues a fill kernel, no memset node. */
 int32_t bc_workspace_init(void *workspace, size_t workspace_bytes, void *stream);
 
@@ -191,7 +191,9 @@ int32_t bc_decode_plan_describe(const bc_shape *shape, const bc_cache *cache, ch
  *   j over all L_s = P+nb+w rows, kvh = floor(h / (Hq/Hkv)).
  * q: [B, Hq, d] in kv_dtype; out: [B, Hq, d] fp32 (fp32 accumulation throughout).
  * A sequence with L_s == 0 sets the state bit and its output is left untouched.
- * The result is deterministic: partial results are combined in a fixed order (no atomics).
+ * The result is deterministic: partial results are combined in a fixed order (no float atomics).
+ * The call asks nothing of the workspace's contents (where sequences are cut into chunks, a fill kernel in
+ * front of the launch clears the counters it uses).
  * Calls sharing one workspace must not overlap in time. */
 int32_t bc_decode_attn(const bc_shape *shape, const bc_cache *cache, const void *q,
                        float *out, const uint8_t *active, void *workspace,

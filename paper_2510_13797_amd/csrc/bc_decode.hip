@@ -1379,16 +1379,20 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.tickets = reinterpret_cast<int32_t*>(ws);
   p.part = reinterpret_cast<float*>(ws + pl.tickets_bytes + pl.arrivals_bytes);
   // a pair's chunks are counted on the line of its sequence's ticket counter; where that has not got a
-  // place for every KV head they have an array, cleared in front of the launch
+  // place for every KV head they have an array, cleared in front of the launch.  Attention alone takes no
+  // tickets and asks nothing of the workspace it is given: its counters are cleared in front of the launch too
+  // (a second launch, as the fold used to be; the steps, whose tickets start at zero anyway, do without).
   p.arrivals = p.tickets + 1;
   p.arrival_stride = kTicketStride;
+  size_t clear_bytes = !k ? pl.tickets_bytes : 0;
   if (pl.arrivals_bytes) {
     p.arrivals = reinterpret_cast<int32_t*>(ws + pl.tickets_bytes);
     p.arrival_stride = shape->Hkv;
-    if (pl.max_chunks > 1)
-      fill_zero_kernel<<<(int)std::min<size_t>(1024, (pl.arrivals_bytes + 1023) / 1024), 256, 0, hs>>>(
-          reinterpret_cast<uint32_t*>(p.arrivals), (int64_t)(pl.arrivals_bytes / 4));
+    clear_bytes = pl.arrivals_bytes;
   }
+  if (pl.max_chunks > 1 && clear_bytes)
+    fill_zero_kernel<<<(int)std::min<size_t>(1024, (clear_bytes + 1023) / 1024), 256, 0, hs>>>(
+        reinterpret_cast<uint32_t*>(pl.arrivals_bytes ? p.arrivals : p.tickets), (int64_t)(clear_bytes / 4));
   p.c = cache->c; p.nb_rw = cache->nb; p.w_rw = cache->w;
   p.new_k = static_cast<const char*>(k); p.new_v = static_cast<const char*>(v);
   p.bk = static_cast<const char*>(bk); p.bv = static_cast<const char*>(bv);

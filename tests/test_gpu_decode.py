@@ -887,3 +887,19 @@ def test_cut_plans_of_more_workgroups_than_run_at_once(dev, B, Hq, Hkv, d, dtype
     st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
     assert st == 0 and int(text.split("chunks=")[1].split()[0]) >= 3, text
     rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,dtype,P", [(3, 6, 2, 128, "bf16", (507, 40, 1100)), (1, 33, 33, 64, "bf16", (1000,)),
+                                                (65, 2, 2, 64, "f32", (130, 90))])
+def test_attention_does_not_depend_on_what_the_workspace_holds(dev, B, Hq, Hkv, d, dtype, P):
+    # a caller who only attends never has to clear the workspace, whatever other calls left in it
+    P = np.resize(np.array(P, np.int32), B)
+    wl = W.Workload("dirty", 115, B, Hq, Hkv, d, dtype, P, np.full(B, 8, np.int32), np.full(B, 3, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) > 1, text
+    for t, filler in enumerate((0xA5, 0x00, 0x01, 0xFF)):
+        rt.ws.fill_(filler)
+        rt.out.fill_(-3.0)
+        q = wl.step_q(t)
+        check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, t)
