@@ -173,7 +173,11 @@ size_t bc_decode_workspace_bytes(const bc_shape *shape, int32_t max_cap);
 
 /* Zero a freshly allocated workspace (it holds per-sequence counters that the step calls
  * expect to find at zero and leave at zero).  Call once after allocating it; a workspace
- * allocated zero-filled needs no call.  Enqueues a fill kernel, no memset node. */
+ * allocated zero-filled needs no call.  Enqueues a fill kernel, no memset node.
+ * One workspace may serve calls of different shapes one after another, if all of them pass the same
+ * workspace_bytes: the counters (128 bytes a sequence) lie at its front, partial results at its back, and the
+ * two may not meet.  The most that any of the shapes needs is enough while they differ only in B and max_cap
+ * and leave the plan to the library; otherwise add 128 bytes for every sequence of the largest batch. */
 int32_t bc_workspace_init(void *workspace, size_t workspace_bytes, void *stream);
 
 /* Which kernel, grid and chunking the decode calls use for this shape and cache (HOST fields of

@@ -1364,8 +1364,8 @@ static bool follows_order(const bc_shape* shape, const bc_cache* cache, const De
 // Attention launch shared by bc_decode_attn (k = beacon_k = NULL) and the fused bc_decode_step.
 static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, const DecodePlan& pl,
                                 const void* q, float* out, const uint8_t* active, void* workspace,
-                                const void* k, const void* v, const void* bk, const void* bv,
-                                hipStream_t hs, const int32_t* budget = nullptr,
+                                size_t workspace_bytes, const void* k, const void* v, const void* bk,
+                                const void* bv, hipStream_t hs, const int32_t* budget = nullptr,
                                 uint8_t* live = nullptr, bool beacon_row = false) {
   DecodeParams p;
   p.k_slab = static_cast<const char*>(cache->k_slab);
@@ -1377,7 +1377,9 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.active = active;
   char* ws = static_cast<char*>(workspace);
   p.tickets = reinterpret_cast<int32_t*>(ws);
-  p.part = reinterpret_cast<float*>(ws + pl.tickets_bytes + pl.arrivals_bytes);
+  // Counters from the front, partial results at the back: calls of another batch size that share the
+  // workspace find their counters as they left them.
+  p.part = reinterpret_cast<float*>(ws + (workspace_bytes - pl.part_bytes) / 256 * 256);
   // a pair's chunks are counted on the line of its sequence's ticket counter; where that has not got a
   // place for every KV head they have an array, cleared in front of the launch.  Attention alone takes no
   // tickets and asks nothing of the workspace it is given: its counters are cleared in front of the launch too
@@ -1510,7 +1512,7 @@ extern "C" int32_t bc_decode_attn(const bc_shape* shape, const bc_cache* cache, 
   DecodePlan pl;
   const int32_t st = check_attention_args(shape, cache, q, out, workspace, workspace_bytes, &pl);
   if (st != BC_OK) return st;
-  return launch_attention(shape, cache, pl, q, out, active, workspace, nullptr, nullptr, nullptr,
+  return launch_attention(shape, cache, pl, q, out, active, workspace, workspace_bytes, nullptr, nullptr, nullptr,
                           nullptr, as_stream(stream));
 }
 
@@ -1518,12 +1520,12 @@ extern "C" int32_t bc_decode_attn(const bc_shape* shape, const bc_cache* cache, 
 static int32_t decode_step_checked(const bc_shape* shape, const bc_cache* cache, const DecodePlan& pl,
                                    const void* k, const void* v, const void* q, float* out,
                                    const void* beacon_k, const void* beacon_v, const uint8_t* active,
-                                   void* workspace, void* stream) {
+                                   void* workspace, size_t workspace_bytes, void* stream) {
   if (!k || !v || !aligned16(k) || !aligned16(v)) return BC_ERR_ARG;
   if ((beacon_k == nullptr) != (beacon_v == nullptr)) return BC_ERR_ARG;
   if (beacon_k && (!aligned16(beacon_k) || !aligned16(beacon_v))) return BC_ERR_ARG;
   // one launch, whichever kernel serves the shape: append, attention and eviction fused
-  return launch_attention(shape, cache, pl, q, out, active, workspace, k, v, beacon_k, beacon_v,
+  return launch_attention(shape, cache, pl, q, out, active, workspace, workspace_bytes, k, v, beacon_k, beacon_v,
                           as_stream(stream));
 }
 
@@ -1534,7 +1536,8 @@ extern "C" int32_t bc_decode_step(const bc_shape* shape, const bc_cache* cache, 
   DecodePlan pl;
   const int32_t st = check_attention_args(shape, cache, q, out, workspace, workspace_bytes, &pl);
   if (st != BC_OK) return st;
-  return decode_step_checked(shape, cache, pl, k, v, q, out, beacon_k, beacon_v, active, workspace, stream);
+  return decode_step_checked(shape, cache, pl, k, v, q, out, beacon_k, beacon_v, active, workspace, workspace_bytes,
+                             stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -1599,7 +1602,7 @@ extern "C" int32_t bc_decode_step_noalloc(const bc_shape* shape, const bc_cache*
       reinterpret_cast<uint32_t*>(ws), n);
   st = launch_status();
   if (st != BC_OK) return st;
-  return decode_step_checked(shape, cache, pl, k, v, q, out, beacon_k, beacon_v, active, ws, stream);
+  return decode_step_checked(shape, cache, pl, k, v, q, out, beacon_k, beacon_v, active, ws, kScratchBytes, stream);
 }
 
 extern "C" int32_t bc_beacon_step(const bc_shape* shape, const bc_cache* cache, const void* k,
@@ -1610,7 +1613,7 @@ extern "C" int32_t bc_beacon_step(const bc_shape* shape, const bc_cache* cache, 
   if (st != BC_OK) return st;
   if (!k || !v || !aligned16(k) || !aligned16(v)) return BC_ERR_ARG;
   // one launch: beacon row at the tail, its attention, compaction
-  return launch_attention(shape, cache, pl, q, out, active, workspace, k, v, k, v,
+  return launch_attention(shape, cache, pl, q, out, active, workspace, workspace_bytes, k, v, k, v,
                           as_stream(stream), nullptr, nullptr, true);
 }
 
@@ -1627,6 +1630,6 @@ extern "C" int32_t bc_decode_step_budget(const bc_shape* shape, const bc_cache* 
   if (beacon_k && (!aligned16(beacon_k) || !aligned16(beacon_v))) return BC_ERR_ARG;
   // The cap is tested on the state the attention saw (before the eviction); the holder of the
   // sequence's last ticket clears the mask after the eviction has used it.
-  return launch_attention(shape, cache, pl, q, out, live, workspace, k, v, beacon_k, beacon_v,
+  return launch_attention(shape, cache, pl, q, out, live, workspace, workspace_bytes, k, v, beacon_k, beacon_v,
                           as_stream(stream), budget, live);
 }

@@ -903,3 +903,29 @@ def test_attention_does_not_depend_on_what_the_workspace_holds(dev, B, Hq, Hkv, 
         rt.out.fill_(-3.0)
         q = wl.step_q(t)
         check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, t)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,dtype,batches", [
+    (2, 1, 64, "f32", ((150, 130), (256, 131), (300, 40))),        # cut, cut, whole
+    (4, 2, 128, "bf16", ((3, 1100), (64, 200), (20, 1000))),
+])
+def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, batches):
+    # one workspace, sized for the largest batch, serves caches of several sizes in turn: the partial
+    # results of one do not lie over the counters of another.  Bit-equal to workspaces of their own.
+    import torch
+    runs = []
+    for i, (B, P) in enumerate(batches):
+        wl = W.Workload("share%d" % i, 116 + i, B, Hq, Hkv, d, dtype, np.full(B, P, np.int32), np.full(B, 8, np.int32),
+                        np.full(B, 3, np.int32))
+        runs.append((wl, make(wl, dev)[0], make(wl, dev)[0]))
+    nbytes = max(_bc().bc_decode_workspace_bytes(rt.shape, rt.max_cap) for _, rt, _ in runs)
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device=dev)
+    for _, _, shared in runs:
+        shared.ws, shared.ws_bytes = ws, nbytes
+    for t in range(1, 8):
+        for wl, own, shared in runs:
+            (k, v), q, (bk, bv) = wl.step_kv(t), wl.step_q(t), wl.beacon_kv(t)
+            assert torch.equal(own.decode_step(k, v, q, bk, bv), shared.decode_step(k, v, q, bk, bv)), (t, wl.B)
+    for _, own, shared in runs:
+        (na, wa, ea), (nb, wb, eb) = own.tables(), shared.tables()
+        assert list(na) == list(nb) and list(wa) == list(wb) and ea == eb == 0

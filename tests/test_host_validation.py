@@ -260,3 +260,27 @@ def test_noalloc_step_rejects_what_does_not_fit_its_scratch_array():
     assert call(big, cache(max_cap=4096, rows_per_workgroup=128)) == bc.BC_ERR_WORKSPACE
     # more counters than the array holds (128 bytes per sequence)
     assert call(shape(B=40000, Hq=1, Hkv=1, d=128, dtype=bc.BC_BF16), cache(max_cap=64)) == bc.BC_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,dtype", [(1, 1, 64, bc.BC_F32), (8, 1, 128, bc.BC_F32), (12, 2, 128, bc.BC_BF16),
+                                            (33, 33, 64, bc.BC_BF16), (64, 8, 64, bc.BC_F32), (4, 1, 64, bc.BC_BF16)])
+def test_batches_that_share_a_workspace_keep_their_counters(Hq, Hkv, d, dtype):
+    # counters: 128 bytes a sequence from the front; partial results at the back (at 256 bytes).  With the most bytes that
+    # either of two batches needs, the partials of neither reach the counters of the other.
+    pad = lambda g: 1 if g <= 1 else 2 if g <= 2 else 4 if g <= 4 else 6 if g <= 6 else 8
+    rows = []
+    for B in sorted({1, 2, 3, 5, 8, 16, 31, 32, 33, 48, 63, 64, 90, 127, 128, 129, 200, 255, 256, 257, 1000, 20000}):
+        s = shape(B=B, Hq=Hq, Hkv=Hkv, d=d, dtype=dtype)
+        most = 0
+        for cap in (40, 129, 300, 1000, 3000, 20000, 150000):
+            for plan in (0, bc.BC_PLAN_PLAIN_ALU):
+                st, text = bc.bc_decode_plan_describe(s, cache(max_cap=cap, plan=plan))
+                chunks = int(text.split("chunks=")[1].split()[0])
+                Gp = 8 if "lds_kernel" in text else pad(Hq // Hkv)
+                if chunks > 1:
+                    most = max(most, B * Hkv * chunks * (Gp * d + 32) * 4)
+        rows.append((B, bc.bc_decode_workspace_bytes(s, 150000), most))
+    assert any(part for _, _, part in rows)
+    for B1, bytes1, part in rows:
+        for B2, bytes2, _ in rows:
+            assert not part or 128 * B2 <= (max(bytes1, bytes2) - part) // 256 * 256, (B1, B2)
