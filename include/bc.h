@@ -315,7 +315,9 @@ int32_t bc_prefill_attn_ws(const bc_shape *shape, const void *q, const void *k, 
  * out / lse as the forward wrote them and dout: [total_rows, Hq, d] in bf16.  Results, fp32:
  * dq [total_rows, Hq, d], dk and dv [total_rows, Hkv, d] (summed over the query heads of a
  * group); every element is written, nothing needs zeroing.  total_rows: HOST copy of
- * row_offsets[B].  workspace: bc_prefill_bwd_workspace_bytes() bytes, no initialisation.
+ * row_offsets[B].  workspace: bc_prefill_bwd_workspace_bytes() bytes, no initialisation (two floats for every
+ * row and query head, and up to eight copies of dk and dv: the fewer rows there are, the more workgroups share
+ * the rows of a key).
  * No atomics: results are reproducible.  scale must be > 0 and finite (else BC_ERR_ARG). */
 size_t bc_prefill_bwd_workspace_bytes(const bc_shape *shape, int64_t total_rows);
 int32_t bc_prefill_attn_bwd(const bc_shape *shape, const void *q, const void *k, const void *v,

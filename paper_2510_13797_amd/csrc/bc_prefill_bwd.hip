@@ -489,6 +489,12 @@ static int dense_splits(const bc_shape* shape, int64_t total_rows) {
   return (int)(n < least || most < least ? least : n > most ? most : n);
 }
 
+// Floats of the workspace's first part (stat), rounded up so that the partials behind it start at 256 bytes:
+// they are stored and summed 16 bytes at a time, and an odd number of rows times heads would put them 8 off.
+static size_t stat_floats(const bc_shape* shape, int64_t total_rows) {
+  return ((size_t)total_rows * shape->Hq * 2 + 63) / 64 * 64;
+}
+
 }  // namespace bc
 
 using namespace bc;
@@ -496,7 +502,7 @@ using namespace bc;
 extern "C" size_t bc_prefill_bwd_workspace_bytes(const bc_shape* shape, int64_t total_rows) {
   if (check_shape(shape) != BC_OK || total_rows < 1) return 0;
   const int hs = dense_splits(shape, total_rows);
-  size_t bytes = (size_t)total_rows * shape->Hq * 2 * sizeof(float);
+  size_t bytes = stat_floats(shape, total_rows) * sizeof(float);
   if (hs > 1) bytes += (size_t)hs * 2 * total_rows * shape->Hkv * shape->d * sizeof(float);
   return bytes;
 }
@@ -527,7 +533,7 @@ extern "C" int32_t bc_prefill_attn_bwd(const bc_shape* shape, const void* q, con
   p.row_off = row_offsets; p.P = P; p.c = c;
   p.dq = dq; p.dk = dk; p.dv = dv;
   p.stat = static_cast<float*>(workspace);
-  p.part = p.stat + (size_t)total_rows * shape->Hq * 2;
+  p.part = p.stat + stat_floats(shape, total_rows);
   p.splits = dense_splits(shape, total_rows);
   p.total_rows = total_rows;
   p.D = shape->d;

@@ -284,3 +284,16 @@ def test_batches_that_share_a_workspace_keep_their_counters(Hq, Hkv, d, dtype):
     for B1, bytes1, part in rows:
         for B2, bytes2, _ in rows:
             assert not part or 128 * B2 <= (max(bytes1, bytes2) - part) // 256 * 256, (B1, B2)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,rows", [(5, 1, 64, 333), (3, 3, 128, 4097), (3, 1, 128, 1), (7, 1, 64, 1023), (12, 2, 128, 33)])
+def test_backward_partials_start_at_a_256_byte_boundary(Hq, Hkv, d, rows):
+    # the workspace is (lse, Delta) of every row and head, then partial dK and dV: 16-byte accesses, whole
+    # planes of rows * Hkv * d floats (a multiple of 256 bytes), whatever rows * Hq is
+    s = shape(B=1, Hq=Hq, Hkv=Hkv, d=d, dtype=bc.BC_BF16)
+    need = bc.bc_prefill_bwd_workspace_bytes(s, rows)
+    stat, plane = rows * Hq * 8, rows * Hkv * d * 4
+    parts = (need - stat) // (2 * plane)
+    assert parts >= (2 if Hq > Hkv else 0) and parts <= 8
+    if parts:
+        assert (need - parts * 2 * plane) % 256 == 0 and need - parts * 2 * plane - stat < 256
