@@ -232,10 +232,11 @@ int32_t bc_decode_step(const bc_shape *shape, const bc_cache *cache, const void 
  * and semantics as bc_decode_step without the workspace: the counters and partial results live in
  * a fixed array in device memory that belongs to the library: BC_NOALLOC_SCRATCH_BYTES and half as
  * much again for padding (one copy per GPU it runs on, held until the process ends).  The call allocates and frees nothing.  Its
- * plan must fit the array: B * 128 bytes of counters, plus - only for batches whose sequences are
- * split into chunks, and only if that fits, or for a forced chunk size - the partial results of
- * bc_decode_workspace_bytes(); a call that needs more returns BC_ERR_WORKSPACE
- * and launches nothing.  Every call on one GPU uses the same array (the counters are cleared at
+ * plan must fit BC_NOALLOC_SCRATCH_BYTES: B * 128 bytes of counters, plus - only for batches whose
+ * sequences are cut into chunks - d + 2 floats for every chunk and query head (the group padded to
+ * 8 heads, fp32: to 1, 2, 4, 6 or 8) and a counter for every (sequence, KV head) pair.  Every
+ * automatic plan fits up to B = 32768; a call that needs more (a forced chunk size on a large batch)
+ * returns BC_ERR_WORKSPACE and launches nothing.  Every call on one GPU uses the same array (the counters are cleared at
  * the start of each call): calls that overlap in time on one GPU, on whatever streams, race -
  * serialise them, or give the overlapping ones a workspace of their own through bc_decode_step. */
 #define BC_NOALLOC_SCRATCH_BYTES (4u << 20)

@@ -1379,7 +1379,7 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.tickets = reinterpret_cast<int32_t*>(ws);
   // Counters from the front, partial results at the back: calls of another batch size that share the
   // workspace find their counters as they left them.
-  p.part = reinterpret_cast<float*>(ws + (workspace_bytes - pl.part_bytes) / 256 * 256);
+  p.part = pl.max_chunks > 1 ? reinterpret_cast<float*>(ws + (workspace_bytes - pl.part_bytes) / 256 * 256) : nullptr;
   // a pair's chunks are counted on the line of its sequence's ticket counter; where that has not got a
   // place for every KV head they have an array, cleared in front of the launch.  Attention alone takes no
   // tickets and asks nothing of the workspace it is given: its counters are cleared in front of the launch too
@@ -1544,9 +1544,9 @@ extern "C" int32_t bc_decode_step(const bc_shape* shape, const bc_cache* cache, 
 // bc_decode_step for callers that cannot allocate: the workspace is a fixed array in device memory
 // ---------------------------------------------------------------------------
 namespace bc {
-// BC_NOALLOC_SCRATCH_BYTES of counters and results, and what the padding of the partials adds to them (at most 96
-// floats instead of 66: one head, d = 64).
+// BC_NOALLOC_SCRATCH_BYTES of counters and results, and what the padding of the partials to whole lines adds.
 constexpr size_t kScratchBytes = BC_NOALLOC_SCRATCH_BYTES / 2 * 3;
+static_assert(2 * (64 + kPartTail) <= 3 * (64 + 2), "the padding of a partial, at most that of one head with d = 64");
 // One copy per GPU the library runs on, at an address of its own, held until the process ends.
 // (In host code the array's name is only a handle: its device address comes from
 // hipGetSymbolAddress, once per device, below.)
@@ -1578,19 +1578,15 @@ extern "C" int32_t bc_decode_step_noalloc(const bc_shape* shape, const bc_cache*
   if (!k || !v || !aligned16(k) || !aligned16(v)) return BC_ERR_ARG;
   if ((beacon_k == nullptr) != (beacon_v == nullptr)) return BC_ERR_ARG;
   if (beacon_k && (!aligned16(beacon_k) || !aligned16(beacon_v))) return BC_ERR_ARG;
-  // what this call's plan touches: the per-sequence counters, and the partial results only when
-  // sequences are split into chunks
-  const size_t pairs = (size_t)shape->B * shape->Hkv;
-  auto results = [&]() {
-    return align256(pairs * 4) + align256(pairs * pl.max_chunks * pl.Gp * shape->d * 4) +
-           align256(pairs * pl.max_chunks * 2 * pl.Gp * 4);
-  };
-  if (pl.max_chunks > 1 && cache->rows_per_workgroup == 0 && pl.tickets_bytes + results() > BC_NOALLOC_SCRATCH_BYTES) {
-    pl.max_chunks = 1;            // (a cut that the array has no room for is left out)
-    pl.size_for(shape);
+  // What this call's plan may touch: the per-sequence counters and, when sequences are cut into chunks, a counter
+  // and the results (o, maximum, denominator) of every pair, without the padding the array has its other half
+  // for.  (The automatic plan cuts at most 256 pairs into 512 chunks together: some 2 MB.)
+  size_t need = pl.tickets_bytes;
+  if (pl.max_chunks > 1) {
+    const size_t pairs = (size_t)shape->B * shape->Hkv, heads = pairs * pl.max_chunks * pl.Gp;
+    need += align256(pairs * 4) + align256(heads * shape->d * 4) + align256(heads * 2 * 4);
   }
-  if (pl.tickets_bytes + (pl.max_chunks > 1 ? results() : 0) > BC_NOALLOC_SCRATCH_BYTES) return BC_ERR_WORKSPACE;
-  if (pl.max_chunks > 1 && pl.total() > kScratchBytes) return BC_ERR_WORKSPACE;
+  if (need > BC_NOALLOC_SCRATCH_BYTES) return BC_ERR_WORKSPACE;
   unsigned char* ws = nullptr;
   st = scratch_of_current_device(&ws);
   if (st != BC_OK) return st;

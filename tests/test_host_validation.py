@@ -297,3 +297,14 @@ def test_backward_partials_start_at_a_256_byte_boundary(Hq, Hkv, d, rows):
     assert parts >= (2 if Hq > Hkv else 0) and parts <= 8
     if parts:
         assert (need - parts * 2 * plane) % 256 == 0 and need - parts * 2 * plane - stat < 256
+
+
+def test_noalloc_step_takes_what_its_documented_size_holds():
+    # 128 bytes a sequence, d + 2 floats for every chunk and padded head, a counter a pair (what fits would be
+    # launched, so only the refusals can be looked at here)
+    call = lambda s, c: bc.bc_decode_step_noalloc(s, c, PTR, PTR, PTR, PTR, None, None, None, None)
+    assert call(shape(B=32769), cache()) == bc.BC_ERR_WORKSPACE
+    # 252 pairs in 4 chunks of 8 heads: 252 * 4 * 8 * 130 * 4 + 126 * 128 + 1024 = 4,210,432 bytes (250: 4,177,024)
+    assert call(shape(B=126, Hq=16, Hkv=2, d=128, dtype=bc.BC_BF16),
+                cache(max_cap=1024, rows_per_workgroup=256)) == bc.BC_ERR_WORKSPACE
+    assert call(shape(B=126, Hq=16, Hkv=2, d=128), cache(max_cap=256, rows_per_workgroup=64)) == bc.BC_ERR_WORKSPACE
