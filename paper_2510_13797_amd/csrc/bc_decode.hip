@@ -363,25 +363,40 @@ __device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairIn
   }
 }
 
+// The kernel arguments, to be read afresh: what only the end of a kernel needs holds no scalar registers before
+// (kept from the start, 38 of them went through vector lanes in front of the first tile requests: one sequence of
+// 1551 rows, 8 KV heads, 11.8 us a step instead of 10.8).
+__device__ __forceinline__ DecodeParams arguments_again() {
+  typedef __attribute__((address_space(4))) const DecodeParams const_params_t;
+  const_params_t* at = (const_params_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));
+  return *(const DecodeParams*)at;
+}
+
 // The end of a workgroup of a cut sequence.
 template <int NT, int D, int ROWB>
-__device__ __forceinline__ void close_pair(const DecodeParams& p, const PairInfo& pi, int* s_arrived) {
-  if (!last_arrival(p, pi, s_arrived)) return;
+__device__ __forceinline__ void close_pair(const PairInfo& pi, int* s_arrived) {
   int drawn = -1;
-  if (pi.update && threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
-  merge_chunks<NT, D>(p, pi);
+  {
+    const DecodeParams p = arguments_again();
+    if (!last_arrival(p, pi, s_arrived)) return;
+    if (pi.update && threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+  }
+  merge_chunks<NT, D>(arguments_again(), pi);
   if (!pi.update || threadIdx.x >= 64) return;
+  const DecodeParams p = arguments_again();
   if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, 0, pi.nchunks, p.max_chunks) - 1)
     finish_step<ROWB>(p, pi, threadIdx.x);
 }
 // The end of a workgroup without rows.  own: see tickets_due().
 template <int NT, int D, int ROWB>
-__device__ __forceinline__ void close_without_chunk(const DecodeParams& p, const PairInfo& pi, int own, int* s_arrived) {
+__device__ __forceinline__ void close_without_chunk(const PairInfo& pi, int own, int* s_arrived) {
   const CloseBy move = closing_move(pi.update, false, pi.nchunks);
-  if (move == CloseBy::arrival) close_pair<NT, D, ROWB>(p, pi, s_arrived);
+  if (move == CloseBy::arrival) close_pair<NT, D, ROWB>(pi, s_arrived);
   if (move != CloseBy::ticket) return;
   __syncthreads();                 // every wave has read the tables
   if (threadIdx.x >= 64) return;
+  const DecodeParams p = arguments_again();
   int drawn = -1;
   if (threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
   if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, own, pi.nchunks, p.max_chunks) - 1)
@@ -526,11 +541,14 @@ template <> __device__ __forceinline__ uint4 load16<true>(const char* p) { retur
 // from the start, in the order it is needed - and every stage waits only for what it is about to
 // read: scores and softmax of a tile run while its V rows are still on their way, so that behind
 // the last byte only one value product is left.
-template <int STREAM, int D, int VS, int NW, bool SHORT = false>
-__global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
+// CHUNKS: the plan cuts sequences into chunks.  A kernel of its own: with the fold compiled into the kernel of
+// whole sequences, 34 scalar registers of that spilled (200 pairs of 1000 rows: 20.6 us a step without, 21.2 with;
+// 320 of 1200: 45.2, 46.6).
+template <int STREAM, int D, int VS, int NW, bool SHORT, bool CHUNKS>
+__device__ __forceinline__ void decode_lds(const DecodeParams& p) {
+  static_assert(!CHUNKS || (VS == 1 && !SHORT), "the straight-line form and the V halves have whole sequences");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   constexpr bool KSTREAM = STREAM == 1, VSTREAM = STREAM >= 1;
-  constexpr bool CHUNKS = VS == 1 && !SHORT;         // the sequence may be cut into chunks
   constexpr int DV = D / VS;               // V (and output) columns of this workgroup
   constexpr int VROWB = DV * 2;            // bytes of its part of a V row, = row pitch of the V tile in LDS
   constexpr int VUPR = VROWB / 16;
@@ -666,7 +684,7 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   }
   if (nothing_to_do) {
     wait_vmcnt<0>();
-    if constexpr (CHUNKS) close_without_chunk<NW * 64, D, ROWB>(p, pi, NW, reinterpret_cast<int*>(lds));
+    if constexpr (CHUNKS) close_without_chunk<NW * 64, D, ROWB>(pi, NW, reinterpret_cast<int*>(lds));
     return;
   }
   // rows the tile loads may touch: the resident rows that are already in the slab
@@ -948,7 +966,7 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   merge_waves_and_store4<NW, DV, D, APITCH, CHUNKS>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
   if constexpr (CHUNKS) {
     if (pi.nchunks > 1) {
-      close_pair<NW * 64, D, ROWB>(p, pi, reinterpret_cast<int*>(lds));
+      close_pair<NW * 64, D, ROWB>(pi, reinterpret_cast<int*>(lds));
       return;
     }
   }
@@ -959,6 +977,15 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
   landed(ticket);
   if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, VS * NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
   finish_step<ROWB>(p, pi, lane);
+}
+
+template <int STREAM, int D, int VS, int NW, bool SHORT = false>
+__global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
+  decode_lds<STREAM, D, VS, NW, SHORT, false>(p);
+}
+template <int STREAM, int D, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_lds_cut_kernel(DecodeParams p) {
+  decode_lds<STREAM, D, 1, NW, false, true>(p);
 }
 
 // ---------------------------------------------------------------------------
@@ -979,7 +1006,7 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   const PairInfo pi = pair_info(p, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x);
   __shared__ int s_arrived;
   if (!pi.live) {
-    close_without_chunk<256, D, RB>(p, pi, 1, &s_arrived);
+    close_without_chunk<256, D, RB>(pi, 1, &s_arrived);
     return;
   }
   const int row_end = pi.row_end;
@@ -1147,7 +1174,7 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   if (pi.nchunks == 1 && pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
   merge_waves_and_store<kValuWaves, D>(p, pi, s_m, s_l, s_acc, G, G * D);
   if (pi.nchunks > 1) {
-    close_pair<256, D, RB>(p, pi, &s_arrived);
+    close_pair<256, D, RB>(pi, &s_arrived);
     return;
   }
   if (!pi.update || wave != 0) return;
@@ -1258,6 +1285,7 @@ struct LdsLaunch {
   int lds_bytes;
 };
 #define BC_LDS_KERNEL(...) decode_lds_kernel<__VA_ARGS__>, "bc::decode_lds_kernel<" #__VA_ARGS__ ">"
+#define BC_LDS_CUT_KERNEL(...) decode_lds_cut_kernel<__VA_ARGS__>, "bc::decode_lds_cut_kernel<" #__VA_ARGS__ ">"
 
 static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, const DecodePlan& pl,
                                  bool ordered) {
@@ -1293,17 +1321,26 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
                             : LdsLaunch{BC_LDS_KERNEL(1, 128, 2, 8), g2, t8, l8};
     return LdsLaunch{BC_LDS_KERNEL(2, 128, 2, 8), g2, t8, l8};
   }
+  // Workgroups of four waves, two per compute unit (64 KB of LDS each at d = 128), so that one's start
+  // and end phases - tables, first bytes, merge, store - overlap with the other's streaming: for
+  // sequences cut into chunks of more pairs than eight-wave workgroups serve well (see make_plan), and
+  // with more pairs than the chip holds workgroups and short caches.  Measured at 512 pairs of 512
+  // rows: 28.2 -> 25.4 us; with long ragged sequences (512 pairs of up to 2700 rows) the longest
+  // streams set the pace and eight waves are faster (54.5 against 62.5 us).
+  const bool small = stream && !(cache->plan & BC_PLAN_NO_SMALL_WORKGROUPS);
+  if (pl.max_chunks > 1) {
+    if (shape->d == 128) {
+      if (small && pl.R == 0 && pairs > kEightWavePairs)
+        return LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 4), grid, 4 * 64, kLdsBytes / 2};
+      return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 8), grid, kLdsWaves * 64, kLdsBytes}
+                    : LdsLaunch{BC_LDS_CUT_KERNEL(0, 128, 8), grid, kLdsWaves * 64, kLdsBytes};
+    }
+    return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 64, 8), grid, kLdsWaves * 64, kLdsBytes / 2}
+                  : LdsLaunch{BC_LDS_CUT_KERNEL(0, 64, 8), grid, kLdsWaves * 64, kLdsBytes / 2};
+  }
   if (shape->d == 128) {
-    // More pairs than the chip holds workgroups, and short caches: workgroups of four waves, two
-    // per compute unit (64 KB of LDS each), so that one's start and end phases - tables, first
-    // bytes, merge, store - overlap with the other's streaming.  Measured at 512 pairs of 512
-    // rows: 28.2 -> 25.4 us; with long ragged sequences (512 pairs of up to 2700 rows) the longest
-    // streams set the pace and eight waves are faster (54.5 against 62.5 us).
-    // The same for sequences cut into chunks of more pairs than eight-wave workgroups serve well.
-    const bool four = (pl.max_chunks > 1 ? pl.R == 0 && pairs > kEightWavePairs
-                                         : pairs > kLptMinPairs && cache->max_cap <= kSplitWaves12MaxCap) &&
-                      stream && !(cache->plan & BC_PLAN_NO_SMALL_WORKGROUPS);
-    if (four) return LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 4), grid, 4 * 64, kLdsBytes / 2};
+    if (small && pairs > kLptMinPairs && cache->max_cap <= kSplitWaves12MaxCap)
+      return LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 4), grid, 4 * 64, kLdsBytes / 2};
     if (two8) return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes}
                             : LdsLaunch{BC_LDS_KERNEL(0, 128, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes};
     return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8), grid, kLdsWaves * 64, kLdsBytes}
@@ -1323,6 +1360,11 @@ static int32_t enable_big_lds() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return BC_ERR_HIP;
   if (done[dev].load(std::memory_order_acquire)) return BC_OK;
   const void* kernels[] = {reinterpret_cast<const void*>(decode_lds_kernel<1, 128, 1, 4>),
+                           reinterpret_cast<const void*>(decode_lds_cut_kernel<1, 128, 4>),
+                           reinterpret_cast<const void*>(decode_lds_cut_kernel<0, 128, 8>),
+                           reinterpret_cast<const void*>(decode_lds_cut_kernel<1, 128, 8>),
+                           reinterpret_cast<const void*>(decode_lds_cut_kernel<0, 64, 8>),
+                           reinterpret_cast<const void*>(decode_lds_cut_kernel<1, 64, 8>),
                            reinterpret_cast<const void*>(decode_lds_kernel<0, 128, 1, 8>),
                            reinterpret_cast<const void*>(decode_lds_kernel<1, 128, 1, 8>),
                            reinterpret_cast<const void*>(decode_lds_kernel<0, 128, 1, 8, true>),

@@ -273,13 +273,13 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
     subprocess.check_call([hipcc] + flags + ["-w", "-I", os.path.join(ROOT, "include"), "-S",
                                              "--cuda-device-only", src, "-o", out])
     text = open(out).read().split("\n")
-    starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc1[78]decode_(lds|valu)_kernel\w+:", l)]
-    assert len(starts) >= 10 + 20
+    starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc\d\ddecode_(lds|lds_cut|valu)_kernel\w+:", l)]
+    assert len(starts) >= 16 + 5 + 20
     for s in starts:
         e = next(i for i in range(s, len(text)) if text[i].startswith(".Lfunc_end"))
         marked = _instructions(text[s:e])
         body = [l[:-len(HAND)] if l.endswith(HAND) else l for l in marked]
-        if "decode_lds_kernel" in text[s]:
+        if "decode_lds_" in text[s]:
             assert any(l.startswith("global_load_lds_dwordx4") for l in body)
             # M0 (the LDS address of a DMA load) is set by the hand-written sequence itself, right in
             # front of every such load, and nothing else in the kernel touches it
