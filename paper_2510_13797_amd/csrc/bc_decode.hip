@@ -1003,7 +1003,7 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   constexpr int ROWS_PER_PASS = kValuWaves * RPI * U;
 
   touch_kernel_arguments();
-  const PairInfo pi = pair_info(p, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x);
+  const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, (int)blockIdx.z);
   __shared__ int s_arrived;
   if (!pi.live) {
     close_without_chunk<256, D, RB>(pi, 1, &s_arrived);
@@ -1203,13 +1203,15 @@ struct DecodePlan {
 
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
 
-constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kEightWavePairs = 32;       // see make_plan
+constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kFewPairs = 32;             // see make_plan
 constexpr long kMostChunks = 64;
 constexpr int kChunkRowsMax = 512;    // rows a chunk of the matrix kernel need not go beyond: two passes of eight waves
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
 
-static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits) {
+// alone: attention without a step.
+static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits, bool alone = false) {
   DecodePlan pl;
+  const long npairs = (long)sh->B * sh->Hkv;
   pl.lds = sh->kv_dtype == BC_BF16 && !(plan_bits & BC_PLAN_PLAIN_ALU);
   if (pl.lds) {
     pl.Gp = 8;
@@ -1220,9 +1222,15 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     const int lpr = sh->d / epl, rpi = 64 / lpr;
     pl.rows_per_pass = kValuWaves * rpi * 8;
   }
-  const long npairs = (long)sh->B * sh->Hkv;
   pl.chunk_rows = pl.lds ? std::min(kChunkRowsMax, std::max(2 * kTileRows, (max_cap + 15) / 16)) : pl.rows_per_pass;
-  pl.split_rows = pl.lds ? kSplitMinRows : pl.rows_per_pass + 1;
+  pl.split_rows = kSplitMinRows;
+  int split_cap = kSplitMinCap;         // capacity from which on the plan has chunks at all
+  if (!pl.lds) {
+    // (a step reads its appended row behind the passes over the slab's)
+    const int whole_passes = (npairs > kFewPairs || pl.Gp * sh->d >= 512 ? 1 : 2) + (alone ? 1 : 0);
+    pl.split_rows = whole_passes * pl.rows_per_pass + 2;
+    split_cap = (alone ? 4 : whole_passes) * pl.rows_per_pass + 1;
+  }
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
     int R = ((rows_override + pl.rows_per_pass - 1) / pl.rows_per_pass) * pl.rows_per_pass;
@@ -1244,11 +1252,24 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster (d = 128, 8
     // pairs, whole against cut: 700 rows 7.9, 9.2 us; 850: 8.9, 9.5; 1000: 9.4, 9.7; 2 pairs, 1000 rows: 9.25, 8.7);
     // where the batch has longer sequences the shorter ones run in the tile loop, cut from 512 rows on (700 rows
-    // whole: 10.1 us).  The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of some 5 us: cut
-    // from the second pass on, with more pairs too (fp32, 64 sequences of 500 rows, 12/2 heads: 62.8 -> 28.2 us).
-    const long at_once = pl.lds && npairs <= kEightWavePairs ? 256 : 512, most_pairs = pl.lds ? 127 : 256;
+    // whole: 10.1 us).
+    // The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of 1 to 7 us (by group and d), against
+    // some 2 us that a fold takes: cut from the second pass on, or from the third where a pass is short and the
+    // batch is small (whole and cut at the second / third pass: 2 pairs, d = 64, groups of one 8.2, 8.9 / 9.3, 9.0
+    // us; 8 pairs, d = 128, groups of two 10.1, 9.9 / 12.0, 9.9, of six 17.0, 15.0 / 22.2, 15.4; 128 pairs, d = 64,
+    // groups of four 13.1, 13.7 / 19.1, 14.7), with up to 256 pairs (fp32, 64 sequences of 500 rows, 12/2 heads: 62.8
+    // -> 27.8 us).  The lengths are not known here: a batch whose sequences are all within the first pass pays for
+    // the workgroups they do not fill, 0 to 0.1 us with up to 32 pairs, 1.5 to 2.5 with more.  256 workgroups run
+    // at once with groups of seven or eight, and of three or more of bf16 rows (over 256 registers), otherwise 512;
+    // beyond that a second round takes more than the cut saves (200 pairs, groups of eight, 500 rows: whole 73.5
+    // us, in 400 workgroups 83.7).  Attention alone has a launch in front to clear its counters, some 1.5 us: its
+    // sequences are cut one pass later, and by capacities beyond four passes.
+    const bool eight_waves = npairs <= kFewPairs ||
+                             (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
+    const bool one_per_cu = pl.lds ? eight_waves : pl.Gp == 8 || (sh->kv_dtype == BC_BF16 && pl.Gp >= 4);
+    const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : 256;
     long chunks = 1;
-    if (npairs <= most_pairs && max_cap >= (pl.lds ? kSplitMinCap : pl.split_rows)) {
+    if (npairs <= most_pairs && max_cap >= split_cap) {
       chunks = at_once / npairs;
       const long by_rows = (max_cap + pl.chunk_rows - 1) / pl.chunk_rows, most = npairs < 128 ? kMostChunks : 4;
       if (chunks > by_rows) chunks = by_rows;
@@ -1257,12 +1278,17 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.R = 0;                                        // spread evenly, decided per sequence
     pl.max_chunks = (int)chunks;
   }
-  // Workspace sizing: the most chunks the automatic plan can choose (64 with few pairs, one
-  // otherwise); a forced chunk size on a large batch may use up to four.
+  // Workspace sizing: the most chunks the automatic plan can choose, 64 with few pairs and four otherwise (a
+  // forced chunk size on a large batch may use as many).
   if (rows_override == kPlanForSizing) pl.max_chunks = npairs < 128 ? 64 : 4;
   pl.size_for(sh);
   return pl;
 }
+
+// The plain-ALU kernel's grid, (KV head, sequence, chunk): the first chunks of all pairs lie side by side and
+// spread over the XCDs, to which workgroups go in turn.  With the chunk in front, short sequences of a plan of
+// four chunks had all their rows on two XCDs of the eight.
+static dim3 valu_grid(const bc_shape* shape, const DecodePlan& pl) { return dim3(shape->Hkv, shape->B, pl.max_chunks); }
 
 template <typename T, int D>
 static void launch_valu(const DecodeParams& p, int G, dim3 grid, hipStream_t st) {
@@ -1330,7 +1356,7 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
   const bool small = stream && !(cache->plan & BC_PLAN_NO_SMALL_WORKGROUPS);
   if (pl.max_chunks > 1) {
     if (shape->d == 128) {
-      if (small && pl.R == 0 && pairs > kEightWavePairs)
+      if (small && pl.R == 0 && pairs > kFewPairs)
         return LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 4), grid, 4 * 64, kLdsBytes / 2};
       return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 8), grid, kLdsWaves * 64, kLdsBytes}
                     : LdsLaunch{BC_LDS_CUT_KERNEL(0, 128, 8), grid, kLdsWaves * 64, kLdsBytes};
@@ -1454,7 +1480,7 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.spec_P = (cache->plan & BC_PLAN_IGNORE_PROMISE) ? 0 : cache->uniform_P;
   p.spec_cap = cache->uniform_cap;
 
-  const dim3 grid(pl.max_chunks, shape->Hkv, shape->B);
+  const dim3 grid = valu_grid(shape, pl);
   if (pl.lds) {
     const int32_t st = enable_big_lds();
     if (st != BC_OK) return st;
@@ -1472,7 +1498,7 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
 
 static int32_t check_attention_args(const bc_shape* shape, const bc_cache* cache, const void* q,
                                     const float* out, const void* workspace, size_t workspace_bytes,
-                                    DecodePlan* pl) {
+                                    DecodePlan* pl, bool alone = false) {
   int32_t st = check_shape(shape);
   if (st != BC_OK) return st;
   st = check_cache(cache);
@@ -1481,7 +1507,7 @@ static int32_t check_attention_args(const bc_shape* shape, const bc_cache* cache
   if (shape->B > 65535 || shape->Hkv > 65535) return BC_ERR_SHAPE;      // grid dimensions
   if (!nonnegative_finite(shape->scale)) return BC_ERR_ARG;   // the kernels take maxima of unscaled scores
   if (cache->rows_per_workgroup < 0 || (cache->plan & ~BC_PLAN_ALL_BITS)) return BC_ERR_ARG;
-  *pl = make_plan(shape, cache->max_cap, cache->rows_per_workgroup, cache->plan);
+  *pl = make_plan(shape, cache->max_cap, cache->rows_per_workgroup, cache->plan, alone);
   if ((cache->plan & BC_PLAN_NEED_MATRIX_KERNEL) && !pl->lds) return BC_ERR_SHAPE;
   if (!workspace || !aligned16(workspace) || workspace_bytes < pl->total()) return BC_ERR_WORKSPACE;
   return BC_OK;
@@ -1541,9 +1567,10 @@ extern "C" int32_t bc_decode_plan_describe(const bc_shape* shape, const bc_cache
     snprintf(text, text_bytes, "%s grid=(%u,%u,%u) threads=%d lds=%d chunks=%d%s", k.name, k.grid.x,
              k.grid.y, k.grid.z, k.threads, k.lds_bytes, pl.max_chunks, merged);
   } else {
-    snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8> grid=(%d,%d,%d) threads=256 chunks=%d%s",
-             shape->kv_dtype == BC_BF16 ? "bc::bf16_t" : "float", shape->d, pl.Gp, pl.max_chunks,
-             shape->Hkv, shape->B, pl.max_chunks, merged);
+    const dim3 grid = valu_grid(shape, pl);
+    snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8> grid=(%u,%u,%u) threads=256 chunks=%d%s",
+             shape->kv_dtype == BC_BF16 ? "bc::bf16_t" : "float", shape->d, pl.Gp, grid.x, grid.y, grid.z,
+             pl.max_chunks, merged);
   }
   return BC_OK;
 }
@@ -1552,7 +1579,7 @@ extern "C" int32_t bc_decode_attn(const bc_shape* shape, const bc_cache* cache, 
                                   float* out, const uint8_t* active, void* workspace,
                                   size_t workspace_bytes, void* stream) {
   DecodePlan pl;
-  const int32_t st = check_attention_args(shape, cache, q, out, workspace, workspace_bytes, &pl);
+  const int32_t st = check_attention_args(shape, cache, q, out, workspace, workspace_bytes, &pl, true);
   if (st != BC_OK) return st;
   return launch_attention(shape, cache, pl, q, out, active, workspace, workspace_bytes, nullptr, nullptr, nullptr,
                           nullptr, as_stream(stream));

@@ -890,7 +890,7 @@ def test_cut_plans_of_more_workgroups_than_run_at_once(dev, B, Hq, Hkv, d, dtype
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,dtype,P", [(3, 6, 2, 128, "bf16", (507, 40, 1100)), (1, 33, 33, 64, "bf16", (1000,)),
-                                                (65, 2, 2, 64, "f32", (130, 90))])
+                                                (65, 2, 2, 64, "f32", (600, 90))])
 def test_attention_does_not_depend_on_what_the_workspace_holds(dev, B, Hq, Hkv, d, dtype, P):
     # a caller who only attends never has to clear the workspace, whatever other calls left in it
     P = np.resize(np.array(P, np.int32), B)
@@ -929,3 +929,23 @@ def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, ba
     for _, own, shared in runs:
         (na, wa, ea), (nb, wb, eb) = own.tables(), shared.tables()
         assert list(na) == list(nb) and list(wa) == list(wb) and ea == eb == 0
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [
+    (2, 8, 1, 128, (62, 66), 2),                     # cut from the second pass over the slab's rows on
+    (2, 2, 1, 64, (126, 250), 1),                    # small batch and short passes: from the third
+    (2, 2, 1, 64, (126, 255), 3),
+    (64, 16, 2, 128, (62, 260, 125), 2),             # groups of eight: one workgroup per compute unit
+    (65, 16, 2, 128, (62, 260, 125), 1),
+    (128, 3, 1, 64, (126, 400, 255), 4),
+])
+def test_fp32_sequences_cut_at_their_passes(dev, B, Hq, Hkv, d, P, chunks):
+    G = 7
+    P = np.resize(np.array(P, np.int32), B)
+    wl = W.Workload("passes", 119, B, Hq, Hkv, d, "f32", P, np.full(B, G, np.int32), np.full(B, 3, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
+    rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
+    q = wl.step_q(77)
+    check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, 77)
