@@ -403,20 +403,16 @@ __device__ __forceinline__ void close_without_chunk(const PairInfo& pi, int own,
     finish_step<ROWB>(p, pi, threadIdx.x);
 }
 
-// Epilogue shared by both kernels: s_m/s_l/s_acc hold one (m, l, o) per wave in LDS;
-// merge them in wave order and write the result or the chunk partial.
-template <int NW, int D, int DOUT = D, int APITCH = D>
+// Epilogue of the plain-ALU kernel: s_m/s_l/s_acc hold one (m, l, o) per wave in LDS; merge them in wave order
+// and write the result or the chunk partial.  CHUNKS: the sequence may be cut into chunks.
+template <int NW, int D, bool CHUNKS>
 __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, const PairInfo& pi,
                                                       const float* s_m, const float* s_l,
                                                       const float* s_acc, int ml_stride,
-                                                      int acc_stride, int col0 = 0) {
-  // APITCH: floats between the accumulator rows of two heads in s_acc
+                                                      int acc_stride) {
   // ml_stride, acc_stride: floats between the entries of two waves in s_m / s_l and in s_acc
-  // D: columns this workgroup holds (all DOUT of a head, or one half starting at col0)
   const int nout = p.g * D;
-  float* po = chunk_partial(p, pi, D, pi.chunk);
-  float* pml = po + p.Gp * D;
-  float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * DOUT + col0;
+  float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * D;
   // (NW * 64 threads: the block size read from the launch descriptor would be one more scalar-cache miss)
   for (int i = threadIdx.x; i < nout; i += NW * 64) {
     const int h = i / D, x = i - h * D;
@@ -428,11 +424,13 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
     for (int wv = 0; wv < NW; ++wv) {
       const float a = fast_exp2(s_m[wv * ml_stride + h] - mx);
       lsum += s_l[wv * ml_stride + h] * a;
-      o += s_acc[wv * acc_stride + h * APITCH + x] * a;
+      o += s_acc[wv * acc_stride + h * D + x] * a;
     }
-    if (pi.nchunks == 1) {
-      __builtin_nontemporal_store(o / lsum, outp + (D == DOUT ? i : h * DOUT + x));   // streamed out: nothing left dirty in L2
+    if (!CHUNKS || pi.nchunks == 1) {
+      __builtin_nontemporal_store(o / lsum, outp + i);   // streamed out: nothing left dirty in L2
     } else {
+      float* po = chunk_partial(p, pi, D, pi.chunk);
+      float* pml = po + p.Gp * D;
       store_part(po + i, o);
       if (x == 0) {
         store_part(pml + h, mx);
@@ -444,7 +442,6 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
 
 // The same merge, four output columns per thread (128-bit LDS reads and stores): fewer waves
 // take part, which shortens this serial tail of the matrix-core kernel.
-// CHUNKS: the sequence may be cut into chunks.
 template <int NW, int D, int DOUT, int APITCH, bool CHUNKS>
 __device__ __forceinline__ void merge_waves_and_store4(const DecodeParams& p, const PairInfo& pi,
                                                        const float* s_m, const float* s_l,
@@ -993,7 +990,9 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_cut_kernel(DecodeParams p)
 // ---------------------------------------------------------------------------
 constexpr int kValuWaves = 4;
 
-template <typename T, int D, int G, int U>
+// CHUNKS: as for the matrix kernel (whole sequences with the fold compiled in: 128 pairs of 20 rows, d = 64, 8.05 us
+// a step instead of 7.8).
+template <typename T, int D, int G, int U, bool CHUNKS>
 __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   constexpr int ES = Elem<T>::size;
   constexpr int EPL = Elem<T>::per16;   // elements per lane per row
@@ -1006,7 +1005,7 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, (int)blockIdx.z);
   __shared__ int s_arrived;
   if (!pi.live) {
-    close_without_chunk<256, D, RB>(pi, 1, &s_arrived);
+    if constexpr (CHUNKS) close_without_chunk<256, D, RB>(pi, 1, &s_arrived);
     return;
   }
   const int row_end = pi.row_end;
@@ -1171,14 +1170,16 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   // they read (the barrier above); the answer comes back under the merge.  The workgroup that draws the
   // sequence's last one finishes the step.
   int ticket = -1;
-  if (pi.nchunks == 1 && pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
-  merge_waves_and_store<kValuWaves, D>(p, pi, s_m, s_l, s_acc, G, G * D);
-  if (pi.nchunks > 1) {
-    close_pair<256, D, RB>(pi, &s_arrived);
-    return;
+  if ((!CHUNKS || pi.nchunks == 1) && pi.update && tid == 0) ticket = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+  merge_waves_and_store<kValuWaves, D, CHUNKS>(p, pi, s_m, s_l, s_acc, G, G * D);
+  if constexpr (CHUNKS) {
+    if (pi.nchunks > 1) {
+      close_pair<256, D, RB>(pi, &s_arrived);
+      return;
+    }
   }
   if (!pi.update || wave != 0) return;
-  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, 1, 1, p.max_chunks) - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, 1, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
   finish_step<RB>(p, pi, lane);
 }
 
@@ -1290,14 +1291,19 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
 // four chunks had all their rows on two XCDs of the eight.
 static dim3 valu_grid(const bc_shape* shape, const DecodePlan& pl) { return dim3(shape->Hkv, shape->B, pl.max_chunks); }
 
+template <typename T, int D, int G>
+static void launch_valu_group(const DecodeParams& p, dim3 grid, hipStream_t st) {
+  if (p.max_chunks > 1) decode_valu_kernel<T, D, G, 8, true><<<grid, 256, 0, st>>>(p);
+  else decode_valu_kernel<T, D, G, 8, false><<<grid, 256, 0, st>>>(p);
+}
 template <typename T, int D>
 static void launch_valu(const DecodeParams& p, int G, dim3 grid, hipStream_t st) {
   switch (G) {
-    case 1: decode_valu_kernel<T, D, 1, 8><<<grid, 256, 0, st>>>(p); break;
-    case 2: decode_valu_kernel<T, D, 2, 8><<<grid, 256, 0, st>>>(p); break;
-    case 4: decode_valu_kernel<T, D, 4, 8><<<grid, 256, 0, st>>>(p); break;
-    case 6: decode_valu_kernel<T, D, 6, 8><<<grid, 256, 0, st>>>(p); break;
-    default: decode_valu_kernel<T, D, 8, 8><<<grid, 256, 0, st>>>(p); break;
+    case 1: launch_valu_group<T, D, 1>(p, grid, st); break;
+    case 2: launch_valu_group<T, D, 2>(p, grid, st); break;
+    case 4: launch_valu_group<T, D, 4>(p, grid, st); break;
+    case 6: launch_valu_group<T, D, 6>(p, grid, st); break;
+    default: launch_valu_group<T, D, 8>(p, grid, st); break;
   }
 }
 
@@ -1568,9 +1574,9 @@ extern "C" int32_t bc_decode_plan_describe(const bc_shape* shape, const bc_cache
              k.grid.y, k.grid.z, k.threads, k.lds_bytes, pl.max_chunks, merged);
   } else {
     const dim3 grid = valu_grid(shape, pl);
-    snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8> grid=(%u,%u,%u) threads=256 chunks=%d%s",
-             shape->kv_dtype == BC_BF16 ? "bc::bf16_t" : "float", shape->d, pl.Gp, grid.x, grid.y, grid.z,
-             pl.max_chunks, merged);
+    snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8, %s> grid=(%u,%u,%u) threads=256 chunks=%d%s",
+             shape->kv_dtype == BC_BF16 ? "bc::bf16_t" : "float", shape->d, pl.Gp, pl.max_chunks > 1 ? "true" : "false",
+             grid.x, grid.y, grid.z, pl.max_chunks, merged);
   }
   return BC_OK;
 }

@@ -276,7 +276,7 @@ def test_batches_that_share_a_workspace_keep_their_counters(Hq, Hkv, d, dtype):
             for plan in (0, bc.BC_PLAN_PLAIN_ALU):
                 st, text = bc.bc_decode_plan_describe(s, cache(max_cap=cap, plan=plan))
                 chunks = int(text.split("chunks=")[1].split()[0])
-                Gp = 8 if "lds_kernel" in text else pad(Hq // Hkv)
+                Gp = 8 if "decode_lds_" in text else pad(Hq // Hkv)
                 if chunks > 1:
                     most = max(most, B * Hkv * chunks * (Gp * d + 32) * 4)
         rows.append((B, bc.bc_decode_workspace_bytes(s, 150000), most))

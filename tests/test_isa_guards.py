@@ -274,7 +274,7 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
                                              "--cuda-device-only", src, "-o", out])
     text = open(out).read().split("\n")
     starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc\d\ddecode_(lds|lds_cut|valu)_kernel\w+:", l)]
-    assert len(starts) >= 16 + 5 + 20
+    assert len(starts) >= 16 + 5 + 20 + 20
     for s in starts:
         e = next(i for i in range(s, len(text)) if text[i].startswith(".Lfunc_end"))
         marked = _instructions(text[s:e])
