@@ -7,14 +7,14 @@
 // A row may start at any element (V odd in bf16: every second row is 2 bytes off): the elements in
 // front of its first 16-byte boundary and behind its last one are taken one by one by the first
 // threads, everything between by 16-byte units (509 rows of 50,257 bf16, loss and gradient pass: 63 -> 13 and
-// 73 -> 23 us against one element per load).
+// 73 -> 20 us against one element per load).
 #include "bc_common.h"
 
 namespace bc {
 namespace {
 
-constexpr int kDistillThreads = 256;       // threads of a workgroup: many tokens,
-constexpr int kDistillThreadsFew = 1024;   // and few (kFewTokens)
+constexpr int kDistillThreads = 256;       // threads of a workgroup: ordinary,
+constexpr int kDistillThreadsMany = 1024;  // and for few, long rows (many_threads())
 constexpr int kMaxTeacher = 1024;          // largest k
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -74,12 +74,19 @@ __device__ __forceinline__ uint4 load16_logits(const uint4* p) {
   return make_uint4(r.x, r.y, r.z, r.w);
 }
 
-template <typename T> __device__ __forceinline__ float load_elem(const void* p, int64_t i);
-template <> __device__ __forceinline__ float load_elem<float>(const void* p, int64_t i) {
-  return static_cast<const float*>(p)[i];
+// one element as its bits, and what the bits mean
+template <typename T> __device__ __forceinline__ uint32_t load_bits(const void* p, int64_t i);
+template <> __device__ __forceinline__ uint32_t load_bits<float>(const void* p, int64_t i) {
+  return static_cast<const uint32_t*>(p)[i];
 }
-template <> __device__ __forceinline__ float load_elem<bf16_t>(const void* p, int64_t i) {
-  return __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t*>(p)[i]) << 16);
+template <> __device__ __forceinline__ uint32_t load_bits<bf16_t>(const void* p, int64_t i) {
+  return static_cast<const uint16_t*>(p)[i];
+}
+template <typename T> __device__ __forceinline__ float bits_value(uint32_t u) {
+  return __uint_as_float(Elem<T>::size == 4 ? u : u << 16);
+}
+template <typename T> __device__ __forceinline__ float load_elem(const void* p, int64_t i) {
+  return bits_value<T>(load_bits<T>(p, i));
 }
 __device__ __forceinline__ uint32_t bf16_rne(float f) {   // finite or inf/nan preserved
   uint32_t u = __float_as_uint(f);
@@ -103,7 +110,15 @@ template <> __device__ __forceinline__ void store_elem<bf16_t>(void* p, int64_t 
 
 // A row of V elements as what lies in front of its first 16-byte boundary, whole 16-byte units, and
 // the rest.
-struct RowSpan { int32_t head, units, tail; };
+struct RowSpan {
+  int32_t head, units, tail;
+  // the element in front of or behind the units that is this thread's, if any (there are at most 14)
+  __device__ __forceinline__ bool has_edge() const { return static_cast<int>(threadIdx.x) < head + tail; }
+  __device__ __forceinline__ int32_t edge(int32_t V) const {
+    const int32_t i = threadIdx.x;
+    return i < head ? i : V - tail + (i - head);
+  }
+};
 template <typename T>
 __device__ __forceinline__ RowSpan row_span(const void* row, int32_t V) {
   RowSpan r;
@@ -114,13 +129,25 @@ __device__ __forceinline__ RowSpan row_span(const void* row, int32_t V) {
   return r;
 }
 
-// f(b, valid) for the B units base + b * NT + tid of a batch: no tests in a full batch, and in the
-// last one whole steps that do not exist are left out.
-template <int NT, int B, typename F>
+// f(b, valid) for the B units base + b * NT + tid of a batch: no tests in a full batch, and in the last one the
+// steps that do not exist are left out: each by a test and jump of its own, or (CHAIN) all by one jump.  A row of 1000
+// logits has one step and seven to leave out: the loss of 1000 such rows takes 5.1 us with CHAIN, 5.6 without;
+// of 4096 x 151,936 logits 190 and 187.  (Clamped loads in place of masked ones: 12.5 us for 1000 rows of 16,000
+// logits instead of 9.7.)
+template <int NT, int B, int I = 0, typename F>
+__device__ __forceinline__ void for_first_steps(int base, int units, const F& f) {
+  if (base + I * NT < units) {
+    f(I, base + I * NT + static_cast<int>(threadIdx.x) < units);
+    if constexpr (I + 1 < B) for_first_steps<NT, B, I + 1>(base, units, f);
+  }
+}
+template <int NT, int B, bool CHAIN, typename F>
 __device__ __forceinline__ void for_batch(int base, int units, const F& f) {
   if (base + B * NT <= units) {
 #pragma unroll
     for (int b = 0; b < B; ++b) f(b, true);
+  } else if constexpr (CHAIN) {
+    for_first_steps<NT, B>(base, units, f);
   } else {
 #pragma unroll
     for (int b = 0; b < B; ++b)
@@ -137,18 +164,15 @@ __device__ __forceinline__ void row_lse(const void* zrow, int32_t V, float* red,
   const RowSpan span = row_span<T>(zrow, V);
   const uint4* row = reinterpret_cast<const uint4*>(static_cast<const char*>(zrow) + span.head * Elem<T>::size);
   float m = kNegBig, s = 0.f;
-  if (static_cast<int>(threadIdx.x) < span.head + span.tail) {     // (at most 14 elements)
-    const int i = threadIdx.x;
-    m = load_elem<T>(zrow, i < span.head ? i : V - span.tail + (i - span.head)) * kLog2e;
-    s = 1.f;
-  }
+  uint32_t edge = 0;              // (looked at behind the units: one round trip for both)
+  if (span.has_edge()) edge = load_bits<T>(zrow, span.edge(V));
   for (int base = 0; base < span.units; base += NT * B) {
     uint4 r[B];
-    for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+    for_batch<NT, B, KEEP>(base, span.units, [&](int b, bool valid) {
       if (valid) r[b] = load16_logits<KEEP>(row + base + b * NT + threadIdx.x);
     });
     float bm = kNegBig;
-    for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+    for_batch<NT, B, KEEP>(base, span.units, [&](int b, bool valid) {
       float x[EPU];
       unpack16(r[b], x, T{});
       float um = kNegBig;
@@ -159,7 +183,7 @@ __device__ __forceinline__ void row_lse(const void* zrow, int32_t V, float* red,
     const float mn = fmaxf(m, bm * kLog2e);
     s *= fast_exp2(m - mn);
     m = mn;
-    for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+    for_batch<NT, B, KEEP>(base, span.units, [&](int b, bool valid) {
       float x[EPU];
       unpack16(r[b], x, T{});
       float acc = 0.f;
@@ -167,6 +191,11 @@ __device__ __forceinline__ void row_lse(const void* zrow, int32_t V, float* red,
       for (int e = 0; e < EPU; ++e) acc += fast_exp2(fmaf(x[e], kLog2e, -m));
       if (valid) s += acc;
     });
+  }
+  if (span.has_edge()) {
+    const float x = bits_value<T>(edge) * kLog2e, mn = fmaxf(m, x);
+    s = s * fast_exp2(m - mn) + fast_exp2(x - mn);
+    m = mn;
   }
   const float M = block_max<NT / 64>(m, red);
   s_out = block_sum<NT / 64>(s * fast_exp2(m - M), red);
@@ -278,16 +307,14 @@ topk_kl_bwd_kernel(DistillParams p) {
     const int off = span.head * Elem<T>::size;
     const uint4* row = reinterpret_cast<const uint4*>(static_cast<const char*>(zrow) + off);
     uint4* out = reinterpret_cast<uint4*>(static_cast<char*>(drow) + off);
-    if (static_cast<int>(threadIdx.x) < span.head + span.tail) {
-      const int i = threadIdx.x, v = i < span.head ? i : p.V - span.tail + (i - span.head);
-      store_elem<T>(drow, v, gs * fast_exp2(fmaf(load_elem<T>(zrow, v), kLog2e, nl)));
-    }
+    uint32_t edge = 0;
+    if (span.has_edge()) edge = load_bits<T>(zrow, span.edge(p.V));
     for (int base = 0; base < span.units; base += NT * B) {
       uint4 r[B];
-      for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+      for_batch<NT, B, true>(base, span.units, [&](int b, bool valid) {
         if (valid) r[b] = load16_logits<KEEP>(row + base + b * NT + threadIdx.x);
       });
-      for_batch<NT, B>(base, span.units, [&](int b, bool valid) {
+      for_batch<NT, B, true>(base, span.units, [&](int b, bool valid) {
         float x[EPU];
         unpack16(r[b], x, T{});
 #pragma unroll
@@ -303,6 +330,8 @@ topk_kl_bwd_kernel(DistillParams p) {
         if (valid) store16_stream(out + base + b * NT + threadIdx.x, w);
       });
     }
+    if (span.has_edge())
+      store_elem<T>(drow, span.edge(p.V), gs * fast_exp2(fmaf(bits_value<T>(edge), kLog2e, nl)));
   } else {
     for (int v = threadIdx.x; v < p.V; v += NT)
       store_elem<T>(drow, v, gs * fast_exp2(fmaf(load_elem<T>(zrow, v), kLog2e, nl)));
@@ -336,11 +365,6 @@ bool rows_aligned_alike(const void* a, const void* b) {
   return ((reinterpret_cast<uintptr_t>(a) ^ reinterpret_cast<uintptr_t>(b)) & 15u) == 0;
 }
 
-// A token has a workgroup to itself; few tokens leave waves unused, and get four times the threads (loss and
-// gradient pass of 64 tokens x 151,936 logits in bf16: 19.8 -> 14.4 and 20.9 -> 17.8 us, of one token 14.5 ->
-// 11.8 and 13.7 -> 10.2; 512 tokens: 28.6 -> 27.7 and 62.7 -> 60.6; with 2048 tokens there is nothing to gain).
-constexpr int64_t kFewTokens = 1024;
-
 // Logits that fit the 256 MB Infinity Cache are loaded with the default policy: the gradient pass, which
 // stores past the caches, then reads most of them from there (both passes, 600 x 151,936 in bf16 = 182 MB:
 // 110 -> 96 us; 243 MB: 145 -> 126; 304 MB: 164 -> 163).  Beyond that they are streamed (395 MB: 233
@@ -349,28 +373,42 @@ bool logits_kept(const DistillParams& p, int32_t dtype) {
   return p.T * p.V * elem_size(dtype) <= (int64_t(256) << 20);
 }
 
+// A token has a workgroup to itself, of 256 threads; 1024 where tokens leave compute units idle (256 or fewer) and a
+// row keeps them busy, and with up to 1024 tokens where the logits are streamed from memory.  Loss and gradient pass
+// in us, 256 against 1024 threads:
+//   bf16, 64 x 151,936: 14.3, 12.5 and 14.1, 11.0; x 32,000: 6.45, 6.35 and 6.2, 5.4; x 16,000: 5.6, 5.7 and 4.95,
+//   4.5; x 8000: 4.95, 5.35 and 4.15, 4.1; f32, 64 x 12,000: 5.3, 5.45 and 4.8, 4.5; x 50,257: 8.7, 7.6 and 8.7, 7.6
+//   bf16, 512 x 8000: 5.5, 7.4 and 4.95, 5.55; 1000 x 1000: 5.1, 11.4 and 4.45, 7.85; 1000 x 50,257: 21.6, 23.1 and
+//   34.9, 33.4 (201 MB: kept in the Infinity Cache)
+//   bf16, 1000 x 151,936: 52.7, 50.1 and 121, 113; f32, 700 x 100,000: 46.0, 45.0 and 110, 106 (streamed); with
+//   2048 tokens there is nothing to gain.
+bool many_threads(const DistillParams& p, int32_t dtype) {
+  return (p.T <= 256 && static_cast<int64_t>(p.V) * elem_size(dtype) >= (30 << 10)) ||
+         (p.T <= 1024 && !logits_kept(p, dtype));
+}
+
 template <typename T, bool KEEP>
-void launch_fwd(const DistillParams& p, hipStream_t s) {
+void launch_fwd(const DistillParams& p, int32_t dtype, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(p.T));
-  if (p.T <= kFewTokens) topk_kl_fwd_kernel<T, kDistillThreadsFew, 4, KEEP><<<grid, kDistillThreadsFew, 0, s>>>(p);
+  if (many_threads(p, dtype)) topk_kl_fwd_kernel<T, kDistillThreadsMany, 4, KEEP><<<grid, kDistillThreadsMany, 0, s>>>(p);
   else topk_kl_fwd_kernel<T, kDistillThreads, 8, KEEP><<<grid, kDistillThreads, 0, s>>>(p);
 }
 template <typename T, bool VEC, bool KEEP>
-void launch_bwd(const DistillParams& p, hipStream_t s) {
+void launch_bwd(const DistillParams& p, int32_t dtype, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(p.T));
-  if (p.T <= kFewTokens) topk_kl_bwd_kernel<T, VEC, kDistillThreadsFew, 4, KEEP><<<grid, kDistillThreadsFew, 0, s>>>(p);
+  if (many_threads(p, dtype)) topk_kl_bwd_kernel<T, VEC, kDistillThreadsMany, 4, KEEP><<<grid, kDistillThreadsMany, 0, s>>>(p);
   else topk_kl_bwd_kernel<T, VEC, kDistillThreads, 8, KEEP><<<grid, kDistillThreads, 0, s>>>(p);
 }
 template <typename T>
 void launch_bwd(const DistillParams& p, int32_t dtype, hipStream_t s) {
-  if (!rows_aligned_alike(p.z, p.dz)) launch_bwd<T, false, true>(p, s);
-  else if (logits_kept(p, dtype)) launch_bwd<T, true, true>(p, s);
-  else launch_bwd<T, true, false>(p, s);
+  if (!rows_aligned_alike(p.z, p.dz)) launch_bwd<T, false, true>(p, dtype, s);
+  else if (logits_kept(p, dtype)) launch_bwd<T, true, true>(p, dtype, s);
+  else launch_bwd<T, true, false>(p, dtype, s);
 }
 template <typename T>
 void launch_fwd(const DistillParams& p, int32_t dtype, hipStream_t s) {
-  if (logits_kept(p, dtype)) launch_fwd<T, true>(p, s);
-  else launch_fwd<T, false>(p, s);
+  if (logits_kept(p, dtype)) launch_fwd<T, true>(p, dtype, s);
+  else launch_fwd<T, false>(p, dtype, s);
 }
 
 }  // namespace

@@ -79,6 +79,13 @@ def test_rows_that_start_anywhere(dev, dtype, T, V, k):
         _grad_close(dz, OD.topk_kl_loss_grad(z, tl, idx, 0.5), dtype, 0.5)
 
 
+@pytest.mark.parametrize("T,V", [(256, 15360), (256, 15359), (257, 15360), (3, 7679), (3, 7680)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_both_sides_of_the_workgroup_size(dev, dtype, T, V):
+    # 1024 threads for up to 256 tokens whose rows have 30 KB or more, 256 otherwise
+    _check(W.DistillWorkload("threads", T, V, 40, dtype), range(T), dev, gs=0.25)
+
+
 def test_paper_vocabulary_all_rows(dev):
     wl = W.distill(T=24)
     _check(wl, range(24), dev)
