@@ -16,7 +16,7 @@
 //                response tokens  -> only the rows up to the end of their window (masked band)
 //              so the dense part of the work is spent on the ~P + S/(c+1) keys every row sees.
 //              A dense block is long (every later row x every head); it is cut into parts (see
-//              dense_splits), which write partial dK/dV to the workspace, and a third kernel adds
+//              dense_parts), which write partial dK/dV to the workspace, and a third kernel adds
 //              them in a fixed order.  Response blocks store their result directly.
 //
 // All contractions are 32x32x16 bf16 MFMA; A and dS are split into two bf16 parts before they
@@ -51,7 +51,7 @@ struct BwdParams {
   float* stat;          // [Hq][total_rows][2]: lse*log2(e), Delta
   float* part;          // [splits][2][total_rows][Hkv][D]: dk, dv partials of the dense key blocks
   int32_t D;            // head dimension (the reduction kernel reads it; the others are templates)
-  int32_t splits;       // workgroups that share a dense key block (1: it stores its result directly)
+  int32_t splits;       // most workgroups that share a dense key block (see dense_parts)
   int64_t total_rows;
   int32_t Hq, Hkv, g;
   HeadTiling tiling;    // dq kernel
@@ -220,12 +220,23 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
 // dkv kernel
 // ---------------------------------------------------------------------------
 constexpr int kDkvKeys = 64;          // keys of a workgroup: two pairs of waves with 32 keys each
+constexpr int kDkvAtOnce = 3 * 256;   // workgroups that run at once
 constexpr int kDkvStages = 2;
 
 // 4 bytes per lane from HBM into LDS
 __device__ __forceinline__ void lds_dma4_s(uint32_t lane_offset, uint64_t base, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                : : "s"(lds_addr), "v"(lane_offset), "s"(base) : "memory");
+}
+
+// Parts each of a trajectory's nd dense key blocks is cut into: as many as run at once if all trajectories are
+// like this one, at most the p.splits there is room for, and two where the heads of a group make the chain long.
+// One part stores its result directly.  (The host does not know how many keys are dense, and reckons with one in
+// eight.  Cut by that alone, 4 uncompressed trajectories of 2200 rows, 8/8 heads, had six parts of 1120 blocks and
+// took 376 us, 318 whole.)
+__device__ __forceinline__ int dense_parts(const BwdParams& p, int nd) {
+  const int blocks = min(max(nd, 1), kDkvAtOnce) * p.npairs, n = (kDkvAtOnce + blocks - 1) / blocks;
+  return min(max(n, p.g > 1 ? 2 : 1), p.splits);
 }
 
 // The two waves of a pair share 32 keys.  One forms the scores and A and adds dO^T.A to dV, the other
@@ -258,13 +269,13 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const int NPB = (Pk + kDkvKeys - 1) / kDkvKeys, NBB = (nbeac + kDkvKeys - 1) / kDkvKeys;
   const int NLB = (nresp + kDkvKeys - 1) / kDkvKeys;
   // The dense blocks (prompt keys, beacons) stream every later row of every head; the tiles of each
-  // are dealt to `splits` workgroups, whose partial sums another kernel adds in a fixed order.
+  // are dealt to `parts` workgroups, whose partial sums another kernel adds in a fixed order.
   // The short response blocks are not cut and store their result directly.
-  const int nd = NPB + NBB;
-  int blk = nd + ((int)blockIdx.y - nd * p.splits), split = -1;
+  const int nd = NPB + NBB, parts = dense_parts(p, nd);
+  int blk = nd + ((int)blockIdx.y - nd * parts), split = -1;
   if (blk < nd) {
-    blk = blockIdx.y / p.splits;
-    if (p.splits > 1) split = blockIdx.y - blk * p.splits;
+    blk = blockIdx.y / parts;
+    if (parts > 1) split = blockIdx.y - blk * parts;
   }
   if (blk >= nd + NLB) return;
   const int kind = blk < NPB ? 0 : blk < NPB + NBB ? 1 : 2;
@@ -326,7 +337,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   // same tiles at the same time - the later readers of a tile find it in the L2.
   const int ntile = (re - rs) / kTileRows + 1;       // row tiles per head
   int it0 = 0, it1 = ntile * p.g;                    // streamed tiles: head-major
-  if (split >= 0) { it0 = it1 * split / p.splits; it1 = ntile * p.g * (split + 1) / p.splits; }
+  if (split >= 0) { it0 = it1 * split / parts; it1 = ntile * p.g * (split + 1) / parts; }
   const int64_t q_row_bytes = (int64_t)p.Hq * ROWB;
   const TileLane tlane = either_tile_lane(lane, wave);
   const uint32_t lds0 = lds_address(lds);
@@ -448,6 +459,8 @@ __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
   const WindowStride ws = window_stride(p.c[b], S);
   const int Pk = ws.c > 0 ? min(p.P[b], S) : S;
   const int nbeac = ws.c > 0 ? (int)window_of(ws, (uint32_t)(S - Pk)) : 0;
+  const int parts = dense_parts(p, (Pk + kDkvKeys - 1) / kDkvKeys + (nbeac + kDkvKeys - 1) / kDkvKeys);
+  if (parts == 1) return;
   const int per_row = p.Hkv * (p.D / 4);         // 16-byte units
   const int64_t units = (int64_t)(Pk + nbeac) * per_row;
   const int64_t plane = p.total_rows * p.Hkv * p.D;
@@ -457,7 +470,7 @@ __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
     const int64_t at = ((off0 + j) * per_row + (i - (int64_t)n * per_row)) * 4;
     f32x4_t sk = f32x4_t{0.f, 0.f, 0.f, 0.f}, sv = sk;
 #pragma unroll 4
-    for (int sp = 0; sp < p.splits; ++sp) {
+    for (int sp = 0; sp < parts; ++sp) {
       sk += *reinterpret_cast<const f32x4_t*>(p.part + (int64_t)(2 * sp) * plane + at);
       sv += *reinterpret_cast<const f32x4_t*>(p.part + (int64_t)(2 * sp + 1) * plane + at);
     }
@@ -473,18 +486,18 @@ static void launch_bwd(const BwdParams& p, bool wide, dim3 dq_grid, dim3 dkv_gri
   prefill_bwd_dkv_kernel<D><<<dkv_grid, kTileWaves * 64, 0, hs>>>(p);
 }
 
-// Workgroups that share a dense key block.  A dense block streams all later rows of all heads, a chain of up
-// to g * rows/32 tiles, and there are few of them: they are cut until as many as run at once (three per
-// CU) are there, taking one key in eight for dense (ratios and prompt lengths are on the device).  Backward of
-// 6 trajectories, 14/2 heads, d = 64, 12,966 rows: two parts 523 us, six 300; one trajectory of 6631 rows,
-// 24/8 heads: 597, three 372; three short trajectories: 118, six 62; more parts than that cost work (16
-// trajectories of 8688 rows: two 2.70 ms, three 2.66, six 2.82; 8 of 3389 rows, 32/8 heads: 2.37, 2.40, 2.55).
-// Parts of fewer than eight tiles are not worth their partial sums.
+// Most workgroups that share a dense key block: what the workspace has room for, and dense_parts() chooses from.
+// A dense block streams all later rows of all heads, a chain of up to g * rows/32 tiles, and there are few of
+// them: they are cut until as many as run at once (three per CU) are there, taking one key in eight for dense
+// (ratios and prompt lengths are on the device).  Backward of 6 trajectories, 14/2 heads, d = 64, 12,966 rows: two
+// parts 523 us, six 300; one trajectory of 6631 rows, 24/8 heads: 597, three 372; three short trajectories: 118,
+// six 62; more parts than that cost work (16 trajectories of 8688 rows: two 2.70 ms, three 2.66, six 2.82; 8 of
+// 3389 rows, 32/8 heads: 2.37, 2.40, 2.55).  Parts of fewer than eight tiles are not worth their partial sums.
 static int dense_splits(const bc_shape* shape, int64_t total_rows) {
-  constexpr int64_t kAtOnce = 3 * 256, kMost = 8;
+  constexpr int64_t kMost = 8;
   const int64_t blocks = total_rows * shape->Hkv / (8 * kDkvKeys) + 1;
   const int64_t tiles = total_rows / shape->B * (shape->Hq / shape->Hkv) / kTileRows;      // of a chain
-  const int64_t n = (kAtOnce + blocks - 1) / blocks, least = shape->Hq > shape->Hkv ? 2 : 1;
+  const int64_t n = (kDkvAtOnce + blocks - 1) / blocks, least = shape->Hq > shape->Hkv ? 2 : 1;
   const int64_t most = tiles / 8 < kMost ? tiles / 8 : kMost;
   return (int)(n < least || most < least ? least : n > most ? most : n);
 }

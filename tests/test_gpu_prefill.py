@@ -496,3 +496,35 @@ def test_prefill_bwd_addresses_beyond_32_bits(dev, d):
         got.append(grads)
     for x, y in zip(*got):
         assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 8, 64), (16, 8, 128)])
+def test_prefill_bwd_parts_follow_the_dense_keys_of_a_trajectory(dev, Hq, Hkv, d):
+    # uncompressed trajectories (every key dense: blocks whole, or in two parts for groups of two) beside
+    # compressed ones (few dense blocks, in parts) in one call; workspace and results hold NaN before it
+    import torch
+    from paper_2510_13797_amd import bc
+    B = 12
+    pw = W.PrefillWorkload("pfb_parts", 72, B, Hq, Hkv, d, "bf16", np.full(B, 30, np.int32), np.full(B, 490, np.int32),
+                           np.resize(np.array([0, 6, 0, 16], np.int32), B))
+    qkv = [pw.qkv(b) for b in range(B)]
+    dos = [pw.dout(b) for b in range(B)]
+    off = np.concatenate([[0], np.cumsum(pw.S)]).astype(np.int64)
+    q, k, v, do = (bc.to_device(np.concatenate(x), "bf16", dev) for x in (*zip(*qkv), dos))
+    out, lse = bc.prefill_attn(q, k, v, off, pw.P, pw.c, Hq, Hkv, d, pw.scale)
+    total = int(off[-1])
+    nan = lambda *shape: torch.full(shape, float("nan"), device=dev)
+    dq, dk, dv = nan(total, Hq, d), nan(total, Hkv, d), nan(total, Hkv, d)
+    shape = bc.bc_shape(B, Hq, Hkv, d, bc.BC_BF16, pw.scale)
+    need = bc.bc_prefill_bwd_workspace_bytes(shape, total)
+    assert (need - total * Hq * 8) // (2 * total * Hkv * d * 4) >= 2          # there is room for two parts
+    ws = nan(need // 4)
+    tables = [torch.from_numpy(x).to(dev) for x in (off, pw.P, pw.c)]
+    p = lambda t: t.data_ptr()
+    assert bc.bc_prefill_attn_bwd(shape, p(q), p(k), p(v), p(out), p(lse), p(do), *map(p, tables), int(pw.S.max()), total,
+                                  p(dq), p(dk), p(dv), p(ws), ws.numel() * 4, None) == bc.BC_OK
+    torch.cuda.synchronize()
+    dq, dk, dv = (x.cpu().numpy() for x in (dq, dk, dv))
+    assert np.isfinite(dq).all() and np.isfinite(dk).all() and np.isfinite(dv).all()
+    for b in (0, 1, B - 1):
+        _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
