@@ -68,7 +68,6 @@ struct DecodeParams {
   int32_t spec_P, spec_cap;   // bc_cache::uniform_P, uniform_cap (0 = no promise)
   int32_t Hq, Hkv, g;  // g = real group size
   int32_t Gp;          // padded group size of the partial layout
-  int32_t D;
   int32_t rows_per_wg; // R: rows per workgroup when a chunk size is forced; otherwise (0) the
                        // resident rows of a sequence are spread evenly over its chunks
   int32_t max_chunks;
@@ -1259,7 +1258,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // us; 8 pairs, d = 128, groups of two 10.1, 9.9 / 12.0, 9.9, of six 17.0, 15.0 / 22.2, 15.4; 128 pairs, d = 64,
     // groups of four 13.1, 13.7 / 19.1, 14.7), with up to 256 pairs (fp32, 64 sequences of 500 rows, 12/2 heads: 62.8
     // -> 27.8 us).  The lengths are not known here: a batch whose sequences are all within the first pass pays for
-    // the workgroups they do not fill, 0 to 0.1 us with up to 32 pairs, 1.5 to 2.5 with more.  256 workgroups run
+    // the workgroups they do not fill, 0.1 to 0.3 us of 8 to 14 with up to 32 pairs, 0.5 to 0.9 with more.  256 workgroups run
     // at once with groups of seven or eight, and of three or more of bf16 rows (over 256 registers), otherwise 512;
     // beyond that a second round takes more than the cut saves (200 pairs, groups of eight, 500 rows: whole 73.5
     // us, in 400 workgroups 83.7).  Attention alone has a launch in front to clear its counters, some 1.5 us: its
@@ -1478,7 +1477,6 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
   p.order = follows_order(shape, cache, pl) ? cache->order : nullptr;
   p.Hq = shape->Hq; p.Hkv = shape->Hkv; p.g = shape->Hq / shape->Hkv;
   p.Gp = pl.Gp;
-  p.D = shape->d;
   p.rows_per_wg = pl.R;
   p.max_chunks = pl.max_chunks;
   p.chunk_rows = pl.chunk_rows; p.split_rows = pl.split_rows;

@@ -30,8 +30,8 @@
 //  - 152 registers, three waves per SIMD: with work of neighbouring tiles interleaved by hand inside a
 //    wave and two waves per SIMD the same loop took 0.80 ms (higher matrix load, lower clock);
 //  - operands of a tile at one register plus constants, no bank conflicts (bc_prefill_tiles.h);
-//  - loads asked for behind the scores' MFMAs, their addresses from a cursor: 0.77 -> 0.70 ms with
-//  - prompt and beacon remainders packed with the band (bc_prefill_tiles.h): 7 % fewer MFMAs.
+//  - loads asked for behind the scores' MFMAs, their addresses from a cursor, and prompt and beacon
+//    remainders packed with the band (7 % fewer MFMAs, bc_prefill_tiles.h): together 0.77 -> 0.70 ms.
 #include <type_traits>
 
 #include "bc_prefill_tiles.h"

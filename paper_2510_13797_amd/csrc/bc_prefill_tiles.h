@@ -207,29 +207,9 @@ __device__ __forceinline__ int opaque(int x) {
   asm volatile("" : "+v"(x));
   return x;
 }
-// Values that are to be worked out by here.
-__device__ __forceinline__ void pin8(float* x) {
-  asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
-}
-
 // Workgroup barrier for LDS traffic whose loads the compiler does not count: no implied wait.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Order of a stretch of straight-line code (a scheduling region of its own): AHEAD LDS reads first,
-// then NM matrix instructions with READS LDS reads and VALU vector instructions behind each.
-template <int NM, int AHEAD, int READS, int VALU, int ID>
-__device__ __forceinline__ void interleave() {
-  constexpr int kMfma = 0x8, kValu = 0x2, kDsRead = 0x100;
-  if constexpr (AHEAD > 0) __builtin_amdgcn_sched_group_barrier(kDsRead, AHEAD, ID);
-#pragma unroll
-  for (int n = 0; n < NM; ++n) {
-    __builtin_amdgcn_sched_group_barrier(kMfma, 1, ID);
-    __builtin_amdgcn_sched_group_barrier(kDsRead, READS, ID);
-    __builtin_amdgcn_sched_group_barrier(kValu, VALU, ID);
-  }
-  __builtin_amdgcn_sched_barrier(0);
 }
 
 // ---------------------------------------------------------------------------
