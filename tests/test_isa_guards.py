@@ -1,4 +1,4 @@
-"""Guards on the generated code of the decode kernel (no GPU needed).
+"""Guards on the generated code of the decode and prefill kernels (no GPU needed).
 
 The decode kernel issues its loads through hand-written instructions that the compiler does not
 track (so that it places no wait for them inside the tile loop); the waits are explicit.  That is
@@ -6,6 +6,8 @@ only correct while the compiler never reads a destination register of such a loa
 and the next wait - e.g. through a register-to-register copy that joins two definitions.  This test
 compiles the file to assembly and checks exactly that, for every instantiation of the kernel
 (and the same for the scalar loads of the table entries in the prologue of both decode kernels).
+The prefill kernels' hand-written loads go to LDS and have no destination registers; what is checked
+of them is the register that holds the LDS address.
 """
 import os
 import re
@@ -262,17 +264,60 @@ def test_checker_flags_a_copy_of_an_inflight_register():
     assert got == ["s_waitcnt vmcnt(4)" + HAND, "landed v[62:65]" + HAND, "v_mov_b32_e32 v1, v62"]
 
 
-def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
+def check_m0(body):
+    """M0 (the LDS address of a DMA load) is set by the hand-written sequence itself, right in front of
+    every such load, and nothing else in the kernel touches it.  -> number of such loads"""
+    n = 0
+    for i, l in enumerate(body):
+        if l.startswith("global_load_lds"):
+            assert body[i - 2].startswith("s_mov_b32 m0, s") and body[i - 1].startswith("s_nop"), body[i - 2:i + 1]
+            n += 1
+        elif re.search(r"\bm0\b", l):
+            assert l.startswith("s_mov_b32 m0, s") and body[i + 2].startswith("global_load_lds"), body[i:i + 3]
+    return n
+
+
+def _assembly(name, tmp_path):
     import __graft_entry__ as G
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("no hipcc")
-    src = os.path.join(ROOT, "paper_2510_13797_amd", "csrc", "bc_decode.hip")
-    out = str(tmp_path / "bc_decode.s")
-    flags = [f for f in G.HIPCC_FLAGS if f not in ("-shared", "-Wall")] + G.FILE_FLAGS.get("bc_decode.hip", [])
+    src = os.path.join(ROOT, "paper_2510_13797_amd", "csrc", name)
+    out = str(tmp_path / (name + ".s"))
+    flags = [f for f in G.HIPCC_FLAGS if f not in ("-shared", "-Wall")] + G.FILE_FLAGS.get(name, [])
     subprocess.check_call([hipcc] + flags + ["-w", "-I", os.path.join(ROOT, "include"), "-S",
                                              "--cuda-device-only", src, "-o", out])
-    text = open(out).read().split("\n")
+    return open(out).read().split("\n")
+
+
+def test_m0_check_flags_other_uses():
+    load = ["s_mov_b32 m0, s4", "s_nop 0", "global_load_lds_dwordx4 v1, s[2:3]"]
+    assert check_m0(load + load) == 2
+    for bad in (load[1:], load[:1] + load[2:], ["s_mov_b32 m0, s4", "v_mov_b32_e32 v1, v2"] + load, ["s_add_i32 s3, m0, 1"] + load):
+        with pytest.raises(AssertionError):
+            check_m0(["s_nop 0", "s_nop 0"] + bad + ["s_nop 0", "s_nop 0"])
+
+
+@pytest.mark.parametrize("name,kernels", [("bc_prefill.hip", {"prefill_kernel": 8}),
+                                          ("bc_prefill_bwd.hip", {"prefill_bwd_dq_kernel": 4, "prefill_bwd_dkv_kernel": 2})])
+def test_prefill_kernels_set_m0_in_front_of_every_load_to_lds(name, kernels, tmp_path):
+    text = _assembly(name, tmp_path)
+    for kernel, count in kernels.items():
+        starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc\d\d%s\w+:" % kernel, l)]
+        assert len(starts) == count, (kernel, len(starts))
+        for s in starts:
+            e = next(i for i in range(s, len(text)) if text[i].startswith(".Lfunc_end"))
+            marked = _instructions(text[s:e])
+            body = [l[:-len(HAND)] if l.endswith(HAND) else l for l in marked]
+            # a tile of K (Q) and of V (dO) at least, from each of the places that ask for one
+            assert check_m0(body) >= 4, text[s][:80]
+            # no hand-written load has a destination register, and nothing of the tile loop lives in scratch
+            assert all("load_lds" in l for l in marked if l.endswith(HAND) and l.startswith("global_load")), text[s][:80]
+            assert not any(l.startswith(("scratch_", "buffer_")) for l in body), text[s][:80]
+
+
+def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
+    text = _assembly("bc_decode.hip", tmp_path)
     starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc\d\ddecode_(lds|lds_cut|valu)_kernel\w+:", l)]
     assert len(starts) >= 16 + 5 + 20 + 20
     for s in starts:
@@ -281,13 +326,7 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
         body = [l[:-len(HAND)] if l.endswith(HAND) else l for l in marked]
         if "decode_lds_" in text[s]:
             assert any(l.startswith("global_load_lds_dwordx4") for l in body)
-            # M0 (the LDS address of a DMA load) is set by the hand-written sequence itself, right in
-            # front of every such load, and nothing else in the kernel touches it
-            for i, l in enumerate(body):
-                if l.startswith("global_load_lds"):
-                    assert body[i - 2].startswith("s_mov_b32 m0, s") and body[i - 1].startswith("s_nop"), body[i - 2:i + 1]
-                elif re.search(r"\bm0\b", l):
-                    assert l.startswith("s_mov_b32 m0, s"), l
+            check_m0(body)
             # the landing marks are there, each behind one of the explicit waits
             marks = [i for i, l in enumerate(body) if l.startswith("landed ")]
             assert len(marks) >= 6, text[s][:80]
