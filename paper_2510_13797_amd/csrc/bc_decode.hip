@@ -2,26 +2,26 @@
 // (Sec. 2 and Sec. 3.1 of the paper: standard attention over whatever is resident).
 //
 // Split-K flash decoding.  Work item = (sequence, KV head) pair x chunk of rows; grid =
-// (max chunks, pairs).  With 128 pairs or more a pair is one chunk and its workgroup finishes
-// it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
-// workgroups (short sequences stay whole, see make_plan); every chunk writes an (m, l, o) partial
-// and the workgroup that is last folds the partials of its pair in chunk order.  No float atomics
-// and no fences: results are bit-reproducible.  Large ragged batches (more pairs than compute
-// units) can dispatch the longest sequences first (bc_sort_by_length).  Batches of at most 128
-// pairs with short caches use two workgroups per pair, each with all K rows and one half of the
-// V columns, so that all compute units pull data and nothing has to be merged.
+// (KV heads, sequences, chunks).  From 128 pairs on (fp32: 257) a pair is one chunk and its workgroup
+// finishes it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
+// workgroups (fp32 from 128 pairs on: four; short sequences stay whole, see make_plan); every chunk
+// writes an (m, l, o) partial and the workgroup that arrives last folds the partials of its pair in
+// chunk order.  No float atomics and no fences: results are bit-reproducible.  Large ragged batches
+// (more pairs than compute units) can dispatch the longest sequences first (bc_sort_by_length).
+// Batches of at most 128 pairs with short caches use two workgroups per pair, each with all K rows and
+// one half of the V columns, so that all compute units pull data and nothing has to be merged.
 //
 // Two main kernels:
-//  * decode_lds_kernel (bf16, d = 128 or 64): every wave streams 32-row K and V tiles from HBM
-//    straight into its own LDS region with 16-byte LDS-DMA loads (1 KB of consecutive bytes
-//    per instruction, 16 KB in flight per wave at d = 128), then forms the q.K products and the p.V
-//    sums of all query heads of the group with 16x16x32 bf16 MFMA tiles fed from LDS (K by
-//    128-bit reads, V by the 16-bit transposing reads), softmax in registers.
+//  * decode_lds_kernel (bf16, d = 128 or 64; decode_lds_cut_kernel where sequences are cut): every
+//    wave streams 32-row K and V tiles from HBM straight into its own LDS region with 16-byte LDS-DMA
+//    loads (1 KB of consecutive bytes per instruction, 16 KB in flight per wave at d = 128), then forms
+//    the q.K products and the p.V sums of all query heads of the group with 16x16x32 bf16 MFMA tiles
+//    fed from LDS (K by 128-bit reads, V by the 16-bit transposing reads), softmax in registers.
 //  * decode_valu_kernel (fp32): rows held in registers, 16 bytes per lane, plain
 //    FMA dot products completed by a DPP all-reduce.
 // Both carry the fused step (append before, eviction after the attention) in the same launch: the
-// appended row is read from the caller's tensors, every reader of a sequence takes a ticket when
-// it is done with the slab, and the holder of the last ticket moves the beacon and the tables.
+// appended row is read from the caller's tensors, everyone who has read a sequence's tables is counted
+// (bc_decode_count.h), and the holder of the sequence's last ticket moves the beacon and the tables.
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
@@ -1247,7 +1247,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // the line from 33 pairs on: a ragged batch does not fill them, and its longest sequence sets the time (90 pairs
     // of up to 2100 rows, cut in two by eight waves or in five by four: 31.5, 27.2 us; of equal length, 1500 rows:
     // 19.0, 20.1); with up to 32 pairs eight waves and 256 are as fast or faster (16 pairs of 3000 rows: 12.0, 13.6;
-    // at 8 pairs 23 chunks take 12.2, sixteen 11.1).
+    // at 8 pairs 23 chunks take 12.2, sixteen 11.1).  (These before the grid went chunk by chunk, see decode_grid().)
     // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster (d = 128, 8
     // pairs, whole against cut: 700 rows 7.9, 9.2 us; 850: 8.9, 9.5; 1000: 9.4, 9.7; 2 pairs, 1000 rows: 9.25, 8.7);
     // where the batch has longer sequences the shorter ones run in the tile loop, cut from 512 rows on (700 rows

@@ -181,8 +181,8 @@ def test_fused_step_on_the_plain_alu_kernel(dev, dtype, d, B):
     # the same single-launch step on the kernel that serves fp32 rows (and bf16 rows when the
     # plan asks for it): ragged ratios with c = 1 and no compression among them, sequences that
     # end early, the budget-free and the beacon-step forms; tables, slabs and outputs each step.
-    # B = 2 with a long prompt spreads a sequence's rows over several workgroups and a merge
-    # launch, each workgroup taking its own ticket.
+    # B = 2 with a long prompt spreads a sequence's rows over several workgroups, which arrive at
+    # their pair's counter; the last folds the partials and takes the pair's ticket.
     P = np.array([1100, 1050], np.int32) if B == 2 else np.array([40, 0, 17, 64, 5, 33], np.int32)
     c = np.array([16, 3], np.int32) if B == 2 else np.array([16, 1, 0, 3, 2, 7], np.int32)
     G = np.array([70, 70], np.int32) if B == 2 else np.array([70, 70, 50, 70, 21, 70], np.int32)
@@ -294,7 +294,7 @@ def test_beacon_step_leaves_other_sequences_alone(dev):
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("bf16", 64)])
 def test_small_batch_rows_spread_over_workgroups(dev, dtype, d):
     # few (sequence, KV head) pairs and long sequences: the rows of a sequence are spread evenly
-    # over several workgroups whose partials a second launch merges; a short sequence in the same
+    # over several workgroups, the last of which folds their partials; a short sequence in the same
     # batch stays whole.  Fused steps (append + attention + eviction) against the oracle.
     B = 3
     Hq, Hkv = (12, 2) if d == 128 else (4, 1)
@@ -311,7 +311,7 @@ def test_small_batch_rows_spread_over_workgroups(dev, dtype, d):
 
 
 def test_very_long_context_next_to_a_short_one(dev):
-    # one sequence of 150,000 resident rows (64 chunks of 2,344 rows and the merge launch) beside
+    # one sequence of 150,000 resident rows (64 chunks of 2,368 rows and their fold) beside
     # one of 40 rows that stays whole; a few fused steps, then attention, against the oracle
     wl = W.Workload("long", 89, 2, 12, 2, 128, "bf16", np.array([150000, 40], np.int32),
                     np.full(2, 6, np.int32), np.array([4, 2], np.int32))
@@ -949,3 +949,18 @@ def test_fp32_sequences_cut_at_their_passes(dev, B, Hq, Hkv, d, P, chunks):
     rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
     q = wl.step_q(77)
     check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, 77)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [
+    (1, 4, 1, 64, (16900,), 34),                      # a chunk for every 512 rows: the fold takes three batches
+    (2, 6, 2, 128, (9000, 8300), 18),
+    (1, 3, 1, 128, (40000,), 64),                     # the most chunks there are
+])
+def test_long_sequences_get_a_chunk_for_every_512_rows(dev, B, Hq, Hkv, d, P, chunks):
+    G = 5
+    wl = W.Workload("chunks512", 120, B, Hq, Hkv, d, "bf16", np.array(P, np.int32), np.full(B, G, np.int32),
+                    np.full(B, 2, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
+    rollout(wl, rt, oc, G, range(1, G + 1), (G,), use_step_call=True)

@@ -1,7 +1,7 @@
 """GPU test of the allocation-free entry point bc_decode_step_noalloc: through the C ABI, against
 bc_decode_step on an identical cache with a workspace of its own - outputs, tables and slabs must
 be identical (the same kernels run) - on two calls in a row, the second on a smaller input that
-takes the split-and-merge path, whose partial results live in the shared scratch array."""
+cuts sequences into chunks, whose partial results live in the shared scratch array."""
 import numpy as np
 import pytest
 
@@ -59,7 +59,7 @@ def test_noalloc_step_equals_the_step_with_a_workspace(dev):
     _same_state(ref, sta)
     assert int(ref.tables()[0][0]) == 2          # two windows were closed on the way
     # second call: a smaller input - 8 sequences of 1500 uncompressed rows, split into chunks whose
-    # partial results go through the scratch array and a merge launch
+    # partial results go through the scratch array
     wl2 = W.batch64(c=0, G=1500, B=8)
     ref2, sta2 = _pair(wl2, dev)
     for rt in (ref2, sta2):
@@ -88,7 +88,7 @@ def test_noalloc_step_equals_the_step_with_a_workspace(dev):
 
 def test_noalloc_step_on_the_plain_alu_path(dev):
     import torch
-    # fp32 rows: the fused step on the plain-ALU kernel, one ticket per workgroup in the scratch array
+    # fp32 rows: the fused step on the plain-ALU kernel, its tickets in the scratch array
     wl = W.tiny()
     ref, sta = _pair(wl, dev)
     for t in range(1, 20):
