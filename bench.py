@@ -162,7 +162,8 @@ def bench_prefill(args):
                         "entry_point": "bc_prefill_attn_ws (conversion pass included)" if use_ws else "bc_prefill_attn",
                         "achieved": round(tflops, 2),
                         "peak": 2500.0, "unit": "TFLOP/s", "frac": round(tflops / 2500.0, 4),
-                        "traffic": stored_value("prefill_fwd_traffic_bytes")}}
+                        # (measured for the two-part form)
+                        "traffic": None if use_ws else stored_value("prefill_fwd_traffic_bytes")}}
     print(json.dumps(rec))
 
 
@@ -292,7 +293,7 @@ def bench_distill(args):
                                              "V=151936 logits (bf16)",
                                  "ms_forward": round(ms_f, 4), "ms_backward": round(ms_b, 4),
                                  "forward_GBps": round(gbs_f, 1), "backward_GBps": round(gbs_b, 1)},
-                      "roofline": {"bound": "hbm", "kernel": "bc::topk_kl_bwd_kernel<bf16_t, true>",
+                      "roofline": {"bound": "hbm", "kernel": "bc::topk_kl_bwd_kernel<bc::bf16_t, true, 256, 8, false>",
                                    "achieved": round(gbs_b, 1), "peak": 8000.0, "unit": "GB/s",
                                    "frac": round(gbs_b / 8000.0, 4),
                                    "traffic": stored_value("distill_bwd_traffic_bytes")}}))
