@@ -183,8 +183,8 @@ int32_t bc_workspace_init(void *workspace, size_t workspace_bytes, void *stream)
 /* Which kernel, grid and chunking the decode calls use for this shape and cache (HOST fields of
  * `cache` only: max_cap, order, the layout promise, rows_per_workgroup, plan; nothing on the
  * device is read).  Writes a NUL-terminated line to text[text_bytes] (HOST memory), cut short if
- * it does not fit; the kernel's name is spelled as profilers print it.  (bc_decode_attn cuts the
- * sequences of fp32 caches later than the step calls, whose plan this is.)  For logs and for
+ * it does not fit; the kernel's name is spelled as profilers print it.  (bc_decode_attn cuts
+ * sequences later than the step calls, whose plan this is.)  For logs and for
  * benchmarks that report which kernel they timed.  Same status codes as bc_decode_attn for a bad
  * shape, cache or plan; text == NULL or text_bytes == 0 is BC_ERR_ARG. */
 int32_t bc_decode_plan_describe(const bc_shape *shape, const bc_cache *cache, char *text,

@@ -1202,7 +1202,8 @@ struct DecodePlan {
 
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
 
-constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kFewPairs = 32;             // see make_plan
+constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kSplitMinRows64 = 832;
+constexpr int kFewPairs = 32;             // see make_plan
 constexpr long kMostChunks = 64;
 constexpr int kChunkRowsMax = 512;    // rows a chunk of the matrix kernel need not go beyond: two passes of eight waves
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
@@ -1250,8 +1251,13 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // at 8 pairs 23 chunks take 12.2, sixteen 11.1).  (These before the grid went chunk by chunk, see decode_grid().)
     // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster (d = 128, 8
     // pairs, whole against cut: 700 rows 7.9, 9.2 us; 850: 8.9, 9.5; 1000: 9.4, 9.7; 2 pairs, 1000 rows: 9.25, 8.7);
-    // where the batch has longer sequences the shorter ones run in the tile loop, cut from 512 rows on (700 rows
-    // whole: 10.1 us).
+    // where the batch has longer sequences the shorter ones run in the tile loop, and are cut from 512 rows on
+    // (capacity 3000, d = 128, whole, cut: 8 pairs 10.8, 10.9 us at 520 rows, 11.7, 10.7 at 700; 64 pairs 13.5, 12.8 and
+    // 14.7, 13.1; 90 pairs 14.6, 14.4 and 15.1, 15.1).  With d = 64, or four chunks for a sequence at most, sequences of
+    // equal length are faster whole up to some 800 and 1000 rows (d = 64, 90 pairs: 9.8, 11.4 at 520, 11.1, 11.6 at 800,
+    // 12.1, 11.9 at 900; 120 pairs, d = 128: 15.7, 16.4 at 700, 18.8, 19.1 at 1000, 22.6, 22.5 at 1300), ragged batches cut
+    // (16 layers of 45 sequences, 14/2 heads, d = 64: 180 us from 832 rows on, 171 from 512); attention alone, which
+    // pays for its counters besides, cuts them later.
     // The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of 1 to 7 us (by group and d), against
     // some 2 us that a fold takes: cut from the second pass on, or from the third where a pass is short and the
     // batch is small (whole and cut at the second / third pass: 2 pairs, d = 64, groups of one 8.2, 8.9 / 9.3, 9.0
@@ -1273,6 +1279,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
       const long by_rows = (max_cap + pl.chunk_rows - 1) / pl.chunk_rows, most = npairs < 128 ? kMostChunks : 4;
       if (chunks > by_rows) chunks = by_rows;
       if (chunks > most) chunks = most;
+      if (pl.lds && alone) pl.split_rows = chunks <= 4 ? 2 * kSplitMinRows : sh->d == 64 ? kSplitMinRows64 : kSplitMinRows;
     }
     pl.R = 0;                                        // spread evenly, decided per sequence
     pl.max_chunks = (int)chunks;

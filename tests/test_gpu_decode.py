@@ -964,3 +964,25 @@ def test_long_sequences_get_a_chunk_for_every_512_rows(dev, B, Hq, Hkv, d, P, ch
     st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
     assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
     rollout(wl, rt, oc, G, range(1, G + 1), (G,), use_step_call=True)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,P", [(3, 6, 2, 128, (507, 509, 1100)), (3, 6, 2, 64, (827, 829, 1100)),
+                                          (62, 4, 2, 128, (1019, 1021, 1100, 60))])
+def test_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, P):
+    # cut from 512 rows on; by attention alone from 832 at d = 64, from 1024 where a sequence has at most four chunks
+    G = 8
+    P = np.resize(np.array(P, np.int32), B)
+    wl = W.Workload("cutline", 121, B, Hq, Hkv, d, "bf16", P, np.full(B, G, np.int32), np.full(B, 5, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) > 1, text
+    sample = None if B <= 24 else range(0, B, 5)
+    for t in range(1, G + 1):
+        (k, v), q, (bk, bv) = wl.step_kv(t), wl.step_q(t), wl.beacon_kv(t)
+        o = rt.decode_step(k, v, q, bk, bv).cpu().numpy()
+        oc.append(k, v)
+        check_attention(o, q, oc, wl, sample, t)
+        oc.compress_evict(bk, bv)
+        check_tables(rt, oc, t)
+        check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, sample, t)
+    check_slabs(rt, oc, sample)
