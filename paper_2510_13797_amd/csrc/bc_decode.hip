@@ -2,9 +2,9 @@
 // (Sec. 2 and Sec. 3.1 of the paper: standard attention over whatever is resident).
 //
 // Split-K flash decoding.  Work item = (sequence, KV head) pair x chunk of rows; grid =
-// (KV heads, sequences, chunks).  From 128 pairs on (fp32: 257) a pair is one chunk and its workgroup
+// (KV heads, sequences, chunks).  From 128 pairs on (fp32: 129) a pair is one chunk and its workgroup
 // finishes it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
-// workgroups (fp32 from 128 pairs on: four; short sequences stay whole, see make_plan); every chunk
+// workgroups (short sequences stay whole, see make_plan); every chunk
 // writes an (m, l, o) partial and the workgroup that arrives last folds the partials of its pair in
 // chunk order.  No float atomics and no fences: results are bit-reproducible.  Large ragged batches
 // (more pairs than compute units) can dispatch the longest sequences first (bc_sort_by_length).
@@ -17,13 +17,15 @@
 //    loads (1 KB of consecutive bytes per instruction, 16 KB in flight per wave at d = 128), then forms
 //    the q.K products and the p.V sums of all query heads of the group with 16x16x32 bf16 MFMA tiles
 //    fed from LDS (K by 128-bit reads, V by the 16-bit transposing reads), softmax in registers.
-//  * decode_valu_kernel (fp32): rows held in registers, 16 bytes per lane, plain
-//    FMA dot products completed by a DPP all-reduce.
+//  * decode_valu_kernel (fp32): rows held in registers, 16 bytes per lane, fed to the fp32 matrix
+//    instructions; for bf16 rows, where the plan asks for it, plain FMA dot products completed by a
+//    DPP all-reduce.
 // Both carry the fused step (append before, eviction after the attention) in the same launch: the
 // appended row is read from the caller's tensors, everyone who has read a sequence's tables is counted
 // (bc_decode_count.h), and the holder of the sequence's last ticket moves the beacon and the tables.
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cstdint>
 #include <cstdio>
 #include <type_traits>
@@ -441,7 +443,8 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
 
 // The same merge, four output columns per thread (128-bit LDS reads and stores): fewer waves
 // take part, which shortens this serial tail of the matrix-core kernel.
-template <int NW, int D, int DOUT, int APITCH, bool CHUNKS>
+// DIVIDE: a correctly rounded quotient, for fp32 rows.
+template <int NW, int D, int DOUT, int APITCH, bool CHUNKS, bool DIVIDE = false>
 __device__ __forceinline__ void merge_waves_and_store4(const DecodeParams& p, const PairInfo& pi,
                                                        const float* s_m, const float* s_l,
                                                        const float* s_acc, int wave_stride, int col0) {
@@ -472,8 +475,9 @@ __device__ __forceinline__ void merge_waves_and_store4(const DecodeParams& p, co
       o += ow[wv] * a;
     }
     if (!CHUNKS || pi.nchunks == 1) {
-      const float inv = __builtin_amdgcn_rcpf(lsum);      // (one rounding error of the hardware reciprocal)
-      __builtin_nontemporal_store(o * inv, reinterpret_cast<f32x4_t*>(outp + h * DOUT + x));
+      if constexpr (DIVIDE) o = f32x4_t{o[0] / lsum, o[1] / lsum, o[2] / lsum, o[3] / lsum};
+      else o *= __builtin_amdgcn_rcpf(lsum);      // (one rounding error of the hardware reciprocal)
+      __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(outp + h * DOUT + x));
     } else {
       float* po = chunk_partial(p, pi, D, pi.chunk);
       float* pml = po + p.Gp * D;
@@ -984,14 +988,244 @@ __global__ __launch_bounds__(NW * 64) void decode_lds_cut_kernel(DecodeParams p)
 }
 
 // ---------------------------------------------------------------------------
-// generic VALU kernel: fp32 rows and d = 64
+// rows in registers: fp32, and bf16 where the plan asks for it
 // ---------------------------------------------------------------------------
 constexpr int kValuWaves = 4;
 
-// CHUNKS: as for the matrix kernel (whole sequences with the fold compiled in: 128 pairs of 20 rows, d = 64, 8.05 us
-// a step instead of 7.8).
+// fp32 rows on the fp32 matrix instructions (products and sums in 32 bits).  A wave's tile is 16 rows (d = 128) or 32
+// (d = 64), 8 KB of K and of V, from HBM into registers:
+//  * S^T[row][head] = K.Q^T in steps of four head-dim indices, one for each 16-lane row of the wave.  Which four does
+//    not matter as long as both operands agree: lane (m, b) takes row m, elements 16*i + 4*b .. +3, and the c-th of
+//    each four form a step.  K comes in as whole 256-byte pieces of four rows and goes through LDS into that order (loaded
+//    in it, neighbouring lanes are different rows and the load path serves 16 bytes a clock: 64 rows 1.75 us instead of 1.44).
+//  * A lane ends with rows 4*b + e of one head, which is the operand of O^T[column][head] += V^T.P^T when step e takes
+//    these rows; lane (m, b) takes columns 64*j + 4*m .. +3 of row 4*b + e as they are loaded, and the c-th of each four
+//    form a block of 16 result columns.  The weights never leave their lane.
+// Half or more of the 16 head columns are padding (groups have up to eight heads); 64 rows of d = 128 on four waves are
+// 0.87 us of matrix issue all the same.
+// What bounds it: launch gap, tables, first bytes and the merge for short sequences (50 rows: 5.0 to 7.7 us a step, 7.5 to
+// 16.4 on FMA instructions with sums over lanes, the form before), 45 GB/s a compute unit for long ones of few pairs, HBM for
+// large batches (12/2 heads, d = 128: 120 sequences of 760 rows 60.1 -> 33.7 us; 16/2 heads, 64 of 1500 rows 110 -> 38.4; 8/1
+// heads, 4 of 508 rows 17.5 -> 10.2).  Eight waves a workgroup: no difference, the load path is the same one.
+template <int D, int G, bool CHUNKS>
+__device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
+  constexpr int RB = D * 4;
+  constexpr int SUB = 128 / D, ROWS = 16 * SUB;    // 16-row blocks of a tile, its rows
+  constexpr int KI = D / 16, VJ = D / 64;          // 16-byte units per lane: of a K block's operand, of a row
+  constexpr int NW = kValuWaves;
+  typedef __attribute__((ext_vector_type(4))) float row16_t;
+
+  touch_kernel_arguments();
+  constexpr int APITCH = D + 4, WSTRIDE = G * APITCH + 2 * G + (2 * G) % 4;      // of the merge at the end, in floats
+  constexpr int LDS = NW * (16 * SUB * RB > 4 * WSTRIDE ? 16 * SUB * RB : 4 * WSTRIDE);
+  __shared__ __attribute__((aligned(1024))) char tiles[LDS];
+  const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0);
+  __shared__ int s_arrived;
+  if (!pi.live) {
+    if constexpr (CHUNKS) close_without_chunk<NW * 64, D, RB>(pi, NW, &s_arrived);
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, kb = lane >> 4;
+  const int ntiles = (pi.row_end - pi.row0 + ROWS - 1) / ROWS;
+  const int64_t stream_off = (pi.base * p.Hkv + (int64_t)pi.kvh * pi.cap) * RB;
+  const char* kbase = p.k_slab + stream_off;
+  const char* vbase = p.v_slab + stream_off;
+  // Fused step: the appended row (always the sequence's last) is not in the slab yet and comes from the caller's
+  // tensors; rows behind the chunk's end repeat its last one (masked).
+  const int64_t new_off = (int64_t)(pi.s * p.Hkv + pi.kvh) * RB;
+  auto row_of = [&](const char* base, const char* appended, int r) {
+    r = min(r, pi.row_end - 1);
+    return r == pi.new_row ? appended + new_off : base + (int64_t)r * RB;
+  };
+
+  // lane (n, kb) brings 16 bytes of rows 4*kb + e: 256 consecutive bytes of four rows an instruction
+  row16_t kk[2][SUB][4][VJ], vv[2][SUB][4][VJ];
+  auto load = [&](int stage, int tile) __attribute__((always_inline)) {
+    const int r0 = pi.row0 + tile * ROWS + 4 * kb;
+#pragma unroll
+    for (int u = 0; u < SUB; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const char* kr = row_of(kbase, p.new_k, r0 + 16 * u + e) + 16 * n;
+#pragma unroll
+        for (int j = 0; j < VJ; ++j)
+          kk[stage][u][e][j] = __builtin_nontemporal_load(reinterpret_cast<const row16_t*>(kr + 256 * j));
+      }
+#pragma unroll
+    for (int u = 0; u < SUB; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const char* vr = row_of(vbase, p.new_v, r0 + 16 * u + e) + 16 * n;
+#pragma unroll
+        for (int j = 0; j < VJ; ++j)
+          vv[stage][u][e][j] = __builtin_nontemporal_load(reinterpret_cast<const row16_t*>(vr + 256 * j));
+      }
+  };
+  // K goes through the wave's part of LDS into operand order, 16-byte unit x of row y at unit x ^ y of each 256 bytes: neither
+  // the writes (16 units of a row) nor the reads (one unit of 16 rows) meet in a bank.
+  char* wk = tiles + wave * (16 * SUB * RB);
+  const int ksrc = n * RB + ((kb ^ n) << 4);      // operand i: ^ 64 * (i % 4), + 256 * (i / 4)
+  auto k_to_lds = [&](int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < SUB; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < VJ; ++j)
+          *reinterpret_cast<row16_t*>(wk + (16 * u + 4 * kb + e) * RB + 256 * j + ((n ^ (4 * kb + e)) << 4)) = kk[stage][u][e][j];
+  };
+
+  // Q^T: column n = query head, the steps' elements as for K (the columns behind the group repeat its last head and are
+  // not looked at)
+  row16_t q[KI];
+  const char* qrow = p.q + (int64_t)(pi.s * p.Hq + pi.kvh * p.g + min(n, p.g - 1)) * RB + 16 * kb;
+#pragma unroll
+  for (int i = 0; i < KI; ++i) q[i] = *reinterpret_cast<const row16_t*>(qrow + 64 * i);
+
+  f32x4_t O[4 * VJ];
+#pragma unroll
+  for (int j = 0; j < 4 * VJ; ++j) O[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m_run = kNegBig, l_run = 0.f;
+  auto work = [&](int stage, int tile, bool last) __attribute__((always_inline)) {
+    const int r0 = pi.row0 + tile * ROWS;
+    float s[SUB][4];
+    float tmax = kNegBig;
+    k_to_lds(stage);
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) {
+      f32x4_t a[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int i = 0; i < KI; ++i) {
+        const row16_t k = *reinterpret_cast<const row16_t*>(wk + 16 * u * RB + (ksrc ^ (64 * (i & 3))) + 256 * (i >> 2));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c], q[i][c], a[c & 1], 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool there = r0 + 16 * u + 4 * kb + e < pi.row_end;
+        s[u][e] = there ? a[0][e] + a[1][e] : kNegBig;
+        tmax = fmaxf(tmax, s[u][e]);
+      }
+    }
+    tmax = rows_allreduce_max(tmax);
+    const float m_new = fmaxf(m_run, tmax * p.qscale);
+    const float alpha = fast_exp2(m_run - m_new);
+    m_run = m_new;
+    float psum = 0.f;
+#pragma unroll
+    for (int u = 0; u < SUB; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool there = r0 + 16 * u + 4 * kb + e < pi.row_end;
+        s[u][e] = there ? fast_exp2(fmaf(s[u][e], p.qscale, -m_new)) : 0.f;
+        psum += s[u][e];
+      }
+    l_run = l_run * alpha + psum;
+#pragma unroll
+    for (int j = 0; j < 4 * VJ; ++j) O[j] *= alpha;
+    // the appended row (the last of the sequence's last tile) outlives the step: stored for later ones (no reader
+    // touches the slab there in this launch)
+    if (last && pi.store_new_row && r0 + ROWS > pi.new_row) {
+#pragma unroll
+      for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (r0 + 16 * u + 4 * kb + e == pi.new_row)
+#pragma unroll
+            for (int j = 0; j < VJ; ++j) {
+              const int64_t at = (int64_t)pi.new_row * RB + 256 * j + 16 * n;
+              *reinterpret_cast<row16_t*>(const_cast<char*>(kbase) + at) = kk[stage][u][e][j];
+              *reinterpret_cast<row16_t*>(const_cast<char*>(vbase) + at) = vv[stage][u][e][j];
+            }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < SUB; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < VJ; ++j)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            O[4 * j + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[stage][u][e][j][c], s[u][e], O[4 * j + c], 0, 0, 0);
+  };
+  // The next tile's loads go out one after every other matrix instruction of the scores: all at once they keep the wave
+  // from its work until the memory pipeline has accepted them.
+  auto spread_loads = []() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Tiles wave, wave + NW, ... of the chunk are this wave's; one is on its way while another is worked on.  (Written out
+  // so that each place knows which loads are out: behind a join the compiler would wait for all of them.)
+  int tile = wave, mine = (ntiles - wave + NW - 1) / NW;
+  if (mine > 0) {
+    load(0, tile);
+    for (; mine > 2; mine -= 2, tile += 2 * NW) {
+      load(1, tile + NW);
+      work(0, tile, false);
+      spread_loads();
+      load(0, tile + 2 * NW);
+      work(1, tile + NW, false);
+      spread_loads();
+    }
+    if (mine == 2) {
+      load(1, tile + NW);
+      work(0, tile, false);
+      spread_loads();
+      work(1, tile + NW, true);
+    } else {
+      work(0, tile, true);
+    }
+  }
+  // Whole sequence: every wave takes a ticket when its reads of the slab are done, and looks at the answer behind the
+  // merge (by hand, as in decode_lds: the compiler would wait for it here).
+  __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), said so that the compiler knows
+  int ticket = -1;
+  if (pi.update && lane == 0 && (!CHUNKS || pi.nchunks == 1)) {
+    const int one = 1;
+    asm volatile("global_atomic_add %0, %1, %2, off sc0" : "=v"(ticket) : "v"(p.tickets + pi.s * kTicketStride), "v"(one) : "memory");
+  }
+  l_run = rows_allreduce_sum(l_run);
+
+  // merge the waves through LDS: lane (n, kb) holds columns 64*j + 16*kb + 4*e .. +3 of head n
+  // (each wave's part of LDS is its own up to the barrier)
+  constexpr int PITCH = LDS / NW / 4;
+  float* s_part = reinterpret_cast<float*>(tiles);
+  float* s_m = s_part + G * APITCH;
+  float* s_l = s_m + G;
+  if (n < G) {
+#pragma unroll
+    for (int j = 0; j < VJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<f32x4_t*>(s_part + wave * PITCH + n * APITCH + 64 * j + 16 * kb + 4 * e) =
+            f32x4_t{O[4 * j][e], O[4 * j + 1][e], O[4 * j + 2][e], O[4 * j + 3][e]};
+    if (kb == 0) { s_m[wave * PITCH + n] = m_run; s_l[wave * PITCH + n] = l_run; }
+  }
+  __syncthreads();
+  merge_waves_and_store4<NW, D, D, APITCH, CHUNKS, true>(p, pi, s_m, s_l, s_part, PITCH, 0);
+  if constexpr (CHUNKS) {
+    if (pi.nchunks > 1) {
+      close_pair<NW * 64, D, RB>(pi, &s_arrived);
+      return;
+    }
+  }
+  if (!pi.update) return;
+  wait_vmcnt<0>();
+  landed(ticket);
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
+  finish_step<RB>(p, pi, lane);
+}
+
+// The same on FMA instructions, for bf16 rows (BC_PLAN_PLAIN_ALU).
+// CHUNKS: as for the matrix kernel.
 template <typename T, int D, int G, int U, bool CHUNKS>
-__global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
+__device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
   constexpr int ES = Elem<T>::size;
   constexpr int EPL = Elem<T>::per16;   // elements per lane per row
   constexpr int LPR = D / EPL;          // lanes per row
@@ -1181,6 +1415,16 @@ __global__ __launch_bounds__(256) void decode_valu_kernel(DecodeParams p) {
   finish_step<RB>(p, pi, lane);
 }
 
+// Waves per SIMD that the plan reckons with: least and most.
+template <typename T, int G> constexpr int kValuLeast = std::is_same<T, float>::value && G < 8 ? 2 : 1;
+template <typename T, int G> constexpr int kValuMost = std::is_same<T, float>::value && G == 8 ? 1 : 8;
+template <typename T, int D, int G, int U, bool CHUNKS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kValuLeast<T, G>, kValuMost<T, G>)))
+void decode_valu_kernel(DecodeParams p) {
+  if constexpr (std::is_same<T, float>::value) decode_f32_rows<D, G, CHUNKS>(p);
+  else decode_alu_rows<T, D, G, U, CHUNKS>(p);
+}
+
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct DecodePlan {
@@ -1230,6 +1474,10 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     const int whole_passes = (npairs > kFewPairs || pl.Gp * sh->d >= 512 ? 1 : 2) + (alone ? 1 : 0);
     pl.split_rows = whole_passes * pl.rows_per_pass + 2;
     split_cap = (alone ? 4 : whole_passes) * pl.rows_per_pass + 1;
+    // fp32: half passes a sequence is read whole for
+    if (sh->kv_dtype == BC_F32)
+      pl.split_rows = npairs > 128 ? INT_MAX
+                                   : ((npairs <= 32 ? 5 : npairs <= 64 ? 7 : 14) + (alone ? 3 : 0)) * (pl.rows_per_pass / 2) + 2;
   }
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
@@ -1260,18 +1508,20 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // pays for its counters besides, cuts them later.
     // The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of 1 to 7 us (by group and d), against
     // some 2 us that a fold takes: cut from the second pass on, or from the third where a pass is short and the
-    // batch is small (whole and cut at the second / third pass: 2 pairs, d = 64, groups of one 8.2, 8.9 / 9.3, 9.0
-    // us; 8 pairs, d = 128, groups of two 10.1, 9.9 / 12.0, 9.9, of six 17.0, 15.0 / 22.2, 15.4; 128 pairs, d = 64,
-    // groups of four 13.1, 13.7 / 19.1, 14.7), with up to 256 pairs (fp32, 64 sequences of 500 rows, 12/2 heads: 62.8
-    // -> 27.8 us).  The lengths are not known here: a batch whose sequences are all within the first pass pays for
-    // the workgroups they do not fill, 0.1 to 0.3 us of 8 to 14 with up to 32 pairs, 0.5 to 0.9 with more.  256 workgroups run
-    // at once with groups of seven or eight, and of three or more of bf16 rows (over 256 registers), otherwise 512;
-    // beyond that a second round takes more than the cut saves (200 pairs, groups of eight, 500 rows: whole 73.5
-    // us, in 400 workgroups 83.7).  Attention alone has a launch in front to clear its counters, some 1.5 us: its
-    // sequences are cut one pass later, and by capacities beyond four passes.
+    // batch is small, with up to 256 pairs.  256 workgroups run at once with groups of three or more (over 256
+    // registers), otherwise 512; beyond that a second round takes more than the cut saves.  Attention alone has a launch in
+    // front to clear its counters, some 1.5 us: its sequences are cut one pass later, and by capacities beyond four passes.
+    // fp32 plans have chunks from the same capacities on, but a pass takes 1.4 us there and a sequence is cut
+    // later: where whole and cut meet is between 2.5 passes with few pairs and 7 with 128, and beyond those one workgroup a
+    // pair draws what HBM gives (us a step, whole / cut; 4 pairs, d = 128: 8.5 / 10.0 at 124 rows, 10.1 / 9.9 at 180, 11.9 / 9.9 at
+    // 252; 40 pairs 10.2 / 10.3 at 180, 11.7 / 10.4 at 252; 64 pairs 11.9 / 11.0 at 252; 120 pairs 15.5 / 15.7 at 380,
+    // 19.1 / 18.3 at 508, d = 64 10.7 / 11.7 at 380, 12.4 / 12.6 at 508, 15.7 / 15.4 at 760; 200 pairs 18.1 / 21.8 at 760, 29.0 / 33.8 at
+    // 1500; 240 pairs 33.3 / 38.2 at 760).  More workgroups than 256 do not help (40 pairs of 760 rows: 480 15.3, 240 13.5).  A
+    // plan whose sequences stay whole after all pays 0.2 to 0.4 us for the workgroups they do not fill.
     const bool eight_waves = npairs <= kFewPairs ||
                              (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
-    const bool one_per_cu = pl.lds ? eight_waves : pl.Gp == 8 || (sh->kv_dtype == BC_BF16 && pl.Gp >= 4);
+    const bool one_per_cu = pl.lds ? eight_waves
+                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs < 128 : pl.Gp >= 4;
     const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : 256;
     long chunks = 1;
     if (npairs <= most_pairs && max_cap >= split_cap) {

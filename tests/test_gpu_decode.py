@@ -986,3 +986,20 @@ def test_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, P):
         check_tables(rt, oc, t)
         check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, sample, t)
     check_slabs(rt, oc, sample)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,rows", [(4, 1, 64, 0), (12, 2, 128, 0), (8, 1, 128, 0), (3, 3, 64, 0), (7, 1, 64, 128),
+                                           (10, 2, 128, 64)])
+def test_fp32_rows_at_the_edges_of_their_tiles(dev, Hq, Hkv, d, rows):
+    # tiles of 16 rows (d = 128) or 32 (d = 64), four waves to a pass: sequences that end in front of, at and behind the edges
+    # of blocks, tiles and passes, with one tile a wave, two, and more; the appended row first in a tile and last; whole
+    # and in forced chunks
+    P = np.array([0, 1, 14, 15, 16, 30, 31, 47, 62, 63, 64, 111, 126, 127, 128, 191, 254, 255, 383, 600], np.int32)
+    B, G = len(P), 5
+    wl = W.Workload("rows32", 123, B, Hq, Hkv, d, "f32", P, np.full(B, G, np.int32),
+                    np.resize(np.array([3, 0, 1, 16], np.int32), B))
+    rt, oc = make(wl, dev)
+    rt.cache.rows_per_workgroup = rows
+    rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
+    q = wl.step_q(77)
+    check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, 77)

@@ -343,3 +343,17 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
         # the six table entries of the prologue (both kernels)
         assert sum(1 for l in body if re.match(r"s_load_dword(x2)? \S+ s\[(?!0:1)\d+:\d+\], 0x0$", l)) >= 6, text[s][:80]
         assert not reads_of_inflight_scalars(body), (text[s][:80], reads_of_inflight_scalars(body)[:3])
+
+
+def test_fp32_decode_kernels_leave_the_ticket_alone_until_it_is_there(tmp_path):
+    # the step's ticket is taken by hand and looked at behind the merge of the waves
+    text = _assembly("bc_decode.hip", tmp_path)
+    starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc18decode_valu_kernelIf\w+:", l)]
+    assert len(starts) == 20
+    for s in starts:
+        e = next(i for i in range(s, len(text)) if text[i].startswith(".Lfunc_end"))
+        marked = _instructions(text[s:e])
+        assert any(l.startswith("global_atomic_add v") and l.endswith(HAND) for l in marked), text[s][:80]
+        assert sum(1 for l in marked if l.startswith("landed ")) >= 1, text[s][:80]
+        assert not reads_of_inflight_registers(marked), (text[s][:80], reads_of_inflight_registers(marked)[:3])
+        assert not any(l.startswith(("scratch_", "buffer_")) for l in marked), text[s][:80]
