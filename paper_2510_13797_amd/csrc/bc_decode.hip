@@ -142,6 +142,16 @@ __device__ __forceinline__ void touch_kernel_arguments() {
   asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d));
 }
 
+// The kernel arguments, to be read afresh: what only the end of a kernel needs holds no scalar registers before
+// (kept from the start, 38 of them went through vector lanes in front of the first tile requests: one sequence of
+// 1551 rows, 8 KV heads, 11.8 us a step instead of 10.8).
+__device__ __forceinline__ DecodeParams arguments_again() {
+  typedef __attribute__((address_space(4))) const DecodeParams const_params_t;
+  const_params_t* at = (const_params_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));
+  return *(const DecodeParams*)at;
+}
+
 // slot: the sequence's index, or its rank in the dispatch order when there is one.  The grid
 // carries (KV head, slot, chunk) in its three dimensions, so that nothing has to be divided
 // before the tables can be requested; all of them are requested together.
@@ -253,24 +263,49 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
   return pi;
 }
 
-// What the holder of a sequence's last ticket does, as one wave, once every reader of the
-// sequence's rows is done with them: the beacon entry goes to its slot behind the earlier beacons
-// (the evicted window's first row), the tables move on, the ticket counter returns to zero.
-template <int ROWB>
-__device__ __forceinline__ void finish_step(const DecodeParams& p, const PairInfo& pi, int lane) {
+// The beacon entry of KV heads head0 .. head0 + heads - 1 goes to its slot behind the earlier beacons (the evicted
+// window's first row): by threads 0 .. threads - 1, once every reader of these heads' rows is done with them.  Four units
+// a thread are asked for before the first is stored.  FROM_LDS: the rows as request_beacon left them.
+constexpr int kBeaconBytes = 4096;
+template <int ROWB, bool FROM_LDS>
+__device__ __forceinline__ void store_beacon(const DecodeParams& p, const PairInfo& pi, int head0, int heads, int thread,
+                                             int threads, const char* lds_rows = nullptr) {
   constexpr int UPR = ROWB / 16;                   // 16-byte units per row
-  if (pi.evict_due) {
-    const int n16 = p.Hkv * UPR;                   // 16-byte units of one K (or V) entry
-    for (int i = lane; i < 2 * n16; i += 64) {
-      const int which = i >= n16, r = which ? i - n16 : i;
-      const int h = r / UPR, u = r & (UPR - 1);
-      const char* src = (which ? p.bv : p.bk) + (int64_t)(pi.s * p.Hkv + h) * ROWB + (u << 4);
-      char* slab = const_cast<char*>(which ? p.v_slab : p.k_slab);
-      const int64_t dst =
-          (pi.base * p.Hkv + (int64_t)h * pi.cap + pi.P + pi.nb) * ROWB + (u << 4);
-      *reinterpret_cast<uint4*>(slab + dst) = *reinterpret_cast<const uint4*>(src);
-    }
+  const int n16 = heads * UPR;                     // 16-byte units of K (or of V)
+  const int64_t src0 = (int64_t)(pi.s * p.Hkv + head0) * ROWB;
+  auto unit = [&](int i) -> u32x4_t {
+    if constexpr (FROM_LDS) return *reinterpret_cast<const u32x4_t*>(lds_rows + (i << 4));
+    else return *reinterpret_cast<const u32x4_t*>((i >= n16 ? p.bv - n16 * 16 : p.bk) + src0 + (i << 4));
+  };
+  auto put = [&](int i, u32x4_t x) {
+    const int which = i >= n16, r = which ? i - n16 : i;
+    const int64_t at = (pi.base * p.Hkv + (int64_t)(head0 + r / UPR) * pi.cap + pi.P + pi.nb) * ROWB + ((r & (UPR - 1)) << 4);
+    if (i < 2 * n16) *reinterpret_cast<u32x4_t*>(const_cast<char*>(which ? p.v_slab : p.k_slab) + at) = x;
+  };
+  for (int i = thread; i < 2 * n16; i += 4 * threads) {
+    const int end = 2 * n16 - 1;
+    const u32x4_t a = unit(i), b = unit(min(i + threads, end)), c = unit(min(i + 2 * threads, end)), d = unit(min(i + 3 * threads, end));
+    put(i, a); put(i + threads, b); put(i + 2 * threads, c); put(i + 3 * threads, d);
   }
+}
+// The beacon rows of all KV heads into LDS (by one wave, uncounted loads), where they fit, for whoever turns out to
+// draw the sequence's last ticket.  Asked for then, they were round trips to pages that nothing had touched yet, at the very
+// end of the step (a step that evicts: 32/8 heads, one sequence of 599 rows 8.3 -> 7.4 us, 64 of 400 23.6 -> 22.9; 12/2 heads, 64 of
+// 527 9.7 before and after).
+template <int ROWB>
+__device__ __forceinline__ bool beacon_fits(const DecodeParams& p) { return 2 * p.Hkv * ROWB <= kBeaconBytes; }
+template <int ROWB>
+__device__ __forceinline__ void request_beacon(const DecodeParams& p, int s, int lane, const char* lds_dst) {
+  const int n = p.Hkv * ROWB;
+  const int64_t at = (int64_t)s * n;
+  for (int i0 = 0; i0 < 2 * n; i0 += 1024) {
+    const int i = min(i0 + 16 * lane, 2 * n - 16);
+    lds_dma16<false>((i >= n ? p.bv - n : p.bk) + at + i, lds_dst + i0);
+  }
+}
+// What the holder of a sequence's last ticket does, as one wave, once every reader of the sequence's tables is done with
+// them: the tables move on, the ticket counter returns to zero.
+__device__ __forceinline__ void move_tables(const DecodeParams& p, const PairInfo& pi, int lane) {
   if (lane == 0) {
     // (past the L2: other words of the line are counted on by workgroups of other XCDs)
     __hip_atomic_store(p.tickets + pi.s * kTicketStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -278,6 +313,15 @@ __device__ __forceinline__ void finish_step(const DecodeParams& p, const PairInf
     p.w_rw[pi.s] = pi.evict_due ? 0 : pi.w_att;
     if (p.budget && pi.nb + pi.w_att >= p.budget[pi.s]) p.live[pi.s] = 0;   // generation interrupted
   }
+}
+// Both, for a sequence that is not cut.
+template <int ROWB>
+__device__ __forceinline__ void finish_step(const DecodeParams& p, const PairInfo& pi, int lane, const char* beacon = nullptr) {
+  if (pi.evict_due) {
+    if (beacon != nullptr) store_beacon<ROWB, true>(p, pi, 0, p.Hkv, lane, 64, beacon);
+    else store_beacon<ROWB, false>(p, pi, 0, p.Hkv, lane, 64);
+  }
+  move_tables(p, pi, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -364,16 +408,6 @@ __device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairIn
   }
 }
 
-// The kernel arguments, to be read afresh: what only the end of a kernel needs holds no scalar registers before
-// (kept from the start, 38 of them went through vector lanes in front of the first tile requests: one sequence of
-// 1551 rows, 8 KV heads, 11.8 us a step instead of 10.8).
-__device__ __forceinline__ DecodeParams arguments_again() {
-  typedef __attribute__((address_space(4))) const DecodeParams const_params_t;
-  const_params_t* at = (const_params_t*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(at));
-  return *(const DecodeParams*)at;
-}
-
 // The end of a workgroup of a cut sequence.
 template <int NT, int D, int ROWB>
 __device__ __forceinline__ void close_pair(const PairInfo& pi, int* s_arrived) {
@@ -382,12 +416,15 @@ __device__ __forceinline__ void close_pair(const PairInfo& pi, int* s_arrived) {
     const DecodeParams p = arguments_again();
     if (!last_arrival(p, pi, s_arrived)) return;
     if (pi.update && threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
+    // everyone who reads this KV head's rows has arrived: its beacon row need not wait for the sequence's last ticket
+    // (one sequence of 1551 rows, 32/8 heads: 10.3 -> 10.1 us)
+    if (pi.evict_due) store_beacon<ROWB, false>(p, pi, pi.kvh, 1, threadIdx.x, NT);
   }
   merge_chunks<NT, D>(arguments_again(), pi);
   if (!pi.update || threadIdx.x >= 64) return;
   const DecodeParams p = arguments_again();
   if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, 0, pi.nchunks, p.max_chunks) - 1)
-    finish_step<ROWB>(p, pi, threadIdx.x);
+    move_tables(p, pi, threadIdx.x);
 }
 // The end of a workgroup without rows.  own: see tickets_due().
 template <int NT, int D, int ROWB>
@@ -500,7 +537,7 @@ constexpr int kSplitWaves12MaxCap = 1100;   // rows: beyond this eight waves are
 constexpr int kTileRows = 32;          // rows per wave tile
 constexpr int kLdsBytes = kLdsWaves * 2 * kTileRows * 256;   // d = 128: 128 KB (half of it for d = 64)
 constexpr int kLdsBytesSplit = kLdsWavesSplit * 3 * kTileRows * 128;   // K tile + half a V tile per wave: 144 KB
-constexpr int kLdsBytesMax = kLdsBytesSplit > kLdsBytes ? kLdsBytesSplit : kLdsBytes;
+constexpr int kLdsBytesMax = (kLdsBytesSplit > kLdsBytes ? kLdsBytesSplit : kLdsBytes) + kBeaconBytes;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
@@ -742,6 +779,12 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
     if (trow0 + kTileRows <= last_slab_row + 1) request_tile_dma(std::false_type{}, kbase_s, vbase_s, trow0, 0);
     else request_tile_dma(std::true_type{}, kbase_s, vbase_s, trow0, last_slab_row);
   }
+  // (the last wave has the fewest tiles; its loads have landed by the barrier in front of the merge)
+  char* beacon = lds + NW * (TILEB + VTILEB);
+  if (pi.evict_due && wave == NW - 1) {
+    const DecodeParams again = arguments_again();
+    if (beacon_fits<ROWB>(again)) request_beacon<ROWB>(again, pi.s, lane, beacon);
+  }
 
   // Fused step, whole sequence: every wave with rows takes a ticket as soon as its last load from the
   // slab has landed (the tables were read at the start), a workgroup without rows takes one; whoever
@@ -975,7 +1018,7 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   wait_vmcnt<0>();     // the ticket has arrived
   landed(ticket);
   if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, VS * NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
-  finish_step<ROWB>(p, pi, lane);
+  finish_step<ROWB>(p, pi, lane, beacon_fits<ROWB>(p) ? beacon : nullptr);
 }
 
 template <int STREAM, int D, int VS, int NW, bool SHORT = false>
@@ -1579,6 +1622,7 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
                                  bool ordered) {
   const int pairs = shape->B * shape->Hkv;
   const dim3 grid = decode_grid(shape, pl);
+  const int lds_full = kLdsBytes + kBeaconBytes, lds_half = kLdsBytes / 2 + kBeaconBytes;      // tiles, beacon rows
   // launches that cannot saturate the memory system are latency-bound: default cache policy
   const bool cacheable = (cache->plan & BC_PLAN_CACHEABLE_LOADS) != 0;
   const bool general = (cache->plan & BC_PLAN_GENERAL_LOOP) != 0;
@@ -1600,7 +1644,8 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
     const bool w12 = cache->max_cap <= kSplitWaves12MaxCap;
     const bool two12 = w12 && cache->max_cap <= 2 * kLdsWavesSplit * kTileRows && !general;
     const dim3 g2(shape->Hkv, slots, 2);
-    const int t12 = kLdsWavesSplit * 64, l12 = kLdsBytesSplit, t8 = kLdsWaves * 64, l8 = kLdsWaves * 3 * kTileRows * 128;
+    const int t12 = kLdsWavesSplit * 64, l12 = kLdsBytesSplit + kBeaconBytes, t8 = kLdsWaves * 64;
+    const int l8 = kLdsWaves * 3 * kTileRows * 128 + kBeaconBytes;
     if (two12) return stream2 ? LdsLaunch{BC_LDS_KERNEL(1, 128, 2, 12, true), g2, t12, l12}
                               : LdsLaunch{BC_LDS_KERNEL(0, 128, 2, 12, true), g2, t12, l12};
     if (!stream2) return w12 ? LdsLaunch{BC_LDS_KERNEL(0, 128, 2, 12), g2, t12, l12}
@@ -1619,25 +1664,25 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
   if (pl.max_chunks > 1) {
     if (shape->d == 128) {
       if (small && pl.R == 0 && pairs > kFewPairs)
-        return LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 4), grid, 4 * 64, kLdsBytes / 2};
-      return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 8), grid, kLdsWaves * 64, kLdsBytes}
-                    : LdsLaunch{BC_LDS_CUT_KERNEL(0, 128, 8), grid, kLdsWaves * 64, kLdsBytes};
+        return LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 4), grid, 4 * 64, lds_half};
+      return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 8), grid, kLdsWaves * 64, lds_full}
+                    : LdsLaunch{BC_LDS_CUT_KERNEL(0, 128, 8), grid, kLdsWaves * 64, lds_full};
     }
-    return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 64, 8), grid, kLdsWaves * 64, kLdsBytes / 2}
-                  : LdsLaunch{BC_LDS_CUT_KERNEL(0, 64, 8), grid, kLdsWaves * 64, kLdsBytes / 2};
+    return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 64, 8), grid, kLdsWaves * 64, lds_half}
+                  : LdsLaunch{BC_LDS_CUT_KERNEL(0, 64, 8), grid, kLdsWaves * 64, lds_half};
   }
   if (shape->d == 128) {
     if (small && pairs > kLptMinPairs && cache->max_cap <= kSplitWaves12MaxCap)
-      return LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 4), grid, 4 * 64, kLdsBytes / 2};
-    if (two8) return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes}
-                            : LdsLaunch{BC_LDS_KERNEL(0, 128, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes};
-    return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8), grid, kLdsWaves * 64, kLdsBytes}
-                  : LdsLaunch{BC_LDS_KERNEL(0, 128, 1, 8), grid, kLdsWaves * 64, kLdsBytes};
+      return LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 4), grid, 4 * 64, lds_half};
+    if (two8) return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8, true), grid, kLdsWaves * 64, lds_full}
+                            : LdsLaunch{BC_LDS_KERNEL(0, 128, 1, 8, true), grid, kLdsWaves * 64, lds_full};
+    return stream ? LdsLaunch{BC_LDS_KERNEL(1, 128, 1, 8), grid, kLdsWaves * 64, lds_full}
+                  : LdsLaunch{BC_LDS_KERNEL(0, 128, 1, 8), grid, kLdsWaves * 64, lds_full};
   }
-  if (two8) return stream ? LdsLaunch{BC_LDS_KERNEL(1, 64, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes / 2}
-                          : LdsLaunch{BC_LDS_KERNEL(0, 64, 1, 8, true), grid, kLdsWaves * 64, kLdsBytes / 2};
-  return stream ? LdsLaunch{BC_LDS_KERNEL(1, 64, 1, 8), grid, kLdsWaves * 64, kLdsBytes / 2}
-                : LdsLaunch{BC_LDS_KERNEL(0, 64, 1, 8), grid, kLdsWaves * 64, kLdsBytes / 2};
+  if (two8) return stream ? LdsLaunch{BC_LDS_KERNEL(1, 64, 1, 8, true), grid, kLdsWaves * 64, lds_half}
+                          : LdsLaunch{BC_LDS_KERNEL(0, 64, 1, 8, true), grid, kLdsWaves * 64, lds_half};
+  return stream ? LdsLaunch{BC_LDS_KERNEL(1, 64, 1, 8), grid, kLdsWaves * 64, lds_half}
+                : LdsLaunch{BC_LDS_KERNEL(0, 64, 1, 8), grid, kLdsWaves * 64, lds_half};
 }
 
 // The LDS kernel needs 128 KB of dynamic LDS: opt in once per device.  Two host threads that get

@@ -1003,3 +1003,16 @@ def test_fp32_rows_at_the_edges_of_their_tiles(dev, Hq, Hkv, d, rows):
     rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
     q = wl.step_q(77)
     check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, 77)
+
+
+@pytest.mark.parametrize("Hkv,d,plan", [(8, 128, 0), (9, 128, 0), (8, 128, 16), (9, 128, 16), (16, 64, 0), (17, 64, 0)])
+def test_beacon_rows_of_as_many_heads_as_fit_lds_and_one_more(dev, Hkv, d, plan):
+    # the step's beacon rows of all KV heads wait in 4 KB of LDS; with more heads they are read when they are written.
+    # Two workgroups per pair (d = 128), one, and d = 64; short and second-tile sequences, an inactive ratio among them
+    P = np.array([3, 60, 290, 400], np.int32)
+    wl = W.Workload("beaconrows", 124, 4, Hkv, Hkv, d, "bf16", P, np.full(4, 12, np.int32), np.array([3, 1, 0, 4], np.int32))
+    rt, oc = make(wl, dev)
+    rt.cache.plan = plan
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and "chunks=1" in text, text
+    rollout(wl, rt, oc, 12, range(1, 13), (4, 12), use_step_call=True)
