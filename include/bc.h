@@ -293,6 +293,12 @@ int32_t bc_prefill_attn(const bc_shape *shape, const void *q, const void *k, con
                         const int64_t *row_offsets, const int32_t *P, const int32_t *c,
                         int32_t max_rows, float *out, float *lse, void *stream);
 
+/* The tables of the prefill calls from HOST arrays, read before the call returns: row_offsets [B + 1], P [B], c [B].
+ * tables: device, 16 * B + 8 bytes, 8-byte aligned: the offsets, then P, then c.  The values travel in kernel arguments
+ * (a copy from ordinary host memory waits for the stream and takes some 14 us), so the call only enqueues work. */
+int32_t bc_trajectory_tables(const int64_t *row_offsets, const int32_t *P, const int32_t *c, int32_t B, void *tables,
+                             void *stream);
+
 /* bc_prefill_attn with a workspace (Fig. 2, Sec. 3.2; same operation, same tensors, same
  * tolerance).  The workspace (device memory, bc_prefill_workspace_bytes() bytes, 16-byte aligned,
  * no initialisation, contents unspecified afterwards) receives a copy of V in half precision.

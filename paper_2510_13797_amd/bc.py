@@ -34,7 +34,7 @@ EXPORTS = [
     "bc_decode_workspace_bytes", "bc_workspace_init", "bc_decode_plan_describe", "bc_decode_attn",
     "bc_compress_evict", "bc_decode_step", "bc_decode_step_noalloc", "bc_beacon_step", "bc_decode_step_budget", "bc_set_ratio",
     "bc_sort_by_length",
-    "bc_prefill_attn", "bc_prefill_workspace_bytes", "bc_prefill_attn_ws",
+    "bc_trajectory_tables", "bc_prefill_attn", "bc_prefill_workspace_bytes", "bc_prefill_attn_ws",
     "bc_prefill_bwd_workspace_bytes", "bc_prefill_attn_bwd",
     "bc_topk_kl_loss", "bc_topk_kl_loss_bwd", "bc_tables_to_host",
 ]
@@ -106,6 +106,8 @@ def load():
     lib.bc_decode_step_budget.argtypes = [sp, cp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.bc_set_ratio.restype = i32
     lib.bc_set_ratio.argtypes = [sp, cp, vp, vp, vp]
+    lib.bc_trajectory_tables.restype = i32
+    lib.bc_trajectory_tables.argtypes = [vp, vp, vp, i32, vp, vp]
     lib.bc_prefill_attn.restype = i32
     lib.bc_prefill_attn.argtypes = [sp, vp, vp, vp, vp, vp, vp, i32, vp, vp, vp]
     lib.bc_prefill_workspace_bytes.restype = C.c_size_t
@@ -229,6 +231,10 @@ def bc_set_ratio(shape, cache, new_c, active, stream):
     return load().bc_set_ratio(C.byref(shape), C.byref(cache), new_c, active, stream)
 
 
+def bc_trajectory_tables(row_offsets, P, c, B, tables, stream):
+    return load().bc_trajectory_tables(row_offsets, P, c, B, tables, stream)
+
+
 def bc_prefill_workspace_bytes(shape, total_rows):
     return load().bc_prefill_workspace_bytes(C.byref(shape), total_rows)
 
@@ -292,13 +298,37 @@ def to_device(x, dtype: str, device):
     return torch.from_numpy(np.ascontiguousarray(x)).to(device)
 
 
+_torch_c = None
+
+
 def _stream_ptr():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream of the current device, as a number (0.2 us; by way of
+    torch.cuda.current_stream() 3 us, a third of a small decode step's call)."""
+    global _torch_c
+    if _torch_c is None:
+        import torch
+        torch.cuda.current_stream()                # (initialises the device if nothing has)
+        _torch_c = torch._C
+    return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _used_here(*tensors):
+    """The current stream uses these tensors, which the caller may free as soon as the call returns: memory that
+    came from another stream is not given out again before this one is done with it."""
+    import torch
+    stream_id, device_index, device_type = torch._C._cuda_getCurrentStream(torch._C._cuda_getDevice())
+    stream = torch.Stream(stream_id=stream_id, device_index=device_index, device_type=device_type)
+    for t in tensors:
+        if t is None:
+            continue
+        if t.is_cuda:
+            t.record_stream(stream)
+        else:
+            torch.cuda.current_stream().synchronize()      # pinned host memory: nothing tracks it
 
 
 class Runtime:
@@ -504,8 +534,8 @@ class Runtime:
 
 
 def _trajectory_tables(row_offsets, P, c, device):
-    """row_offsets [B+1] int64, P, c [B] int32 in one device buffer: one copy instead of three (each a
-    round trip of some 12 us from pageable memory).  Returns (buffer, the three addresses)."""
+    """row_offsets [B+1] int64, P, c [B] int32 in one device buffer, sent in kernel arguments.
+    Returns (buffer, the three addresses)."""
     import torch
     B = len(row_offsets) - 1
     host = np.empty(2 * B + 1, dtype=np.int64)
@@ -513,8 +543,9 @@ def _trajectory_tables(row_offsets, P, c, device):
     tables = host[B + 1:].view(np.int32)
     tables[:B] = np.asarray(P, dtype=np.int32).reshape(-1)[:B]
     tables[B:] = np.asarray(c, dtype=np.int32).reshape(-1)[:B]
-    dev = torch.from_numpy(host).to(device)
-    at = dev.data_ptr()
+    dev = torch.empty(2 * B + 1, dtype=torch.int64, device=device)
+    at, src = dev.data_ptr(), host.ctypes.data
+    _check(bc_trajectory_tables(src, src + 8 * (B + 1), src + 8 * (B + 1) + 4 * B, B, at, _stream_ptr()))
     return dev, at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B
 
 
@@ -522,7 +553,9 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     """bc_prefill_attn (or, workspace=True, bc_prefill_attn_ws) on device tensors.
 
     q [R, Hq, d], k, v [R, Hkv, d] bf16 device tensors (trajectories concatenated);
-    row_offsets [B+1] int64, P, c [B] int32 (host arrays).  Returns (out fp32 [R,Hq,d], lse or None).
+    row_offsets [B+1] int64, P, c [B] int32 (host arrays).  Returns (out fp32 [R,Hq,d], lse or None), which the
+    current stream works on: like every call here it only enqueues (until it did, copies of the tables and a wait at
+    the end cost some 20 us a call; forward and gradients of three short trajectories 154 -> 79 us).
     """
     import torch
     load()
@@ -534,7 +567,7 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     R = int(row_offsets[-1])
     out = torch.empty(R, Hq, d, dtype=torch.float32, device=dev)
     lse = torch.empty(R, Hq, dtype=torch.float32, device=dev) if want_lse else None
-    max_rows = int(np.diff(row_offsets).max())
+    max_rows = int((row_offsets[1:] - row_offsets[:-1]).max())
     if workspace:
         nbytes = int(bc_prefill_workspace_bytes(shape, R))
         ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
@@ -543,7 +576,7 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     else:
         _check(bc_prefill_attn(shape, _ptr(q), _ptr(k), _ptr(v), off_at, P_at, c_at, max_rows,
                                _ptr(out), _ptr(lse), _stream_ptr()))
-    torch.cuda.current_stream().synchronize()      # the tables (and the workspace) may be freed after this
+    _used_here(q, k, v)      # (tables and workspace are the current stream's own)
     return out, lse
 
 
@@ -566,11 +599,11 @@ def prefill_attn_bwd(q, k, v, out, lse, dout, row_offsets, P, c, Hq, Hkv, d, sca
             x[:first] = float("nan")
     ws_bytes = int(bc_prefill_bwd_workspace_bytes(shape, R))
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    max_rows = int(np.diff(row_offsets).max())
+    max_rows = int((row_offsets[1:] - row_offsets[:-1]).max())
     _check(bc_prefill_attn_bwd(shape, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout),
                                off_at, P_at, c_at, max_rows, R, _ptr(dq), _ptr(dk), _ptr(dv),
                                _ptr(ws), ws_bytes, _stream_ptr()))
-    torch.cuda.current_stream().synchronize()
+    _used_here(q, k, v, out, lse, dout)
     return dq, dk, dv
 
 
@@ -599,7 +632,7 @@ def topk_kl_loss(student_logits, teacher_logits, teacher_idx):
     _check(bc_topk_kl_loss(T, V, k, _ptr(student_logits), _logits_code(student_logits),
                            _ptr(teacher_logits), _ptr(teacher_idx), _ptr(loss), _ptr(lse), _ptr(mean),
                            _stream_ptr()))
-    torch.cuda.current_stream().synchronize()
+    _used_here(student_logits, teacher_logits, teacher_idx)
     return loss, lse, mean
 
 
@@ -613,5 +646,5 @@ def topk_kl_loss_bwd(student_logits, teacher_logits, teacher_idx, lse, grad_scal
     _check(bc_topk_kl_loss_bwd(T, V, k, _ptr(student_logits), _logits_code(student_logits),
                                _ptr(teacher_logits), _ptr(teacher_idx), _ptr(lse), float(grad_scale),
                                _ptr(dz), _stream_ptr()))
-    torch.cuda.current_stream().synchronize()
+    _used_here(student_logits, teacher_logits, teacher_idx, lse)
     return dz

@@ -32,6 +32,8 @@
 //  - operands of a tile at one register plus constants, no bank conflicts (bc_prefill_tiles.h);
 //  - loads asked for behind the scores' MFMAs, their addresses from a cursor, and prompt and beacon
 //    remainders packed with the band (7 % fewer MFMAs, bc_prefill_tiles.h): together 0.77 -> 0.70 ms.
+#include <cstddef>
+#include <cstring>
 #include <type_traits>
 
 #include "bc_prefill_tiles.h"
@@ -297,6 +299,37 @@ __global__ void prefill_clear_flag_kernel(int32_t* flag) { flag[0] = 0; }
 
 constexpr size_t kPfFlagBytes = 256;
 
+// Words that travel in the kernel arguments.  Two sizes: the small one is what 31 trajectories take; the large
+// one keeps the arguments under 4 KB, and more trajectories take more launches.
+template <int N> struct ArgumentWords {
+  uint32_t* dst;
+  int32_t n;
+  uint32_t w[N];
+};
+template <int N>
+__global__ __launch_bounds__(256) void store_words_kernel(ArgumentWords<N> a) {
+  typedef __attribute__((address_space(4))) const uint32_t const_word_t;      // (a.w[i] would go through scratch)
+  const_word_t* w = (const_word_t*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ArgumentWords<N>, w) / 4;
+  for (int i = threadIdx.x; i < a.n; i += blockDim.x) a.dst[i] = w[i];
+}
+template <int N>
+static void store_words(uint32_t* dst, const uint32_t* src, int n, hipStream_t hs) {
+  ArgumentWords<N> a;
+  a.dst = dst;
+  a.n = n;
+  memcpy(a.w, src, (size_t)n * 4);
+  store_words_kernel<N><<<1, 256, 0, hs>>>(a);
+}
+static void store_words(uint32_t* dst, const void* src, int64_t n, hipStream_t hs) {
+  constexpr int kFew = 126, kMany = 1000;
+  const uint32_t* from = static_cast<const uint32_t*>(src);
+  for (int64_t at = 0; at < n; at += kMany) {
+    const int m = (int)(n - at < kMany ? n - at : kMany);
+    if (m <= kFew) store_words<kFew>(dst + at, from + at, m, hs);
+    else store_words<kMany>(dst + at, from + at, m, hs);
+  }
+}
+
 template <int D, bool HALF>
 static void launch_prefill_d(const PrefillParams& p, bool wide, dim3 grid, hipStream_t hs) {
   if (wide) prefill_kernel<D, HALF, true><<<grid, kTileWaves * 64, 0, hs>>>(p);
@@ -347,6 +380,23 @@ static int32_t prefill_forward(const bc_shape* shape, const void* q, const void*
 }  // namespace bc
 
 using namespace bc;
+
+extern "C" int32_t bc_trajectory_tables(const int64_t* row_offsets, const int32_t* P, const int32_t* c, int32_t B,
+                                        void* tables, void* stream) {
+  if (!row_offsets || !P || !c || !tables || (reinterpret_cast<uintptr_t>(tables) & 7u)) return BC_ERR_ARG;
+  if (B < 1) return BC_ERR_SHAPE;
+  hipStream_t hs = as_stream(stream);
+  uint32_t* dst = static_cast<uint32_t*>(tables);
+  const int64_t offset_words = 2 * ((int64_t)B + 1);
+  if (P == reinterpret_cast<const int32_t*>(row_offsets + B + 1) && c == P + B) {      // one array already
+    store_words(dst, row_offsets, offset_words + 2 * (int64_t)B, hs);
+  } else {
+    store_words(dst, row_offsets, offset_words, hs);
+    store_words(dst + offset_words, P, B, hs);
+    store_words(dst + offset_words + B, c, B, hs);
+  }
+  return launch_status();
+}
 
 extern "C" size_t bc_prefill_workspace_bytes(const bc_shape* shape, int64_t total_rows) {
   if (check_shape(shape) != BC_OK || total_rows < 1) return 0;

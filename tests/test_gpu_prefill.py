@@ -528,3 +528,97 @@ def test_prefill_bwd_parts_follow_the_dense_keys_of_a_trajectory(dev, Hq, Hkv, d
     assert np.isfinite(dq).all() and np.isfinite(dk).all() and np.isfinite(dv).all()
     for b in (0, 1, B - 1):
         _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 62, 63, 249, 250, 700])
+def test_tables_that_travel_in_kernel_arguments(dev, B):
+    # 31 trajectories fit the small form (126 words), 249 one launch of the large one (1000); one array and three
+    import torch
+    from paper_2510_13797_amd import bc
+    r = np.random.default_rng(B)
+    host = np.empty(2 * B + 1, np.int64)
+    host[:B + 1] = np.cumsum(r.integers(1, 1 << 33, B + 1))
+    pc = host[B + 1:].view(np.int32)
+    pc[:] = r.integers(-5, 1 << 30, 2 * B)
+    off, P, c = host[:B + 1].copy(), pc[:B].copy(), pc[B:].copy()
+    at = host.ctypes.data
+    for arrays in ((at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B), (off.ctypes.data, P.ctypes.data, c.ctypes.data)):
+        out = torch.full((2 * B + 2,), -1, dtype=torch.int64, device=dev)
+        assert bc.bc_trajectory_tables(*arrays, B, out.data_ptr(), None) == bc.BC_OK
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:-1], host) and got[-1] == -1
+    assert bc.bc_trajectory_tables(at, at, at, B, None, None) == bc.BC_ERR_ARG
+    assert bc.bc_trajectory_tables(at, at, at, B, out.data_ptr() + 4, None) == bc.BC_ERR_ARG
+    assert bc.bc_trajectory_tables(at, at, at, 0, out.data_ptr(), None) == bc.BC_ERR_SHAPE
+
+
+def _small_training_step(dev, seed):
+    import torch
+    g = torch.Generator(device=dev).manual_seed(seed)
+    off, P, c = np.array([0, 300, 700, 1900]), np.array([20, 0, 64], np.int32), np.array([4, 0, 16], np.int32)
+    rnd = lambda h: torch.randn(1900, h, 128, generator=g, device=dev).to(torch.bfloat16)
+    return (off, P, c, 6, 2, 128, 128 ** -0.5), [rnd(6), rnd(2), rnd(2)], rnd(6)
+
+
+def test_inputs_of_another_stream_may_be_freed_behind_the_call(dev):
+    # the calls only enqueue their work: memory of inputs that were made on another stream must not be given
+    # out again there before that work has read it
+    import torch
+    from paper_2510_13797_amd import bc
+    args, qkv, do = _small_training_step(dev, 7)
+    want, lse = bc.prefill_attn(*qkv, *args)
+    want_grads = bc.prefill_attn_bwd(*qkv, want, lse, do, *args)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            copies, do2 = [x.clone() for x in qkv], do.clone()
+        side.synchronize()
+        big = torch.empty(1 << 28, dtype=torch.uint8, device=dev)
+        for _ in range(4):
+            big.fill_(1)                                  # keeps the calls' work waiting
+        out, lse2 = bc.prefill_attn(*copies, *args)
+        grads = bc.prefill_attn_bwd(*copies, out, lse2, do2, *args)
+        sizes = [x.shape for x in copies] + [do2.shape]
+        del copies, do2
+        with torch.cuda.stream(side):
+            junk = [torch.full(n, float("nan"), dtype=torch.bfloat16, device=dev) for n in sizes]
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and all(torch.equal(a, b) for a, b in zip(grads, want_grads))
+        del junk
+
+
+def test_training_calls_captured_in_a_graph(dev):
+    # forward, gradients and both passes of the loss in one graph: replayed on other inputs, with eager work and
+    # synchronizations between the replays, every replay equal to the eager calls
+    import torch
+    from paper_2510_13797_amd import bc
+    args, qkv, do = _small_training_step(dev, 8)
+    z = torch.randn(64, 3001, device=dev).to(torch.bfloat16)
+    tl, idx = torch.randn(64, 9, device=dev), torch.randint(0, 3001, (64, 9), device=dev, dtype=torch.int32)
+
+    def step():
+        ws_out, _ = bc.prefill_attn(*qkv, *args, workspace=True)
+        out, lse = bc.prefill_attn(*qkv, *args)
+        loss, zlse, mean = bc.topk_kl_loss(z, tl, idx)
+        return [ws_out, out, lse, loss, zlse, mean, bc.topk_kl_loss_bwd(z, tl, idx, zlse, 0.5),
+                *bc.prefill_attn_bwd(*qkv, out, lse, do, *args)]
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        step()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            got = step()
+    for seed in (11, 12, 13):
+        _, qkv2, do2 = _small_training_step(dev, seed)
+        for x, y in zip(qkv + [do], qkv2 + [do2]):
+            x.copy_(y)
+        z.normal_()
+        torch.cuda.synchronize()
+        want = [x.clone() for x in step()]
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), seed
