@@ -1265,7 +1265,7 @@ __device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
   finish_step<RB>(p, pi, lane);
 }
 
-// The same on FMA instructions, for bf16 rows (BC_PLAN_PLAIN_ALU).
+// The same on FMA instructions, for bf16 rows (BC_PLAN_PLAIN_ALU) and small fp32 groups (fma_is_faster).
 // CHUNKS: as for the matrix kernel.
 template <typename T, int D, int G, int U, bool CHUNKS>
 __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
@@ -1459,12 +1459,12 @@ __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
 }
 
 // Waves per SIMD that the plan reckons with: least and most.
-template <typename T, int G> constexpr int kValuLeast = std::is_same<T, float>::value && G < 8 ? 2 : 1;
-template <typename T, int G> constexpr int kValuMost = std::is_same<T, float>::value && G == 8 ? 1 : 8;
-template <typename T, int D, int G, int U, bool CHUNKS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kValuLeast<T, G>, kValuMost<T, G>)))
+template <int G, bool FMA> constexpr int kValuLeast = !FMA && G < 8 ? 2 : 1;
+template <int G, bool FMA> constexpr int kValuMost = !FMA && G == 8 ? 1 : 8;
+template <typename T, int D, int G, int U, bool CHUNKS, bool FMA = !std::is_same<T, float>::value>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kValuLeast<G, FMA>, kValuMost<G, FMA>)))
 void decode_valu_kernel(DecodeParams p) {
-  if constexpr (std::is_same<T, float>::value) decode_f32_rows<D, G, CHUNKS>(p);
+  if constexpr (!FMA) decode_f32_rows<D, G, CHUNKS>(p);
   else decode_alu_rows<T, D, G, U, CHUNKS>(p);
 }
 
@@ -1472,6 +1472,7 @@ static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct DecodePlan {
   bool lds;           // LDS/MFMA kernel (bf16, d = 128) or the VALU kernel
+  bool fma;           // the latter on FMA instructions (bf16 always, fp32 by fma_is_faster())
   int Gp;             // padded group size
   int rows_per_pass;  // rows one pass of a workgroup covers
   int R;              // rows per workgroup
@@ -1494,6 +1495,19 @@ constexpr int kFewPairs = 32;             // see make_plan
 constexpr long kMostChunks = 64;
 constexpr int kChunkRowsMax = 512;    // rows a chunk of the matrix kernel need not go beyond: two passes of eight waves
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
+
+// fp32 groups of one or two on FMA instructions: they need so few registers there that four (groups of two), six (d = 128) or seven
+// workgroups share a compute unit, two on the matrix instructions, which waste 14 or 15 columns of 16 besides.  Where all
+// workgroups run at once on FMA but not on the matrix instructions, FMA is faster (FMA, matrix, us a step of 50 / 130 rows; groups of one, d = 128: 512 pairs 10.7, 10.0 / 19.2, 17.0; 880 13.2, 15.5 /
+// 26.1, 28.5; 1200 15.4, 19.4 / 31.9, 37.9; 2000 25.6, 27.7 / 58.2, 54.7; d = 64: 880 14.0, 12.7 / 18.8, 18.9; 1200 15.4, 15.8 / 21.0, 24.5;
+// 2000 23.9, 22.1 / 37.6, 34.0; groups of two, d = 64: 512 10.4, 8.4 / 13.6, 11.9; 880 12.5, 12.7 / 17.2, 19.5; 1200 18.2, 16.2 / 26.6,
+// 25.1; ragged, 2040 pairs of 17 to 104 rows, groups of one, d = 128: 27 and 30, 1584 of 10 to 55, d = 64:
+// 16 and 19).
+static bool fma_is_faster(long npairs, int Gp, int d, int max_cap) {
+  if (Gp == 2) return npairs > 512 && npairs <= 1024;
+  if (Gp != 1) return false;
+  return d == 64 ? npairs > 1024 && npairs <= 1792 : npairs > 512 && (npairs <= 1536 || max_cap <= 128);
+}
 
 // alone: attention without a step.
 static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits, bool alone = false) {
@@ -1520,7 +1534,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // fp32: half passes a sequence is read whole for
     if (sh->kv_dtype == BC_F32)
       pl.split_rows = npairs > 128 ? INT_MAX
-                                   : ((npairs <= 32 ? 5 : npairs <= 64 ? 7 : 14) + (alone ? 3 : 0)) * (pl.rows_per_pass / 2) + 2;
+                                   : ((npairs <= 32 ? 5 : npairs <= 64 ? 7 : npairs <= 96 ? 9 : 14) + (alone ? 3 : 0)) * (pl.rows_per_pass / 2) + 2;
   }
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
@@ -1559,12 +1573,14 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // pair draws what HBM gives (us a step, whole / cut; 4 pairs, d = 128: 8.5 / 10.0 at 124 rows, 10.1 / 9.9 at 180, 11.9 / 9.9 at
     // 252; 40 pairs 10.2 / 10.3 at 180, 11.7 / 10.4 at 252; 64 pairs 11.9 / 11.0 at 252; 120 pairs 15.5 / 15.7 at 380,
     // 19.1 / 18.3 at 508, d = 64 10.7 / 11.7 at 380, 12.4 / 12.6 at 508, 15.7 / 15.4 at 760; 200 pairs 18.1 / 21.8 at 760, 29.0 / 33.8 at
-    // 1500; 240 pairs 33.3 / 38.2 at 760).  More workgroups than 256 do not help (40 pairs of 760 rows: 480 15.3, 240 13.5).  A
+    // 1500; 240 pairs 33.3 / 38.2 at 760; 90 pairs in groups of seven, d = 64, 19.4 / 16.5 at 800).  More workgroups than 256 do not
+    // help (40 pairs of 760 rows: 480 15.3, 240 13.5; 120 ragged ones of 200 to 1200, d = 128, 29.2, 26.5) but for the longest of
+    // many ragged sequences with the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, 34.0).  A
     // plan whose sequences stay whole after all pays 0.2 to 0.4 us for the workgroups they do not fill.
     const bool eight_waves = npairs <= kFewPairs ||
                              (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
     const bool one_per_cu = pl.lds ? eight_waves
-                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs < 128 : pl.Gp >= 4;
+                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs <= (sh->d == 64 ? 64 : 127) : pl.Gp >= 4;
     const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : 256;
     long chunks = 1;
     if (npairs <= most_pairs && max_cap >= split_cap) {
@@ -1577,6 +1593,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.R = 0;                                        // spread evenly, decided per sequence
     pl.max_chunks = (int)chunks;
   }
+  pl.fma = !pl.lds && (sh->kv_dtype == BC_BF16 || (pl.max_chunks == 1 && fma_is_faster(npairs, pl.Gp, sh->d, max_cap)));
   // Workspace sizing: the most chunks the automatic plan can choose, 64 with few pairs and four otherwise (a
   // forced chunk size on a large batch may use as many).
   if (rows_override == kPlanForSizing) pl.max_chunks = npairs < 128 ? 64 : 4;
@@ -1591,18 +1608,24 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
 static dim3 decode_grid(const bc_shape* shape, const DecodePlan& pl) { return dim3(shape->Hkv, shape->B, pl.max_chunks); }
 
 template <typename T, int D, int G>
-static void launch_valu_group(const DecodeParams& p, dim3 grid, hipStream_t st) {
+static void launch_valu_group(const DecodeParams& p, bool fma, dim3 grid, hipStream_t st) {
+  if constexpr (std::is_same<T, float>::value && G <= 2) {
+    if (fma) {
+      decode_valu_kernel<T, D, G, 8, false, true><<<grid, 256, 0, st>>>(p);
+      return;
+    }
+  }
   if (p.max_chunks > 1) decode_valu_kernel<T, D, G, 8, true><<<grid, 256, 0, st>>>(p);
   else decode_valu_kernel<T, D, G, 8, false><<<grid, 256, 0, st>>>(p);
 }
 template <typename T, int D>
-static void launch_valu(const DecodeParams& p, int G, dim3 grid, hipStream_t st) {
-  switch (G) {
-    case 1: launch_valu_group<T, D, 1>(p, grid, st); break;
-    case 2: launch_valu_group<T, D, 2>(p, grid, st); break;
-    case 4: launch_valu_group<T, D, 4>(p, grid, st); break;
-    case 6: launch_valu_group<T, D, 6>(p, grid, st); break;
-    default: launch_valu_group<T, D, 8>(p, grid, st); break;
+static void launch_valu(const DecodeParams& p, const DecodePlan& pl, dim3 grid, hipStream_t st) {
+  switch (pl.Gp) {
+    case 1: launch_valu_group<T, D, 1>(p, pl.fma, grid, st); break;
+    case 2: launch_valu_group<T, D, 2>(p, pl.fma, grid, st); break;
+    case 4: launch_valu_group<T, D, 4>(p, pl.fma, grid, st); break;
+    case 6: launch_valu_group<T, D, 6>(p, pl.fma, grid, st); break;
+    default: launch_valu_group<T, D, 8>(p, pl.fma, grid, st); break;
   }
 }
 
@@ -1793,11 +1816,11 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
     const LdsLaunch k = pick_lds_kernel(shape, cache, pl, p.order != nullptr);
     k.fn<<<k.grid, k.threads, k.lds_bytes, hs>>>(p);
   } else if (shape->kv_dtype == BC_BF16) {
-    if (shape->d == 128) launch_valu<bf16_t, 128>(p, pl.Gp, grid, hs);
-    else launch_valu<bf16_t, 64>(p, pl.Gp, grid, hs);
+    if (shape->d == 128) launch_valu<bf16_t, 128>(p, pl, grid, hs);
+    else launch_valu<bf16_t, 64>(p, pl, grid, hs);
   } else {
-    if (shape->d == 128) launch_valu<float, 128>(p, pl.Gp, grid, hs);
-    else launch_valu<float, 64>(p, pl.Gp, grid, hs);
+    if (shape->d == 128) launch_valu<float, 128>(p, pl, grid, hs);
+    else launch_valu<float, 64>(p, pl, grid, hs);
   }
   return launch_status();
 }
@@ -1874,9 +1897,9 @@ extern "C" int32_t bc_decode_plan_describe(const bc_shape* shape, const bc_cache
              k.grid.y, k.grid.z, k.threads, k.lds_bytes, pl.max_chunks, merged);
   } else {
     const dim3 grid = decode_grid(shape, pl);
-    snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8, %s> grid=(%u,%u,%u) threads=256 chunks=%d%s",
+    snprintf(text, text_bytes, "bc::decode_valu_kernel<%s, %d, %d, 8, %s, %s> grid=(%u,%u,%u) threads=256 chunks=%d%s",
              shape->kv_dtype == BC_BF16 ? "bc::bf16_t" : "float", shape->d, pl.Gp, pl.max_chunks > 1 ? "true" : "false",
-             grid.x, grid.y, grid.z, pl.max_chunks, merged);
+             pl.fma ? "true" : "false", grid.x, grid.y, grid.z, pl.max_chunks, merged);
   }
   return BC_OK;
 }
