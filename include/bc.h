@@ -334,6 +334,20 @@ int32_t bc_prefill_attn_bwd(const bc_shape *shape, const void *q, const void *k,
                             int32_t max_rows, int64_t total_rows, float *dq, float *dk, float *dv,
                             void *workspace, size_t workspace_bytes, void *stream);
 
+/* bc_prefill_attn (workspace NULL) or bc_prefill_attn_ws, and bc_prefill_attn_bwd, with row_offsets, P and c as HOST arrays,
+ * read before the call returns.  Up to BC_INLINE_TRAJECTORIES trajectories travel in the kernels' arguments; with more, tables
+ * (device, 16 * B + 8 bytes, 8-byte aligned, else may be NULL) receives them as bc_trajectory_tables leaves them. */
+#define BC_INLINE_TRAJECTORIES 16
+int32_t bc_prefill_attn_host(const bc_shape *shape, const void *q, const void *k, const void *v,
+                             const int64_t *row_offsets, const int32_t *P, const int32_t *c, int32_t max_rows,
+                             int64_t total_rows, float *out, float *lse, void *tables, void *workspace,
+                             size_t workspace_bytes, void *stream);
+int32_t bc_prefill_attn_bwd_host(const bc_shape *shape, const void *q, const void *k, const void *v,
+                                 const float *out, const float *lse, const void *dout,
+                                 const int64_t *row_offsets, const int32_t *P, const int32_t *c, int32_t max_rows,
+                                 int64_t total_rows, float *dq, float *dk, float *dv, void *tables, void *workspace,
+                                 size_t workspace_bytes, void *stream);
+
 /* Token-level distillation loss of the training recipe (Eq. 1, Sec. 3.2) with the teacher given
  * by its stored top-k logits per token (App. A; k = 100 there).  The teacher distribution is the
  * softmax over its k stored logits; the student's log-probabilities are its full-vocabulary

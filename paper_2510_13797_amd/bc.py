@@ -35,7 +35,7 @@ EXPORTS = [
     "bc_compress_evict", "bc_decode_step", "bc_decode_step_noalloc", "bc_beacon_step", "bc_decode_step_budget", "bc_set_ratio",
     "bc_sort_by_length",
     "bc_trajectory_tables", "bc_prefill_attn", "bc_prefill_workspace_bytes", "bc_prefill_attn_ws",
-    "bc_prefill_bwd_workspace_bytes", "bc_prefill_attn_bwd",
+    "bc_prefill_bwd_workspace_bytes", "bc_prefill_attn_bwd", "bc_prefill_attn_host", "bc_prefill_attn_bwd_host",
     "bc_topk_kl_loss", "bc_topk_kl_loss_bwd", "bc_tables_to_host",
 ]
 DIAG_EXPORTS = ["bc_diag_stream_read"]
@@ -118,6 +118,10 @@ def load():
     lib.bc_prefill_bwd_workspace_bytes.argtypes = [sp, i64]
     lib.bc_prefill_attn_bwd.restype = i32
     lib.bc_prefill_attn_bwd.argtypes = [sp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i64, vp, vp, vp, vp, sz, vp]
+    lib.bc_prefill_attn_host.restype = i32
+    lib.bc_prefill_attn_host.argtypes = [sp, vp, vp, vp, vp, vp, vp, i32, i64, vp, vp, vp, vp, sz, vp]
+    lib.bc_prefill_attn_bwd_host.restype = i32
+    lib.bc_prefill_attn_bwd_host.argtypes = [sp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i64, vp, vp, vp, vp, vp, sz, vp]
     lib.bc_topk_kl_loss.restype = i32
     lib.bc_topk_kl_loss.argtypes = [i64, i32, i32, vp, i32, vp, vp, vp, vp, vp, vp]
     lib.bc_topk_kl_loss_bwd.restype = i32
@@ -258,6 +262,18 @@ def bc_prefill_attn_bwd(shape, q, k, v, out, lse, dout, row_offsets, P, c, max_r
                         dv, ws, ws_bytes, stream):
     return load().bc_prefill_attn_bwd(C.byref(shape), q, k, v, out, lse, dout, row_offsets, P, c,
                                       max_rows, total_rows, dq, dk, dv, ws, ws_bytes, stream)
+
+
+def bc_prefill_attn_host(shape, q, k, v, row_offsets, P, c, max_rows, total_rows, out, lse, tables, workspace,
+                         workspace_bytes, stream):
+    return load().bc_prefill_attn_host(C.byref(shape), q, k, v, row_offsets, P, c, max_rows, total_rows, out, lse,
+                                       tables, workspace, workspace_bytes, stream)
+
+
+def bc_prefill_attn_bwd_host(shape, q, k, v, out, lse, dout, row_offsets, P, c, max_rows, total_rows, dq, dk, dv,
+                             tables, ws, ws_bytes, stream):
+    return load().bc_prefill_attn_bwd_host(C.byref(shape), q, k, v, out, lse, dout, row_offsets, P, c, max_rows,
+                                           total_rows, dq, dk, dv, tables, ws, ws_bytes, stream)
 
 
 def bc_topk_kl_loss(T, V, k, student_logits, logits_dtype, teacher_logits, teacher_idx, loss_per_token,
@@ -533,9 +549,12 @@ class Runtime:
         return out[0], out[1]
 
 
+BC_INLINE_TRAJECTORIES = 16
+
+
 def _trajectory_tables(row_offsets, P, c, device):
-    """row_offsets [B+1] int64, P, c [B] int32 in one device buffer, sent in kernel arguments.
-    Returns (buffer, the three addresses)."""
+    """row_offsets [B+1] int64, P, c [B] int32 as one host array and its three addresses, and device memory for them
+    where they do not fit the kernels' arguments (else None)."""
     import torch
     B = len(row_offsets) - 1
     host = np.empty(2 * B + 1, dtype=np.int64)
@@ -543,10 +562,9 @@ def _trajectory_tables(row_offsets, P, c, device):
     tables = host[B + 1:].view(np.int32)
     tables[:B] = np.asarray(P, dtype=np.int32).reshape(-1)[:B]
     tables[B:] = np.asarray(c, dtype=np.int32).reshape(-1)[:B]
-    dev = torch.empty(2 * B + 1, dtype=torch.int64, device=device)
-    at, src = dev.data_ptr(), host.ctypes.data
-    _check(bc_trajectory_tables(src, src + 8 * (B + 1), src + 8 * (B + 1) + 4 * B, B, at, _stream_ptr()))
-    return dev, at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B
+    at = host.ctypes.data
+    dev = torch.empty(2 * B + 1, dtype=torch.int64, device=device) if B > BC_INLINE_TRAJECTORIES else None
+    return host, (at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B), dev
 
 
 def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, workspace=False):
@@ -563,19 +581,17 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     row_offsets = np.asarray(row_offsets, dtype=np.int64)
     B = len(row_offsets) - 1
     shape = bc_shape(B, Hq, Hkv, d, BC_BF16, float(scale))
-    tables, off_at, P_at, c_at = _trajectory_tables(row_offsets, P, c, dev)
+    host, at, tables = _trajectory_tables(row_offsets, P, c, dev)
     R = int(row_offsets[-1])
     out = torch.empty(R, Hq, d, dtype=torch.float32, device=dev)
     lse = torch.empty(R, Hq, dtype=torch.float32, device=dev) if want_lse else None
     max_rows = int((row_offsets[1:] - row_offsets[:-1]).max())
+    ws, nbytes = None, 0
     if workspace:
         nbytes = int(bc_prefill_workspace_bytes(shape, R))
         ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-        _check(bc_prefill_attn_ws(shape, _ptr(q), _ptr(k), _ptr(v), off_at, P_at, c_at, max_rows, R,
-                                  _ptr(out), _ptr(lse), _ptr(ws), nbytes, _stream_ptr()))
-    else:
-        _check(bc_prefill_attn(shape, _ptr(q), _ptr(k), _ptr(v), off_at, P_at, c_at, max_rows,
-                               _ptr(out), _ptr(lse), _stream_ptr()))
+    _check(bc_prefill_attn_host(shape, _ptr(q), _ptr(k), _ptr(v), *at, max_rows, R, _ptr(out), _ptr(lse), _ptr(tables),
+                                _ptr(ws), nbytes, _stream_ptr()))
     _used_here(q, k, v)      # (tables and workspace are the current stream's own)
     return out, lse
 
@@ -589,7 +605,7 @@ def prefill_attn_bwd(q, k, v, out, lse, dout, row_offsets, P, c, Hq, Hkv, d, sca
     B = len(row_offsets) - 1
     R = int(row_offsets[-1])
     shape = bc_shape(B, Hq, Hkv, d, BC_BF16, float(scale))
-    tables, off_at, P_at, c_at = _trajectory_tables(row_offsets, P, c, dev)
+    host, at, tables = _trajectory_tables(row_offsets, P, c, dev)
     # the kernels write every row of a trajectory (filling the gradients of 139,008 rows of 12/2 heads first
     # took 0.165 ms); rows in front of the first one get NaN here
     first = int(row_offsets[0])
@@ -600,9 +616,8 @@ def prefill_attn_bwd(q, k, v, out, lse, dout, row_offsets, P, c, Hq, Hkv, d, sca
     ws_bytes = int(bc_prefill_bwd_workspace_bytes(shape, R))
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
     max_rows = int((row_offsets[1:] - row_offsets[:-1]).max())
-    _check(bc_prefill_attn_bwd(shape, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout),
-                               off_at, P_at, c_at, max_rows, R, _ptr(dq), _ptr(dk), _ptr(dv),
-                               _ptr(ws), ws_bytes, _stream_ptr()))
+    _check(bc_prefill_attn_bwd_host(shape, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout), *at, max_rows, R,
+                                    _ptr(dq), _ptr(dk), _ptr(dv), _ptr(tables), _ptr(ws), ws_bytes, _stream_ptr()))
     _used_here(q, k, v, out, lse, dout)
     return dq, dk, dv
 

@@ -49,7 +49,7 @@ struct PrefillParams {
   const char* k;
   const char* v;
   const char* v16;         // V rounded to half precision, same layout (workspace form only)
-  const int32_t* flag;     // workspace form: 0 = every V entry fits half precision, 1 = not; else NULL
+  const uint32_t* flags;   // workspace form: kPfFlagBytes verdicts of the conversion pass, 0 = every V entry fits; else NULL
   const int64_t* row_off;
   const int32_t* P;
   const int32_t* c;
@@ -60,43 +60,46 @@ struct PrefillParams {
   int32_t npairs;     // (trajectory, KV head) pairs
   int32_t pstride;    // pairs per head split in the grid, see pair_stride()
   float qscale;       // softmax scale * log2(e)
+  InlineTables tab;
 };
+
+constexpr size_t kPfFlagBytes = 256;
 
 #define BC_INLINE __attribute__((always_inline))      // lambdas: their captures stay in registers
 
 constexpr float kPfRedo = 256.f;      // a lane's 16 weights may sum to this before the reference moves
 constexpr float kPfLazy = 2.0f;       // ... and then it moves where a row's maximum is this much (log2) above it
 
+template <int D> constexpr int prefill_lds() { return kTileStages * 2 * kTileRows * D * 2; }
+
 // One wave = 32 query rows of one head, four waves per workgroup (heads of one KV head or row blocks).
 // HALF: the weights enter the value product as one half-precision part (11 bits) against V in half
 // precision, instead of two bf16 parts against V in bf16: a third fewer matrix instructions and no
 // split.  V's copy in half precision is exact for entries between 2^-14 and 65504 in magnitude (bf16
-// has fewer mantissa bits), which a conversion pass checks; both forms of the kernel are launched and
-// each leaves at once when the pass's verdict is for the other.
+// has fewer mantissa bits), which a conversion pass checks; its verdict chooses the form.
 template <int D, bool HALF, bool WIDE>
-__global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_kernel(PrefillParams p) {
-  if (p.flag != nullptr && (p.flag[0] != 0) == HALF) return;
+__device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) {
   constexpr int ROWB = D * 2;                 // bytes of a K or V row
   constexpr int KS = D / 16;                  // k-steps of the score product
   constexpr int NJ = D / 32;                  // 32-column blocks of the output
   constexpr int TILE = kTileRows * ROWB;      // bytes of one K (or V) tile
   constexpr int NLD = TILE / 1024 / kTileWaves;     // LDS-DMA instructions per wave, tile and tensor
-  constexpr int LDS = kTileStages * 2 * TILE;
+  constexpr int LDS = prefill_lds<D>();
   constexpr int OW = D / 2;                   // output columns that go through LDS at a time
   static_assert(LDS >= kTileWaves * 32 * OW * 4, "the output tiles fit the ring's LDS");
-  __shared__ __attribute__((aligned(1024))) char lds[LDS];
 
   const int hh = blockIdx.x / p.pstride, pair = blockIdx.x - hh * p.pstride;
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
-  const int64_t off0 = p.row_off[b];
-  const int S = (int)(p.row_off[b + 1] - off0);
+  const Trajectory traj = trajectory(p, b);
+  const int64_t off0 = traj.off0;
+  const int S = traj.rows;
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const int r0 = (gridDim.y - 1 - blockIdx.y) * rows_wg;        // long tiles first
   if (r0 >= S) return;
   const int r1 = min(r0 + rows_wg - 1, S - 1);
-  const WindowStride ws = window_stride(p.c[b], S);
-  const KeyRuns runs(ws, p.P[b], r0, r1);
+  const WindowStride ws = window_stride(traj.c, S);
+  const KeyRuns runs(ws, traj.P, r0, r1);
   const int NT = runs.NT;
 
   const int lane = threadIdx.x & 63;
@@ -276,28 +279,57 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_kernel(PrefillPara
     p.lse[(off0 + r) * p.Hq + kvh * p.g + head] = (m_run + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
 }
 
-// V in half precision for the workspace form: 8 entries per thread and pass; the verdict word is
-// set when a finite entry does not fit (65520 and beyond rounds to infinity).
-__global__ __launch_bounds__(256) void prefill_v16_kernel(const uint4* __restrict__ v, uint4* __restrict__ v16,
-                                                          int64_t units, int32_t* flag) {
-  bool over = false;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < units; i += (int64_t)gridDim.x * blockDim.x) {
-    float f[8];
-    unpack16(v[i], f, bf16_t{});
-    uint32_t h[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      over = over || (fabsf(f[e]) >= 65520.f && fabsf(f[e]) < __builtin_inff()) ||
-             (fabsf(f[e + 1]) >= 65520.f && fabsf(f[e + 1]) < __builtin_inff());
-      h[e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pf_f32x2_t{f[e], f[e + 1]}, pf_f16x2_t));
+// EITHER: the form the conversion pass found V to fit, one of the two by a branch that is uniform over the launch.  (As two
+// launches, of which one left at its first instruction, with a third that cleared the verdict and a fourth that stored the tables, a
+// call took 30 us where its kernels' work is 10 to 15; now 19.  Large launches run at the power limit: 27,109 rows 489 us, both.)
+template <int D, bool EITHER, bool WIDE>
+__global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_kernel(PrefillParams p) {
+  __shared__ __attribute__((aligned(1024))) char lds[prefill_lds<D>()];
+  if constexpr (EITHER) {
+    static_assert(kPfFlagBytes == 64 * 4, "a word of verdicts per lane");
+    if (!__any(p.flags[threadIdx.x & 63] != 0)) {
+      prefill_rows<D, true, WIDE>(p, lds);
+      return;
     }
-    v16[i] = make_uint4(h[0], h[1], h[2], h[3]);
   }
-  if (__any(over) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+  prefill_rows<D, false, WIDE>(p, lds);
 }
-__global__ void prefill_clear_flag_kernel(int32_t* flag) { flag[0] = 0; }
 
-constexpr size_t kPfFlagBytes = 256;
+// V in half precision for the workspace form, 8 entries per unit.  Each workgroup leaves a verdict byte: whether a
+// finite entry of its does not fit (65520 and beyond rounds to infinity).  One workgroup of sixteen waves per compute
+// unit, four units of a thread on their way together: 27,109 rows of 8 heads, 55 MB read and 55 written, 21 us.
+__global__ __launch_bounds__(1024) void prefill_v16_kernel(const uint4* __restrict__ v, uint4* __restrict__ v16,
+                                                           int64_t units, uint8_t* flags) {
+  __shared__ int s_over;
+  if (threadIdx.x == 0) s_over = 0;
+  __syncthreads();
+  bool over = false;
+  const int64_t step = (int64_t)gridDim.x * 1024;
+  for (int64_t i0 = (int64_t)blockIdx.x * 1024 + threadIdx.x; i0 < units; i0 += 4 * step) {
+    u32x4_t x[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      x[n] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(v + (i0 + n * step < units ? i0 + n * step : i0)));
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      float f[8];
+      unpack16(make_uint4(x[n].x, x[n].y, x[n].z, x[n].w), f, bf16_t{});
+      uint32_t h[4];
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        over = over || (fabsf(f[e]) >= 65520.f && fabsf(f[e]) < __builtin_inff()) ||
+               (fabsf(f[e + 1]) >= 65520.f && fabsf(f[e + 1]) < __builtin_inff());
+        h[e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pf_f32x2_t{f[e], f[e + 1]}, pf_f16x2_t));
+      }
+      if (i0 + n * step < units) v16[i0 + n * step] = make_uint4(h[0], h[1], h[2], h[3]);
+    }
+  }
+  if (__any(over) && (threadIdx.x & 63) == 0) atomicOr(&s_over, 1);
+  __syncthreads();
+  // (workgroups that are not there are answered for by the first)
+  if (threadIdx.x == 0) flags[blockIdx.x] = (uint8_t)s_over;
+  if (blockIdx.x == 0 && threadIdx.x >= gridDim.x && threadIdx.x < kPfFlagBytes) flags[threadIdx.x] = 0;
+}
 
 // Words that travel in the kernel arguments.  Two sizes: the small one is what 31 trajectories take; the large
 // one keeps the arguments under 4 KB, and more trajectories take more launches.
@@ -330,28 +362,25 @@ static void store_words(uint32_t* dst, const void* src, int64_t n, hipStream_t h
   }
 }
 
-template <int D, bool HALF>
+template <int D, bool EITHER>
 static void launch_prefill_d(const PrefillParams& p, bool wide, dim3 grid, hipStream_t hs) {
-  if (wide) prefill_kernel<D, HALF, true><<<grid, kTileWaves * 64, 0, hs>>>(p);
-  else prefill_kernel<D, HALF, false><<<grid, kTileWaves * 64, 0, hs>>>(p);
+  if (wide) prefill_kernel<D, EITHER, true><<<grid, kTileWaves * 64, 0, hs>>>(p);
+  else prefill_kernel<D, EITHER, false><<<grid, kTileWaves * 64, 0, hs>>>(p);
 }
-template <bool HALF>
+template <bool EITHER>
 static void launch_prefill(const PrefillParams& p, int d, bool wide, dim3 grid, hipStream_t hs) {
-  if (d == 128) launch_prefill_d<128, HALF>(p, wide, grid, hs);
-  else launch_prefill_d<64, HALF>(p, wide, grid, hs);
+  if (d == 128) launch_prefill_d<128, EITHER>(p, wide, grid, hs);
+  else launch_prefill_d<64, EITHER>(p, wide, grid, hs);
 }
 
-// Shared by the two entry points.  workspace == nullptr: the two-part form alone.
-static int32_t prefill_forward(const bc_shape* shape, const void* q, const void* k, const void* v,
-                               const int64_t* row_offsets, const int32_t* P, const int32_t* c,
-                               int32_t max_rows, int64_t total_rows, float* out, float* lse,
-                               void* workspace, void* stream) {
-  PrefillParams p;
+// Shared by the entry points; p has its tables.  workspace == nullptr: the two-part form alone.
+static int32_t prefill_forward(PrefillParams& p, const bc_shape* shape, const void* q, const void* k, const void* v,
+                               int32_t max_rows, int64_t total_rows, float* out, float* lse, void* workspace,
+                               void* stream) {
   p.q = static_cast<const char*>(q);
   p.k = static_cast<const char*>(k);
   p.v = static_cast<const char*>(v);
-  p.v16 = nullptr; p.flag = nullptr;
-  p.row_off = row_offsets; p.P = P; p.c = c;
+  p.v16 = nullptr; p.flags = nullptr;
   p.out = out; p.lse = lse;
   p.Hq = shape->Hq; p.Hkv = shape->Hkv; p.g = shape->Hq / shape->Hkv;
   p.qscale = shape->scale * kLog2e;
@@ -363,18 +392,37 @@ static int32_t prefill_forward(const bc_shape* shape, const void* q, const void*
   const bool wide = rows_span_4gb(max_rows, shape);
   hipStream_t hs = as_stream(stream);
   if (workspace) {
-    int32_t* flag = static_cast<int32_t*>(workspace);
     char* v16 = static_cast<char*>(workspace) + kPfFlagBytes;
     const int64_t units = total_rows * shape->Hkv * shape->d / 8;
-    const int64_t blocks = (units + 255) / 256;
-    prefill_clear_flag_kernel<<<1, 1, 0, hs>>>(flag);
-    prefill_v16_kernel<<<(int)(blocks < 4096 ? blocks : 4096), 256, 0, hs>>>(
-        static_cast<const uint4*>(v), reinterpret_cast<uint4*>(v16), units, flag);
-    p.v16 = v16; p.flag = flag;
+    const int64_t blocks = (units + 1023) / 1024;
+    prefill_v16_kernel<<<(int)(blocks < (int64_t)kPfFlagBytes ? blocks : (int64_t)kPfFlagBytes), 1024, 0, hs>>>(
+        static_cast<const uint4*>(v), reinterpret_cast<uint4*>(v16), units, static_cast<uint8_t*>(workspace));
+    p.v16 = v16; p.flags = static_cast<const uint32_t*>(workspace);
     launch_prefill<true>(p, shape->d, wide, grid, hs);
+  } else {
+    launch_prefill<false>(p, shape->d, wide, grid, hs);
   }
-  launch_prefill<false>(p, shape->d, wide, grid, hs);
   return launch_status();
+}
+
+// What every form checks; the tables are device or host arrays.
+static int32_t check_prefill(const bc_shape* shape, const void* q, const void* k, const void* v, const void* row_offsets,
+                             const void* P, const void* c, int32_t max_rows, const float* out) {
+  const int32_t st = check_shape(shape);
+  if (st != BC_OK) return st;
+  if (shape->kv_dtype != BC_BF16) return BC_ERR_SHAPE;
+  if (!q || !k || !v || !row_offsets || !P || !c || !out) return BC_ERR_ARG;
+  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return BC_ERR_ARG;
+  if (max_rows < 1 || max_rows >= (1 << 26)) return BC_ERR_ARG;
+  if (!positive_finite(shape->scale)) return BC_ERR_ARG;       // the kernel takes maxima of unscaled scores
+  return BC_OK;
+}
+static int32_t check_prefill_workspace(const bc_shape* shape, int32_t max_rows, int64_t total_rows, const void* workspace,
+                                       size_t workspace_bytes) {
+  if (total_rows < max_rows) return BC_ERR_ARG;
+  if (!workspace || !aligned16(workspace) || workspace_bytes < bc_prefill_workspace_bytes(shape, total_rows))
+    return BC_ERR_WORKSPACE;
+  return BC_OK;
 }
 
 }  // namespace bc
@@ -408,28 +456,38 @@ extern "C" int32_t bc_prefill_attn_ws(const bc_shape* shape, const void* q, cons
                                       const int32_t* c, int32_t max_rows, int64_t total_rows,
                                       float* out, float* lse, void* workspace,
                                       size_t workspace_bytes, void* stream) {
-  int32_t st = check_shape(shape);
+  int32_t st = check_prefill(shape, q, k, v, row_offsets, P, c, max_rows, out);
   if (st != BC_OK) return st;
-  if (shape->kv_dtype != BC_BF16) return BC_ERR_SHAPE;
-  if (!q || !k || !v || !row_offsets || !P || !c || !out) return BC_ERR_ARG;
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return BC_ERR_ARG;
-  if (max_rows < 1 || max_rows >= (1 << 26) || total_rows < max_rows) return BC_ERR_ARG;
-  if (!positive_finite(shape->scale)) return BC_ERR_ARG;
-  if (!workspace || !aligned16(workspace) || workspace_bytes < bc_prefill_workspace_bytes(shape, total_rows))
-    return BC_ERR_WORKSPACE;
-  return prefill_forward(shape, q, k, v, row_offsets, P, c, max_rows, total_rows, out, lse, workspace, stream);
+  st = check_prefill_workspace(shape, max_rows, total_rows, workspace, workspace_bytes);
+  if (st != BC_OK) return st;
+  PrefillParams p;
+  p.row_off = row_offsets; p.P = P; p.c = c;
+  return prefill_forward(p, shape, q, k, v, max_rows, total_rows, out, lse, workspace, stream);
 }
 
 extern "C" int32_t bc_prefill_attn(const bc_shape* shape, const void* q, const void* k,
                                    const void* v, const int64_t* row_offsets, const int32_t* P,
                                    const int32_t* c, int32_t max_rows, float* out, float* lse,
                                    void* stream) {
-  int32_t st = check_shape(shape);
+  const int32_t st = check_prefill(shape, q, k, v, row_offsets, P, c, max_rows, out);
   if (st != BC_OK) return st;
-  if (shape->kv_dtype != BC_BF16) return BC_ERR_SHAPE;
-  if (!q || !k || !v || !row_offsets || !P || !c || !out) return BC_ERR_ARG;
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return BC_ERR_ARG;
-  if (max_rows < 1 || max_rows >= (1 << 26)) return BC_ERR_ARG;
-  if (!positive_finite(shape->scale)) return BC_ERR_ARG;       // the kernel takes maxima of unscaled scores
-  return prefill_forward(shape, q, k, v, row_offsets, P, c, max_rows, 0, out, lse, nullptr, stream);
+  PrefillParams p;
+  p.row_off = row_offsets; p.P = P; p.c = c;
+  return prefill_forward(p, shape, q, k, v, max_rows, 0, out, lse, nullptr, stream);
+}
+
+extern "C" int32_t bc_prefill_attn_host(const bc_shape* shape, const void* q, const void* k, const void* v,
+                                        const int64_t* row_offsets, const int32_t* P, const int32_t* c,
+                                        int32_t max_rows, int64_t total_rows, float* out, float* lse, void* tables,
+                                        void* workspace, size_t workspace_bytes, void* stream) {
+  int32_t st = check_prefill(shape, q, k, v, row_offsets, P, c, max_rows, out);
+  if (st != BC_OK) return st;
+  if (workspace) {
+    st = check_prefill_workspace(shape, max_rows, total_rows, workspace, workspace_bytes);
+    if (st != BC_OK) return st;
+  }
+  PrefillParams p;
+  st = host_tables(p, row_offsets, P, c, shape->B, tables, stream);
+  if (st != BC_OK) return st;
+  return prefill_forward(p, shape, q, k, v, max_rows, total_rows, out, lse, workspace, stream);
 }

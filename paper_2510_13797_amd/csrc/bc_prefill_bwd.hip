@@ -59,6 +59,7 @@ struct BwdParams {
   int32_t pstride;      // see pair_stride()
   float scale;
   float qscale;         // scale * log2(e)
+  InlineTables tab;
 };
 
 #define BC_INLINE __attribute__((always_inline))      // lambdas: their captures stay in registers
@@ -78,14 +79,15 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
   const int hh = blockIdx.x / p.pstride, pair = blockIdx.x - hh * p.pstride;
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
-  const int64_t off0 = p.row_off[b];
-  const int S = (int)(p.row_off[b + 1] - off0);
+  const Trajectory traj = trajectory(p, b);
+  const int64_t off0 = traj.off0;
+  const int S = traj.rows;
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const int r0 = (gridDim.y - 1 - blockIdx.y) * rows_wg;        // long tiles first
   if (r0 >= S) return;
   const int r1 = min(r0 + rows_wg - 1, S - 1);
-  const WindowStride ws = window_stride(p.c[b], S);
-  const KeyRuns runs(ws, p.P[b], r0, r1);
+  const WindowStride ws = window_stride(traj.c, S);
+  const KeyRuns runs(ws, traj.P, r0, r1);
   const int NT = runs.NT;
 
   const int lane = threadIdx.x & 63;
@@ -256,10 +258,11 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   // are dispatched before any short one
   if ((int)blockIdx.x >= p.npairs) return;
   const int kvh = blockIdx.x % p.Hkv, b = blockIdx.x / p.Hkv;
-  const int64_t off0 = p.row_off[b];
-  const int S = (int)(p.row_off[b + 1] - off0);
-  const int P0 = p.P[b];
-  const WindowStride ws = window_stride(p.c[b], S);
+  const Trajectory traj = trajectory(p, b);
+  const int64_t off0 = traj.off0;
+  const int S = traj.rows;
+  const int P0 = traj.P;
+  const WindowStride ws = window_stride(traj.c, S);
   const int c = ws.c, cp1 = ws.stride;
   // key blocks of this (trajectory, KV head): prompt keys | gathered beacons | response rows.
   // Without compression every row behaves like a prompt row (plain causal).
@@ -453,11 +456,12 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
 // of 16 for 16 trajectories of 8688 rows: one row in twelve is dense).
 __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
   const int b = blockIdx.x;
-  const int64_t off0 = p.row_off[b];
-  const int S = (int)(p.row_off[b + 1] - off0);
+  const Trajectory traj = trajectory(p, b);
+  const int64_t off0 = traj.off0;
+  const int S = traj.rows;
   if (S <= 0) return;
-  const WindowStride ws = window_stride(p.c[b], S);
-  const int Pk = ws.c > 0 ? min(p.P[b], S) : S;
+  const WindowStride ws = window_stride(traj.c, S);
+  const int Pk = ws.c > 0 ? min(traj.P, S) : S;
   const int nbeac = ws.c > 0 ? (int)window_of(ws, (uint32_t)(S - Pk)) : 0;
   const int parts = dense_parts(p, (Pk + kDkvKeys - 1) / kDkvKeys + (nbeac + kDkvKeys - 1) / kDkvKeys);
   if (parts == 1) return;
@@ -520,30 +524,13 @@ extern "C" size_t bc_prefill_bwd_workspace_bytes(const bc_shape* shape, int64_t 
   return bytes;
 }
 
-extern "C" int32_t bc_prefill_attn_bwd(const bc_shape* shape, const void* q, const void* k,
-                                       const void* v, const float* out, const float* lse,
-                                       const void* dout, const int64_t* row_offsets,
-                                       const int32_t* P, const int32_t* c, int32_t max_rows,
-                                       int64_t total_rows, float* dq, float* dk, float* dv,
-                                       void* workspace, size_t workspace_bytes, void* stream) {
-  int32_t st = check_shape(shape);
-  if (st != BC_OK) return st;
-  if (shape->kv_dtype != BC_BF16) return BC_ERR_SHAPE;
-  if (!q || !k || !v || !out || !lse || !dout || !row_offsets || !P || !c || !dq || !dk || !dv)
-    return BC_ERR_ARG;
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out) || !aligned16(dout) ||
-      !aligned16(dq) || !aligned16(dk) || !aligned16(dv))
-    return BC_ERR_ARG;
-  if (max_rows < 1 || max_rows >= (1 << 26) || total_rows < max_rows) return BC_ERR_ARG;
-  if (!positive_finite(shape->scale)) return BC_ERR_ARG;
-  if (!workspace || !aligned16(workspace) ||
-      workspace_bytes < bc_prefill_bwd_workspace_bytes(shape, total_rows))
-    return BC_ERR_WORKSPACE;
-  BwdParams p;
+// p has its tables.
+static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void* q, const void* k, const void* v,
+                                const float* out, const float* lse, const void* dout, int32_t max_rows,
+                                int64_t total_rows, float* dq, float* dk, float* dv, void* workspace, void* stream) {
   p.q = static_cast<const char*>(q); p.k = static_cast<const char*>(k);
   p.v = static_cast<const char*>(v); p.out = out; p.lse = lse;
   p.dout = static_cast<const char*>(dout);
-  p.row_off = row_offsets; p.P = P; p.c = c;
   p.dq = dq; p.dk = dk; p.dv = dv;
   p.stat = static_cast<float*>(workspace);
   p.part = p.stat + stat_floats(shape, total_rows);
@@ -570,4 +557,52 @@ extern "C" int32_t bc_prefill_attn_bwd(const bc_shape* shape, const void* q, con
     prefill_bwd_reduce_kernel<<<dim3(shape->B, (int)(blocks < 128 ? blocks : 128)), 256, 0, hs>>>(p);
   }
   return launch_status();
+}
+
+static int32_t check_backward(const bc_shape* shape, const void* q, const void* k, const void* v, const float* out,
+                              const float* lse, const void* dout, const void* row_offsets, const void* P, const void* c,
+                              int32_t max_rows, int64_t total_rows, const float* dq, const float* dk, const float* dv,
+                              const void* workspace, size_t workspace_bytes) {
+  const int32_t st = check_shape(shape);
+  if (st != BC_OK) return st;
+  if (shape->kv_dtype != BC_BF16) return BC_ERR_SHAPE;
+  if (!q || !k || !v || !out || !lse || !dout || !row_offsets || !P || !c || !dq || !dk || !dv)
+    return BC_ERR_ARG;
+  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out) || !aligned16(dout) ||
+      !aligned16(dq) || !aligned16(dk) || !aligned16(dv))
+    return BC_ERR_ARG;
+  if (max_rows < 1 || max_rows >= (1 << 26) || total_rows < max_rows) return BC_ERR_ARG;
+  if (!positive_finite(shape->scale)) return BC_ERR_ARG;
+  if (!workspace || !aligned16(workspace) ||
+      workspace_bytes < bc_prefill_bwd_workspace_bytes(shape, total_rows))
+    return BC_ERR_WORKSPACE;
+  return BC_OK;
+}
+
+extern "C" int32_t bc_prefill_attn_bwd(const bc_shape* shape, const void* q, const void* k,
+                                       const void* v, const float* out, const float* lse,
+                                       const void* dout, const int64_t* row_offsets,
+                                       const int32_t* P, const int32_t* c, int32_t max_rows,
+                                       int64_t total_rows, float* dq, float* dk, float* dv,
+                                       void* workspace, size_t workspace_bytes, void* stream) {
+  const int32_t st = check_backward(shape, q, k, v, out, lse, dout, row_offsets, P, c, max_rows, total_rows, dq, dk, dv,
+                                    workspace, workspace_bytes);
+  if (st != BC_OK) return st;
+  BwdParams p;
+  p.row_off = row_offsets; p.P = P; p.c = c;
+  return prefill_backward(p, shape, q, k, v, out, lse, dout, max_rows, total_rows, dq, dk, dv, workspace, stream);
+}
+
+extern "C" int32_t bc_prefill_attn_bwd_host(const bc_shape* shape, const void* q, const void* k, const void* v,
+                                            const float* out, const float* lse, const void* dout,
+                                            const int64_t* row_offsets, const int32_t* P, const int32_t* c,
+                                            int32_t max_rows, int64_t total_rows, float* dq, float* dk, float* dv,
+                                            void* tables, void* workspace, size_t workspace_bytes, void* stream) {
+  int32_t st = check_backward(shape, q, k, v, out, lse, dout, row_offsets, P, c, max_rows, total_rows, dq, dk, dv,
+                              workspace, workspace_bytes);
+  if (st != BC_OK) return st;
+  BwdParams p;
+  st = host_tables(p, row_offsets, P, c, shape->B, tables, stream);
+  if (st != BC_OK) return st;
+  return prefill_backward(p, shape, q, k, v, out, lse, dout, max_rows, total_rows, dq, dk, dv, workspace, stream);
 }

@@ -2,6 +2,7 @@
 // visibility of a tile's keys as bits, tiles of 32 rows staged in LDS in the order the matrix
 // operands are read, and the operand and result helpers of the 32x32x16 matrix instructions.
 #pragma once
+#include <cstddef>
 #include <type_traits>
 
 #include "bc_common.h"
@@ -15,6 +16,49 @@ constexpr int kTileStages = 3;        // tiles in LDS: one in use, two on their 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(8))) short s16x8_t;
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+// ---------------------------------------------------------------------------
+// tables of the trajectories
+// ---------------------------------------------------------------------------
+// In device memory or, from the calls that take them as host arrays, for up to BC_INLINE_TRAJECTORIES trajectories in the kernel
+// arguments (a launch in front that stored them took 3 us a call, 10 % of a small forward and backward pass).
+struct InlineTables {
+  int64_t row_off[BC_INLINE_TRAJECTORIES + 1];
+  int32_t P[BC_INLINE_TRAJECTORIES], c[BC_INLINE_TRAJECTORIES];
+};
+struct Trajectory { int64_t off0; int rows, P, c; };
+// Params: the only argument of the kernel, with row_off (null: inline), P, c and tab.
+template <typename Params>
+__device__ __forceinline__ Trajectory trajectory(const Params& p, int b) {
+  Trajectory t;
+  int64_t end;
+  if (p.row_off != nullptr) {
+    t.off0 = p.row_off[b]; end = p.row_off[b + 1]; t.P = p.P[b]; t.c = p.c[b];
+  } else {
+    typedef __attribute__((address_space(4))) const char const_char_t;
+    typedef __attribute__((address_space(4))) const InlineTables const_tables_t;
+    const_tables_t* in = (const_tables_t*)((const_char_t*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Params, tab));
+    t.off0 = in->row_off[b]; end = in->row_off[b + 1]; t.P = in->P[b]; t.c = in->c[b];
+  }
+  t.rows = (int)(end - t.off0);
+  return t;
+}
+// Host arrays -> p; tables: device memory for more trajectories than fit.
+template <typename Params>
+int32_t host_tables(Params& p, const int64_t* row_offsets, const int32_t* P, const int32_t* c, int32_t B, void* tables,
+                    void* stream) {
+  if (B <= BC_INLINE_TRAJECTORIES) {
+    p.row_off = nullptr; p.P = nullptr; p.c = nullptr;
+    for (int b = 0; b < B; ++b) { p.tab.row_off[b] = row_offsets[b]; p.tab.P[b] = P[b]; p.tab.c[b] = c[b]; }
+    p.tab.row_off[B] = row_offsets[B];
+    return BC_OK;
+  }
+  const int32_t st = bc_trajectory_tables(row_offsets, P, c, B, tables, stream);
+  p.row_off = static_cast<const int64_t*>(tables);
+  p.P = reinterpret_cast<const int32_t*>(p.row_off + B + 1);
+  p.c = p.P + B;
+  return st;
+}
 
 // ---------------------------------------------------------------------------
 // key list of a query tile

@@ -622,3 +622,54 @@ def test_training_calls_captured_in_a_graph(dev):
             graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, want)), seed
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 40])
+def test_host_tables_equal_device_tables(dev, B):
+    # up to 16 trajectories travel in the kernels' arguments, more through device memory; all three forms, bit for bit
+    import ctypes as C
+    import torch
+    from paper_2510_13797_amd import bc
+    r = np.random.default_rng(B)
+    S = r.integers(1, 150, B)
+    off = np.concatenate([[0], np.cumsum(S)]).astype(np.int64)
+    P, c = r.integers(0, 60, B).astype(np.int32), r.integers(0, 9, B).astype(np.int32)
+    R, Hq, Hkv, d = int(off[-1]), 4, 2, 64
+    q, k, v, do = (torch.randn(R, h, d, device=dev).to(torch.bfloat16) for h in (Hq, Hkv, Hkv, Hq))
+    shape = bc.bc_shape(B, Hq, Hkv, d, bc.BC_BF16, 0.125)
+    tab = [torch.from_numpy(x).to(dev) for x in (off, P, c)]
+    ptr = lambda t: t.data_ptr()
+    outs = [torch.full((R, h, d), float("nan"), device=dev) for h in (Hq, Hq, Hq, Hkv, Hkv)]
+    lse = torch.full((R, Hq), float("nan"), device=dev)
+    n1, n2 = bc.bc_prefill_workspace_bytes(shape, R), bc.bc_prefill_bwd_workspace_bytes(shape, R)
+    ws1, ws2 = (torch.full((n,), 255, dtype=torch.uint8, device=dev) for n in (n1, n2))
+    m = int(S.max())
+    assert bc.bc_prefill_attn_ws(shape, ptr(q), ptr(k), ptr(v), *map(ptr, tab), m, R, ptr(outs[0]), None, ptr(ws1), n1, None) == 0
+    assert bc.bc_prefill_attn(shape, ptr(q), ptr(k), ptr(v), *map(ptr, tab), m, ptr(outs[1]), ptr(lse), None) == 0
+    assert bc.bc_prefill_attn_bwd(shape, ptr(q), ptr(k), ptr(v), ptr(outs[1]), ptr(lse), ptr(do), *map(ptr, tab), m, R,
+                                  *map(ptr, outs[2:]), ptr(ws2), n2, None) == 0
+    args = (off, P, c, Hq, Hkv, d, 0.125)
+    got = [bc.prefill_attn(q, k, v, *args, workspace=True)[0], *bc.prefill_attn(q, k, v, *args)]
+    got += bc.prefill_attn_bwd(q, k, v, got[1], got[2], do, *args)
+    want = [outs[0], outs[1], lse, *outs[2:]]
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    h = [x.ctypes.data for x in (off, P, c)]
+    st = bc.bc_prefill_attn_host(shape, ptr(q), ptr(k), ptr(v), *h, m, R, ptr(outs[0]), None, None, None, 0, None)
+    assert st == (bc.BC_OK if B <= 16 else bc.BC_ERR_ARG)
+    assert bc.bc_prefill_attn_host(shape, ptr(q), ptr(k), ptr(v), *h, m, R, ptr(outs[0]), None, None, ptr(ws1), n1 - 1, None) \
+        == bc.BC_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("rows,at", [(3, 0), (257, 0), (257, 256), (9000, 8999), (9000, 4097)])
+def test_every_workgroup_of_the_conversion_pass_has_a_verdict(dev, rows, at):
+    # V entries that do not fit half precision, in the first and last rows the pass reads, with few workgroups and
+    # with all 256: the two-part form's bits
+    import torch
+    from paper_2510_13797_amd import bc
+    q, k, v = (torch.randn(rows, 2, 64, device=dev).to(torch.bfloat16) for _ in range(3))
+    args = (np.array([0, rows]), np.array([min(rows, 32)], np.int32), np.array([4], np.int32), 2, 2, 64, 0.125)
+    half = bc.prefill_attn(q, k, v, *args, workspace=True)[0]
+    plain = bc.prefill_attn(q, k, v, *args)[0]
+    assert not torch.equal(half, plain) and float((half - plain).abs().max()) < 2e-3
+    v[at, 1, 63] = 70000.0
+    assert torch.equal(bc.prefill_attn(q, k, v, *args, workspace=True)[0], bc.prefill_attn(q, k, v, *args)[0])
