@@ -130,18 +130,19 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
     }
   };
   issue_tile(0);
-  if (NT > 1) issue_tile(1);
 
-  // this lane's query row; Q^T as the B operand (column = row, k = head-dim index)
-  const int r = min(rw0 + col, r1);
+  // this lane's query row; Q^T as the B operand (column = row, k = head-dim index).  The wave's rows come through the
+  // stages behind the first tile's.
+  const int r = min(rw0 + col, r1), rw = min(rw0, r1);
   bf16x8_t qb[KS];
-  {
-    const char* qrow = p.q + ((off0 + r) * p.Hq + kvh * p.g + min(head, p.g - 1)) * ROWB + 16 * half;
-#pragma unroll
-    for (int i = 0; i < KS; ++i)
-      qb[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qrow + 32 * i));
-  }
-  landed_operands(qb);      // no wait for these loads inside the tile loop
+  static_assert(LDS >= (2 + kTileWaves) * TILE, "the waves' rows fit behind the first tile");
+  issue_wave_rows<D>(p.q + ((off0 + rw) * p.Hq + kvh * p.g + min(head, p.g - 1)) * ROWB, (uint32_t)p.Hq * ROWB, r1 - rw,
+                     lane, lds_address(lds) + (2 + wave) * TILE);
+  wait_vmcnt<0>();
+  read_wave_rows<D>(lds + (2 + wave) * TILE, lane, qb);
+  landed_operands(qb);
+  lds_barrier();            // every wave has its rows
+  if (NT > 1) issue_tile(1);
   const int own = runs.window_start(r);
   const HalfSelectors sel = half_selectors();
 

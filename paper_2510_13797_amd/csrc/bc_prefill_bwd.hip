@@ -67,12 +67,20 @@ struct BwdParams {
 // ---------------------------------------------------------------------------
 // dq kernel
 // ---------------------------------------------------------------------------
-// The forward's walk with the same workgroups: four waves, 32 query rows of one head each.
+// The forward's walk with the same workgroups: four waves, 32 query rows of one head each.  Its registers let two
+// workgroups share a compute unit, so there is LDS for a fourth tile (16 trajectories of 8688 rows 1.131 -> 1.071 ms under
+// the profiler; a fifth gives nothing more, and the forward loses its third workgroup to a fourth: 0.70 -> 0.81 ms) and, before
+// the walk, for the rows of all waves: with those through LDS and Delta from whole rows a pass of three short
+// trajectories takes 72.8 us instead of 75.4.  What is left in front of the first product, some 10,000 cycles, is
+// mostly the first touch of the output's rows.
+constexpr int kDqStages = 4;
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdParams p) {
   constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
   constexpr int NLD = TILE / 1024 / kTileWaves;     // LDS-DMA instructions per wave, tile and tensor
-  constexpr int LDS = kTileStages * 2 * TILE;
+  constexpr int RING = kDqStages * 2 * TILE, ROWS = (2 + 2 * kTileWaves) * TILE, LDS = RING > ROWS ? RING : ROWS;
+  constexpr int LOOK = kDqStages - 1;
+  static_assert(LOOK == 3, "the counts of begin_pass");
   static_assert(LDS >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
   __shared__ __attribute__((aligned(1024))) char lds[LDS];
 
@@ -115,31 +123,56 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
     }
   };
   issue_tile(0);
-  if (NT > 1) issue_tile(1);
 
-  // this lane's query row: Q^T and dO^T as B operands, log-sum-exp and Delta of the row
-  const int r = min(rw0 + col, r1);
-  const int64_t rh = (off0 + r) * p.Hq + kvh * p.g + min(head, p.g - 1);
-  bf16x8_t qb[KS], dob[KS];
-  float delta = 0.f;
+  // Q and dO of the wave's rows, into the LDS behind the first tile
+  const int r = min(rw0 + col, r1), rw = min(rw0, r1);
+  const int64_t first = (off0 + rw) * p.Hq + kvh * p.g + min(head, p.g - 1);
+  issue_wave_rows<D>(p.q + first * ROWB, (uint32_t)p.Hq * ROWB, r1 - rw, lane, lds_address(lds) + (2 + 2 * wave) * TILE);
+  issue_wave_rows<D>(p.dout + first * ROWB, (uint32_t)p.Hq * ROWB, r1 - rw, lane, lds_address(lds) + (3 + 2 * wave) * TILE);
+  // Delta: sixteen lanes a row, four rows at a time
+  float part[8];
+  {
+    float4 o[8][D / 64];
+    uint2 y[8][D / 64];
 #pragma unroll
-  for (int i = 0; i < KS; ++i) {
-    const int64_t e = rh * D + 16 * i + 8 * half;
-    qb[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(p.q + e * 2));
-    const uint4 y = *reinterpret_cast<const uint4*>(p.dout + e * 2);
-    dob[i] = __builtin_bit_cast(bf16x8_t, y);
-    const float4 o0 = *reinterpret_cast<const float4*>(p.out + e);
-    const float4 o1 = *reinterpret_cast<const float4*>(p.out + e + 4);
-    float dy[8];
-    unpack16(y, dy, bf16_t{});
-    delta += dy[0] * o0.x + dy[1] * o0.y + dy[2] * o0.z + dy[3] * o0.w +
-             dy[4] * o1.x + dy[5] * o1.y + dy[6] * o1.z + dy[7] * o1.w;
+    for (int n = 0; n < 8; ++n) {
+      const int64_t e = (first + (int64_t)min(4 * n + (lane >> 4), r1 - rw) * p.Hq) * D + 4 * (lane & 15);
+#pragma unroll
+      for (int t = 0; t < D / 64; ++t) {
+        o[n][t] = *reinterpret_cast<const float4*>(p.out + e + 64 * t);
+        y[n][t] = *reinterpret_cast<const uint2*>(p.dout + (e + 64 * t) * 2);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      part[n] = 0.f;
+#pragma unroll
+      for (int t = 0; t < D / 64; ++t)
+        part[n] += __uint_as_float(y[n][t].x << 16) * o[n][t].x + __uint_as_float(y[n][t].x & 0xffff0000u) * o[n][t].y +
+                   __uint_as_float(y[n][t].y << 16) * o[n][t].z + __uint_as_float(y[n][t].y & 0xffff0000u) * o[n][t].w;
+      part[n] = group_allreduce_sum<16>(part[n]);
+    }
   }
-  delta = halves_sum(delta);
-  float lse2 = p.lse[rh] * kLog2e;
-  landed_operands(qb);      // no wait for these loads inside the tile loop
+  float lse2 = p.lse[(off0 + r) * p.Hq + kvh * p.g + min(head, p.g - 1)] * kLog2e;
+  // this lane's query row: Q^T and dO^T as B operands, log-sum-exp and Delta of the row
+  char* mine = lds + (2 + 2 * wave) * TILE;
+  bf16x8_t qb[KS], dob[KS];
+  wait_vmcnt<0>();
+  read_wave_rows<D>(mine, lane, qb);
+  read_wave_rows<D>(mine + TILE, lane, dob);
+  landed_operands(qb);
   landed_operands(dob);
+  asm volatile("" : : : "memory");      // (Delta's floats replace the operands' rows)
+  float row_delta = part[0];
+#pragma unroll
+  for (int n = 1; n < 8; ++n) row_delta = (lane & 7) == n ? part[n] : row_delta;
+  if ((lane & 8) == 0) reinterpret_cast<float*>(mine)[4 * (lane & 7) + (lane >> 4)] = row_delta;
+  float delta = reinterpret_cast<const float*>(mine)[col];
   asm volatile("" : "+v"(delta), "+v"(lse2));
+  lds_barrier();            // every wave has its rows
+#pragma unroll
+  for (int t = 1; t < LOOK; ++t)
+    if (t < NT) issue_tile(t);
   const int own = runs.window_start(r);
   const HalfSelectors sel = half_selectors();
 
@@ -162,7 +195,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(a), qb[i], s, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(a + TILE), dob[i], dp, 0, 0, 0);
     }
-    if (kt + 2 < NT) issue_tile(stage >= 1 ? stage - 1 : kTileStages - 1);
+    if (kt + LOOK < NT) issue_tile(stage >= 1 ? stage - 1 : kDqStages - 1);
     float ds[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -183,11 +216,12 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
     }
   };
   auto begin_pass = [&](int kt) BC_INLINE {
-    if (kt + 1 < NT) wait_vmcnt<2 * NLD>();         // (the next tile's loads may stay out)
+    if (kt + 2 < NT) wait_vmcnt<4 * NLD>();         // (the loads of the next two tiles may stay out)
+    else if (kt + 1 < NT) wait_vmcnt<2 * NLD>();
     else wait_vmcnt<0>();
     lds_barrier();
   };
-  auto end_pass = [&]() BC_INLINE { stage = stage + 1 == kTileStages ? 0 : stage + 1; };
+  auto end_pass = [&]() BC_INLINE { stage = stage + 1 == kDqStages ? 0 : stage + 1; };
 
   int kt = 0;
   for (const int nd = min(runs.dense, ntw); kt < nd; ++kt) {
@@ -202,7 +236,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
   }
   for (; kt < NT; ++kt) {
     begin_pass(kt);
-    if (kt + 2 < NT) issue_tile(stage >= 1 ? stage - 1 : kTileStages - 1);
+    if (kt + LOOK < NT) issue_tile(stage >= 1 ? stage - 1 : kDqStages - 1);
     end_pass();
   }
   lds_barrier();          // the tile stages are free: the epilogue reuses LDS

@@ -240,6 +240,26 @@ __device__ __forceinline__ void issue_block(const char* tile_base, OFF lane_offs
   }
 }
 
+// A wave's own 32 rows (row `last` repeated behind it) into a tile of its own in LDS, from where they are read as operands.
+// Loaded straight into the operands' registers, 16 bytes of 32 rows at a time, they took most of a workgroup's time
+// before its first product: with dO and the output 16,000 cycles of an idle chip, 12,000 with whole rows.
+template <int D>
+__device__ __forceinline__ void issue_wave_rows(const char* first, uint32_t row_bytes, int last, int lane, uint32_t lds_addr) {
+#pragma unroll
+  for (int rg = 0; rg < kTileRows / 8; ++rg) {
+    const TileLane t = rows_tile_lane(lane, rg);
+    const uint32_t o = (uint32_t)min(t.row, last) * row_bytes + t.in_row;
+#pragma unroll
+    for (int n = 0; n < D / 64; ++n) issue_block<false>(first + 128 * n, o, lds_addr + n * 4096 + rg * 1024);
+  }
+}
+template <int D>
+__device__ __forceinline__ void read_wave_rows(const char* tile, int lane, bf16x8_t (&x)[D / 16]) {
+  const char* a = tile + rows_read_offset(lane);
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) x[i] = *reinterpret_cast<const bf16x8_t*>(a + rows_read_imm<D>(i));
+}
+
 // The point by which operands loaded before a tile loop have landed: the compiler waits here and not
 // in front of their first use inside the loop, where the wait would cover the tiles' loads too.
 template <int N>
