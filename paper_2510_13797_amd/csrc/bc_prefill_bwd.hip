@@ -282,7 +282,6 @@ __device__ __forceinline__ int dense_parts(const BwdParams& p, int nd) {
 template <int D>
 __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(BwdParams p) {
   constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
-  constexpr int NLD = TILE / 1024 / kTileWaves;
   constexpr int RING = kDkvStages * 2 * TILE, STAT = RING, XCH = RING + kDkvStages * 256;
   constexpr int OUT = kTileWaves * 32 * (D / 2) * 4;
   constexpr int LDS = XCH + 2 * 4096;
@@ -376,22 +375,26 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   int it0 = 0, it1 = ntile * p.g;                    // streamed tiles: head-major
   if (split >= 0) { it0 = it1 * split / parts; it1 = ntile * p.g * (split + 1) / parts; }
   const int64_t q_row_bytes = (int64_t)p.Hq * ROWB;
-  const TileLane tlane = either_tile_lane(lane, wave);
+  const TileLane tlane = either_tile_lane(lane, 2 * kg);       // (the next eight rows at the same place)
   const uint32_t lds0 = lds_address(lds);
   int issue_h = it0 / ntile, issue_rt = ntile - 1 - (it0 - issue_h * ntile);
+  // By the keys' waves alone, half a tile each: they have the time, the others form A meanwhile.
   auto issue_tile = [&](int stage) BC_INLINE {
     const int h = kvh * p.g + issue_h, row0 = rs + issue_rt * kTileRows;
     if (--issue_rt < 0) { issue_rt = ntile - 1; ++issue_h; }
     const int left = S - 1 - row0;                   // (rows that do not exist repeat the last one)
-    const uint32_t o = (uint32_t)min(tlane.row, left) * (uint32_t)q_row_bytes + tlane.in_row;
     const int64_t at = (off0 + row0) * q_row_bytes + (int64_t)h * ROWB;
-    const uint32_t dst = lds0 + stage * (2 * TILE) + wave * 1024;
 #pragma unroll
-    for (int n = 0; n < NLD; ++n) {
-      lds_dma16_s<false>(o, (uint64_t)(p.q + at + 128 * n), dst + n * 4096);
-      lds_dma16_s<false>(o, (uint64_t)(p.dout + at + 128 * n), dst + TILE + n * 4096);
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t o = (uint32_t)min(tlane.row + 8 * u, left) * (uint32_t)q_row_bytes + tlane.in_row;
+      const uint32_t dst = lds0 + stage * (2 * TILE) + (2 * kg + u) * 1024;
+#pragma unroll
+      for (int n = 0; n < D / 64; ++n) {
+        lds_dma16_s<false>(o, (uint64_t)(p.q + at + 128 * n), dst + n * 4096);
+        lds_dma16_s<false>(o, (uint64_t)(p.dout + at + 128 * n), dst + TILE + n * 4096);
+      }
     }
-    if (wave == 0) {       // 32 rows' log-sum-exp, then their Delta
+    if (kg == 0) {         // 32 rows' log-sum-exp, then their Delta
       const float* st = p.stat + ((int64_t)h * p.total_rows + off0 + row0) * 2;
       lds_dma4_s((uint32_t)min(col, left) * 8u + half * 4u, (uint64_t)st, lds0 + STAT + stage * 256);
     }
@@ -406,34 +409,36 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds + XCH + kg * 4096) + lane;
 
   int rt = issue_rt, stage = 1;
-  if (it0 < it1) issue_tile(0);
+  if (keys_role && it0 < it1) issue_tile(0);
   for (int it = it0; it < it1; ++it) {
     stage ^= 1;
     const char* tile = lds + stage * (2 * TILE);
     const int row0 = rs + rt * kTileRows;
     if (--rt < 0) rt = ntile - 1;
     // tile `it` has landed, and everyone has finished tile it-1
-    wait_vmcnt<0>();
+    if (keys_role) wait_vmcnt<0>();
     lds_barrier();
     // a row tile that ends in front of the pair's first key, or starts behind the last row any of its
     // keys is seen from, adds nothing here
     const bool busy = row0 + kTileRows - 1 >= any_first && row0 <= any_last;
     f32x16_t x = f32x16_t{0.f};
+    f32x4_t stat[4];         // log-sum-exp or Delta of the lane's rows
     if (busy) {
+      const float* st = reinterpret_cast<const float*>(lds + STAT + stage * 256) + (keys_role ? 32 : 0) + 4 * half;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) stat[q] = *reinterpret_cast<const f32x4_t*>(st + 8 * q);
 #pragma unroll
       for (int i = 0; i < KS; ++i)
         x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
             *reinterpret_cast<const bf16x8_t*>(tile + roff[i & 1] + rows_read_imm<D>(i)), op[i], x, 0, 0, 0);
     }
-    if (it + 1 < it1) issue_tile(stage ^ 1);
-    const float* stat = reinterpret_cast<const float*>(lds + STAT + stage * 256) + 4 * half;
+    if (keys_role && it + 1 < it1) issue_tile(stage ^ 1);
     float val[16];
     if (busy && !keys_role) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f32x4_t lse2 = *reinterpret_cast<const f32x4_t*>(stat + 8 * q);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[4 * q + e] = fast_exp2(fmaf(x[4 * q + e], p.qscale, -lse2[e]));
+        for (int e = 0; e < 4; ++e) val[4 * q + e] = fast_exp2(fmaf(x[4 * q + e], p.qscale, -stat[q][e]));
       }
       if (row0 < all_first || row0 + kTileRows - 1 > all_last) {
         const int from = jkey - row0, upto = last - row0;
@@ -452,9 +457,9 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
     if (keys_role) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f32x4_t a = xch[64 * q], delta = *reinterpret_cast<const f32x4_t*>(stat + 32 + 8 * q);
+        const f32x4_t a = xch[64 * q];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[4 * q + e] = a[e] * (x[4 * q + e] - delta[e]);
+        for (int e = 0; e < 4; ++e) val[4 * q + e] = a[e] * (x[4 * q + e] - stat[q][e]);
       }
     }
     // dV^T += dO^T.A or dK^T += Q^T.dS
