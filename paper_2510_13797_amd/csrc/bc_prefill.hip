@@ -273,9 +273,8 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
   float* my = reinterpret_cast<float*>(lds + wave * (32 * OW * 4));
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass)
-    store_rows<D>(my, O, inv, pass, lane, [&](int t) -> float* {
-      return rw0 + t <= rw1 ? p.out + ((off0 + rw0 + t) * p.Hq + kvh * p.g + head) * D : nullptr;
-    });
+    store_rows<D>(my, O, inv, pass, lane, p.out + ((off0 + rw0) * p.Hq + kvh * p.g + head) * D, p.Hq * D,
+                  [&](int t) { return rw0 + t <= rw1 ? t : -1; });
   if (p.lse && half == 0 && rw0 + col <= rw1)
     p.lse[(off0 + r) * p.Hq + kvh * p.g + head] = (m_run + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
 }
