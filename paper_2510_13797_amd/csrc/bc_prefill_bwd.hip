@@ -17,7 +17,8 @@
 //              so the dense part of the work is spent on the ~P + S/(c+1) keys every row sees.
 //              A dense block is long (every later row x every head); it is cut into parts (see
 //              dense_parts), which write partial dK/dV to the workspace, and a third kernel adds
-//              them in a fixed order.  Response blocks store their result directly.
+//              them in a fixed order.  Response blocks are cut only where the chip is not full (band_splits)
+//              and store their result directly otherwise.
 //
 // All contractions are 32x32x16 bf16 MFMA; A and dS are split into two bf16 parts before they
 // enter a product (their rounding would otherwise dominate the error); tiles of 32 rows are gathered
@@ -52,6 +53,7 @@ struct BwdParams {
   float* part;          // [splits][2][total_rows][Hkv][D]: dk, dv partials of the dense key blocks
   int32_t D;            // head dimension (the reduction kernel reads it; the others are templates)
   int32_t splits;       // most workgroups that share a dense key block (see dense_parts)
+  int32_t band;         // workgroups that share a response block (see band_splits), at most `splits`
   int64_t total_rows;
   int32_t Hq, Hkv, g;
   HeadTiling tiling;    // dq kernel
@@ -305,13 +307,12 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const int NLB = (nresp + kDkvKeys - 1) / kDkvKeys;
   // The dense blocks (prompt keys, beacons) stream every later row of every head; the tiles of each
   // are dealt to `parts` workgroups, whose partial sums another kernel adds in a fixed order.
-  // The short response blocks are not cut and store their result directly.
-  const int nd = NPB + NBB, parts = dense_parts(p, nd);
-  int blk = nd + ((int)blockIdx.y - nd * parts), split = -1;
-  if (blk < nd) {
-    blk = blockIdx.y / parts;
-    if (parts > 1) split = blockIdx.y - blk * parts;
-  }
+  // The short response blocks are cut where the chip is not full; a block of one part stores its result directly.
+  const int nd = NPB + NBB, dense = dense_parts(p, nd);
+  const int at = (int)blockIdx.y - nd * dense;                  // place among the response blocks' parts
+  const int parts = at < 0 ? dense : p.band;
+  const int of = at < 0 ? (int)blockIdx.y : at;
+  const int blk = of / parts + (at < 0 ? 0 : nd), split = parts > 1 ? of % parts : -1;
   if (blk >= nd + NLB) return;
   const int kind = blk < NPB ? 0 : blk < NPB + NBB ? 1 : 2;
 
@@ -488,8 +489,8 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
                   [&](int t) { return __shfl(key_row, t, 64); });
 }
 
-// Sum of the head-split partials of the dense keys (prompt rows and beacons), in split order.  The other
-// rows were written directly.  grid: x = trajectory, y = blocks that share its dense keys (a thread for every
+// Sum of the partials of the dense keys (prompt rows and beacons) and, where the response blocks were cut too, of the
+// response rows, in split order.  Rows of blocks in one part were written directly.  grid: x = trajectory, y = blocks that share its dense keys (a thread for every
 // 16 bytes of every row, which had to find the row's trajectory and whether it is dense, took 47 us instead
 // of 16 for 16 trajectories of 8688 rows: one row in twelve is dense).
 __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
@@ -502,19 +503,38 @@ __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
   const int Pk = ws.c > 0 ? min(traj.P, S) : S;
   const int nbeac = ws.c > 0 ? (int)window_of(ws, (uint32_t)(S - Pk)) : 0;
   const int parts = dense_parts(p, (Pk + kDkvKeys - 1) / kDkvKeys + (nbeac + kDkvKeys - 1) / kDkvKeys);
-  if (parts == 1) return;
+  if (parts == 1 && p.band == 1) return;
   const int per_row = p.Hkv * (p.D / 4);         // 16-byte units
-  const int64_t units = (int64_t)(Pk + nbeac) * per_row;
+  const bool every_row = p.band > 1;
+  const int64_t units = (int64_t)(every_row ? S : Pk + nbeac) * per_row;
   const int64_t plane = p.total_rows * p.Hkv * p.D;
   for (int64_t i = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; i < units; i += (int64_t)gridDim.y * blockDim.x) {
-    const int n = (int)(i / per_row);            // dense key, its row, the place of the unit
-    const int j = n < Pk ? n : Pk + (n - Pk) * ws.stride + ws.c;
+    const int n = (int)(i / per_row);            // dense key or row, the row, the place of the unit
+    int j = n, sum = parts;
+    if (every_row) {
+      const uint32_t u = (uint32_t)(n - Pk);
+      if (n >= Pk && (int)(u - window_of(ws, u) * (uint32_t)ws.stride) != ws.c) sum = p.band;
+      if (sum == 1) continue;
+    } else if (n >= Pk) {
+      j = Pk + (n - Pk) * ws.stride + ws.c;
+    }
     const int64_t at = ((off0 + j) * per_row + (i - (int64_t)n * per_row)) * 4;
     f32x4_t sk = f32x4_t{0.f, 0.f, 0.f, 0.f}, sv = sk;
-#pragma unroll 4
-    for (int sp = 0; sp < parts; ++sp) {
-      sk += *reinterpret_cast<const f32x4_t*>(p.part + (int64_t)(2 * sp) * plane + at);
-      sv += *reinterpret_cast<const f32x4_t*>(p.part + (int64_t)(2 * sp + 1) * plane + at);
+    // four parts on their way at a time, also of the last three
+    for (int s0 = 0; s0 < sum; s0 += 4) {
+      f32x4_t xk[4], xv[4];
+#pragma unroll
+      for (int n4 = 0; n4 < 4; ++n4) {
+        const float* from = p.part + (int64_t)(2 * min(s0 + n4, sum - 1)) * plane + at;
+        xk[n4] = *reinterpret_cast<const f32x4_t*>(from);
+        xv[n4] = *reinterpret_cast<const f32x4_t*>(from + plane);
+      }
+#pragma unroll
+      for (int n4 = 0; n4 < 4; ++n4) {
+        if (s0 + n4 >= sum) break;
+        sk += xk[n4];
+        sv += xv[n4];
+      }
     }
     *reinterpret_cast<f32x4_t*>(p.dk + at) = sk;
     *reinterpret_cast<f32x4_t*>(p.dv + at) = sv;
@@ -542,6 +562,20 @@ static int dense_splits(const bc_shape* shape, int64_t total_rows) {
   const int64_t n = (kDkvAtOnce + blocks - 1) / blocks, least = shape->Hq > shape->Hkv ? 2 : 1;
   const int64_t most = tiles / 8 < kMost ? tiles / 8 : kMost;
   return (int)(n < least || most < least ? least : n > most ? most : n);
+}
+
+// Workgroups that share a response block: a chain of about three tiles for each head of a group, which is what a launch of
+// a few trajectories takes where the chip is not full.  As many as run at once beside the dense blocks' parts, at least
+// two heads each.  Three trajectories of 336 to 795 rows, 12/2 heads, whole 69.3 us a pass, in three parts 67.1
+// (the dense blocks' chains are as long); three of 300 rows, 14/2 heads, d = 64, 56.9 and 50.2.  Groups of fewer than six
+// heads stay whole: two trajectories of 216 rows, 4/1 heads, 44.5 and in two parts 44.9, the longer sum takes what is saved.
+static int band_splits(const bc_shape* shape, int64_t total_rows, int splits) {
+  const int64_t pairs = (int64_t)shape->B * shape->Hkv, g = shape->Hq / shape->Hkv;
+  if (g < 6) return 1;
+  const int64_t blocks = total_rows * shape->Hkv / kDkvKeys;        // one in eight dense, as above
+  const int64_t n = (kDkvAtOnce - (blocks / 8 + 2 * pairs) * splits) / (blocks - blocks / 8 + pairs);
+  const int64_t most = g / 2 < splits ? g / 2 : splits;
+  return (int)(n < 1 ? 1 : n > most ? most : n);
 }
 
 // Floats of the workspace's first part (stat), rounded up so that the partials behind it start at 256 bytes:
@@ -573,6 +607,7 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.stat = static_cast<float*>(workspace);
   p.part = p.stat + stat_floats(shape, total_rows);
   p.splits = dense_splits(shape, total_rows);
+  p.band = band_splits(shape, total_rows, p.splits);
   p.total_rows = total_rows;
   p.D = shape->d;
   p.Hq = shape->Hq; p.Hkv = shape->Hkv; p.g = shape->Hq / shape->Hkv;
@@ -586,13 +621,13 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   const int key_blocks = (max_rows + kDkvKeys - 1) / kDkvKeys;
   // key blocks: at most `key_blocks` dense-causal blocks + the gathered beacons + `key_blocks` response blocks
   const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
-  const dim3 dkv_grid(p.pstride, (2 * key_blocks + 2) * p.splits + key_blocks);
+  const dim3 dkv_grid(p.pstride, (2 * key_blocks + 2) * p.splits + key_blocks * p.band);
   const bool wide = rows_span_4gb(max_rows, shape);
   if (shape->d == 128) launch_bwd<128>(p, wide, dq_grid, dkv_grid, hs);
   else launch_bwd<64>(p, wide, dq_grid, dkv_grid, hs);
   if (p.splits > 1) {
-    const int64_t blocks = ((int64_t)max_rows * shape->Hkv * (shape->d / 4) + 255) / 256;
-    prefill_bwd_reduce_kernel<<<dim3(shape->B, (int)(blocks < 128 ? blocks : 128)), 256, 0, hs>>>(p);
+    const int64_t blocks = ((int64_t)max_rows * shape->Hkv * (shape->d / 4) + 255) / 256, most = p.band > 1 ? 1024 : 128;
+    prefill_bwd_reduce_kernel<<<dim3(shape->B, (int)(blocks < most ? blocks : most)), 256, 0, hs>>>(p);
   }
   return launch_status();
 }

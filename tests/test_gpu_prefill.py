@@ -473,6 +473,13 @@ def test_prefill_bwd_key_blocks_and_their_parts_at_the_edges(dev, P, R, Hq, Hkv,
         _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
 
 
+@pytest.mark.parametrize("P", [1, 64])
+@pytest.mark.parametrize("R,Hq,Hkv,d", [(1, 12, 2, 128), (63, 7, 1, 128), (65, 8, 1, 64), (190, 18, 3, 64)])
+def test_prefill_bwd_response_blocks_in_parts(dev, P, R, Hq, Hkv, d):
+    # groups of six heads and more on a chip that is not full: response blocks in two to four parts too, every row summed
+    test_prefill_bwd_key_blocks_and_their_parts_at_the_edges(dev, P, R, Hq, Hkv, d)
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_prefill_bwd_addresses_beyond_32_bits(dev, d):
     # as above for the gradients: 512 heads make rows of 128 or 64 KB, so a stated 4 GB of K rows needs
