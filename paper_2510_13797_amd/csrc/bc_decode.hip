@@ -1531,10 +1531,12 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     const int whole_passes = (npairs > kFewPairs || pl.Gp * sh->d >= 512 ? 1 : 2) + (alone ? 1 : 0);
     pl.split_rows = whole_passes * pl.rows_per_pass + 2;
     split_cap = (alone ? 4 : whole_passes) * pl.rows_per_pass + 1;
-    // fp32: half passes a sequence is read whole for
-    if (sh->kv_dtype == BC_F32)
-      pl.split_rows = npairs > 128 ? INT_MAX
-                                   : ((npairs <= 32 ? 5 : npairs <= 64 ? 7 : npairs <= 96 ? 9 : 14) + (alone ? 3 : 0)) * (pl.rows_per_pass / 2) + 2;
+    // fp32: half passes a sequence is read whole for; with more than 128 pairs every sequence is.  The plan has chunks only where
+    // its capacity lets a sequence be cut.
+    if (sh->kv_dtype == BC_F32) {
+      const int half_passes = (npairs <= 32 ? 5 : npairs <= 64 ? 7 : npairs <= 96 ? 9 : 14) + (alone ? 3 : 0);
+      pl.split_rows = split_cap = half_passes * (pl.rows_per_pass / 2) + 2;
+    }
   }
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
@@ -1568,20 +1570,20 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // batch is small, with up to 256 pairs.  256 workgroups run at once with groups of three or more (over 256
     // registers), otherwise 512; beyond that a second round takes more than the cut saves.  Attention alone has a launch in
     // front to clear its counters, some 1.5 us: its sequences are cut one pass later, and by capacities beyond four passes.
-    // fp32 plans have chunks from the same capacities on, but a pass takes 1.4 us there and a sequence is cut
-    // later: where whole and cut meet is between 2.5 passes with few pairs and 7 with 128, and beyond those one workgroup a
+    // An fp32 pass takes 1.4 us, and a sequence is cut later: where whole and cut meet is between 2.5 passes with few pairs and 7 with 128, and beyond those one workgroup a
     // pair draws what HBM gives (us a step, whole / cut; 4 pairs, d = 128: 8.5 / 10.0 at 124 rows, 10.1 / 9.9 at 180, 11.9 / 9.9 at
     // 252; 40 pairs 10.2 / 10.3 at 180, 11.7 / 10.4 at 252; 64 pairs 11.9 / 11.0 at 252; 120 pairs 15.5 / 15.7 at 380,
     // 19.1 / 18.3 at 508, d = 64 10.7 / 11.7 at 380, 12.4 / 12.6 at 508, 15.7 / 15.4 at 760; 200 pairs 18.1 / 21.8 at 760, 29.0 / 33.8 at
     // 1500; 240 pairs 33.3 / 38.2 at 760; 90 pairs in groups of seven, d = 64, 19.4 / 16.5 at 800).  More workgroups than 256 do not
     // help (40 pairs of 760 rows: 480 15.3, 240 13.5; 120 ragged ones of 200 to 1200, d = 128, 29.2, 26.5) but for the longest of
-    // many ragged sequences with the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, 34.0).  A
-    // plan whose sequences stay whole after all pays 0.2 to 0.4 us for the workgroups they do not fill.
+    // many ragged sequences with the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, 34.0).
+    // Chunks that no sequence can use cost 0.3 to 0.6 us a step, and attention alone the launch that clears the counters (3 and 2 chunks
+    // against none: 130 pairs, 300 rows, 12/2 heads 13.5, 13.0 us, alone 15.4, 13.5; 250 pairs 17.5, 17.2, alone 18.6, 16.6).
     const bool eight_waves = npairs <= kFewPairs ||
                              (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
     const bool one_per_cu = pl.lds ? eight_waves
                             : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs <= (sh->d == 64 ? 64 : 127) : pl.Gp >= 4;
-    const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : 256;
+    const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : sh->kv_dtype == BC_F32 ? 128 : 256;
     long chunks = 1;
     if (npairs <= most_pairs && max_cap >= split_cap) {
       chunks = at_once / npairs;

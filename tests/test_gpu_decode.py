@@ -65,6 +65,12 @@ def check_attention(o, q, oc, wl, seqs=None, t=None):
     return worst
 
 
+def partials_written(rt, filler=0):
+    """Whether a call left partial results of a cut sequence in the workspace, whose bytes were `filler` (behind the counters)."""
+    counters = -(-rt.B * 128 // 256) * 256 + (-(-rt.B * rt.Hkv * 4 // 256) * 256 if rt.Hkv >= 32 else 0)
+    return bool((rt.ws[counters:] != filler).any())
+
+
 def rollout(wl, rt, oc, steps, attn_steps, slab_steps, table_every=1, tail_form=False,
             use_step_call=False, seq_sample=None, beacon_call=False, before_step=None):
     """Alg. 1 for `steps` decode steps; sequences whose generation is over stay resident."""
@@ -857,8 +863,9 @@ def test_fused_steps_under_graph_replay(dev):
     (1, 33, 33, 64, "bf16", (1000,), 15),                   # more KV heads than counters beside the ticket
     (34, 2, 1, 128, "bf16", (1000, 30), 15),                # workgroups of four waves
     (33, 3, 1, 64, "bf16", (1030, 500), 15),
-    (2, 8, 1, 128, "f32", (58, 59), 2),                     # one pass of rows and one row more
-    (65, 2, 2, 64, "f32", (130, 90), 2),                    # 130 pairs on the plain-ALU kernel
+    (2, 8, 1, 128, "f32", (58, 59), 1),                     # capacities that never let a sequence be cut have no chunks
+    (65, 2, 2, 64, "f32", (130, 90), 1),
+    (2, 8, 1, 128, "f32", (158, 400), 7),
 ])
 def test_sequences_cut_into_chunks(dev, B, Hq, Hkv, d, dtype, P, chunks):
     # partials folded by a pair's last workgroup, one ticket per pair, evictions among the steps (c = 3)
@@ -890,7 +897,7 @@ def test_cut_plans_of_more_workgroups_than_run_at_once(dev, B, Hq, Hkv, d, dtype
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,dtype,P", [(3, 6, 2, 128, "bf16", (507, 40, 1100)), (1, 33, 33, 64, "bf16", (1000,)),
-                                                (65, 2, 2, 64, "f32", (600, 90))])
+                                                (50, 2, 2, 64, "f32", (1300, 90)), (3, 8, 1, 128, "f32", (500, 400, 90))])
 def test_attention_does_not_depend_on_what_the_workspace_holds(dev, B, Hq, Hkv, d, dtype, P):
     # a caller who only attends never has to clear the workspace, whatever other calls left in it
     P = np.resize(np.array(P, np.int32), B)
@@ -903,11 +910,12 @@ def test_attention_does_not_depend_on_what_the_workspace_holds(dev, B, Hq, Hkv, 
         rt.out.fill_(-3.0)
         q = wl.step_q(t)
         check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, t)
+        assert partials_written(rt, filler)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,dtype,batches", [
-    (2, 1, 64, "f32", ((150, 130), (256, 131), (300, 40))),        # cut, cut, whole
-    (4, 2, 128, "bf16", ((3, 1100), (64, 200), (20, 1000))),
+    (2, 1, 64, "f32", ((100, 930), (128, 931), (300, 40))),        # cut, cut, whole
+    (4, 2, 128, "bf16", ((3, 1100), (64, 200), (20, 1000))),       # cut, whole, cut
 ])
 def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, batches):
     # one workspace, sized for the largest batch, serves caches of several sizes in turn: the partial
@@ -926,18 +934,22 @@ def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, ba
         for wl, own, shared in runs:
             (k, v), q, (bk, bv) = wl.step_kv(t), wl.step_q(t), wl.beacon_kv(t)
             assert torch.equal(own.decode_step(k, v, q, bk, bv), shared.decode_step(k, v, q, bk, bv)), (t, wl.B)
+            assert partials_written(own) == (wl.P[0] > 900), (t, wl.B)
     for _, own, shared in runs:
         (na, wa, ea), (nb, wb, eb) = own.tables(), shared.tables()
         assert list(na) == list(nb) and list(wa) == list(wb) and ea == eb == 0
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [
-    (2, 8, 1, 128, (62, 66), 2),                     # cut from the second pass over the slab's rows on
-    (2, 2, 1, 64, (126, 250), 1),                    # small batch and short passes: from the third
-    (2, 2, 1, 64, (126, 255), 3),
-    (64, 16, 2, 128, (62, 260, 125), 2),             # groups of eight: one workgroup per compute unit
+    (2, 8, 1, 128, (62, 66), 1),
+    (2, 2, 1, 64, (126, 250), 1),
+    (2, 2, 1, 64, (126, 255), 1),
+    (2, 2, 1, 64, (318, 314), 3),                    # the first sequence comes to the line in the sixth step
+    (64, 16, 2, 128, (62, 260, 125), 1),
+    (64, 16, 2, 128, (62, 446, 125), 2),             # groups of eight: one workgroup per compute unit
     (65, 16, 2, 128, (62, 260, 125), 1),
-    (128, 3, 1, 64, (126, 400, 255), 4),
+    (128, 3, 1, 64, (126, 400, 255), 1),
+    (128, 3, 1, 64, (126, 894, 255), 4),
 ])
 def test_fp32_sequences_cut_at_their_passes(dev, B, Hq, Hkv, d, P, chunks):
     G = 7
@@ -947,6 +959,7 @@ def test_fp32_sequences_cut_at_their_passes(dev, B, Hq, Hkv, d, P, chunks):
     st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
     assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
     rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
+    assert partials_written(rt) == (chunks > 1)
     q = wl.step_q(77)
     check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, 77)
 
