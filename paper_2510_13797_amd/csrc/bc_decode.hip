@@ -2,7 +2,7 @@
 // (Sec. 2 and Sec. 3.1 of the paper: standard attention over whatever is resident).
 //
 // Split-K flash decoding.  Work item = (sequence, KV head) pair x chunk of rows; grid =
-// (KV heads, sequences, chunks).  From 128 pairs on (fp32: 129) a pair is one chunk and its workgroup
+// (KV heads, sequences, chunks).  From 128 pairs on (fp32: 129, but see f32_split_rows) a pair is one chunk and its workgroup
 // finishes it.  With fewer pairs the resident rows of a sequence are spread evenly over up to 64
 // workgroups (short sequences stay whole, see make_plan); every chunk
 // writes an (m, l, o) partial and the workgroup that arrives last folds the partials of its pair in
@@ -1509,6 +1509,29 @@ static bool fma_is_faster(long npairs, int Gp, int d, int max_cap) {
   return d == 64 ? npairs > 1024 && npairs <= 1792 : npairs > 512 && (npairs <= 1536 || max_cap <= 128);
 }
 
+// Rows from which on an fp32 sequence is cut (the plan of a capacity below that has one chunk).  A workgroup goes through 64 (d =
+// 128) or 128 rows a pass; whole and cut meet in the third pass, with more than 64 pairs of d = 128 in the fourth or fifth (us a step,
+// whole / cut.  d = 64 at 300, 350, 400 rows: 8 pairs 8.8 / 7.7, 8.9 / 7.7, 10.7 / 7.8; 64 pairs 9.5 / 8.5, 9.6 / 8.7, 11.3 / 8.9; 100 pairs
+// 10.4 / 9.8, 10.2 / 10.3, 12.0 / 10.8; 127 pairs 10.7 / 10.3, 10.6 / 10.7, 12.3 / 11.2.  d = 128 at 150, 200, 260 rows: 8 pairs 8.9 / 8.1, 10.6 /
+// 8.1, 12.1 / 8.1; 64 pairs 9.3 / 8.7, 11.1 / 9.0, 12.7 / 10.7; 96 pairs 10.1 / 10.3, 11.7 / 10.7, 13.0 / 12.4; 127 pairs 10.3 / 10.8, 12.3 / 11.6,
+// 14.1 / 13.2, of groups of eight 11.0 / 12.3, 12.9 / 13.0, 14.7 / 14.9).  The lines are lower than batches of equal length call for: the
+// longest sequences of a ragged one set its time (100 pairs of 37 to 1000 rows, d = 64: 18.9 cut from 898 rows on, 13.3 from 258 on; 64 pairs of 37
+// to 500: 11.0 from 450, 8.6).  Attention alone has a launch in front to clear its counters, 1 to 2 us where there are many, and is cut
+// later (33 pairs, d = 64, 400 rows: 10.2 / 9.1; 64 pairs, d = 128, groups of six, 230 rows: 10.3 / 11.2; 100 pairs, d = 128, 300 and 350 rows: 13.2
+// / 13.6, 15.0 / 13.8; 128 pairs of 500: 18.8 / 18.0, of groups of six 18.7 / 19.7).
+// More than 128 pairs: whole, without the fold and its workgroups (200 pairs in two chunks, d = 64: 29.2 / 33.2 at 1500 rows, 37.1 / 42.5
+// at 2000; 150 pairs of 500 rows in plans of one and three chunks that cut none of them: 11.7, 12.3, attention alone on 130 of 300 rows 13.5, 15.4).  Only groups of one and two with d = 64,
+// which one workgroup a pair draws the least for, are cut where they are long and three chunks run at once (150 pairs: 26.6 / 24.6 at 1500 rows, 32.7 /
+// 32.7 at 2000; three sequences of 1500 rows among those of 50 to 300 23.8 / 15.4, of 4400 59.7 / 28.4; 170 pairs of 37 to 2000 31.4 / 32.5).
+constexpr long kF32MostPairs = 512 / 3;
+constexpr int kF32SplitRowsMany = 1408;
+static int f32_split_rows(long npairs, int Gp, int d, int rows_per_pass, bool alone) {
+  if (npairs > 128) return npairs <= kF32MostPairs && d == 64 && Gp <= 2 ? kF32SplitRowsMany + (alone ? 128 : 0) : INT_MAX;
+  const bool early = npairs <= 32 || (d == 64 && npairs <= 64);
+  const int passes = alone ? (early ? 3 : npairs <= 96 ? 4 : 8) : d == 64 || npairs <= 64 ? 2 : npairs <= 96 ? 3 : 4;
+  return passes * rows_per_pass + 2;
+}
+
 // alone: attention without a step.
 static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits, bool alone = false) {
   DecodePlan pl;
@@ -1531,12 +1554,8 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     const int whole_passes = (npairs > kFewPairs || pl.Gp * sh->d >= 512 ? 1 : 2) + (alone ? 1 : 0);
     pl.split_rows = whole_passes * pl.rows_per_pass + 2;
     split_cap = (alone ? 4 : whole_passes) * pl.rows_per_pass + 1;
-    // fp32: half passes a sequence is read whole for; with more than 128 pairs every sequence is.  The plan has chunks only where
-    // its capacity lets a sequence be cut.
-    if (sh->kv_dtype == BC_F32) {
-      const int half_passes = (npairs <= 32 ? 5 : npairs <= 64 ? 7 : npairs <= 96 ? 9 : 14) + (alone ? 3 : 0);
-      pl.split_rows = split_cap = half_passes * (pl.rows_per_pass / 2) + 2;
-    }
+    // fp32: a plan has chunks only where its capacity lets a sequence be cut
+    if (sh->kv_dtype == BC_F32) pl.split_rows = split_cap = f32_split_rows(npairs, pl.Gp, sh->d, pl.rows_per_pass, alone);
   }
   if (rows_override > 0) {
     // forced chunk size (experiments, tests): fixed rows per workgroup
@@ -1570,20 +1589,14 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // batch is small, with up to 256 pairs.  256 workgroups run at once with groups of three or more (over 256
     // registers), otherwise 512; beyond that a second round takes more than the cut saves.  Attention alone has a launch in
     // front to clear its counters, some 1.5 us: its sequences are cut one pass later, and by capacities beyond four passes.
-    // An fp32 pass takes 1.4 us, and a sequence is cut later: where whole and cut meet is between 2.5 passes with few pairs and 7 with 128, and beyond those one workgroup a
-    // pair draws what HBM gives (us a step, whole / cut; 4 pairs, d = 128: 8.5 / 10.0 at 124 rows, 10.1 / 9.9 at 180, 11.9 / 9.9 at
-    // 252; 40 pairs 10.2 / 10.3 at 180, 11.7 / 10.4 at 252; 64 pairs 11.9 / 11.0 at 252; 120 pairs 15.5 / 15.7 at 380,
-    // 19.1 / 18.3 at 508, d = 64 10.7 / 11.7 at 380, 12.4 / 12.6 at 508, 15.7 / 15.4 at 760; 200 pairs 18.1 / 21.8 at 760, 29.0 / 33.8 at
-    // 1500; 240 pairs 33.3 / 38.2 at 760; 90 pairs in groups of seven, d = 64, 19.4 / 16.5 at 800).  More workgroups than 256 do not
-    // help (40 pairs of 760 rows: 480 15.3, 240 13.5; 120 ragged ones of 200 to 1200, d = 128, 29.2, 26.5) but for the longest of
-    // many ragged sequences with the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, 34.0).
-    // Chunks that no sequence can use cost 0.3 to 0.6 us a step, and attention alone the launch that clears the counters (3 and 2 chunks
-    // against none: 130 pairs, 300 rows, 12/2 heads 13.5, 13.0 us, alone 15.4, 13.5; 250 pairs 17.5, 17.2, alone 18.6, 16.6).
+    // fp32: lines in f32_split_rows().  More workgroups than 256 do not help there (40 pairs of 760 rows: 480 15.3, 240 13.5; 120 ragged
+    // ones of 200 to 1200, d = 128, 29.2, 26.5; 128 pairs of 350, in four chunks and in two 16.3, 14.2) but for many pairs with
+    // the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, and 34.0 with 256).
     const bool eight_waves = npairs <= kFewPairs ||
                              (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
     const bool one_per_cu = pl.lds ? eight_waves
-                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs <= (sh->d == 64 ? 64 : 127) : pl.Gp >= 4;
-    const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : sh->kv_dtype == BC_F32 ? 128 : 256;
+                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs <= (sh->d == 64 ? 64 : 128) : pl.Gp >= 4;
+    const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : sh->kv_dtype == BC_F32 ? kF32MostPairs : 256;
     long chunks = 1;
     if (npairs <= most_pairs && max_cap >= split_cap) {
       chunks = at_once / npairs;

@@ -865,7 +865,7 @@ def test_fused_steps_under_graph_replay(dev):
     (33, 3, 1, 64, "bf16", (1030, 500), 15),
     (2, 8, 1, 128, "f32", (58, 59), 1),                     # capacities that never let a sequence be cut have no chunks
     (65, 2, 2, 64, "f32", (130, 90), 1),
-    (2, 8, 1, 128, "f32", (158, 400), 7),
+    (2, 8, 1, 128, "f32", (126, 400), 7),
 ])
 def test_sequences_cut_into_chunks(dev, B, Hq, Hkv, d, dtype, P, chunks):
     # partials folded by a pair's last workgroup, one ticket per pair, evictions among the steps (c = 3)
@@ -914,7 +914,7 @@ def test_attention_does_not_depend_on_what_the_workspace_holds(dev, B, Hq, Hkv, 
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,dtype,batches", [
-    (2, 1, 64, "f32", ((100, 930), (128, 931), (300, 40))),        # cut, cut, whole
+    (2, 1, 64, "f32", ((100, 930), (150, 1410), (300, 40))),       # cut, cut, whole
     (4, 2, 128, "bf16", ((3, 1100), (64, 200), (20, 1000))),       # cut, whole, cut
 ])
 def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, batches):
@@ -943,13 +943,10 @@ def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, ba
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [
     (2, 8, 1, 128, (62, 66), 1),
     (2, 2, 1, 64, (126, 250), 1),
-    (2, 2, 1, 64, (126, 255), 1),
-    (2, 2, 1, 64, (318, 314), 3),                    # the first sequence comes to the line in the sixth step
-    (64, 16, 2, 128, (62, 260, 125), 1),
-    (64, 16, 2, 128, (62, 446, 125), 2),             # groups of eight: one workgroup per compute unit
+    (2, 2, 1, 64, (126, 255), 3),
+    (64, 16, 2, 128, (62, 260, 125), 2),             # groups of eight: one workgroup per compute unit
     (65, 16, 2, 128, (62, 260, 125), 1),
-    (128, 3, 1, 64, (126, 400, 255), 1),
-    (128, 3, 1, 64, (126, 894, 255), 4),
+    (128, 3, 1, 64, (126, 400, 255), 4),
 ])
 def test_fp32_sequences_cut_at_their_passes(dev, B, Hq, Hkv, d, P, chunks):
     G = 7
@@ -962,6 +959,33 @@ def test_fp32_sequences_cut_at_their_passes(dev, B, Hq, Hkv, d, P, chunks):
     assert partials_written(rt) == (chunks > 1)
     q = wl.step_q(77)
     check_attention(rt.decode_attn(q).cpu().numpy(), q, oc, wl, None, 77)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,line,alone", [
+    (2, 8, 1, 128, 130, 194), (32, 1, 1, 64, 258, 386), (33, 6, 1, 128, 130, 258), (32, 4, 2, 64, 258, 386), (65, 2, 1, 128, 194, 258),
+    (96, 1, 1, 64, 258, 514), (97, 7, 1, 128, 258, 514), (64, 4, 2, 64, 258, 1026), (129, 1, 1, 64, 1408, 1536), (170, 2, 1, 64, 1408, 1536)])
+def test_fp32_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, line, alone):
+    # every seventh sequence reaches the line in the sixth of seven steps (c = 3), the others stay below it; attention alone has a
+    # line of its own.  Partial results show whether a sequence was cut
+    G = 7
+    P = np.full(B, 9, np.int32)
+    P[1:line // 7:3] = np.arange(len(P[1:line // 7:3])) * 5 + 1
+    P[::7] = line - 4
+    wl = W.Workload("line32", 126, B, Hq, Hkv, d, "f32", P, np.full(B, G, np.int32), np.full(B, 3, np.int32))
+    rt, oc = make(wl, dev)
+    sample = sorted({0, 1, B // 2, B - 1} | set(range(0, B, 7)[:4]) | set(range(0, B, 7)[-2:]))
+    written = {}
+    rollout(wl, rt, oc, G, range(1, G + 1), (), use_step_call=True, seq_sample=sample,
+            before_step=lambda t: written.update({t: partials_written(rt)}))
+    assert [written[t] for t in range(1, G + 1)] == [False] * 6 + [True]
+    check_slabs(rt, oc, sample)
+    for rows in (alone - 1, alone, alone + 70):
+        wa = W.Workload("alone32", 127, B, Hq, Hkv, d, "f32", np.where(P == line - 4, rows, P).astype(np.int32), np.full(B, 0, np.int32),
+                        np.full(B, 3, np.int32))
+        ra, oa = make(wa, dev)
+        q = wa.step_q(5)
+        check_attention(ra.decode_attn(q).cpu().numpy(), q, oa, wa, sample, rows)
+        assert partials_written(ra) == (rows >= alone), rows
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [

@@ -286,8 +286,10 @@ def test_batches_that_share_a_workspace_keep_their_counters(Hq, Hkv, d, dtype):
             assert not part or 128 * B2 <= (max(bytes1, bytes2) - part) // 256 * 256, (B1, B2)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,d,line", [(2, 8, 1, 128, 162), (32, 4, 1, 64, 322), (33, 2, 1, 128, 226), (64, 1, 1, 64, 450),
-                                             (65, 2, 1, 128, 290), (48, 14, 2, 64, 578), (97, 1, 1, 128, 450), (64, 12, 2, 64, 898)])
+@pytest.mark.parametrize("B,Hq,Hkv,d,line", [(2, 8, 1, 128, 130), (1, 4, 1, 64, 258), (32, 4, 1, 64, 258), (33, 2, 1, 128, 130),
+                                             (64, 1, 1, 64, 258), (64, 1, 1, 128, 130), (65, 2, 1, 128, 194), (48, 14, 2, 64, 258),
+                                             (96, 1, 1, 128, 194), (97, 1, 1, 128, 258), (64, 12, 2, 64, 258), (64, 16, 2, 128, 258),
+                                             (129, 2, 1, 64, 1408), (85, 2, 2, 64, 1408)])
 def test_fp32_plans_have_chunks_only_where_a_sequence_can_be_cut(B, Hq, Hkv, d, line):
     # line: rows from which on a step cuts a sequence.  A capacity one row short of it gets the kernel without the fold
     for cap, cut in ((line - 1, False), (line, True), (20000, True)):
@@ -295,7 +297,8 @@ def test_fp32_plans_have_chunks_only_where_a_sequence_can_be_cut(B, Hq, Hkv, d, 
         assert st == 0 and (int(text.split("chunks=")[1].split()[0]) > 1) == cut, (cap, text)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,d", [(129, 2, 1, 64), (129, 6, 1, 128), (65, 2, 2, 128), (100, 16, 2, 128), (128, 4, 2, 64), (257, 1, 1, 64)])
+@pytest.mark.parametrize("B,Hq,Hkv,d", [(129, 3, 1, 64), (129, 6, 1, 128), (65, 2, 2, 128), (85, 16, 2, 64), (171, 2, 1, 64), (100, 16, 2, 128),
+                                        (128, 4, 2, 64), (257, 1, 1, 64)])
 def test_fp32_batches_that_are_never_cut_have_plans_of_one_chunk(B, Hq, Hkv, d):
     for cap in (66, 197, 1000, 4400, 150000):
         st, text = bc.bc_decode_plan_describe(shape(B=B, Hq=Hq, Hkv=Hkv, d=d), cache(max_cap=cap))
