@@ -1498,15 +1498,24 @@ constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace
 
 // fp32 groups of one or two on FMA instructions: they need so few registers there that four (groups of two), six (d = 128) or seven
 // workgroups share a compute unit, two on the matrix instructions, which waste 14 or 15 columns of 16 besides.  Where all
-// workgroups run at once on FMA but not on the matrix instructions, FMA is faster (FMA, matrix, us a step of 50 / 130 rows; groups of one, d = 128: 512 pairs 10.7, 10.0 / 19.2, 17.0; 880 13.2, 15.5 /
+// workgroups run at once on FMA but not on the matrix instructions, FMA is faster for short sequences of equal length (FMA,
+// matrix, us a step of 50 / 130 rows; groups of one, d = 128: 512 pairs 10.7, 10.0 / 19.2, 17.0; 880 13.2, 15.5 /
 // 26.1, 28.5; 1200 15.4, 19.4 / 31.9, 37.9; 2000 25.6, 27.7 / 58.2, 54.7; d = 64: 880 14.0, 12.7 / 18.8, 18.9; 1200 15.4, 15.8 / 21.0, 24.5;
 // 2000 23.9, 22.1 / 37.6, 34.0; groups of two, d = 64: 512 10.4, 8.4 / 13.6, 11.9; 880 12.5, 12.7 / 17.2, 19.5; 1200 18.2, 16.2 / 26.6,
 // 25.1; ragged, 2040 pairs of 17 to 104 rows, groups of one, d = 128: 27 and 30, 1584 of 10 to 55, d = 64:
-// 16 and 19).
+// 16 and 19).  From some 200 rows on both take what HBM takes (520 pairs of 600 rows, groups of one, d = 128: 63, 68; 1000 104, 104), and
+// where few workgroups are left for a second round of the matrix form they fill in behind the short ones of a ragged batch, while FMA is slow on the
+// long ones (matrix / FMA time, lengths spread evenly up to 130, 200, 400, 600 rows; groups of one, d = 128: 520 pairs 0.87, 0.81, 0.77, 0.73;
+// 660 1.03, 0.95, 0.87, 0.85; 800 1.07, 1.02, 0.92, 0.93; d = 64: 1060 0.98, 0.89, 0.80, 0.77; 1250 1.07, 0.97, 0.87, 0.83; groups of two, d = 64: 520
+// 0.89, 0.86, 0.83, 0.78; 720 1.01, 0.98, 0.98, 0.97; d = 128: 520 0.81, 0.74, 0.71, 0.67; 720 0.96, 0.92, 0.84, 0.84): so only
+// for capacities of up to 256 rows, and for those beyond 136 with 128 pairs more (groups of two of d = 128: 160 and 64).  What that
+// costs are batches of equal length and some 50 % more workgroups than run at once (800 pairs of 400 rows, groups of one, d = 128: FMA 59, matrix 64).
 static bool fma_is_faster(long npairs, int Gp, int d, int max_cap) {
-  if (Gp == 2) return npairs > 512 && npairs <= 1024;
-  if (Gp != 1) return false;
-  return d == 64 ? npairs > 1024 && npairs <= 1792 : npairs > 512 && (npairs <= 1536 || max_cap <= 128);
+  const bool wide_pair = Gp == 2 && d == 128;
+  if (Gp > 2 || max_cap > (wide_pair ? 160 : 256)) return false;
+  const long above = (Gp == 1 && d == 64 ? 1024 : 512) + (max_cap <= (wide_pair ? 64 : 136) ? 0 : 128);
+  const long most = Gp == 2 ? 1024 : d == 64 ? 1792 : max_cap <= 128 ? LONG_MAX : 1536;
+  return npairs > above && npairs <= most;
 }
 
 // Rows from which on an fp32 sequence is cut (the plan of a capacity below that has one chunk).  A workgroup goes through 64 (d =

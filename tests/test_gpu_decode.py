@@ -1055,7 +1055,7 @@ def test_beacon_rows_of_as_many_heads_as_fit_lds_and_one_more(dev, Hkv, d, plan)
     rollout(wl, rt, oc, 12, range(1, 13), (4, 12), use_step_call=True)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,d", [(65, 8, 8, 128), (161, 8, 8, 128), (129, 8, 8, 64), (65, 16, 8, 64)])
+@pytest.mark.parametrize("B,Hq,Hkv,d", [(65, 8, 8, 128), (161, 8, 8, 128), (129, 8, 8, 64), (65, 16, 8, 64), (65, 16, 8, 128)])
 def test_fp32_groups_of_one_and_two_on_fma_instructions(dev, B, Hq, Hkv, d):
     # large batches of short sequences whose groups are so small that the FMA form is the faster one
     P = np.resize(np.array([0, 3, 31, 40, 17], np.int32), B)

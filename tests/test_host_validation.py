@@ -305,6 +305,19 @@ def test_fp32_batches_that_are_never_cut_have_plans_of_one_chunk(B, Hq, Hkv, d):
         assert st == 0 and "chunks=1" in text and ", true, " not in text, (cap, text)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,cap,fma", [
+    (512, 1, 1, 128, 50, False), (513, 1, 1, 128, 136, True), (640, 1, 1, 128, 137, False), (641, 1, 1, 128, 256, True),
+    (1536, 1, 1, 128, 256, True), (1537, 1, 1, 128, 128, True), (1537, 1, 1, 128, 129, False), (800, 1, 1, 128, 257, False),
+    (1024, 1, 1, 64, 50, False), (1025, 1, 1, 64, 136, True), (1152, 1, 1, 64, 137, False), (1153, 1, 1, 64, 256, True),
+    (1400, 1, 1, 64, 257, False), (1793, 1, 1, 64, 50, False), (512, 2, 1, 64, 50, False), (513, 2, 1, 64, 136, True),
+    (640, 2, 1, 64, 137, False), (641, 2, 1, 64, 256, True), (700, 2, 1, 64, 257, False), (1025, 2, 1, 64, 50, False),
+    (513, 2, 1, 128, 64, True), (640, 2, 1, 128, 65, False), (641, 2, 1, 128, 160, True), (641, 2, 1, 128, 161, False),
+    (600, 3, 1, 64, 50, False), (600, 8, 1, 128, 50, False)])
+def test_fp32_batches_that_run_on_fma_instructions(B, Hq, Hkv, d, cap, fma):
+    st, text = bc.bc_decode_plan_describe(shape(B=B, Hq=Hq, Hkv=Hkv, d=d), cache(max_cap=cap))
+    assert st == 0 and ("false, true>" in text) == fma and "chunks=1" in text, text
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,rows", [(5, 1, 64, 333), (3, 3, 128, 4097), (3, 1, 128, 1), (7, 1, 64, 1023), (12, 2, 128, 33)])
 def test_backward_partials_start_at_a_256_byte_boundary(Hq, Hkv, d, rows):
     # the workspace is (lse, Delta) of every row and head, then partial dK and dV: 16-byte accesses, whole
