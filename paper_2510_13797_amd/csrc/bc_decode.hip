@@ -1458,12 +1458,11 @@ __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
   finish_step<RB>(p, pi, lane);
 }
 
-// Two workgroups of the matrix form share a compute unit.  (Groups of seven and eight used to be compiled for one, which only their FMA
-// form needs: us a step with one / two, groups of eight; 8 pairs of 200 rows, d = 64, 7.7 / 7.3; 100 of 100 to 1000 17.6 / 14.1, d = 128 22.0 / 20.9;
-// 300 of 200 rows 14.4 / 12.3, 22.8 / 19.5; 800 of 500 rows 49.1 / 42.2, 85.7 / 78.9; but 300 ragged ones of 100 to 1000, whose long sequences then share
-// compute units as those of smaller groups do, 28.3 / 31.7, 47.0 / 54.6, and 500 of them 36.9 / 35.1.)
+// Waves per SIMD that the plan reckons with: least and most.
+template <int G, bool FMA> constexpr int kValuLeast = !FMA && G < 8 ? 2 : 1;
+template <int G, bool FMA> constexpr int kValuMost = !FMA && G == 8 ? 1 : 8;
 template <typename T, int D, int G, int U, bool CHUNKS, bool FMA = !std::is_same<T, float>::value>
-__global__ __launch_bounds__(256, FMA ? 1 : 2)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kValuLeast<G, FMA>, kValuMost<G, FMA>)))
 void decode_valu_kernel(DecodeParams p) {
   if constexpr (!FMA) decode_f32_rows<D, G, CHUNKS>(p);
   else decode_alu_rows<T, D, G, U, CHUNKS>(p);
@@ -1524,7 +1523,7 @@ static bool fma_is_faster(long npairs, int Gp, int d, int max_cap) {
 // whole / cut.  d = 64 at 300, 350, 400 rows: 8 pairs 8.8 / 7.7, 8.9 / 7.7, 10.7 / 7.8; 64 pairs 9.5 / 8.5, 9.6 / 8.7, 11.3 / 8.9; 100 pairs
 // 10.4 / 9.8, 10.2 / 10.3, 12.0 / 10.8; 127 pairs 10.7 / 10.3, 10.6 / 10.7, 12.3 / 11.2.  d = 128 at 150, 200, 260 rows: 8 pairs 8.9 / 8.1, 10.6 /
 // 8.1, 12.1 / 8.1; 64 pairs 9.3 / 8.7, 11.1 / 9.0, 12.7 / 10.7; 96 pairs 10.1 / 10.3, 11.7 / 10.7, 13.0 / 12.4; 127 pairs 10.3 / 10.8, 12.3 / 11.6,
-// 14.1 / 13.2).  The lines are lower than batches of equal length call for: the
+// 14.1 / 13.2, of groups of eight 11.0 / 12.3, 12.9 / 13.0, 14.7 / 14.9).  The lines are lower than batches of equal length call for: the
 // longest sequences of a ragged one set its time (100 pairs of 37 to 1000 rows, d = 64: 18.9 cut from 898 rows on, 13.3 from 258 on; 64 pairs of 37
 // to 500: 11.0 from 450, 8.6).  Attention alone has a launch in front to clear its counters, 1 to 2 us where there are many, and is cut
 // later (33 pairs, d = 64, 400 rows: 10.2 / 9.1; 64 pairs, d = 128, groups of six, 230 rows: 10.3 / 11.2; 100 pairs, d = 128, 300 and 350 rows: 13.2
@@ -1601,12 +1600,11 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // front to clear its counters, some 1.5 us: its sequences are cut one pass later, and by capacities beyond four passes.
     // fp32: lines in f32_split_rows().  More workgroups than 256 do not help there (40 pairs of 760 rows: 480 15.3, 240 13.5; 120 ragged
     // ones of 200 to 1200, d = 128, 29.2, 26.5; 128 pairs of 350, in four chunks and in two 16.3, 14.2) but for many pairs with
-    // the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, and 34.0 with 256; groups of eight 33.3, 36.6, three sequences of 2000 rows among
-    // 80 of 50 to 300 12.8, 16.5, but 80 of 1000 15.0, 13.8).
+    // the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, and 34.0 with 256).
     const bool eight_waves = npairs <= kFewPairs ||
                              (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
     const bool one_per_cu = pl.lds ? eight_waves
-                            : sh->kv_dtype == BC_F32 ? npairs <= (sh->d == 64 ? 64 : 128) : pl.Gp >= 4;
+                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs <= (sh->d == 64 ? 64 : 128) : pl.Gp >= 4;
     const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : sh->kv_dtype == BC_F32 ? kF32MostPairs : 256;
     long chunks = 1;
     if (npairs <= most_pairs && max_cap >= split_cap) {
