@@ -11,6 +11,7 @@ fails loudly when libbc.so is missing.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 
 import numpy as np
@@ -347,6 +348,22 @@ def _used_here(*tensors):
             torch.cuda.current_stream().synchronize()      # pinned host memory: nothing tracks it
 
 
+def _on_its_device(call):
+    """The call with the device of its first tensor as the current one (0.4 us where it is already): it enqueues its work on the
+    current stream, and that has to be the stream its results and workspace are allocated on."""
+    name = call.__code__.co_varnames[0]
+
+    @functools.wraps(call)
+    def on_its_device(*args, **kwargs):
+        import torch
+        first = args[0] if args else kwargs.get(name)
+        if getattr(first, "is_cuda", False) and first.device.index != torch._C._cuda_getDevice():
+            with torch.cuda.device(first.device):
+                return call(*args, **kwargs)
+        return call(*args, **kwargs)
+    return on_its_device
+
+
 class Runtime:
     """Owns slabs, tables and workspace of one batch of caches; calls the C ABI."""
 
@@ -567,6 +584,7 @@ def _trajectory_tables(row_offsets, P, c, device):
     return host, (at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B), dev
 
 
+@_on_its_device
 def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, workspace=False):
     """bc_prefill_attn (or, workspace=True, bc_prefill_attn_ws) on device tensors.
 
@@ -596,6 +614,7 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     return out, lse
 
 
+@_on_its_device
 def prefill_attn_bwd(q, k, v, out, lse, dout, row_offsets, P, c, Hq, Hkv, d, scale):
     """bc_prefill_attn_bwd on device tensors (see prefill_attn); returns (dq, dk, dv) fp32."""
     import torch
@@ -631,6 +650,7 @@ def _logits_code(t):
     raise BcError("logits must be bf16 or fp32 device tensors")
 
 
+@_on_its_device
 def topk_kl_loss(student_logits, teacher_logits, teacher_idx):
     """bc_topk_kl_loss on device tensors: student_logits [T, V] bf16/fp32, teacher_logits [T, k]
     fp32, teacher_idx [T, k] int32.  Returns (loss_per_token [T], lse [T], loss_mean [1]) fp32."""
@@ -651,6 +671,7 @@ def topk_kl_loss(student_logits, teacher_logits, teacher_idx):
     return loss, lse, mean
 
 
+@_on_its_device
 def topk_kl_loss_bwd(student_logits, teacher_logits, teacher_idx, lse, grad_scale):
     """bc_topk_kl_loss_bwd on device tensors; returns dlogits [T, V] in the logits' dtype."""
     import torch

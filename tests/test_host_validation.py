@@ -4,6 +4,7 @@ Every call here is rejected by the library's own checks before it touches a devi
 pointer values are made-up addresses that are never dereferenced, and each case breaks exactly
 one documented precondition of include/bc.h and expects the status the header names for it.
 """
+import inspect
 
 import pytest
 
@@ -340,3 +341,41 @@ def test_noalloc_step_takes_what_its_documented_size_holds():
     assert call(shape(B=126, Hq=16, Hkv=2, d=128, dtype=bc.BC_BF16),
                 cache(max_cap=1024, rows_per_workgroup=256)) == bc.BC_ERR_WORKSPACE
     assert call(shape(B=126, Hq=16, Hkv=2, d=128), cache(max_cap=256, rows_per_workgroup=64)) == bc.BC_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("name,inputs", [("prefill_attn", 10), ("prefill_attn_bwd", 13), ("topk_kl_loss", 3), ("topk_kl_loss_bwd", 5)])
+@pytest.mark.parametrize("device,current,enters", [(1, 0, True), (0, 0, False), (0, 1, True)])
+def test_tensor_calls_work_on_the_device_of_their_tensors(monkeypatch, name, inputs, device, current, enters):
+    # the calls return while their work is under way: on another device's stream their workspace could be given out
+    # again, and their results read, before it is done
+    import types
+    import torch
+    inside = []
+
+    class Guard:
+        def __init__(self, dev):
+            self.dev = dev
+
+        def __enter__(self):
+            inside.append(self.dev)
+
+        def __exit__(self, *exc):
+            inside.append("left")
+
+    class Reached(Exception):
+        pass
+
+    def reached():
+        raise Reached()
+
+    monkeypatch.setattr(torch.cuda, "device", Guard)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: current, raising=False)
+    monkeypatch.setattr(bc, "load", reached)
+    x = types.SimpleNamespace(is_cuda=True, device=torch.device("cuda", device))
+    call = getattr(bc, name)
+    with pytest.raises(Reached):
+        call(*[x] * inputs)
+    assert inside == ([x.device, "left"] if enters else [])
+    with pytest.raises(Reached):
+        call(**{n: x for n in list(inspect.signature(call).parameters)[:inputs]})
+    assert inside == ([x.device, "left"] * 2 if enters else [])
