@@ -1458,7 +1458,9 @@ __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
   finish_step<RB>(p, pi, lane);
 }
 
-// Waves per SIMD that the plan reckons with: least and most.
+// Waves per SIMD that the plan reckons with: least and most.  (The matrix form's registers let groups of seven and eight have two as well:
+// us a step with one / two, groups of eight, 8 pairs of 200 rows, d = 64, 7.7 / 7.3; 300 of 200 rows 14.4 / 12.3, d = 128 22.8 / 19.5; 800 of 500 rows
+// 49.1 / 42.2, 85.7 / 78.9; but 300 ragged ones of 100 to 1000, whose long sequences then share compute units, 28.3 / 31.7, 47.0 / 54.6.)
 template <int G, bool FMA> constexpr int kValuLeast = !FMA && G < 8 ? 2 : 1;
 template <int G, bool FMA> constexpr int kValuMost = !FMA && G == 8 ? 1 : 8;
 template <typename T, int D, int G, int U, bool CHUNKS, bool FMA = !std::is_same<T, float>::value>
