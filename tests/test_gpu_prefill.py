@@ -667,10 +667,13 @@ def test_host_tables_equal_device_tables(dev, B):
         == bc.BC_ERR_WORKSPACE
 
 
-@pytest.mark.parametrize("rows,at", [(3, 0), (257, 0), (257, 256), (9000, 8999), (9000, 4097)])
+@pytest.mark.parametrize("rows,at", [(3, 0), (257, 0), (257, 256), (9000, 8999), (9000, 4097), (16384, 16383), (17000, 16383),
+                                     (17000, 16384), (17000, 16999), (70000, 0), (70000, 32767), (70000, 32768), (70000, 50000),
+                                     (70000, 65535), (70000, 65536), (70000, 69999)])
 def test_every_workgroup_of_the_conversion_pass_has_a_verdict(dev, rows, at):
     # V entries that do not fit half precision, in the first and last rows the pass reads, with few workgroups and
-    # with all 256: the two-part form's bits
+    # with all 256, of which each thread takes a unit in every 16384 rows here, four of them together: in each of the four, in the
+    # next round and in the last row.  The two-part form's bits
     import torch
     from paper_2510_13797_amd import bc
     q, k, v = (torch.randn(rows, 2, 64, device=dev).to(torch.bfloat16) for _ in range(3))
