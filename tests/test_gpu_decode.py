@@ -988,6 +988,15 @@ def test_fp32_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, line, alone):
         assert partials_written(ra) == (rows >= alone), rows
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,P", [(5, 6, 2, 128, (126, 300, 40)), (40, 6, 2, 64, (254, 20, 700))])
+def test_fp32_cut_sequences_and_the_beacons_own_step(dev, B, Hq, Hkv, d, P):
+    G = 8
+    wl = W.Workload("beacon32", 128, B, Hq, Hkv, d, "f32", np.resize(np.array(P, np.int32), B), np.full(B, G, np.int32), np.full(B, 3, np.int32))
+    rt, oc = make(wl, dev)
+    rollout(wl, rt, oc, G, range(1, G + 1), (3, G), beacon_call=True, seq_sample=range(min(B, 9)))
+    assert partials_written(rt)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [
     (1, 4, 1, 64, (16900,), 34),                      # a chunk for every 512 rows: the fold takes three batches
     (2, 6, 2, 128, (9000, 8300), 18),

@@ -99,6 +99,20 @@ def test_noalloc_step_on_the_plain_alu_path(dev):
     _same_state(ref, sta)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,P", [(20, 4, 1, 64, (253, 600, 40)), (34, 12, 2, 128, (189, 20, 700))])
+def test_noalloc_step_on_cut_fp32_sequences(dev, B, Hq, Hkv, d, P):
+    import torch
+    from paper_2510_13797_amd import bc
+    wl = W.Workload("noalloc32", 98, B, Hq, Hkv, d, "f32", np.resize(np.array(P, np.int32), B), np.full(B, 8, np.int32), np.full(B, 3, np.int32))
+    ref, sta = _pair(wl, dev)
+    st, text = bc.bc_decode_plan_describe(sta.shape, sta.cache)
+    assert st == 0 and "merge" in text, text
+    for t in range(1, 9):
+        (k, v), q, (bk, bv) = wl.step_kv(t), wl.step_q(t), wl.beacon_kv(t)
+        assert torch.equal(ref.decode_step(k, v, q, bk, bv), sta.decode_step_noalloc(k, v, q, bk, bv)), t
+    _same_state(ref, sta)
+
+
 def test_noalloc_step_captured_in_a_graph(dev):
     import torch
     from paper_2510_13797_amd import bc
