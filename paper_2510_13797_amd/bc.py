@@ -591,7 +591,8 @@ def prefill_attn(q, k, v, row_offsets, P, c, Hq, Hkv, d, scale, want_lse=True, w
     q [R, Hq, d], k, v [R, Hkv, d] bf16 device tensors (trajectories concatenated);
     row_offsets [B+1] int64, P, c [B] int32 (host arrays).  Returns (out fp32 [R,Hq,d], lse or None), which the
     current stream works on: like every call here it only enqueues (until it did, copies of the tables and a wait at
-    the end cost some 20 us a call; forward and gradients of three short trajectories 154 -> 79 us).
+    the end cost some 20 us a call; forward and gradients of three short trajectories 154 -> 79 us).  Other streams, and
+    code that reads the results through their addresses, wait for it first.
     """
     import torch
     load()
@@ -653,7 +654,9 @@ def _logits_code(t):
 @_on_its_device
 def topk_kl_loss(student_logits, teacher_logits, teacher_idx):
     """bc_topk_kl_loss on device tensors: student_logits [T, V] bf16/fp32, teacher_logits [T, k]
-    fp32, teacher_idx [T, k] int32.  Returns (loss_per_token [T], lse [T], loss_mean [1]) fp32."""
+    fp32, teacher_idx [T, k] int32.  Returns (loss_per_token [T], lse [T], loss_mean [1]) fp32, which the current stream
+    works on: the call only enqueues (it used to wait for the stream).  Other streams, and code that reads them through their
+    addresses, wait for it first."""
     import torch
     load()
     T, V = student_logits.shape
@@ -673,7 +676,8 @@ def topk_kl_loss(student_logits, teacher_logits, teacher_idx):
 
 @_on_its_device
 def topk_kl_loss_bwd(student_logits, teacher_logits, teacher_idx, lse, grad_scale):
-    """bc_topk_kl_loss_bwd on device tensors; returns dlogits [T, V] in the logits' dtype."""
+    """bc_topk_kl_loss_bwd on device tensors; returns dlogits [T, V] in the logits' dtype, which the current stream works on
+    (see topk_kl_loss)."""
     import torch
     load()
     T, V = student_logits.shape

@@ -281,7 +281,10 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
 
 // EITHER: the form the conversion pass found V to fit, one of the two by a branch that is uniform over the launch.  (As two
 // launches, of which one left at its first instruction, with a third that cleared the verdict and a fourth that stored the tables, a
-// call took 30 us where its kernels' work is 10 to 15; now 19.  Large launches run at the power limit: 27,109 rows 489 us, both.)
+// call took 30 us where its kernels' work is 10 to 15; now 19.  Large launches run at the power limit: 27,109 rows 489 us, both.
+// Both forms in one kernel keep 25 scalar registers in vector lanes, and at d = 64 four waves a SIMD where the half-precision form alone had five.  That
+// costs nothing that shows: read afresh in each form, without spills, 16 trajectories of 8688 rows, d = 64, 367 us and 363, 27,109 rows of 32/8 heads 287 and 287,
+// d = 128 484 and 486, three short ones 19.4 to 20.8 and 19.9.)
 template <int D, bool EITHER, bool WIDE>
 __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_kernel(PrefillParams p) {
   __shared__ __attribute__((aligned(1024))) char lds[prefill_lds<D>()];

@@ -33,7 +33,7 @@
 // every 768 matrix cycles of a SIMD.  The dq kernel needs 209 registers (Q, dO and dQ of 32 rows), two waves per
 // SIMD; held to 168 it spilled in the tile loop.  A dkv tile is a chain of 3,700 cycles, alone on a compute unit or with two
 // neighbours.  Since these figures: dq rows and results through LDS whole rows at a time, tiles loaded by the waves that wait,
-// a whole forward and backward pass of that batch 3398 -> 3286 us.
+// a whole forward and backward pass of that batch 3398 -> 3286 us (on one card; cards differ by 3 %).
 #include "bc_prefill_tiles.h"
 
 namespace bc {
@@ -569,8 +569,10 @@ static int dense_splits(const bc_shape* shape, int64_t total_rows) {
 // Workgroups that share a response block: a chain of about three tiles for each head of a group, which is what a launch of
 // a few trajectories takes where the chip is not full.  As many as run at once beside the dense blocks' parts, at least
 // two heads each.  Three trajectories of 336 to 795 rows, 12/2 heads, whole 69.3 us a pass, in three parts 67.1
-// (the dense blocks' chains are as long); three of 300 rows, 14/2 heads, d = 64, 56.9 and 50.2.  Groups of fewer than six
-// heads stay whole: two trajectories of 216 rows, 4/1 heads, 44.5 and in two parts 44.9, the longer sum takes what is saved.
+// (the dense blocks' chains are as long); three of 300 rows, 14/2 heads, d = 64, 56.9 and 50.2; of 380 rows (forward and gradients in one
+// graph), 12/2 heads 59.5 and 51.9, d = 64 45.9 and 40.0, but three of 830 rows 69.4 and 71.0.  Groups of fewer than six heads stay
+// whole: two trajectories of 216 rows, 4/1 heads, 44.5 and in two parts 44.9, called one by one.  In one graph groups of five gain as those of six do (two of
+// 270 rows, 5/1 heads 51.8 and 45.7, three of 830 64.6 and 65.1), groups of four half as much (43.0 and 40.1, 55.5 and 56.0).
 static int band_splits(const bc_shape* shape, int64_t total_rows, int splits) {
   const int64_t pairs = (int64_t)shape->B * shape->Hkv, g = shape->Hq / shape->Hkv;
   if (g < 6) return 1;

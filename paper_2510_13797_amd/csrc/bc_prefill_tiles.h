@@ -21,7 +21,9 @@ typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 // tables of the trajectories
 // ---------------------------------------------------------------------------
 // In device memory or, from the calls that take them as host arrays, for up to BC_INLINE_TRAJECTORIES trajectories in the kernel
-// arguments (a launch in front that stored them took 3 us a call, 10 % of a small forward and backward pass).
+// arguments (a launch in front that stored them took 3 us a call, 10 % of a small forward and backward pass).  Sixteen are 400 bytes of
+// them; 4 KB would hold some 240.  (128 inline, trajectories of some 200 rows, 4/1 heads, forward and gradients: 3 and 16 trajectories 43.0 and
+// 45.5 us with either, 17 52.2 through memory and 48.1 inline, 40 61.3 and 56.6, 100 102.5 and 98.8.)
 struct InlineTables {
   int64_t row_off[BC_INLINE_TRAJECTORIES + 1];
   int32_t P[BC_INLINE_TRAJECTORIES], c[BC_INLINE_TRAJECTORIES];
@@ -321,7 +323,7 @@ __device__ __forceinline__ void store_rows(float* my, const f32x16_t (&acc)[D / 
           f32x4_t{a[4 * i] * mul, a[4 * i + 1] * mul, a[4 * i + 2] * mul, a[4 * i + 3] * mul};
     }
   // All reads, then all stores: each read stood behind a store that it might alias and a branch, and a workgroup's end took
-  // 5,000 to 6,000 cycles (16 trajectories of 8688 rows 3293 -> 3281 us a pass, three short ones 72.8 -> 71.1).
+  // 5,000 to 6,000 cycles (three short trajectories 72.8 -> 71.1 us a pass; 16 of 8688 rows 3293 -> 3281, little more than two runs differ by).
   f32x4_t val[32 / RPP];
   int to[32 / RPP];
 #pragma unroll
