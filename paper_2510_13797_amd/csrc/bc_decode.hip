@@ -1137,17 +1137,26 @@ __device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
     k_to_lds(stage);
 #pragma unroll
     for (int u = 0; u < SUB; ++u) {
-      f32x4_t a[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+      // Eight sums side by side, of 8 (d = 64) or 16 products, then a tree.  (As two sums, and all rows of a wave in one sum below, results were
+      // 1.2 to 2 times as far from 64 bits as the FMA form's, which sums four products and then over lanes.  Relative error of FMA, two sums, as
+      // here, 1e-7: 64 sequences, d = 64, 40 rows 1.3, 1.9, 1.3, 120 rows 1.5, 2.0, 1.6, 600 rows with scores twice as wide 2.7, 4.4, 2.7; d = 128 1.3, 2.1, 1.4,
+      // then 1.5, 2.6, 1.6 and 2.6, 4.9, 2.9; 200 of 1500 rows 2.4, 4.3, 2.0; 1.01 of FMA's on the average of what was measured.  It costs 1.2 % of a
+      // step; sums of eight products at d = 128 too, 0.99, spill a register.)
+      f32x4_t score[8];
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
         const row16_t k = *reinterpret_cast<const row16_t*>(wk + 16 * u * RB + (ksrc ^ (64 * (i & 3))) + 256 * (i >> 2));
 #pragma unroll
-        for (int c = 0; c < 4; ++c) a[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c], q[i][c], a[c & 1], 0, 0, 0);
+        for (int c = 0; c < 4; ++c) {
+          f32x4_t& sum = score[4 * (i & 1) + c];
+          sum = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c], q[i][c], i < 2 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
+        }
       }
+      score[0] = ((score[0] + score[1]) + (score[2] + score[3])) + ((score[4] + score[5]) + (score[6] + score[7]));
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const bool there = r0 + 16 * u + 4 * kb + e < pi.row_end;
-        s[u][e] = there ? a[0][e] + a[1][e] : kNegBig;
+        s[u][e] = there ? score[0][e] : kNegBig;
         tmax = fmaxf(tmax, s[u][e]);
       }
     }
@@ -1165,8 +1174,6 @@ __device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
         psum += s[u][e];
       }
     l_run = l_run * alpha + psum;
-#pragma unroll
-    for (int j = 0; j < 4 * VJ; ++j) O[j] *= alpha;
     // the appended row (the last of the sequence's last tile) outlives the step: stored for later ones (no reader
     // touches the slab there in this launch)
     if (last && pi.store_new_row && r0 + ROWS > pi.new_row) {
@@ -1183,15 +1190,22 @@ __device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
             }
       }
     }
+    // sixteen rows by themselves, then to the rest
 #pragma unroll
-    for (int u = 0; u < SUB; ++u)
+    for (int u = 0; u < SUB; ++u) {
+      f32x4_t T[4 * VJ];
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int j = 0; j < VJ; ++j)
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            O[4 * j + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[stage][u][e][j][c], s[u][e], O[4 * j + c], 0, 0, 0);
+          for (int c = 0; c < 4; ++c) {
+            f32x4_t& sum = T[4 * j + c];
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[stage][u][e][j][c], s[u][e], e == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
+          }
+#pragma unroll
+      for (int j = 0; j < 4 * VJ; ++j) O[j] = u == 0 ? O[j] * alpha + T[j] : O[j] + T[j];
+    }
   };
   // The next tile's loads go out one after every other matrix instruction of the scores: all at once they keep the wave
   // from its work until the memory pipeline has accepted them.

@@ -1034,6 +1034,31 @@ def test_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, P):
     check_slabs(rt, oc, sample)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,width,bound", [
+    (64, 4, 1, 64, 40, 4.0, 2.45e-7), (64, 4, 1, 64, 600, 2.0, 3.4e-7), (64, 6, 1, 128, 120, 1.0, 1.85e-7), (64, 6, 1, 128, 600, 2.0, 3.3e-7),
+    (200, 6, 1, 128, 1500, 0.02, 2.5e-7)])
+def test_fp32_sums_are_as_close_to_64_bits_as_short_ones(dev, B, Hq, Hkv, d, P, width, bound):
+    # 2-norm of the difference over that of the result.  bound: 1.25 times what sums of four products, of eight rows, and over lanes
+    # give for these inputs (1.96, 2.71, 1.49, 2.61, 2.00e-7); one running sum of a row's products and of a wave's rows gives 3.15, 4.40,
+    # 2.55, 4.88, 3.57e-7
+    import torch
+    rt = _bc().Runtime(B, Hq, Hkv, d, "f32", d ** -0.5, np.full(B, P), np.zeros(B, np.int32), np.full(B, P + 2), dev)
+    g = torch.Generator(device=dev).manual_seed(3)
+    n = B * (P + 2) * Hkv * d
+    rt.k_slab.copy_(torch.randn(n, generator=g, device=dev))
+    rt.v_slab.copy_(torch.randn(n, generator=g, device=dev))
+    q = width * torch.randn(B, Hq, d, generator=g, device=dev)
+    o = rt.decode_attn(q).cpu().numpy().astype(np.float64)
+    K, V = (x.view(B, Hkv, P + 2, d)[:, :, :P].cpu().numpy().astype(np.float64) for x in (rt.k_slab, rt.v_slab))
+    q = q.cpu().numpy().astype(np.float64)
+    e2 = r2 = 0.0
+    for s in range(0, B, B // 32):
+        ref = OA.decode_attention(q[s], K[s].transpose(1, 0, 2), V[s].transpose(1, 0, 2), d ** -0.5)
+        e2 += float(((o[s] - ref) ** 2).sum())
+        r2 += float((ref ** 2).sum())
+    assert (e2 / r2) ** 0.5 < bound, (e2 / r2) ** 0.5
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,rows", [(4, 1, 64, 0), (12, 2, 128, 0), (8, 1, 128, 0), (3, 3, 64, 0), (7, 1, 64, 128),
                                            (10, 2, 128, 64)])
 def test_fp32_rows_at_the_edges_of_their_tiles(dev, Hq, Hkv, d, rows):
