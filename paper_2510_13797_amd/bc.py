@@ -315,16 +315,17 @@ def to_device(x, dtype: str, device):
     return torch.from_numpy(np.ascontiguousarray(x)).to(device)
 
 
-_torch_c = None
+_torch_c = _torch_stream = None       # torch._C and torch.Stream, once a call has used the device
 
 
 def _stream_ptr():
     """torch's current stream of the current device, as a number (0.2 us; by way of
     torch.cuda.current_stream() 3 us, a third of a small decode step's call)."""
-    global _torch_c
+    global _torch_c, _torch_stream
     if _torch_c is None:
         import torch
         torch.cuda.current_stream()                # (initialises the device if nothing has)
+        _torch_stream = torch.Stream
         _torch_c = torch._C
     return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
 
@@ -335,16 +336,17 @@ def _ptr(t):
 
 def _used_here(*tensors):
     """The current stream uses these tensors, which the caller may free as soon as the call returns: memory that
-    came from another stream is not given out again before this one is done with it."""
-    import torch
-    stream_id, device_index, device_type = torch._C._cuda_getCurrentStream(torch._C._cuda_getDevice())
-    stream = torch.Stream(stream_id=stream_id, device_index=device_index, device_type=device_type)
+    came from another stream is not given out again before this one is done with it.  (Behind a call that has asked for
+    the stream.)"""
+    stream_id, device_index, device_type = _torch_c._cuda_getCurrentStream(_torch_c._cuda_getDevice())
+    stream = _torch_stream(stream_id=stream_id, device_index=device_index, device_type=device_type)
     for t in tensors:
         if t is None:
             continue
         if t.is_cuda:
             t.record_stream(stream)
         else:
+            import torch
             torch.cuda.current_stream().synchronize()      # pinned host memory: nothing tracks it
 
 
@@ -355,11 +357,14 @@ def _on_its_device(call):
 
     @functools.wraps(call)
     def on_its_device(*args, **kwargs):
-        import torch
         first = args[0] if args else kwargs.get(name)
-        if getattr(first, "is_cuda", False) and first.device.index != torch._C._cuda_getDevice():
-            with torch.cuda.device(first.device):
+        if getattr(first, "is_cuda", False):
+            if _torch_c is not None and first.device.index == _torch_c._cuda_getDevice():
                 return call(*args, **kwargs)
+            import torch
+            if first.device.index != torch._C._cuda_getDevice():
+                with torch.cuda.device(first.device):
+                    return call(*args, **kwargs)
         return call(*args, **kwargs)
     return on_its_device
 
@@ -572,7 +577,6 @@ BC_INLINE_TRAJECTORIES = 16
 def _trajectory_tables(row_offsets, P, c, device):
     """row_offsets [B+1] int64, P, c [B] int32 as one host array and its three addresses, and device memory for them
     where they do not fit the kernels' arguments (else None)."""
-    import torch
     B = len(row_offsets) - 1
     host = np.empty(2 * B + 1, dtype=np.int64)
     host[:B + 1] = row_offsets
@@ -580,7 +584,10 @@ def _trajectory_tables(row_offsets, P, c, device):
     tables[:B] = np.asarray(P, dtype=np.int32).reshape(-1)[:B]
     tables[B:] = np.asarray(c, dtype=np.int32).reshape(-1)[:B]
     at = host.ctypes.data
-    dev = torch.empty(2 * B + 1, dtype=torch.int64, device=device) if B > BC_INLINE_TRAJECTORIES else None
+    dev = None
+    if B > BC_INLINE_TRAJECTORIES:
+        import torch
+        dev = torch.empty(2 * B + 1, dtype=torch.int64, device=device)
     return host, (at, at + 8 * (B + 1), at + 8 * (B + 1) + 4 * B), dev
 
 
