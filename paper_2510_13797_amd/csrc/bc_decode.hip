@@ -1472,13 +1472,10 @@ __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
   finish_step<RB>(p, pi, lane);
 }
 
-// Waves per SIMD that the plan reckons with: least and most.  (The matrix form's registers let groups of seven and eight have two as well:
-// us a step with one / two, groups of eight, 8 pairs of 200 rows, d = 64, 7.7 / 7.3; 300 of 200 rows 14.4 / 12.3, d = 128 22.8 / 19.5; 800 of 500 rows
-// 49.1 / 42.2, 85.7 / 78.9; but 300 ragged ones of 100 to 1000, whose long sequences then share compute units, 28.3 / 31.7, 47.0 / 54.6.)
-template <int G, bool FMA> constexpr int kValuLeast = !FMA && G < 8 ? 2 : 1;
-template <int G, bool FMA> constexpr int kValuMost = !FMA && G == 8 ? 1 : 8;
+// Two workgroups of the matrix form share a compute unit.  (Groups of seven and eight used to be compiled for one, which only their FMA form
+// needs: see kLonePairs for what is left of that.)
 template <typename T, int D, int G, int U, bool CHUNKS, bool FMA = !std::is_same<T, float>::value>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kValuLeast<G, FMA>, kValuMost<G, FMA>)))
+__global__ __launch_bounds__(256, FMA ? 1 : 2)
 void decode_valu_kernel(DecodeParams p) {
   if constexpr (!FMA) decode_f32_rows<D, G, CHUNKS>(p);
   else decode_alu_rows<T, D, G, U, CHUNKS>(p);
@@ -1489,6 +1486,7 @@ static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 struct DecodePlan {
   bool lds;           // LDS/MFMA kernel (bf16, d = 128) or the VALU kernel
   bool fma;           // the latter on FMA instructions (bf16 always, fp32 by fma_is_faster())
+  int lone_bytes;     // LDS that keeps its workgroups from sharing a compute unit, or none (see kLonePairs)
   int Gp;             // padded group size
   int rows_per_pass;  // rows one pass of a workgroup covers
   int R;              // rows per workgroup
@@ -1539,7 +1537,7 @@ static bool fma_is_faster(long npairs, int Gp, int d, int max_cap) {
 // whole / cut.  d = 64 at 300, 350, 400 rows: 8 pairs 8.8 / 7.7, 8.9 / 7.7, 10.7 / 7.8; 64 pairs 9.5 / 8.5, 9.6 / 8.7, 11.3 / 8.9; 100 pairs
 // 10.4 / 9.8, 10.2 / 10.3, 12.0 / 10.8; 127 pairs 10.7 / 10.3, 10.6 / 10.7, 12.3 / 11.2.  d = 128 at 150, 200, 260 rows: 8 pairs 8.9 / 8.1, 10.6 /
 // 8.1, 12.1 / 8.1; 64 pairs 9.3 / 8.7, 11.1 / 9.0, 12.7 / 10.7; 96 pairs 10.1 / 10.3, 11.7 / 10.7, 13.0 / 12.4; 127 pairs 10.3 / 10.8, 12.3 / 11.6,
-// 14.1 / 13.2, of groups of eight 11.0 / 12.3, 12.9 / 13.0, 14.7 / 14.9).  The lines are lower than batches of equal length call for: the
+// 14.1 / 13.2).  The lines are lower than batches of equal length call for: the
 // longest sequences of a ragged one set its time (100 pairs of 37 to 1000 rows, d = 64: 18.9 cut from 898 rows on, 13.3 from 258 on; 64 pairs of 37
 // to 500: 11.0 from 450, 8.6).  Attention alone has a launch in front to clear its counters, 1 to 2 us where there are many, and is cut
 // later (33 pairs, d = 64, 400 rows: 10.2 / 9.1; 64 pairs, d = 128, groups of six, 230 rows: 10.3 / 11.2; 100 pairs, d = 128, 300 and 350 rows: 13.2
@@ -1556,6 +1554,15 @@ static int f32_split_rows(long npairs, int Gp, int d, int rows_per_pass, bool al
   const int passes = alone ? (early ? 3 : npairs <= 96 ? 4 : 8) : d == 64 || npairs <= 64 ? 2 : npairs <= 96 ? 3 : 4;
   return passes * rows_per_pass + 2;
 }
+
+// Groups of seven and eight, few more pairs than compute units: one workgroup each, by LDS that nobody uses, so that the pairs
+// left over start behind short sequences and not beside long ones, whose time doubles.  us a step, two a compute unit / one: 260 pairs of 100 to
+// 1000 rows, d = 64, 27.8 / 23.9, d = 128 48.3 / 37.8, 272 28.4 / 24.6 and 48.8 / 38.3, 288 31.2 / 33.9 and 51.6 / 54.3, 304 31.5 / 33.9 and 52.0 / 54.1;
+// 272 of 20 to 200 11.5 / 12.0 and 15.7 / 14.5; of equal length two are always better (260 of 300 rows 16.5 / 18.7, 25.3 / 26.9).
+// Compiled for one workgroup, as these groups were, 300 of 200 rows 15.6, and 12.7 with two, d = 128
+// 23.3 and 20.0; 800 of 500 50.5 and 43.0, 85.9 and 79.3; 100 of 100 to 1000, d = 64, 15.5 and 14.3; 8 of 200 7.7 and 7.5.
+constexpr int kLonePairs = 280;
+constexpr int kLoneBytes = 52 << 10;      // with the tiles' 32 KB more than half of a compute unit's
 
 // alone: attention without a step.
 static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits, bool alone = false) {
@@ -1620,7 +1627,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     const bool eight_waves = npairs <= kFewPairs ||
                              (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
     const bool one_per_cu = pl.lds ? eight_waves
-                            : sh->kv_dtype == BC_F32 ? pl.Gp == 8 || npairs <= (sh->d == 64 ? 64 : 128) : pl.Gp >= 4;
+                            : sh->kv_dtype == BC_F32 ? npairs <= (sh->d == 64 ? 64 : 128) : pl.Gp >= 4;
     const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : sh->kv_dtype == BC_F32 ? kF32MostPairs : 256;
     long chunks = 1;
     if (npairs <= most_pairs && max_cap >= split_cap) {
@@ -1634,6 +1641,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     pl.max_chunks = (int)chunks;
   }
   pl.fma = !pl.lds && (sh->kv_dtype == BC_BF16 || (pl.max_chunks == 1 && fma_is_faster(npairs, pl.Gp, sh->d, max_cap)));
+  pl.lone_bytes = !pl.lds && !pl.fma && pl.Gp == 8 && pl.max_chunks == 1 && npairs > 256 && npairs <= kLonePairs ? kLoneBytes : 0;
   // Workspace sizing: the most chunks the automatic plan can choose, 64 with few pairs and four otherwise (a
   // forced chunk size on a large batch may use as many).
   if (rows_override == kPlanForSizing) pl.max_chunks = npairs < 128 ? 64 : 4;
@@ -1648,24 +1656,24 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
 static dim3 decode_grid(const bc_shape* shape, const DecodePlan& pl) { return dim3(shape->Hkv, shape->B, pl.max_chunks); }
 
 template <typename T, int D, int G>
-static void launch_valu_group(const DecodeParams& p, bool fma, dim3 grid, hipStream_t st) {
+static void launch_valu_group(const DecodeParams& p, const DecodePlan& pl, dim3 grid, hipStream_t st) {
   if constexpr (std::is_same<T, float>::value && G <= 2) {
-    if (fma) {
+    if (pl.fma) {
       decode_valu_kernel<T, D, G, 8, false, true><<<grid, 256, 0, st>>>(p);
       return;
     }
   }
   if (p.max_chunks > 1) decode_valu_kernel<T, D, G, 8, true><<<grid, 256, 0, st>>>(p);
-  else decode_valu_kernel<T, D, G, 8, false><<<grid, 256, 0, st>>>(p);
+  else decode_valu_kernel<T, D, G, 8, false><<<grid, 256, pl.lone_bytes, st>>>(p);
 }
 template <typename T, int D>
 static void launch_valu(const DecodeParams& p, const DecodePlan& pl, dim3 grid, hipStream_t st) {
   switch (pl.Gp) {
-    case 1: launch_valu_group<T, D, 1>(p, pl.fma, grid, st); break;
-    case 2: launch_valu_group<T, D, 2>(p, pl.fma, grid, st); break;
-    case 4: launch_valu_group<T, D, 4>(p, pl.fma, grid, st); break;
-    case 6: launch_valu_group<T, D, 6>(p, pl.fma, grid, st); break;
-    default: launch_valu_group<T, D, 8>(p, pl.fma, grid, st); break;
+    case 1: launch_valu_group<T, D, 1>(p, pl, grid, st); break;
+    case 2: launch_valu_group<T, D, 2>(p, pl, grid, st); break;
+    case 4: launch_valu_group<T, D, 4>(p, pl, grid, st); break;
+    case 6: launch_valu_group<T, D, 6>(p, pl, grid, st); break;
+    default: launch_valu_group<T, D, 8>(p, pl, grid, st); break;
   }
 }
 

@@ -1059,6 +1059,27 @@ def test_fp32_sums_are_as_close_to_64_bits_as_short_ones(dev, B, Hq, Hkv, d, P, 
     assert (e2 / r2) ** 0.5 < bound, (e2 / r2) ** 0.5
 
 
+@pytest.mark.parametrize("g,d", [(7, 64), (8, 64), (7, 128), (8, 128)])
+@pytest.mark.parametrize("B", [256, 257, 280, 281])
+def test_fp32_groups_of_seven_and_eight_with_more_pairs_than_compute_units(dev, g, d, B):
+    # one workgroup a compute unit from 257 to 280 pairs, two otherwise; lengths around the tiles, the last pairs longest.  1e-5: fp32 rows
+    import torch
+    P = np.array([1 + (7 * s) % 140 for s in range(B)], np.int32)
+    P[-3:] = 300, 301, 433
+    rt = _bc().Runtime(B, g, 1, d, "f32", d ** -0.5, P, np.zeros(B, np.int32), P, dev)
+    gen = torch.Generator(device=dev).manual_seed(4)
+    n = int(P.sum()) * d
+    rt.k_slab.copy_(torch.randn(n, generator=gen, device=dev))
+    rt.v_slab.copy_(torch.randn(n, generator=gen, device=dev))
+    q = torch.randn(B, g, d, generator=gen, device=dev)
+    o = rt.decode_attn(q).cpu().numpy()
+    K, V = (x.view(-1, 1, d).cpu().numpy().astype(np.float64) for x in (rt.k_slab, rt.v_slab))
+    at = np.concatenate([[0], np.cumsum(P)])
+    for s in list(range(0, B, 17)) + [B - 4, B - 3, B - 2, B - 1]:
+        ref = OA.decode_attention(q[s].cpu().numpy().astype(np.float64), K[at[s]:at[s + 1]], V[at[s]:at[s + 1]], d ** -0.5)
+        assert np.abs(o[s] - ref).max() < 1e-5, s
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,rows", [(4, 1, 64, 0), (12, 2, 128, 0), (8, 1, 128, 0), (3, 3, 64, 0), (7, 1, 64, 128),
                                            (10, 2, 128, 64)])
 def test_fp32_rows_at_the_edges_of_their_tiles(dev, Hq, Hkv, d, rows):
