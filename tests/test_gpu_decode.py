@@ -944,7 +944,7 @@ def test_steps_of_different_batches_share_a_workspace(dev, Hq, Hkv, d, dtype, ba
     (2, 8, 1, 128, (62, 66), 1),
     (2, 2, 1, 64, (126, 250), 1),
     (2, 2, 1, 64, (126, 255), 3),
-    (64, 16, 2, 128, (62, 260, 125), 2),             # groups of eight: one workgroup per compute unit
+    (64, 16, 2, 128, (62, 260, 125), 2),             # groups of eight
     (65, 16, 2, 128, (62, 260, 125), 1),
     (128, 3, 1, 64, (126, 400, 255), 4),
 ])
