@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
   static_assert(LDS >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
   __shared__ __attribute__((aligned(1024))) char lds[LDS];
 
-  const int hh = blockIdx.x / p.pstride, pair = blockIdx.x - hh * p.pstride;
+  const int hh = blockIdx.x / p.pstride, pair = pair_in_turn(blockIdx.x - hh * p.pstride, p.pstride);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
@@ -292,8 +292,9 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   __shared__ __attribute__((aligned(1024))) char lds[LDS];
   // grid: x = (trajectory, KV head), y = key block; the long dense blocks of every trajectory
   // are dispatched before any short one
-  if ((int)blockIdx.x >= p.npairs) return;
-  const int kvh = blockIdx.x % p.Hkv, b = blockIdx.x / p.Hkv;
+  const int pair = pair_in_turn(blockIdx.x, p.pstride);
+  if (pair >= p.npairs) return;
+  const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
   const int64_t off0 = traj.off0;
   const int S = traj.rows;

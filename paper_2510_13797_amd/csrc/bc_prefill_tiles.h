@@ -361,6 +361,14 @@ inline HeadTiling head_tiling(int g) {
 // few pairs that would leave XCDs idle (three trajectories with two KV heads: six of eight XCDs at
 // work), and the tiles are dealt out evenly instead.
 inline int pair_stride(int npairs) { return npairs % 8 == 0 || npairs > 64 ? (npairs + 7) & ~7 : npairs; }
+// Inside an XCD they go to its four shader engines in turn, and a workgroup waits for a place in the engine whose turn it is.  A pair
+// at the same place in every row of the grid has all its workgroups on one engine, and trajectories of different length or ratio
+// then wait for the engine of the heaviest while the others stand idle (8 of 1482 to 5617 rows, ratios of 2 to 32, 32/8 heads, forward with
+// workspace: a third of the compute units idle, a call takes 487 us; 394 with the pairs of an XCD changing places from row to row; 16 equal
+// trajectories take what they took).  A grid of pairs that is no multiple of 8 changes places by itself.
+__device__ __forceinline__ int pair_in_turn(int at, int pstride) {
+  return pstride % 8 == 0 ? (int)((at + 8u * blockIdx.y) % (unsigned)pstride) : at;
+}
 
 // Whether byte offsets inside a trajectory's K or V rows may need more than 32 bits.
 inline bool rows_span_4gb(int32_t max_rows, const bc_shape* sh) {

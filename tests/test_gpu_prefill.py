@@ -247,6 +247,20 @@ def test_config5_bwd_full_size(dev):
     print("config5 bwd dq/dk/dv", errs)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv", [(8, 1, 1), (5, 8, 8), (3, 48, 16), (9, 14, 7), (67, 2, 1), (72, 1, 1), (65, 2, 2)])
+def test_prefill_pairs_that_change_places_from_row_to_row(dev, B, Hq, Hkv, form):
+    # numbers of (trajectory, KV head) pairs that fill rows of eight, one row to many, or are padded to them (63, 67): every row and
+    # every gradient element of every pair
+    rng = np.random.default_rng([20251013, 79, B, Hkv])
+    P, R = rng.integers(1, 40, size=B).astype(np.int32), rng.integers(0, 150, size=B).astype(np.int32)
+    pw = W.PrefillWorkload("pf_turn", 400 + B, B, Hq, Hkv, 64, "bf16", P, R, rng.choice([0, 2, 5, 16], size=B).astype(np.int32))
+    qkv, off, out, lse = _run(pw, dev)
+    _, dos, _, dq, dk, dv = _run_bwd(pw, dev)
+    for b in range(pw.B):
+        _check_rows(pw, qkv, off, out, lse, b, list(range(int(pw.S[b]))))
+        _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
+
+
 @pytest.mark.parametrize("case", range(8))
 def test_prefill_randomised_forward_and_backward(dev, case, form):
     # seeded random trajectory counts, prompt and response lengths, ratios and head layouts;
