@@ -144,7 +144,6 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
   lds_barrier();            // every wave has its rows
   if (NT > 1) issue_tile(1);
   const int own = runs.window_start(r);
-  const HalfSelectors sel = half_selectors();
 
   f32x16_t O[NJ];
 #pragma unroll
@@ -225,7 +224,7 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
     for (int s = 0; s < 2; ++s) {
       bf16x8_t ph, pl;
       if constexpr (HALF) ph = __builtin_bit_cast(bf16x8_t, make_uint4(h16[4 * s], h16[4 * s + 1], h16[4 * s + 2], h16[4 * s + 3]));
-      else split8(pe + 8 * s, ph, pl, sel);
+      else split8(pe + 8 * s, ph, pl);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const bf16x8_t av = cols_operand<D>(tile + voff, j, s);

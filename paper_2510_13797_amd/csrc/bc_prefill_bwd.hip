@@ -178,7 +178,6 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
   for (int t = 1; t < LOOK; ++t)
     if (t < NT) issue_tile(t);
   const int own = runs.window_start(r);
-  const HalfSelectors sel = half_selectors();
 
   f32x16_t dQ[NJ];
 #pragma unroll
@@ -210,7 +209,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       bf16x8_t hi, lo;
-      split8(ds + 8 * k, hi, lo, sel);
+      split8(ds + 8 * k, hi, lo);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const bf16x8_t kc = cols_operand<D>(tile + coff[k], j, k);
@@ -409,7 +408,6 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const int rows_tile = keys_role ? TILE : 0, cols_tile = TILE - rows_tile;     // Q or dO by rows, the other by columns
   const int roff[2] = {rows_tile + either_rows_offset(lane), rows_tile + (either_rows_offset(lane) ^ 128)};
   const int coff[2] = {cols_tile + either_cols_offset(lane, 0), cols_tile + either_cols_offset(lane, 1)};
-  const HalfSelectors sel = half_selectors();
   f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds + XCH + kg * 4096) + lane;
 
   int rt = issue_rt, stage = 1;
@@ -470,7 +468,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       bf16x8_t hi, lo;
-      split8(val + 8 * k, hi, lo, sel);
+      split8(val + 8 * k, hi, lo);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const bf16x8_t rc = cols_operand<D>(tile + coff[k], j, k);
