@@ -369,22 +369,30 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   }
   landed_operands(op);
 
-  // Row tiles are streamed from the last row of the range backwards: all dense key blocks of a
-  // (trajectory, KV head) pair need the rows from the end of the trajectory back to their own
-  // keys, start together (they are neighbours in dispatch order, on the same XCD) and so walk the
-  // same tiles at the same time - the later readers of a tile find it in the L2.
+  // Row tiles are streamed from the last row of the range backwards, all heads of a row tile one behind the other, and the parts of
+  // a block take them in turn.  All dense key blocks and parts of a (trajectory, KV head) pair need the rows from the end of
+  // the trajectory back to their own keys, start together (they are neighbours in dispatch order, on the same XCD) and so walk
+  // the same rows at the same time: the later readers of a tile find it in the L2.  (Head by head and part behind part, blocks of different
+  // length were soon at different heads: 16 trajectories of 8688 rows read 5.4 GB past the L2 and take 3218 us a
+  // pass, 3.9 GB and 3190 now.)
   const int ntile = (re - rs) / kTileRows + 1;       // row tiles per head
-  int it0 = 0, it1 = ntile * p.g;                    // streamed tiles: head-major
-  if (split >= 0) { it0 = it1 * split / parts; it1 = ntile * p.g * (split + 1) / parts; }
+  const int stride = split >= 0 ? parts : 1, first = split >= 0 ? split : 0;
+  const int count = (ntile * p.g - first + stride - 1) / stride;       // tiles of this workgroup
+  const int step_h = stride % p.g, step_rt = stride / p.g;
+  struct Place { int h, rt; };
+  auto advance = [&](Place& x) BC_INLINE {
+    x.h += step_h; x.rt -= step_rt;
+    if (x.h >= p.g) { x.h -= p.g; --x.rt; }
+  };
   const int64_t q_row_bytes = (int64_t)p.Hq * ROWB;
   const TileLane tlane = either_tile_lane(lane, 2 * kg);       // (the next eight rows at the same place)
   const uint32_t lds0 = lds_address(lds);
-  int issue_h = it0 / ntile, issue_rt = ntile - 1 - (it0 - issue_h * ntile);
+  Place next{first % p.g, ntile - 1 - first / p.g};
   // By the keys' waves alone, half a tile each, while the others form A.  (By all four waves it was 460 of the 3,700
   // cycles of a tile's chain: 16 trajectories of 8688 rows 3331 -> 3293 us a pass, three short ones 74.8 -> 72.8.)
   auto issue_tile = [&](int stage) BC_INLINE {
-    const int h = kvh * p.g + issue_h, row0 = rs + issue_rt * kTileRows;
-    if (--issue_rt < 0) { issue_rt = ntile - 1; ++issue_h; }
+    const int h = kvh * p.g + next.h, row0 = rs + next.rt * kTileRows;
+    advance(next);
     const int left = S - 1 - row0;                   // (rows that do not exist repeat the last one)
     const int64_t at = (off0 + row0) * q_row_bytes + (int64_t)h * ROWB;
 #pragma unroll
@@ -410,13 +418,14 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const int coff[2] = {cols_tile + either_cols_offset(lane, 0), cols_tile + either_cols_offset(lane, 1)};
   f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds + XCH + kg * 4096) + lane;
 
-  int rt = issue_rt, stage = 1;
-  if (keys_role && it0 < it1) issue_tile(0);
-  for (int it = it0; it < it1; ++it) {
+  Place now = next;
+  int stage = 1;
+  if (keys_role && count > 0) issue_tile(0);
+  for (int it = 0; it < count; ++it) {
     stage ^= 1;
     const char* tile = lds + stage * (2 * TILE);
-    const int row0 = rs + rt * kTileRows;
-    if (--rt < 0) rt = ntile - 1;
+    const int row0 = rs + now.rt * kTileRows;
+    advance(now);
     // tile `it` has landed, and everyone has finished tile it-1
     if (keys_role) wait_vmcnt<0>();
     lds_barrier();
@@ -434,7 +443,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
         x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
             *reinterpret_cast<const bf16x8_t*>(tile + roff[i & 1] + rows_read_imm<D>(i)), op[i], x, 0, 0, 0);
     }
-    if (keys_role && it + 1 < it1) issue_tile(stage ^ 1);
+    if (keys_role && it + 1 < count) issue_tile(stage ^ 1);
     float val[16];
     if (busy && !keys_role) {
 #pragma unroll
