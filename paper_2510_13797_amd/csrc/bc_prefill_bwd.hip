@@ -72,18 +72,19 @@ struct BwdParams {
 // dq kernel
 // ---------------------------------------------------------------------------
 // The forward's walk with the same workgroups: four waves, 32 query rows of one head each.  Its registers let two
-// workgroups share a compute unit, so there is LDS for a fourth tile (16 trajectories of 8688 rows 1.131 -> 1.071 ms under
-// the profiler; a fifth gives nothing more, and the forward loses its third workgroup to a fourth: 0.70 -> 0.81 ms) and, before
+// workgroups share a compute unit, so there is LDS for five tiles - one by columns, the next by rows, two on their way and one
+// that is asked for - (the forward loses its third workgroup to a fourth: 0.70 -> 0.81 ms) and, before
 // the walk, for the rows of all waves: with those through LDS and Delta from whole rows a pass of three short
 // trajectories takes 72.8 us instead of 75.4.  What is left in front of the first product, some 10,000 cycles, is
 // mostly the first touch of the output's rows.
-constexpr int kDqStages = 4;
+// A third workgroup fits at d = 64 (16 trajectories of 7200 to 8700 rows, 14/2 heads: 623 -> 605 us with the passes below).
+constexpr int kDqStages = 5;
 template <int D, bool WIDE>
-__global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdParams p) {
+__global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_dq_kernel(BwdParams p) {
   constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
   constexpr int NLD = TILE / 1024 / kTileWaves;     // LDS-DMA instructions per wave, tile and tensor
   constexpr int RING = kDqStages * 2 * TILE, ROWS = (2 + 2 * kTileWaves) * TILE, LDS = RING > ROWS ? RING : ROWS;
-  constexpr int LOOK = kDqStages - 1;
+  constexpr int LOOK = kDqStages - 2;
   static_assert(LOOK == 3, "the counts of begin_pass");
   static_assert(LDS >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
   __shared__ __attribute__((aligned(1024))) char lds[LDS];
@@ -185,62 +186,95 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_dq_kernel(BwdP
   const int roff[2] = {either_rows_offset(lane), either_rows_offset(lane) ^ 128};
   const int coff[2] = {either_cols_offset(lane, 0), either_cols_offset(lane, 1)};
 
-  int stage = 0;
-  auto work = [&](int kt, auto masked) BC_INLINE {
-    constexpr bool MASKED = decltype(masked)::value;
-    const char* tile = lds + stage * (2 * TILE);
-    uint32_t see = ~0u;
-    if constexpr (MASKED) see = runs.visible((kt - runs.dense) * kTileRows, r, own, lane) >> (4 * half);
-    f32x16_t s = f32x16_t{0.f}, dp = f32x16_t{0.f};
-#pragma unroll
-    for (int i = 0; i < KS; ++i) {
-      const char* a = tile + roff[i & 1] + rows_read_imm<D>(i);
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(a), qb[i], s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(a + TILE), dob[i], dp, 0, 0, 0);
-    }
-    if (kt + LOOK < NT) issue_tile(stage >= 1 ? stage - 1 : kDqStages - 1);
-    float ds[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      ds[e] = fast_exp2(fmaf(s[e], p.qscale, -lse2)) * (dp[e] - delta);
-      if constexpr (MASKED) ds[e] = keep_if_visible(ds[e], see, e);
-    }
-    // dQ^T += K^T . dS^T
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      bf16x8_t hi, lo;
-      split8(ds + 8 * k, hi, lo);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const bf16x8_t kc = cols_operand<D>(tile + coff[k], j, k);
-        dQ[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kc, hi, dQ[j], 0, 0, 0);
-        dQ[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kc, lo, dQ[j], 0, 0, 0);
-      }
-    }
+  // A pass forms dS of tile kt and adds the tile before it to dQ.  Its order is written out (step_fence(): nothing is moved across):
+  // the split of the tile before stands beside the scores' matrix instructions, exponentials and dS beside dQ's, and LDS operands
+  // are asked for several instructions ahead.  In one chain a tile - scores, dS, dQ - a wave left the matrix pipe idle for half of
+  // its time, and the compiler, left to itself, asks for an operand in front of the instruction that takes it and puts all vector
+  // work in one place (the same passes without the order: 1072 us as before).  16 trajectories of 8688 rows, 12/2 heads 1072 -> 1027 us
+  // under the profiler, at the power limit 15.2 -> 14.1 million cycles; three short ones 18.4 -> 17.4.
+  constexpr int SLOTS = 4 * NJ, PRE = 3;         // matrix instructions of a tile's dQ; steps that row operands are ahead
+  float ds[16];
+  Parts y;
+  auto col_of = [&](const char* tile, int n) BC_INLINE { return cols_operand<D>(tile + coff[n / NJ], n % NJ, n / NJ); };
+  auto step_dq = [&](const bf16x8_t& c, int m) BC_INLINE {        // dQ^T += K^T . dS^T: operand m / 2, part m % 2
+    const int n = m / 2;
+    dQ[n % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c, y.operand(m & 1, n / NJ), dQ[n % NJ], 0, 0, 0);
   };
+  auto split = [&](int g) BC_INLINE { y.split(g, ds[2 * g], ds[2 * g + 1]); };
+  int stage = 0;
+  auto next_stage = [&]() BC_INLINE { stage = stage + 1 == kDqStages ? 0 : stage + 1; };
   auto begin_pass = [&](int kt) BC_INLINE {
     if (kt + 2 < NT) wait_vmcnt<4 * NLD>();         // (the loads of the next two tiles may stay out)
     else if (kt + 1 < NT) wait_vmcnt<2 * NLD>();
     else wait_vmcnt<0>();
     lds_barrier();
+    // tile kt has landed, and everyone has finished tile kt - 2, whose stage is the one tile kt + LOOK goes into
+    if (kt + LOOK < NT) issue_tile(stage >= 2 ? stage - 2 : stage + kDqStages - 2);
   };
-  auto end_pass = [&]() BC_INLINE { stage = stage + 1 == kDqStages ? 0 : stage + 1; };
+  auto form_ds = [&](int kt, const char* tile, auto more, const char* before, auto masked) BC_INLINE {
+    constexpr bool MORE = decltype(more)::value, MASKED = decltype(masked)::value;      // MORE: there is a tile before
+    uint32_t see = ~0u;
+    if constexpr (MASKED) see = runs.visible((kt - runs.dense) * kTileRows, r, own, lane) >> (4 * half);
+    bf16x8_t rk[KS], rv[KS], c[2 * NJ];
+    f32x16_t s = f32x16_t{0.f}, dp = f32x16_t{0.f};
+    auto rows = [&](int i) BC_INLINE {
+      const char* a = tile + roff[i & 1] + rows_read_imm<D>(i);
+      rk[i] = *reinterpret_cast<const bf16x8_t*>(a);
+      rv[i] = *reinterpret_cast<const bf16x8_t*>(a + TILE);
+    };
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) rows(i);
+    step_fence();
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rk[i], qb[i], s, 0, 0, 0);
+      if (i + PRE < KS) rows(i + PRE);
+      if constexpr (MORE) {
+#pragma unroll
+        for (int g = i * 8 / KS; g < (i + 1) * 8 / KS; ++g) split(g);
+      }
+      step_fence();
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rv[i], dob[i], dp, 0, 0, 0);
+      if (MORE && i >= KS - NJ) c[i - KS + NJ] = col_of(before, i - KS + NJ);
+      step_fence();
+    }
+#pragma unroll
+    for (int m = 0; m < SLOTS; ++m) {
+      if constexpr (MORE) {
+        step_dq(c[m / 2], m);
+        if (m % 2 == 0 && m / 2 + NJ < 2 * NJ) c[m / 2 + NJ] = col_of(before, m / 2 + NJ);
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e)               // (the scores are there behind the second instruction)
+        if (m == 2 + e * (SLOTS - 3) / 15) {
+          ds[e] = fast_exp2(fmaf(s[e], p.qscale, -lse2)) * (dp[e] - delta);
+          if constexpr (MASKED) ds[e] = keep_if_visible(ds[e], see, e);
+          asm volatile("" : "+v"(ds[e]));        // (worked out here and not behind the next barrier)
+        }
+      step_fence();
+    }
+  };
 
-  int kt = 0;
-  for (const int nd = min(runs.dense, ntw); kt < nd; ++kt) {
-    begin_pass(kt);
-    work(kt, std::false_type{});
-    end_pass();
-  }
-  for (; kt < ntw; ++kt) {
-    begin_pass(kt);
-    work(kt, std::true_type{});
-    end_pass();
+  begin_pass(0);
+  int kt = 1;
+  if (ntw > 0) {
+    form_ds(0, lds, std::false_type{}, lds, std::true_type{});       // (the words of a dense tile have all bits set)
+    auto pass = [&](auto masked) BC_INLINE {
+      const char* before = lds + stage * (2 * TILE);
+      next_stage();
+      begin_pass(kt);
+      form_ds(kt, lds + stage * (2 * TILE), std::true_type{}, before, masked);
+    };
+    for (const int nd = min(runs.dense, ntw); kt < nd; ++kt) pass(std::false_type{});
+    for (; kt < ntw; ++kt) pass(std::true_type{});
+#pragma unroll
+    for (int g = 0; g < 8; ++g) split(g);
+#pragma unroll
+    for (int m = 0; m < SLOTS; ++m) step_dq(col_of(lds + stage * (2 * TILE), m / 2), m);
   }
   for (; kt < NT; ++kt) {
+    next_stage();
     begin_pass(kt);
-    if (kt + LOOK < NT) issue_tile(stage >= 1 ? stage - 1 : kDqStages - 1);
-    end_pass();
   }
   lds_barrier();          // the tile stages are free: the epilogue reuses LDS
   if (ntw == 0) return;

@@ -309,6 +309,23 @@ __device__ __forceinline__ void split8(const float* x, bf16x8_t& hi, bf16x8_t& l
   lo = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
+// The same pair by pair, for code that spreads the work over other instructions: a lane's 16 values of a 32x32 product as the two parts of
+// the operands of the next one.
+struct Parts {
+  uint32_t h[8], l[8];
+  __device__ __forceinline__ void split(int n, float a, float b) {
+    h[n] = pack2_bf16(a, b);
+    l[n] = pack2_bf16(a - __uint_as_float(h[n] << 16), b - __uint_as_float(h[n] & 0xffff0000u));
+    asm volatile("" : "+v"(h[n]), "+v"(l[n]));        // (worked out here and not where they are used)
+  }
+  __device__ __forceinline__ bf16x8_t operand(int part, int k) const {       // values 8 * k ..
+    const uint32_t* w = (part ? l : h) + 4 * k;
+    return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+  }
+};
+// Between two steps of code whose order is written out.
+__device__ __forceinline__ void step_fence() { __builtin_amdgcn_sched_barrier(0); }
+
 // Half the columns (pass 0 or 1) of a wave's 32 x D results (accumulator layout: lane l holds
 // columns 32*j + 8*i + 4*(l/32) .. +3 of row l%32) -> LDS -> bursts of D/2 floats per row.
 // row(t): which row of `base` row t goes to, or -1.  Written once, not read again by the launch: streaming.
