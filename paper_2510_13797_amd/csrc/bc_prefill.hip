@@ -27,7 +27,7 @@
 //  - 32x32x16 instead of 16x16x32: half the operand reads per product, and vector work of other waves
 //    fits beside it (a loop of MFMA and FMA bursts, two waves per SIMD, six FMA per 32x32x16 or three per
 //    16x16x32: 1.01 against 1.29 times the MFMA time alone);
-//  - 152 registers, three waves per SIMD: with work of neighbouring tiles interleaved by hand inside a
+//  - at most 168 registers, three waves per SIMD: with work of neighbouring tiles interleaved by hand inside a
 //    wave and two waves per SIMD the same loop took 0.80 ms (higher matrix load, lower clock);
 //  - operands of a tile at one register plus constants, no bank conflicts (bc_prefill_tiles.h);
 //  - loads asked for behind the scores' MFMAs, their addresses from a cursor, and prompt and beacon
@@ -196,8 +196,23 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
                (((pe[8] + pe[9]) + (pe[10] + pe[11])) + ((pe[12] + pe[13]) + (pe[14] + pe[15])));
       }
     };
+    // The order of a pass is written out (step_fence(): nothing is moved across), LDS operands are asked for several instructions
+    // ahead and not, as the compiler has it, in front of the instruction that takes them (three short trajectories 14.8 -> 14.2 us;
+    // 27,109 rows of 32/8 heads with the half-precision form 389 -> 385; 16 trajectories of 8688 rows, at the power limit, take what
+    // they took).
+    bf16x8_t r[KS], c[2 * NJ];
+    auto col_of = [&](int n) BC_INLINE { return cols_operand<D>(tile + voff, n % NJ, n / NJ); };
+#pragma unroll
+    for (int i = 0; i < KS; ++i) r[i] = *reinterpret_cast<const bf16x8_t*>(tile + koff + rows_read_imm<D>(i));
+    step_fence();
     {
-      const f32x16_t s = scores(tile + koff);
+      f32x16_t s = f32x16_t{0.f};
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i], qb[i], s, 0, 0, 0);
+        if (i >= KS - NJ) c[i - KS + NJ] = col_of(i - KS + NJ);
+        step_fence();
+      }
       // the next loads, behind the scores' matrix instructions: at the head of the pass the four
       // waves' sixteen instructions stood in front of all matrix work
       if (kt + 2 < NT) issue_tile(stage >= 1 ? stage - 1 : kTileStages - 1);
@@ -220,21 +235,31 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
     }
     l_run += psum;
     // O^T += V^T . P^T ; V^T through the transposing LDS read
+    if constexpr (HALF) {
+      step_fence();
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      bf16x8_t ph, pl;
-      if constexpr (HALF) ph = __builtin_bit_cast(bf16x8_t, make_uint4(h16[4 * s], h16[4 * s + 1], h16[4 * s + 2], h16[4 * s + 3]));
-      else split8(pe + 8 * s, ph, pl);
+      for (int n = 0; n < 2 * NJ; ++n) {
+        const uint32_t* w = h16 + 4 * (n / NJ);
+        O[n % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(pf_f16x8_t, c[n]),
+                                                           __builtin_bit_cast(pf_f16x8_t, make_uint4(w[0], w[1], w[2], w[3])),
+                                                           O[n % NJ], 0, 0, 0);
+        if (n + NJ < 2 * NJ) c[n + NJ] = col_of(n + NJ);
+        step_fence();
+      }
+    } else {
+      Parts y;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const bf16x8_t av = cols_operand<D>(tile + voff, j, s);
-        if constexpr (HALF) {
-          O[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(pf_f16x8_t, av),
-                                                        __builtin_bit_cast(pf_f16x8_t, ph), O[j], 0, 0, 0);
-        } else {
-          O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ph, O[j], 0, 0, 0);
-          O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pl, O[j], 0, 0, 0);
-        }
+      for (int g = 0; g < 4; ++g) y.split(g, pe[2 * g], pe[2 * g + 1]);
+      step_fence();
+#pragma unroll
+      for (int m = 0; m < 4 * NJ; ++m) {
+        const int n = m / 2;
+        O[n % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c[n], y.operand(m & 1, n / NJ), O[n % NJ], 0, 0, 0);
+        if (m % 2 == 0 && n + NJ < 2 * NJ) c[n + NJ] = col_of(n + NJ);
+#pragma unroll
+        for (int g = 4; g < 8; ++g)
+          if (m == (g - 4) * NJ / 2) y.split(g, pe[2 * g], pe[2 * g + 1]);
+        step_fence();
       }
     }
   };
