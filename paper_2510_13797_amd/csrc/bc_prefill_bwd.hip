@@ -16,7 +16,7 @@
 //                response tokens  -> only the rows up to the end of their window (masked band)
 //              so the dense part of the work is spent on the ~P + S/(c+1) keys every row sees.
 //              A dense block is long (every later row x every head); it is cut into parts (see
-//              dense_parts), which write partial dK/dV to the workspace, and a third kernel adds
+//              KeyParts), which write partial dK/dV to the workspace, and a third kernel adds
 //              them in a fixed order.  Response blocks are cut only where the chip is not full (band_splits)
 //              and store their result directly otherwise.
 //
@@ -52,9 +52,10 @@ struct BwdParams {
   float* dk;
   float* dv;
   float* stat;          // [Hq][total_rows][2]: lse*log2(e), Delta
-  float* part;          // [splits][2][total_rows][Hkv][D]: dk, dv partials of the dense key blocks
+  float* part;          // splits * 2 * total_rows rows [Hkv][D]: partial dk, dv (see KeyParts)
   int32_t D;            // head dimension (the reduction kernel reads it; the others are templates)
-  int32_t splits;       // most workgroups that share a dense key block (see dense_parts)
+  int32_t splits;       // rows of partial sums there is room for, per row, of dk and of dv
+  int32_t most;         // most workgroups that share a dense key block
   int32_t band;         // workgroups that share a response block (see band_splits), at most `splits`
   int64_t total_rows;
   int32_t Hq, Hkv, g;
@@ -301,15 +302,43 @@ __device__ __forceinline__ void lds_dma4_s(uint32_t lane_offset, uint64_t base, 
                : : "s"(lds_addr), "v"(lane_offset), "s"(base) : "memory");
 }
 
-// Parts each of a trajectory's nd dense key blocks is cut into: as many as run at once if all trajectories are
-// like this one, at most the p.splits there is room for, and two where the heads of a group make the chain long.
-// One part stores its result directly.  (The host does not know how many keys are dense, and reckons with one in
-// eight.  Cut by that alone, 4 uncompressed trajectories of 2200 rows, 8/8 heads, had six parts of 1120 blocks and
-// took 376 us, 318 whole.)
-__device__ __forceinline__ int dense_parts(const BwdParams& p, int nd) {
-  const int blocks = min(max(nd, 1), kDkvAtOnce) * p.npairs, n = (kDkvAtOnce + blocks - 1) / blocks;
-  return min(max(n, p.g > 1 ? 2 : 1), p.splits);
-}
+// The key blocks of a trajectory and what they are cut into.  Its dense blocks: as many parts as run at once if all trajectories are
+// like this one, and two where the heads of a group make the chain long.  One part stores its result directly.  (The host does not
+// know how many keys are dense, and reckons with one in eight.  Cut by that alone, 4 uncompressed trajectories of 2200 rows,
+// 8/8 heads, had six parts of 1120 blocks and took 376 us, 318 whole.)
+// The partial sums lie by key, not by row: part for part the dense keys' dk, then their dv, behind them the same of the response
+// tokens where their blocks are cut.  A trajectory has room for `splits` sums of every row, and the fewer of its rows are dense the more
+// parts fit: up to p.most of at least eight tiles and some 18 MB together.  us a pass, at most eight parts and sixteen: three trajectories of
+// 336 to 795 rows, a third of them dense, 12/2 heads 65.1, 60.5; one of 2100 rows, ratio 16, 99.7, 80.1; three of 720 rows, ratio 32, d = 64, 50.1,
+// 45.9; with 27 MB the first takes 62.5, with 12 64.3, with at most twelve parts 61.7.
+constexpr float kPartBytes = 18e6f;
+struct KeyParts {
+  int prompt, beacons, tokens;       // keys: treated as dense-causal, complete windows' beacons, response rows that are no beacons
+  int prompt_blocks, dense_blocks;
+  int parts;                         // of a dense block
+  __device__ __forceinline__ KeyParts(const BwdParams& p, const Trajectory& t, const WindowStride& ws) {
+    prompt = ws.c > 0 ? min(t.P, t.rows) : t.rows;               // without compression every row behaves like a prompt row
+    beacons = ws.c > 0 ? (int)window_of(ws, (uint32_t)(t.rows - prompt)) : 0;
+    tokens = t.rows - prompt - beacons;
+    prompt_blocks = (prompt + kDkvKeys - 1) / kDkvKeys;
+    dense_blocks = prompt_blocks + (beacons + kDkvKeys - 1) / kDkvKeys;
+    const int blocks = min(max(dense_blocks, 1), kDkvAtOnce) * p.npairs, n = (kDkvAtOnce + blocks - 1) / blocks;
+    int most = p.splits;
+    if (p.most > p.splits) {         // (room for p.splits there always is: the tokens have p.band <= p.splits)
+      const int room = (p.splits * t.rows - (p.band > 1 ? p.band * tokens : 0)) / max(prompt + beacons, 1);
+      const int few = (int)(kPartBytes / (8.f * p.D * p.npairs * max(prompt + beacons, 1)));
+      most = max(most, min(min(p.most, min(room, few)), t.rows / kTileRows * p.g / 8));
+    }
+    parts = min(max(n, p.g > 1 ? 2 : 1), most);
+  }
+  // first row of sum `of` of the dense keys (the tokens) of a trajectory; of: 2 * part + (0 for dk, 1 for dv)
+  __device__ __forceinline__ int64_t dense_row(const BwdParams& p, int64_t off0, int of) const {
+    return 2 * p.splits * off0 + (int64_t)of * (prompt + beacons);
+  }
+  __device__ __forceinline__ int64_t token_row(const BwdParams& p, int64_t off0, int of) const {
+    return dense_row(p, off0, 2 * parts) + (int64_t)of * tokens;
+  }
+};
 
 // The two waves of a pair share 32 keys.  One forms the scores and A and adds dO^T.A to dV, the other
 // forms dA, takes A through LDS, and adds Q^T.dS to dK: three of the six products each, and half of the
@@ -331,26 +360,22 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const Trajectory traj = trajectory(p, b);
   const int64_t off0 = traj.off0;
   const int S = traj.rows;
-  const int P0 = traj.P;
   const WindowStride ws = window_stride(traj.c, S);
   const int c = ws.c, cp1 = ws.stride;
-  // key blocks of this (trajectory, KV head): prompt keys | gathered beacons | response rows.
-  // Without compression every row behaves like a prompt row (plain causal).
-  const int Pk = c > 0 ? min(P0, S) : S;                        // keys treated as dense-causal
-  const int nresp = S - Pk;                                     // response rows (tokens and beacons)
-  const int nbeac = c > 0 ? (int)window_of(ws, (uint32_t)nresp) : 0;   // complete windows
-  const int NPB = (Pk + kDkvKeys - 1) / kDkvKeys, NBB = (nbeac + kDkvKeys - 1) / kDkvKeys;
-  const int NLB = (nresp + kDkvKeys - 1) / kDkvKeys;
+  // key blocks of this (trajectory, KV head): prompt keys | gathered beacons | response rows
+  const KeyParts cut(p, traj, ws);
+  const int Pk = cut.prompt, nresp = S - Pk, nbeac = cut.beacons;
+  const int NPB = cut.prompt_blocks, nd = cut.dense_blocks, NLB = (nresp + kDkvKeys - 1) / kDkvKeys;
   // The dense blocks (prompt keys, beacons) stream every later row of every head; the tiles of each
   // are dealt to `parts` workgroups, whose partial sums another kernel adds in a fixed order.
   // The short response blocks are cut where the chip is not full; a block of one part stores its result directly.
-  const int nd = NPB + NBB, dense = dense_parts(p, nd);
+  const int dense = cut.parts;
   const int at = (int)blockIdx.y - nd * dense;                  // place among the response blocks' parts
   const int parts = at < 0 ? dense : p.band;
   const int of = at < 0 ? (int)blockIdx.y : at;
   const int blk = of / parts + (at < 0 ? 0 : nd), split = parts > 1 ? of % parts : -1;
   if (blk >= nd + NLB) return;
-  const int kind = blk < NPB ? 0 : blk < NPB + NBB ? 1 : 2;
+  const int kind = blk < NPB ? 0 : blk < nd ? 1 : 2;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -360,24 +385,28 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
 
   // this lane's key, the rows the block streams, and the rows the key is seen from: [jkey, last]
   int jkey, last;
+  int sum_at;          // the key's place among the partial sums of its kind
   bool key_ok;
   int rs, re;          // first and last streamed row
   if (kind == 0) {
     const int j0 = blk * kDkvKeys;
     jkey = j0 + 32 * kg + col; key_ok = jkey < Pk;
+    sum_at = jkey;
     rs = j0; re = S - 1; last = re;
   } else if (kind == 1) {
     const int m0 = (blk - NPB) * kDkvKeys, m = m0 + 32 * kg + col;
     key_ok = m < nbeac; jkey = Pk + m * cp1 + c;
+    sum_at = Pk + m;
     rs = Pk + m0 * cp1 + c; re = S - 1; last = re;
   } else {
-    const int j0 = Pk + (blk - NPB - NBB) * kDkvKeys;
+    const int j0 = Pk + (blk - nd) * kDkvKeys;
     jkey = j0 + 32 * kg + col; key_ok = jkey < S;
     const int jl = min(j0 + kDkvKeys - 1, S - 1);
     const int wl = (int)window_of(ws, (uint32_t)(jl - Pk));
     rs = j0; re = min(S - 1, Pk + (wl + 1) * cp1 - 1);      // through the closing beacon
     const uint32_t u = (uint32_t)(min(jkey, S - 1) - Pk), w = window_of(ws, u);
     if ((int)(u - w * (uint32_t)cp1) == c) key_ok = false;  // beacon rows belong to the beacon blocks
+    sum_at = (int)(u - w);
     last = min(re, Pk + ((int)w + 1) * cp1 - 1);            // a response token: inside its own window
   }
   if (!key_ok) { jkey = rs; last = -1; }       // loads stay in range; seen from no row
@@ -523,65 +552,70 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   lds_barrier();
 
   // every key row is owned by exactly one lane column of one block: plain stores
-  float* base = keys_role ? p.dk : p.dv;
-  if (split >= 0) base = p.part + (int64_t)(2 * split + (keys_role ? 0 : 1)) * p.total_rows * p.Hkv * D;
+  float* base = (keys_role ? p.dk : p.dv) + off0 * p.Hkv * D;
+  if (split >= 0) {
+    const int of = 2 * split + (keys_role ? 0 : 1);
+    base = p.part + (kind == 2 ? cut.token_row(p, off0, of) : cut.dense_row(p, off0, of)) * p.Hkv * D;
+  }
   float* my = reinterpret_cast<float*>(lds + wave * (32 * (D / 2) * 4));
-  const int key_row = key_ok ? jkey : -1;
+  const int key_row = !key_ok ? -1 : split >= 0 ? sum_at : jkey;
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass)
-    store_rows<D>(my, acc, keys_role ? p.scale : 1.0f, pass, lane, base + (off0 * p.Hkv + kvh) * D, p.Hkv * D,
+    store_rows<D>(my, acc, keys_role ? p.scale : 1.0f, pass, lane, base + kvh * D, p.Hkv * D,
                   [&](int t) { return __shfl(key_row, t, 64); });
 }
 
 // Sum of the partials of the dense keys (prompt rows and beacons) and, where the response blocks were cut too, of the
-// response rows, in split order.  Rows of blocks in one part were written directly.  grid: x = trajectory, y = blocks that share its dense keys (a thread for every
-// 16 bytes of every row, which had to find the row's trajectory and whether it is dense, took 47 us instead
+// response tokens, in split order.  Rows of blocks in one part were written directly.  grid: x = trajectory, y = blocks that share its
+// keys (a thread for every 16 bytes of every row, which had to find the row's trajectory and whether it is dense, took 47 us instead
 // of 16 for 16 trajectories of 8688 rows: one row in twelve is dense).
 __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
   const int b = blockIdx.x;
   const Trajectory traj = trajectory(p, b);
   const int64_t off0 = traj.off0;
-  const int S = traj.rows;
-  if (S <= 0) return;
-  const WindowStride ws = window_stride(traj.c, S);
-  const int Pk = ws.c > 0 ? min(traj.P, S) : S;
-  const int nbeac = ws.c > 0 ? (int)window_of(ws, (uint32_t)(S - Pk)) : 0;
-  const int parts = dense_parts(p, (Pk + kDkvKeys - 1) / kDkvKeys + (nbeac + kDkvKeys - 1) / kDkvKeys);
-  if (parts == 1 && p.band == 1) return;
+  if (traj.rows <= 0) return;
+  const WindowStride ws = window_stride(traj.c, traj.rows);
+  const KeyParts cut(p, traj, ws);
+  const int ndense = cut.prompt + cut.beacons;
+  const int first = cut.parts > 1 ? 0 : ndense, end = ndense + (p.band > 1 ? cut.tokens : 0);      // dense keys, then tokens
   const int per_row = p.Hkv * (p.D / 4);         // 16-byte units
-  const bool every_row = p.band > 1;
-  const int64_t units = (int64_t)(every_row ? S : Pk + nbeac) * per_row;
-  const int64_t plane = p.total_rows * p.Hkv * p.D;
+  const int64_t units = (int64_t)(end - first) * per_row;
   for (int64_t i = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; i < units; i += (int64_t)gridDim.y * blockDim.x) {
-    const int n = (int)(i / per_row);            // dense key or row, the row, the place of the unit
-    int j = n, sum = parts;
-    if (every_row) {
-      const uint32_t u = (uint32_t)(n - Pk);
-      if (n >= Pk && (int)(u - window_of(ws, u) * (uint32_t)ws.stride) != ws.c) sum = p.band;
-      if (sum == 1) continue;
-    } else if (n >= Pk) {
-      j = Pk + (n - Pk) * ws.stride + ws.c;
+    const int k = units <= 0xffffffffll ? (int)((uint32_t)i / (uint32_t)per_row) : (int)(i / per_row);
+    const int n = first + k;                     // key, its row, the place of the unit
+    const int unit = (int)(i - (int64_t)k * per_row) * 4;
+    int row, sum, plane;
+    int64_t at;
+    if (n < ndense) {
+      row = n < cut.prompt ? n : cut.prompt + (n - cut.prompt) * ws.stride + ws.c;
+      sum = cut.parts; plane = ndense; at = cut.dense_row(p, off0, 0) + n;
+    } else {
+      const int m = n - ndense;
+      row = cut.prompt + m + m / ws.c;
+      sum = p.band; plane = cut.tokens; at = cut.token_row(p, off0, 0) + m;
     }
-    const int64_t at = ((off0 + j) * per_row + (i - (int64_t)n * per_row)) * 4;
+    const float* from = p.part + at * p.Hkv * p.D + unit;
+    const int64_t step = (int64_t)plane * p.Hkv * p.D;
     f32x4_t sk = f32x4_t{0.f, 0.f, 0.f, 0.f}, sv = sk;
-    // four parts on their way at a time, also of the last three
-    for (int s0 = 0; s0 < sum; s0 += 4) {
-      f32x4_t xk[4], xv[4];
+    // eight parts on their way at a time, also of the last seven
+    for (int s0 = 0; s0 < sum; s0 += 8) {
+      f32x4_t xk[8], xv[8];
 #pragma unroll
-      for (int n4 = 0; n4 < 4; ++n4) {
-        const float* from = p.part + (int64_t)(2 * min(s0 + n4, sum - 1)) * plane + at;
-        xk[n4] = *reinterpret_cast<const f32x4_t*>(from);
-        xv[n4] = *reinterpret_cast<const f32x4_t*>(from + plane);
+      for (int e = 0; e < 8; ++e) {
+        const float* x = from + 2 * min(s0 + e, sum - 1) * step;
+        xk[e] = *reinterpret_cast<const f32x4_t*>(x);
+        xv[e] = *reinterpret_cast<const f32x4_t*>(x + step);
       }
 #pragma unroll
-      for (int n4 = 0; n4 < 4; ++n4) {
-        if (s0 + n4 >= sum) break;
-        sk += xk[n4];
-        sv += xv[n4];
+      for (int e = 0; e < 8; ++e) {
+        if (s0 + e >= sum) break;
+        sk += xk[e];
+        sv += xv[e];
       }
     }
-    *reinterpret_cast<f32x4_t*>(p.dk + at) = sk;
-    *reinterpret_cast<f32x4_t*>(p.dv + at) = sv;
+    const int64_t to = (off0 + row) * p.Hkv * p.D + unit;
+    *reinterpret_cast<f32x4_t*>(p.dk + to) = sk;
+    *reinterpret_cast<f32x4_t*>(p.dv + to) = sv;
   }
 }
 
@@ -592,15 +626,16 @@ static void launch_bwd(const BwdParams& p, bool wide, dim3 dq_grid, dim3 dkv_gri
   prefill_bwd_dkv_kernel<D><<<dkv_grid, kTileWaves * 64, 0, hs>>>(p);
 }
 
-// Most workgroups that share a dense key block: what the workspace has room for, and dense_parts() chooses from.
+// Partial sums the workspace has room for, of every row: what KeyParts chooses from.
 // A dense block streams all later rows of all heads, a chain of up to g * rows/32 tiles, and there are few of
 // them: they are cut until as many as run at once (three per CU) are there, taking one key in eight for dense
 // (ratios and prompt lengths are on the device).  Backward of 6 trajectories, 14/2 heads, d = 64, 12,966 rows: two
 // parts 523 us, six 300; one trajectory of 6631 rows, 24/8 heads: 597, three 372; three short trajectories: 118,
 // six 62; more parts than that cost work (16 trajectories of 8688 rows: two 2.70 ms, three 2.66, six 2.82; 8 of
 // 3389 rows, 32/8 heads: 2.37, 2.40, 2.55).  Parts of fewer than eight tiles are not worth their partial sums.
+constexpr int kMostSplits = 8, kMostParts = 16;
 static int dense_splits(const bc_shape* shape, int64_t total_rows) {
-  constexpr int64_t kMost = 8;
+  constexpr int64_t kMost = kMostSplits;
   const int64_t blocks = total_rows * shape->Hkv / (8 * kDkvKeys) + 1;
   const int64_t tiles = total_rows / shape->B * (shape->Hq / shape->Hkv) / kTileRows;      // of a chain
   const int64_t n = (kDkvAtOnce + blocks - 1) / blocks, least = shape->Hq > shape->Hkv ? 2 : 1;
@@ -653,6 +688,7 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.stat = static_cast<float*>(workspace);
   p.part = p.stat + stat_floats(shape, total_rows);
   p.splits = dense_splits(shape, total_rows);
+  p.most = p.splits == kMostSplits ? kMostParts : p.splits;       // (more parts only where the chip is not full)
   p.band = band_splits(shape, total_rows, p.splits);
   p.total_rows = total_rows;
   p.D = shape->d;
@@ -665,9 +701,15 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.tiling = head_tiling(p.g);
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const int key_blocks = (max_rows + kDkvKeys - 1) / kDkvKeys;
-  // key blocks: at most `key_blocks` dense-causal blocks + the gathered beacons + `key_blocks` response blocks
+  // Key blocks of a trajectory: at most `key_blocks` of response rows, and of prompt keys and gathered beacons, which are rows of it
+  // too, one more.  The parts of the latter together are at most two each, or as many workgroups as run at once and the last of each
+  // block's (see KeyParts).  A workgroup that finds no part costs 1 us in a thousand.
+  const int dense_blocks = key_blocks + 1;
+  const int64_t at_once = kDkvAtOnce / p.npairs + dense_blocks, all = (int64_t)dense_blocks * p.most;
+  const int64_t least = (int64_t)dense_blocks * (p.most < 2 ? p.most : 2);
+  const int64_t dense_parts = all < at_once ? all : at_once < least ? least : at_once;
   const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
-  const dim3 dkv_grid(p.pstride, (2 * key_blocks + 2) * p.splits + key_blocks * p.band);
+  const dim3 dkv_grid(p.pstride, (int)(dense_parts + (int64_t)key_blocks * p.band));
   const bool wide = rows_span_4gb(max_rows, shape);
   if (shape->d == 128) launch_bwd<128>(p, wide, dq_grid, dkv_grid, hs);
   else launch_bwd<64>(p, wide, dq_grid, dkv_grid, hs);

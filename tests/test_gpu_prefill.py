@@ -494,6 +494,28 @@ def test_prefill_bwd_response_blocks_in_parts(dev, P, R, Hq, Hkv, d):
     test_prefill_bwd_key_blocks_and_their_parts_at_the_edges(dev, P, R, Hq, Hkv, d)
 
 
+@pytest.mark.parametrize("P,R,c,Hq,Hkv,d", [(5, 900, 32, 12, 2, 128), (130, 500, 1, 6, 1, 128), (60, 640, 0, 6, 1, 64), (64, 1100, 300, 8, 1, 64)])
+def test_prefill_bwd_as_many_parts_as_there_is_room_for(dev, P, R, c, Hq, Hkv, d):
+    # one trajectory on an idle chip: few dense keys (sixteen parts), two thirds and all of the rows dense, a last window that stays open;
+    # workspace and results hold NaN before the call
+    import torch
+    from paper_2510_13797_amd import bc
+    pw = W.PrefillWorkload("pfb_room", 73, 1, Hq, Hkv, d, "bf16", np.array([P], np.int32), np.array([R], np.int32), np.array([c], np.int32))
+    qkv, dos = [pw.qkv(0)], [pw.dout(0)]
+    off, total = np.array([0, pw.S[0]], np.int64), int(pw.S[0])
+    q, k, v, do = (bc.to_device(x[0], "bf16", dev) for x in (*zip(*qkv), dos))
+    out, lse = bc.prefill_attn(q, k, v, off, pw.P, pw.c, Hq, Hkv, d, pw.scale)
+    dq, dk, dv = (torch.full(shape, float("nan"), device=dev) for shape in ((total, Hq, d), (total, Hkv, d), (total, Hkv, d)))
+    shape = bc.bc_shape(1, Hq, Hkv, d, bc.BC_BF16, pw.scale)
+    ws = torch.full((bc.bc_prefill_bwd_workspace_bytes(shape, total) // 4,), float("nan"), device=dev)
+    tables = [torch.from_numpy(x).to(dev) for x in (off, pw.P, pw.c)]
+    st = bc.bc_prefill_attn_bwd(shape, *(t.data_ptr() for t in (q, k, v, out, lse, do, *tables)), total, total,
+                                *(t.data_ptr() for t in (dq, dk, dv, ws)), ws.numel() * 4, None)
+    assert st == bc.BC_OK
+    torch.cuda.synchronize()
+    _check_bwd(pw, qkv, dos, off, dq.cpu().numpy(), dk.cpu().numpy(), dv.cpu().numpy(), 0)
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_prefill_bwd_addresses_beyond_32_bits(dev, d):
     # as above for the gradients: 512 heads make rows of 128 or 64 KB, so a stated 4 GB of K rows needs
