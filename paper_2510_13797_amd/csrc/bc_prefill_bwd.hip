@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_
     store_rows<D>(my, dQ, p.scale, pass, lane, p.dq + ((off0 + rw0) * p.Hq + kvh * p.g + head) * D, p.Hq * D,
                   [&](int t) { return rw0 + t <= rw1 ? t : -1; });
   if (rw0 + col <= rw1)
-    p.stat[((int64_t)(kvh * p.g + head) * p.total_rows + off0 + r) * 2 + half] = half ? delta : lse2;
+    p.stat[((int64_t)(kvh * p.g + head) * p.total_rows + off0 + r) * 2 + half] = half ? -delta : lse2;
 }
 
 // ---------------------------------------------------------------------------
@@ -349,8 +349,8 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
   constexpr int RING = kDkvStages * 2 * TILE, STAT = RING, XCH = RING + kDkvStages * 256;
   constexpr int OUT = kTileWaves * 32 * (D / 2) * 4;
-  constexpr int LDS = XCH + 2 * 4096;
-  static_assert(LDS >= OUT, "the gradient tiles fit");
+  constexpr int KEYS_AT = XCH + 2 * 4096, LDS = KEYS_AT + kTileWaves * 768;
+  static_assert(KEYS_AT >= OUT, "the gradient tiles fit");
   __shared__ __attribute__((aligned(1024))) char lds[LDS];
   // grid: x = (trajectory, KV head), y = key block; the long dense blocks of every trajectory
   // are dispatched before any short one
@@ -479,76 +479,116 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const int rows_tile = keys_role ? TILE : 0, cols_tile = TILE - rows_tile;     // Q or dO by rows, the other by columns
   const int roff[2] = {rows_tile + either_rows_offset(lane), rows_tile + (either_rows_offset(lane) ^ 128)};
   const int coff[2] = {cols_tile + either_cols_offset(lane, 0), cols_tile + either_cols_offset(lane, 1)};
+  const int soff = STAT + (keys_role ? 128 : 0) + 16 * half;
   f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds + XCH + kg * 4096) + lane;
+  // the lane's key, the last row it is seen from and where its sums go: in LDS, every register of the loop is in use
+  int* kept_key = reinterpret_cast<int*>(lds + KEYS_AT + wave * 768) + lane;
+  kept_key[0] = jkey;
+  kept_key[64] = last;
+  kept_key[128] = !key_ok ? -1 : split >= 0 ? sum_at : jkey;
+  constexpr int EARLY = D == 64 ? NJ : 0;       // column operands the keys' waves ask for in front of the second barrier
+  constexpr int SLOTS = 4 * NJ, PRE = KS < 8 ? KS : 8;        // matrix instructions of a column product; steps row operands are ahead
 
-  Place now = next;
-  int stage = 1;
-  if (keys_role && count > 0) issue_tile(0);
-  for (int it = 0; it < count; ++it) {
-    stage ^= 1;
-    const char* tile = lds + stage * (2 * TILE);
-    const int row0 = rs + now.rt * kTileRows;
-    advance(now);
-    // tile `it` has landed, and everyone has finished tile it-1
-    if (keys_role) wait_vmcnt<0>();
-    lds_barrier();
-    // a row tile that ends in front of the pair's first key, or starts behind the last row any of its
-    // keys is seen from, adds nothing here
-    const bool busy = row0 + kTileRows - 1 >= any_first && row0 <= any_last;
-    f32x16_t x = f32x16_t{0.f};
-    f32x4_t stat[4];         // log-sum-exp or Delta of the lane's rows
-    if (busy) {
-      const float* st = reinterpret_cast<const float*>(lds + STAT + stage * 256) + (keys_role ? 32 : 0) + 4 * half;
+  // The order of a pass is written out (step_fence(): nothing is moved across): LDS operands are asked for several instructions
+  // ahead, and both kinds of wave have a loop of their own.  Forward and gradients, us a pass: one trajectory of 2100 rows 80.1 -> 77.2, one of
+  // 300, 4/1 heads, 41.5 -> 40.0, three of 336 to 795 60.1 -> 59.3, eight of 1100 to 3300 778 -> 771; 16 of 8688, at the power limit, 3172
+  // and 3165.  All 168 registers are in use: one spilled into the loop waits for the tile's loads with its own (3200 -> 3330), and two
+  // workgroups a compute unit with one barrier a pass and tiles worked on two at a time took 1486 us in place of 1467 on the
+  // large batch.
+  auto passes = [&](auto keys) BC_INLINE {
+    constexpr bool KEYS = decltype(keys)::value;
+    Place now = next;
+    int stage = 1;
+    if (KEYS && count > 0) issue_tile(0);
+    for (int it = 0; it < count; ++it) {
+      stage ^= 1;
+      const char* tile = lds + stage * (2 * TILE);
+      const int row0 = rs + now.rt * kTileRows;
+      advance(now);
+      // tile `it` has landed, and everyone has finished tile it-1
+      if constexpr (KEYS) wait_vmcnt<0>();
+      lds_barrier();
+      // a row tile that ends in front of the pair's first key, or starts behind the last row any of its
+      // keys is seen from, adds nothing here
+      const bool busy = row0 + kTileRows - 1 >= any_first && row0 <= any_last;
+      f32x16_t x;              // scores, or dA - Delta: the sums of dA start at -Delta
+      bf16x8_t c[2 * NJ];
+      float val[16];           // A, or dS
+      auto col_of = [&](int n) BC_INLINE { return cols_operand<D>(tile + coff[n / NJ], n % NJ, n / NJ); };
+      if (busy) {
+        f32x4_t stat[4];       // log-sum-exp or -Delta of the lane's rows
+        auto stats = [&](int q) BC_INLINE { stat[q] = *reinterpret_cast<const f32x4_t*>(lds + soff + stage * 256 + 32 * q); };
+        bf16x8_t r[KS];
+        auto row_of = [&](int i) BC_INLINE { r[i] = *reinterpret_cast<const bf16x8_t*>(tile + roff[i & 1] + rows_read_imm<D>(i)); };
+        if constexpr (KEYS) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) stat[q] = *reinterpret_cast<const f32x4_t*>(st + 8 * q);
+          for (int q = 0; q < 4; ++q) {
+            stats(q);
 #pragma unroll
-      for (int i = 0; i < KS; ++i)
-        x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            *reinterpret_cast<const bf16x8_t*>(tile + roff[i & 1] + rows_read_imm<D>(i)), op[i], x, 0, 0, 0);
-    }
-    if (keys_role && it + 1 < count) issue_tile(stage ^ 1);
-    float val[16];
-    if (busy && !keys_role) {
+            for (int e = 0; e < 4; ++e) x[4 * q + e] = stat[q][e];
+          }
+        } else {
+          x = f32x16_t{0.f};
+        }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+        for (int i = 0; i < PRE; ++i) row_of(i);
+        step_fence();
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[4 * q + e] = fast_exp2(fmaf(x[4 * q + e], p.qscale, -stat[q][e]));
+        for (int i = 0; i < KS; ++i) {
+          x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i], op[i], x, 0, 0, 0);
+          if (i + PRE < KS) row_of(i + PRE);
+          if (!KEYS && i >= KS - 4) stats(i - KS + 4);
+          if (KEYS && i >= KS - EARLY) c[i - KS + EARLY] = col_of(i - KS + EARLY);
+          step_fence();
+        }
+        if constexpr (!KEYS) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) val[e] = fast_exp2(fmaf(x[e], p.qscale, -stat[e / 4][e % 4]));
+          if (row0 < all_first || row0 + kTileRows - 1 > all_last) {
+            const int from = kept_key[0] - row0, upto = kept_key[64] - row0;
+            const uint32_t mine = from >= 32 ? 0u : ~0u << max(from, 0);
+            const uint32_t past = upto < 0 ? 0u : upto >= 31 ? ~0u : (2u << upto) - 1u;
+            const uint32_t see = (mine & past) >> (4 * half);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) val[e] = keep_if_visible(val[e], see, e);
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            xch[64 * q] = f32x4_t{val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
+        }
       }
-      if (row0 < all_first || row0 + kTileRows - 1 > all_last) {
-        const int from = jkey - row0, upto = last - row0;
-        const uint32_t mine = from >= 32 ? 0u : ~0u << max(from, 0);
-        const uint32_t past = upto < 0 ? 0u : upto >= 31 ? ~0u : (2u << upto) - 1u;
-        const uint32_t see = (mine & past) >> (4 * half);
+      if (KEYS && it + 1 < count) issue_tile(stage ^ 1);
+      lds_barrier();       // A of tile `it` is there
+      if (!busy) continue;
+      if constexpr (KEYS) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) val[e] = keep_if_visible(val[e], see, e);
+        for (int q = 0; q < 4; ++q) {
+          const f32x4_t a = xch[64 * q];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) val[4 * q + e] = a[e] * x[4 * q + e];
+        }
       }
+      // dV^T += dO^T.A or dK^T += Q^T.dS
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        xch[64 * q] = f32x4_t{val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
-    }
-    lds_barrier();       // A of tile `it` is there
-    if (!busy) continue;
-    if (keys_role) {
+      for (int n = KEYS ? EARLY : 0; n < NJ; ++n) c[n] = col_of(n);
+      Parts y;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4_t a = xch[64 * q];
+      for (int g = 0; g < 4; ++g) y.split(g, val[2 * g], val[2 * g + 1]);
+      step_fence();
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[4 * q + e] = a[e] * (x[4 * q + e] - stat[q][e]);
-      }
-    }
-    // dV^T += dO^T.A or dK^T += Q^T.dS
+      for (int m = 0; m < SLOTS; ++m) {
+        const int n = m / 2;
+        acc[n % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c[n], y.operand(m & 1, n / NJ), acc[n % NJ], 0, 0, 0);
+        if (m % 2 == 0 && n + NJ < 2 * NJ) c[n + NJ] = col_of(n + NJ);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      bf16x8_t hi, lo;
-      split8(val + 8 * k, hi, lo);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const bf16x8_t rc = cols_operand<D>(tile + coff[k], j, k);
-        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rc, hi, acc[j], 0, 0, 0);
-        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rc, lo, acc[j], 0, 0, 0);
+        for (int g = 4; g < 8; ++g)
+          if (m == (g - 4) * NJ / 2) y.split(g, val[2 * g], val[2 * g + 1]);
+        step_fence();
       }
     }
-  }
+  };
+  if (keys_role) passes(std::true_type{});
+  else passes(std::false_type{});
   lds_barrier();
 
   // every key row is owned by exactly one lane column of one block: plain stores
@@ -558,7 +598,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
     base = p.part + (kind == 2 ? cut.token_row(p, off0, of) : cut.dense_row(p, off0, of)) * p.Hkv * D;
   }
   float* my = reinterpret_cast<float*>(lds + wave * (32 * (D / 2) * 4));
-  const int key_row = !key_ok ? -1 : split >= 0 ? sum_at : jkey;
+  const int key_row = kept_key[128];
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass)
     store_rows<D>(my, acc, keys_role ? p.scale : 1.0f, pass, lane, base + kvh * D, p.Hkv * D,
