@@ -25,15 +25,12 @@
 // into LDS by 16-byte LDS-DMA loads, in the order that serves row and column operands alike
 // (bc_prefill_tiles.h).
 //
-// What bounds both: matrix and vector issue of a SIMD that overlap only in part.  On 16 trajectories of 8688 rows
-// (12/2 heads, d = 128) the dkv kernel issues 1458 GFLOP of MFMA work in 1.60 ms (matrix pipe busy 48 % of the
-// cycles, a fifth of that together with vector work), the dq kernel 947 in 1.11 ms (44 %); a library product of
-// 16384^3 runs at 1.34 PFLOP/s here.  The forms before, 16x16x32 MFMA with 16 rows of two heads or 16 keys per wave
-// and tiles read at half rate by bank conflicts, took 1.24 and 1.83 ms: the dkv kernel read 128 KB of LDS per CU for
-// every 768 matrix cycles of a SIMD.  The dq kernel needs 209 registers (Q, dO and dQ of 32 rows), two waves per
-// SIMD; held to 168 it spilled in the tile loop.  A dkv tile is a chain of 3,700 cycles, alone on a compute unit or with two
-// neighbours.  Since these figures: dq rows and results through LDS whole rows at a time, tiles loaded by the waves that wait,
-// a whole forward and backward pass of that batch 3398 -> 3286 us (on one card; cards differ by 3 %).
+// What bounds both: the card's power limit on large launches, the chain of a tile's steps on small ones.  On 16 trajectories of 8688
+// rows (12/2 heads, d = 128) the dkv kernel issues 1458 GFLOP of MFMA work in 1.48 ms, the dq kernel 947 in 1.03 (under the profiler; both with the
+// matrix pipe half busy at 1.75 to 1.8 GHz; a loop of such products alone runs at 1.75 PFLOP/s and 1.75 GHz, with the operand reads and
+// vector work of the dq kernel at 1.3): fewer cycles give a lower clock and half of what they should.  The forms before, 16x16x32
+// MFMA with 16 rows of two heads or 16 keys per wave and tiles read at half rate by bank conflicts, took 1.24 and 1.83 ms.
+// A forward and backward pass of that batch takes 3125 to 3170 us (cards differ by 3 %), of three trajectories of 336 to 795 rows 59.
 #include "bc_prefill_tiles.h"
 
 namespace bc {

@@ -293,24 +293,11 @@ __device__ __forceinline__ float halves_sum(float x) {
   return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
-// 8 floats (consecutive k indices) -> hi and lo bf16x8 operands with hi + lo ~ x to 16 bits.  The remainder x - hi is exact.  (By the
-// bf16 dot product, one instruction instead of two, the decode kernels' way, each of the sixteen of a tile held up the matrix pipe by
-// some eight cycles: a loop of 32x32x16 products with one beside each ran at 78 % of the pipe, with four FMA at 90 %.
-// 16 trajectories of 8688 rows: dkv 22.5 -> 20.4 million cycles, dq 15.8 -> 15.2, forward 10.0 -> 9.6.)
-__device__ __forceinline__ void split8(const float* x, bf16x8_t& hi, bf16x8_t& lo) {
-  uint32_t h[4], l[4];
-#pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    const uint32_t hp = pack2_bf16(x[e], x[e + 1]);
-    h[e >> 1] = hp;
-    l[e >> 1] = pack2_bf16(x[e] - __uint_as_float(hp << 16), x[e + 1] - __uint_as_float(hp & 0xffff0000u));
-  }
-  hi = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
-  lo = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
-}
-
-// The same pair by pair, for code that spreads the work over other instructions: a lane's 16 values of a 32x32 product as the two parts of
-// the operands of the next one.
+// A lane's 16 values of a 32x32 product as the two bf16 parts (to 16 bits together) of the operands of the next one, pair by pair, so
+// that the work spreads over other instructions.  The remainder x - h is exact.  (By the bf16 dot product, one instruction instead of two,
+// the decode kernels' way, each of the sixteen of a tile held up the matrix pipe by some eight cycles: a loop of 32x32x16 products with one
+// beside each ran at 78 % of the pipe, with four FMA at 90 %.  16 trajectories of 8688 rows: dkv 22.5 -> 20.4 million cycles,
+// dq 15.8 -> 15.2, forward 10.0 -> 9.6.)
 struct Parts {
   uint32_t h[8], l[8];
   __device__ __forceinline__ void split(int n, float a, float b) {
