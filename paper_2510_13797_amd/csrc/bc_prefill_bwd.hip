@@ -10,6 +10,7 @@
 //  dq kernel   the forward's walk with the forward's workgroups: four waves, each 32 query rows of
 //              one head, over prompt run, gathered beacon run and masked band.  Also writes
 //              (lse*log2e, Delta) per row, head-major, for the second kernel.
+//              (Small launches: a kernel of its own does that, and the workgroups of both kernels are one launch.)
 //  dkv kernel  one workgroup = 64 keys of one KV head; three kinds of key block:
 //                prompt keys      -> stream every later row of every head of the group (dense)
 //                gathered beacons -> the same, from the first beacon's row on (dense)
@@ -30,7 +31,7 @@
 // matrix pipe half busy at 1.75 to 1.8 GHz; a loop of such products alone runs at 1.75 PFLOP/s and 1.75 GHz, with the operand reads and
 // vector work of the dq kernel at 1.3): fewer cycles give a lower clock and half of what they should.  The forms before, 16x16x32
 // MFMA with 16 rows of two heads or 16 keys per wave and tiles read at half rate by bank conflicts, took 1.24 and 1.83 ms.
-// A forward and backward pass of that batch takes 3125 to 3170 us (cards differ by 3 %), of three trajectories of 336 to 795 rows 59.
+// A forward and backward pass of that batch takes 3125 to 3170 us (cards differ by 3 %), of three trajectories of 336 to 795 rows 54.
 #include "bc_prefill_tiles.h"
 
 namespace bc {
@@ -48,7 +49,7 @@ struct BwdParams {
   float* dq;
   float* dk;
   float* dv;
-  float* stat;          // [Hq][total_rows][2]: lse*log2(e), Delta
+  float* stat;          // [Hq][total_rows][2]: lse*log2(e), -Delta
   float* part;          // splits * 2 * total_rows rows [Hkv][D]: partial dk, dv (see KeyParts)
   int32_t D;            // head dimension (the reduction kernel reads it; the others are templates)
   int32_t splits;       // rows of partial sums there is room for, per row, of dk and of dv
@@ -77,24 +78,39 @@ struct BwdParams {
 // mostly the first touch of the output's rows.
 // A third workgroup fits at d = 64 (16 trajectories of 7200 to 8700 rows, 14/2 heads: 623 -> 605 us with the passes below).
 constexpr int kDqStages = 5;
-template <int D, bool WIDE>
-__global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_dq_kernel(BwdParams p) {
+
+// Delta of a row: sixteen lanes with four of every 64 columns each, the same in all of them.
+template <int D>
+__device__ __forceinline__ float row_dot(const float4 (&o)[D / 64], const uint2 (&y)[D / 64]) {
+  float sum = 0.f;
+#pragma unroll
+  for (int t = 0; t < D / 64; ++t)
+    sum += __uint_as_float(y[t].x << 16) * o[t].x + __uint_as_float(y[t].x & 0xffff0000u) * o[t].y +
+           __uint_as_float(y[t].y << 16) * o[t].z + __uint_as_float(y[t].y & 0xffff0000u) * o[t].w;
+  return group_allreduce_sum<16>(sum);
+}
+template <int D> constexpr int dq_lds() {
+  constexpr int TILE = kTileRows * D * 2, RING = kDqStages * 2 * TILE, ROWS = (2 + 2 * kTileWaves) * TILE;
+  return RING > ROWS ? RING : ROWS;
+}
+// Rows of a workgroup by, heads hh of the group; at_x and the launch's row of the grid give the pair.  JOINED: log-sum-exp and
+// Delta are in the workspace.
+template <int D, bool WIDE, bool JOINED>
+__device__ __forceinline__ void dq_block(const BwdParams& p, char* lds, int at_x, int hh, int by, int ny) {
   constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
   constexpr int NLD = TILE / 1024 / kTileWaves;     // LDS-DMA instructions per wave, tile and tensor
-  constexpr int RING = kDqStages * 2 * TILE, ROWS = (2 + 2 * kTileWaves) * TILE, LDS = RING > ROWS ? RING : ROWS;
   constexpr int LOOK = kDqStages - 2;
   static_assert(LOOK == 3, "the counts of begin_pass");
-  static_assert(LDS >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
-  __shared__ __attribute__((aligned(1024))) char lds[LDS];
+  static_assert(dq_lds<D>() >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
 
-  const int hh = blockIdx.x / p.pstride, pair = pair_in_turn(blockIdx.x - hh * p.pstride, p.pstride);
+  const int pair = pair_in_turn(at_x, p.pstride);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
   const int64_t off0 = traj.off0;
   const int S = traj.rows;
   const int rows_wg = kTileRows * p.tiling.row_blocks;
-  const int r0 = (gridDim.y - 1 - blockIdx.y) * rows_wg;        // long tiles first
+  const int r0 = (ny - 1 - by) * rows_wg;        // long tiles first
   if (r0 >= S) return;
   const int r1 = min(r0 + rows_wg - 1, S - 1);
   const WindowStride ws = window_stride(traj.c, S);
@@ -134,29 +150,29 @@ __global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_
   issue_wave_rows<D>(p.dout + first * ROWB, (uint32_t)p.Hq * ROWB, r1 - rw, lane, lds_address(lds) + (3 + 2 * wave) * TILE);
   // Delta: sixteen lanes a row, four rows at a time
   float part[8];
-  {
+  if constexpr (!JOINED) {
     float4 o[8][D / 64];
     uint2 y[8][D / 64];
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
-      const int64_t e = (first + (int64_t)min(4 * n + (lane >> 4), r1 - rw) * p.Hq) * D + 4 * (lane & 15);
+      const uint32_t e = (uint32_t)min(4 * n + (lane >> 4), r1 - rw) * (uint32_t)(p.Hq * D) + 4 * (lane & 15);
 #pragma unroll
       for (int t = 0; t < D / 64; ++t) {
-        o[n][t] = *reinterpret_cast<const float4*>(p.out + e + 64 * t);
-        y[n][t] = *reinterpret_cast<const uint2*>(p.dout + (e + 64 * t) * 2);
+        o[n][t] = *reinterpret_cast<const float4*>(p.out + first * D + e + 64 * t);
+        y[n][t] = *reinterpret_cast<const uint2*>(p.dout + first * ROWB + 2 * (uint64_t)(e + 64 * t));
       }
     }
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
-      part[n] = 0.f;
-#pragma unroll
-      for (int t = 0; t < D / 64; ++t)
-        part[n] += __uint_as_float(y[n][t].x << 16) * o[n][t].x + __uint_as_float(y[n][t].x & 0xffff0000u) * o[n][t].y +
-                   __uint_as_float(y[n][t].y << 16) * o[n][t].z + __uint_as_float(y[n][t].y & 0xffff0000u) * o[n][t].w;
-      part[n] = group_allreduce_sum<16>(part[n]);
-    }
+    for (int n = 0; n < 8; ++n) part[n] = row_dot<D>(o[n], y[n]);
   }
-  float lse2 = p.lse[(off0 + r) * p.Hq + kvh * p.g + min(head, p.g - 1)] * kLog2e;
+  float lse2, delta;
+  if constexpr (JOINED) {
+    const float* stat = p.stat + ((int64_t)(kvh * p.g + min(head, p.g - 1)) * p.total_rows + off0 + r) * 2;
+    lse2 = stat[0];
+    delta = -stat[1];
+  } else {
+    lse2 = p.lse[(off0 + r) * p.Hq + kvh * p.g + min(head, p.g - 1)] * kLog2e;
+  }
   // this lane's query row: Q^T and dO^T as B operands, log-sum-exp and Delta of the row
   char* mine = lds + (2 + 2 * wave) * TILE;
   bf16x8_t qb[KS], dob[KS];
@@ -165,12 +181,14 @@ __global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_
   read_wave_rows<D>(mine + TILE, lane, dob);
   landed_operands(qb);
   landed_operands(dob);
-  asm volatile("" : : : "memory");      // (Delta's floats replace the operands' rows)
-  float row_delta = part[0];
+  if constexpr (!JOINED) {
+    asm volatile("" : : : "memory");      // (Delta's floats replace the operands' rows)
+    float row_delta = part[0];
 #pragma unroll
-  for (int n = 1; n < 8; ++n) row_delta = (lane & 7) == n ? part[n] : row_delta;
-  if ((lane & 8) == 0) reinterpret_cast<float*>(mine)[4 * (lane & 7) + (lane >> 4)] = row_delta;
-  float delta = reinterpret_cast<const float*>(mine)[col];
+    for (int n = 1; n < 8; ++n) row_delta = (lane & 7) == n ? part[n] : row_delta;
+    if ((lane & 8) == 0) reinterpret_cast<float*>(mine)[4 * (lane & 7) + (lane >> 4)] = row_delta;
+    delta = reinterpret_cast<const float*>(mine)[col];
+  }
   asm volatile("" : "+v"(delta), "+v"(lse2));
   lds_barrier();            // every wave has its rows
 #pragma unroll
@@ -282,8 +300,15 @@ __global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_
   for (int pass = 0; pass < 2; ++pass)
     store_rows<D>(my, dQ, p.scale, pass, lane, p.dq + ((off0 + rw0) * p.Hq + kvh * p.g + head) * D, p.Hq * D,
                   [&](int t) { return rw0 + t <= rw1 ? t : -1; });
-  if (rw0 + col <= rw1)
+  if (!JOINED && rw0 + col <= rw1)
     p.stat[((int64_t)(kvh * p.g + head) * p.total_rows + off0 + r) * 2 + half] = half ? -delta : lse2;
+}
+
+template <int D, bool WIDE>
+__global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_dq_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>()];
+  const int hh = blockIdx.x / p.pstride;
+  dq_block<D, WIDE, false>(p, lds, blockIdx.x - hh * p.pstride, hh, blockIdx.y, gridDim.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -341,14 +366,14 @@ struct KeyParts {
 // forms dA, takes A through LDS, and adds Q^T.dS to dK: three of the six products each, and half of the
 // accumulators and key operands, so that three waves fit a SIMD where one wave per 32 keys (two times 64
 // accumulators and 64 operand registers) would leave room for one.
+template <int D> constexpr int dkv_lds() { return kDkvStages * (4 * kTileRows * D + 256) + 2 * 4096 + kTileWaves * 768; }
 template <int D>
-__global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(BwdParams p) {
+__device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by) {
   constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
   constexpr int RING = kDkvStages * 2 * TILE, STAT = RING, XCH = RING + kDkvStages * 256;
   constexpr int OUT = kTileWaves * 32 * (D / 2) * 4;
-  constexpr int KEYS_AT = XCH + 2 * 4096, LDS = KEYS_AT + kTileWaves * 768;
-  static_assert(KEYS_AT >= OUT, "the gradient tiles fit");
-  __shared__ __attribute__((aligned(1024))) char lds[LDS];
+  constexpr int KEYS_AT = XCH + 2 * 4096;
+  static_assert(KEYS_AT >= OUT && KEYS_AT + kTileWaves * 768 == dkv_lds<D>(), "the gradient tiles fit");
   // grid: x = (trajectory, KV head), y = key block; the long dense blocks of every trajectory
   // are dispatched before any short one
   const int pair = pair_in_turn(blockIdx.x, p.pstride);
@@ -367,9 +392,9 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   // are dealt to `parts` workgroups, whose partial sums another kernel adds in a fixed order.
   // The short response blocks are cut where the chip is not full; a block of one part stores its result directly.
   const int dense = cut.parts;
-  const int at = (int)blockIdx.y - nd * dense;                  // place among the response blocks' parts
+  const int at = (int)by - nd * dense;                  // place among the response blocks' parts
   const int parts = at < 0 ? dense : p.band;
-  const int of = at < 0 ? (int)blockIdx.y : at;
+  const int of = at < 0 ? (int)by : at;
   const int blk = of / parts + (at < 0 ? 0 : nd), split = parts > 1 ? of % parts : -1;
   if (blk >= nd + NLB) return;
   const int kind = blk < NPB ? 0 : blk < nd ? 1 : 2;
@@ -378,7 +403,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int kg = wave >> 1;                                     // the pair's 32 keys of the block
-  const bool keys_role = ((wave ^ blockIdx.x ^ blockIdx.y) & 1) != 0;   // dA, dS, dK; otherwise scores, A, dV
+  const bool keys_role = ((wave ^ blockIdx.x ^ by) & 1) != 0;   // dA, dS, dK; otherwise scores, A, dV
 
   // this lane's key, the rows the block streams, and the rows the key is seen from: [jkey, last]
   int jkey, last;
@@ -589,7 +614,10 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   lds_barrier();
 
   // every key row is owned by exactly one lane column of one block: plain stores
-  float* base = (keys_role ? p.dk : p.dv) + off0 * p.Hkv * D;
+  using global_float = __attribute__((address_space(1))) float;
+  global_float *dk = (global_float*)p.dk, *dv = (global_float*)p.dv;
+  asm("" : "+s"(dk), "+s"(dv));        // (chosen by address, they went through scratch memory)
+  float* base = (float*)(keys_role ? dk : dv) + off0 * p.Hkv * D;
   if (split >= 0) {
     const int of = 2 * split + (keys_role ? 0 : 1);
     base = p.part + (kind == 2 ? cut.token_row(p, off0, of) : cut.dense_row(p, off0, of)) * p.Hkv * D;
@@ -600,6 +628,48 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
   for (int pass = 0; pass < 2; ++pass)
     store_rows<D>(my, acc, keys_role ? p.scale : 1.0f, pass, lane, base + kvh * D, p.Hkv * D,
                   [&](int t) { return __shfl(key_row, t, 64); });
+}
+
+template <int D>
+__global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) char lds[dkv_lds<D>()];
+  dkv_block<D>(p, lds, blockIdx.y);
+}
+
+// Launches that leave the chip idle are a chain of kernels that each wait for the one before, and the dkv kernel waits for nothing but
+// Delta.  So Delta has a kernel of its own there, and the workgroups of both kernels go out together, dq first: three trajectories of 336 to
+// 795 rows, 12/2 heads, dq 18 and dkv 18 us become 6 and 26 under the profiler, a pass of forward and gradients 58.9 -> 54.0.  Delta's kernel is
+// the first touch of `out`: with 64 rows a workgroup, four loads of a thread out at once, it takes 6.4 us, with 16 rows 6.2.
+constexpr int kDeltaRows = 16;        // rows of one head that a workgroup takes at a time: sixteen lanes a row
+template <int D>
+__global__ __launch_bounds__(256) void prefill_bwd_delta_kernel(BwdParams p) {
+  const Trajectory traj = trajectory(p, blockIdx.x);
+  const int64_t units = (int64_t)traj.rows * p.Hq;
+  const int lane = threadIdx.x & 15;
+  for (int64_t i = (int64_t)blockIdx.y * kDeltaRows + (threadIdx.x >> 4); i < units; i += (int64_t)gridDim.y * kDeltaRows) {
+    const int64_t at = traj.off0 * p.Hq + i;
+    float4 o[D / 64];
+    uint2 y[D / 64];
+#pragma unroll
+    for (int t = 0; t < D / 64; ++t) {
+      o[t] = *reinterpret_cast<const float4*>(p.out + at * D + 4 * lane + 64 * t);
+      y[t] = *reinterpret_cast<const uint2*>(p.dout + (at * D + 4 * lane + 64 * t) * 2);
+    }
+    const float lse2 = p.lse[at] * kLog2e, delta = row_dot<D>(o, y);
+    const int64_t row = i / p.Hq;
+    const int head = (int)(i - row * p.Hq);
+    if (lane < 2) p.stat[((int64_t)head * p.total_rows + traj.off0 + row) * 2 + lane] = lane ? -delta : lse2;
+  }
+}
+template <int D>
+__global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_joined_kernel(BwdParams p, int dq_rows) {
+  __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>() > dkv_lds<D>() ? dq_lds<D>() : dkv_lds<D>()];
+  if ((int)blockIdx.y < dq_rows * p.tiling.splits) {
+    const int by = blockIdx.y / p.tiling.splits;
+    dq_block<D, false, true>(p, lds, blockIdx.x, blockIdx.y - by * p.tiling.splits, by, dq_rows);
+  } else {
+    dkv_block<D>(p, lds, blockIdx.y - dq_rows * p.tiling.splits);
+  }
 }
 
 // Sum of the partials of the dense keys (prompt rows and beacons) and, where the response blocks were cut too, of the
@@ -657,10 +727,37 @@ __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
 }
 
 template <int D>
-static void launch_bwd(const BwdParams& p, bool wide, dim3 dq_grid, dim3 dkv_grid, hipStream_t hs) {
+static void launch_bwd(const BwdParams& p, bool joined, bool wide, dim3 dq_grid, dim3 dkv_grid, int32_t max_rows, hipStream_t hs) {
+  if (joined) {          // (never wide: all rows together are at most 128 for each of the joined kernel's dq workgroups)
+    const int64_t n = ((int64_t)max_rows * p.Hq + kDeltaRows - 1) / kDeltaRows;
+    prefill_bwd_delta_kernel<D><<<dim3(p.npairs / p.Hkv, (int)(n < 1024 ? n : 1024)), 256, 0, hs>>>(p);
+    const dim3 grid(p.pstride, dq_grid.y * p.tiling.splits + dkv_grid.y);
+    prefill_bwd_joined_kernel<D><<<grid, kTileWaves * 64, 0, hs>>>(p, (int)dq_grid.y);
+    return;
+  }
   if (wide) prefill_bwd_dq_kernel<D, true><<<dq_grid, kTileWaves * 64, 0, hs>>>(p);
   else prefill_bwd_dq_kernel<D, false><<<dq_grid, kTileWaves * 64, 0, hs>>>(p);
   prefill_bwd_dkv_kernel<D><<<dkv_grid, kTileWaves * 64, 0, hs>>>(p);
+}
+
+// Whether dq and dkv blocks go out in one launch: where the dq kernel's workgroups (of trajectories of the mean length) are no more than
+// the compute units, and for four pairs and fewer, whose dkv kernel does not fill the chip either, no more than run at once.  Otherwise the
+// chip has work for one kernel after the other, with three dkv workgroups a compute unit in place of two and none for Delta.  Forward and
+// gradients, us a pass, in two launches and in one, ratio 16, 4, 0 (those rows of a ratio that lie on the other side of the line in brackets):
+//   trajectories x tokens, heads   dq workgroups
+//   1 x 500, 12/2                     54, 60,  48    49.1 41.0 | 53.4  43.3 |  67.0  53.0
+//   1 x 500, 8/8                      40, 40,  32    46.2 39.2 | 51.2  39.4 |  62.8  45.2
+//   1 x 1000, 14/2, d = 64           136,156, 128    47.1 41.3 | 56.2  48.0 |  89.7  69.2
+//   6 x 384, 12/2                    252,288, 216    50.9 50.8 |(56.6  60.6)|  65.2  58.2
+//   4 x 600, 12/2                    240,288, 240    54.5 54.5 |(64.9  64.3)|  81.6  71.0
+//   2 x 500, 32/8                    272,304, 256   (54.7 57.1)|(67.0  68.3)|  83.8  78.0
+//   8 x 500, 12/2                    432,480, 384   (69.3 75.2)|(76.7  83.1)| (89.7  87.5)
+//   1 x 4000, 12/2 (two pairs)       402,468, 378     119  109 |  224   205 |   420   379
+//   2 x 2000, 12/2 (four)            408,468, 384    89.1 83.8 |  140   135 |   232   209
+static bool joins(const BwdParams& p, const bc_shape* shape) {
+  const int64_t rows = kTileRows * p.tiling.row_blocks * (int64_t)shape->B;
+  const int64_t blocks = (p.total_rows + rows - 1) / rows * p.npairs * p.tiling.splits;
+  return blocks <= (p.npairs <= 4 ? 512 : 256);
 }
 
 // Partial sums the workspace has room for, of every row: what KeyParts chooses from.
@@ -726,7 +823,6 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.part = p.stat + stat_floats(shape, total_rows);
   p.splits = dense_splits(shape, total_rows);
   p.most = p.splits == kMostSplits ? kMostParts : p.splits;       // (more parts only where the chip is not full)
-  p.band = band_splits(shape, total_rows, p.splits);
   p.total_rows = total_rows;
   p.D = shape->d;
   p.Hq = shape->Hq; p.Hkv = shape->Hkv; p.g = shape->Hq / shape->Hkv;
@@ -737,6 +833,8 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.pstride = pair_stride(p.npairs);
   p.tiling = head_tiling(p.g);
   const int rows_wg = kTileRows * p.tiling.row_blocks;
+  const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
+  p.band = band_splits(shape, total_rows, p.splits);
   const int key_blocks = (max_rows + kDkvKeys - 1) / kDkvKeys;
   // Key blocks of a trajectory: at most `key_blocks` of response rows, and of prompt keys and gathered beacons, which are rows of it
   // too, one more.  The parts of the latter together are at most two each, or as many workgroups as run at once and the last of each
@@ -745,11 +843,10 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   const int64_t at_once = kDkvAtOnce / p.npairs + dense_blocks, all = (int64_t)dense_blocks * p.most;
   const int64_t least = (int64_t)dense_blocks * (p.most < 2 ? p.most : 2);
   const int64_t dense_parts = all < at_once ? all : at_once < least ? least : at_once;
-  const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
   const dim3 dkv_grid(p.pstride, (int)(dense_parts + (int64_t)key_blocks * p.band));
-  const bool wide = rows_span_4gb(max_rows, shape);
-  if (shape->d == 128) launch_bwd<128>(p, wide, dq_grid, dkv_grid, hs);
-  else launch_bwd<64>(p, wide, dq_grid, dkv_grid, hs);
+  const bool wide = rows_span_4gb(max_rows, shape), joined = joins(p, shape);
+  if (shape->d == 128) launch_bwd<128>(p, joined, wide, dq_grid, dkv_grid, max_rows, hs);
+  else launch_bwd<64>(p, joined, wide, dq_grid, dkv_grid, max_rows, hs);
   if (p.splits > 1) {
     const int64_t blocks = ((int64_t)max_rows * shape->Hkv * (shape->d / 4) + 255) / 256, most = p.band > 1 ? 1024 : 128;
     prefill_bwd_reduce_kernel<<<dim3(shape->B, (int)(blocks < most ? blocks : most)), 256, 0, hs>>>(p);

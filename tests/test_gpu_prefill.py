@@ -516,6 +516,35 @@ def test_prefill_bwd_as_many_parts_as_there_is_room_for(dev, P, R, c, Hq, Hkv, d
     _check_bwd(pw, qkv, dos, off, dq.cpu().numpy(), dk.cpu().numpy(), dv.cpu().numpy(), 0)
 
 
+@pytest.mark.parametrize("P,R,c,Hq,Hkv,d", [
+    ([11, 11, 11, 11], [592] * 4, [16] * 4, 12, 2, 128), ([11, 11, 12, 11], [592] * 4, [16] * 4, 12, 2, 128),   # 10 x 24 workgroups of dq, 11 x 24
+    ([80, 80, 80, 80], [1476] * 4, [3] * 4, 8, 1, 64), ([80, 81, 80, 80], [1476] * 4, [3] * 4, 8, 1, 64),       # four pairs: 64 x 8, 65 x 8
+    ([1, 0, 700, 40], [0, 33, 3, 0], [5, 0, 2, 4], 7, 1, 64), ([31, 64, 1], [65, 32, 700], [1, 16, 300], 3, 3, 128)])
+def test_prefill_bwd_in_one_launch_and_in_two(dev, P, R, c, Hq, Hkv, d):
+    # both sides of the lines up to which the two kinds of workgroup are one launch, and trajectories of very different length in one;
+    # workspace and results hold NaN before the call
+    import torch
+    from paper_2510_13797_amd import bc
+    B, i32 = len(P), lambda x: np.array(x, np.int32)
+    pw = W.PrefillWorkload("pfb_joined", 79, B, Hq, Hkv, d, "bf16", i32(P), i32(R), i32(c))
+    qkv, dos = [pw.qkv(b) for b in range(B)], [pw.dout(b) for b in range(B)]
+    off = np.concatenate([[0], np.cumsum(pw.S)]).astype(np.int64)
+    total, most = int(off[-1]), int(pw.S.max())
+    q, k, v, do = (bc.to_device(np.concatenate(x), "bf16", dev) for x in (*zip(*qkv), dos))
+    out, lse = bc.prefill_attn(q, k, v, off, pw.P, pw.c, Hq, Hkv, d, pw.scale)
+    dq, dk, dv = (torch.full((total, h, d), float("nan"), device=dev) for h in (Hq, Hkv, Hkv))
+    shape = bc.bc_shape(B, Hq, Hkv, d, bc.BC_BF16, pw.scale)
+    ws = torch.full((bc.bc_prefill_bwd_workspace_bytes(shape, total) // 4,), float("nan"), device=dev)
+    tables = [torch.from_numpy(x).to(dev) for x in (off, pw.P, pw.c)]
+    st = bc.bc_prefill_attn_bwd(shape, *(t.data_ptr() for t in (q, k, v, out, lse, do, *tables)), most, total,
+                                *(t.data_ptr() for t in (dq, dk, dv, ws)), ws.numel() * 4, None)
+    assert st == bc.BC_OK
+    torch.cuda.synchronize()
+    dq, dk, dv = (x.cpu().numpy() for x in (dq, dk, dv))
+    for b in range(B):
+        _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_prefill_bwd_addresses_beyond_32_bits(dev, d):
     # as above for the gradients: 512 heads make rows of 128 or 64 KB, so a stated 4 GB of K rows needs
