@@ -88,7 +88,7 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
   constexpr int OW = D / 2;                   // output columns that go through LDS at a time
   static_assert(LDS >= kTileWaves * 32 * OW * 4, "the output tiles fit the ring's LDS");
 
-  const int hh = blockIdx.x / p.pstride, pair = pair_in_turn(blockIdx.x - hh * p.pstride, p.pstride);
+  const int hh = blockIdx.x / p.pstride, pair = pair_in_turn(blockIdx.x - hh * p.pstride, p.pstride, blockIdx.y);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);

@@ -103,7 +103,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* lds, int at_x
   static_assert(LOOK == 3, "the counts of begin_pass");
   static_assert(dq_lds<D>() >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
 
-  const int pair = pair_in_turn(at_x, p.pstride);
+  const int pair = pair_in_turn(at_x, p.pstride, blockIdx.y);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
@@ -376,7 +376,7 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
   static_assert(KEYS_AT >= OUT && KEYS_AT + kTileWaves * 768 == dkv_lds<D>(), "the gradient tiles fit");
   // grid: x = (trajectory, KV head), y = key block; the long dense blocks of every trajectory
   // are dispatched before any short one
-  const int pair = pair_in_turn(blockIdx.x, p.pstride);
+  const int pair = pair_in_turn(blockIdx.x, p.pstride, blockIdx.y);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);

@@ -6,11 +6,10 @@
 #include <type_traits>
 
 #include "bc_common.h"
+#include "bc_prefill_grid.h"
 
 namespace bc {
 
-constexpr int kTileRows = 32;         // rows of a staged tile; query rows of a wave
-constexpr int kTileWaves = 4;         // waves of a workgroup
 constexpr int kTileStages = 3;        // tiles in LDS: one in use, two on their way
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
@@ -343,38 +342,6 @@ __device__ __forceinline__ void store_rows(float* my, const f32x16_t (&acc)[D / 
 #pragma unroll
   for (int n = 0; n < 32 / RPP; ++n)
     if (to[n] >= 0) __builtin_nontemporal_store(val[n], reinterpret_cast<f32x4_t*>(at + (int64_t)to[n] * row_stride));
-}
-
-// ---------------------------------------------------------------------------
-// how the heads of a group are dealt to the waves of a workgroup (host)
-// ---------------------------------------------------------------------------
-struct HeadTiling {
-  int32_t heads;        // query heads per workgroup: 4, 2 or 1
-  int32_t splits;       // workgroups that share a group's heads
-  int32_t row_blocks;   // blocks of 32 query rows per workgroup: kTileWaves / heads
-};
-// Four waves, one per SIMD: three workgroups then fit a CU whatever SIMD each starts on (six waves
-// per workgroup, all heads of a group of six: 1.22 against 0.77 ms, the second workgroup found no
-// SIMD with room for two more waves).  As many heads as divide the group into fours or twos without a
-// remainder, since more rows per workgroup mean a longer masked band: groups of six with one head and
-// 128 rows took 0.75, with two heads and 64 rows 0.70 ms; groups of four with two heads 0.523, with
-// four heads and 32 rows 0.511 ms.
-inline HeadTiling head_tiling(int g) {
-  const int heads = g % 4 == 0 || g == 7 ? 4 : g % 2 == 0 ? 2 : 1;
-  return {heads, (g + heads - 1) / heads, kTileWaves / heads};
-}
-// Workgroups go to the 8 XCDs in turn.  With the pairs of a row tile (and its head splits) padded to a
-// multiple of 8, all tiles of a pair - which read the same prompt and beacon rows - share an L2; for
-// few pairs that would leave XCDs idle (three trajectories with two KV heads: six of eight XCDs at
-// work), and the tiles are dealt out evenly instead.
-inline int pair_stride(int npairs) { return npairs % 8 == 0 || npairs > 64 ? (npairs + 7) & ~7 : npairs; }
-// Inside an XCD they go to its four shader engines in turn, and a workgroup waits for a place in the engine whose turn it is.  A pair
-// at the same place in every row of the grid has all its workgroups on one engine, and trajectories of different length or ratio
-// then wait for the engine of the heaviest while the others stand idle (8 of 1482 to 5617 rows, ratios of 2 to 32, 32/8 heads, forward with
-// workspace: a third of the compute units idle, a call takes 487 us; 394 with the pairs of an XCD changing places from row to row; 16 equal
-// trajectories take what they took).  A grid of pairs that is no multiple of 8 changes places by itself.
-__device__ __forceinline__ int pair_in_turn(int at, int pstride) {
-  return pstride % 8 == 0 ? (int)((at + 8u * blockIdx.y) % (unsigned)pstride) : at;
 }
 
 // Whether byte offsets inside a trajectory's K or V rows may need more than 32 bits.
