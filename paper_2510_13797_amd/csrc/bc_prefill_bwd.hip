@@ -314,8 +314,6 @@ __global__ __launch_bounds__(kTileWaves * 64, D == 64 ? 3 : 2) void prefill_bwd_
 // ---------------------------------------------------------------------------
 // dkv kernel
 // ---------------------------------------------------------------------------
-constexpr int kDkvKeys = 64;          // keys of a workgroup: two pairs of waves with 32 keys each
-constexpr int kDkvAtOnce = 3 * 256;   // workgroups that run at once
 constexpr int kDkvStages = 2;
 
 // 4 bytes per lane from HBM into LDS
@@ -324,16 +322,8 @@ __device__ __forceinline__ void lds_dma4_s(uint32_t lane_offset, uint64_t base, 
                : : "s"(lds_addr), "v"(lane_offset), "s"(base) : "memory");
 }
 
-// The key blocks of a trajectory and what they are cut into.  Its dense blocks: as many parts as run at once if all trajectories are
-// like this one, and two where the heads of a group make the chain long.  One part stores its result directly.  (The host does not
-// know how many keys are dense, and reckons with one in eight.  Cut by that alone, 4 uncompressed trajectories of 2200 rows,
-// 8/8 heads, had six parts of 1120 blocks and took 376 us, 318 whole.)
-// The partial sums lie by key, not by row: part for part the dense keys' dk, then their dv, behind them the same of the response
-// tokens where their blocks are cut.  A trajectory has room for `splits` sums of every row, and the fewer of its rows are dense the more
-// parts fit: up to p.most of at least eight tiles and some 18 MB together.  us a pass, at most eight parts and sixteen: three trajectories of
-// 336 to 795 rows, a third of them dense, 12/2 heads 65.1, 60.5; one of 2100 rows, ratio 16, 99.7, 80.1; three of 720 rows, ratio 32, d = 64, 50.1,
-// 45.9; with 27 MB the first takes 62.5, with 12 64.3, with at most twelve parts 61.7.
-constexpr float kPartBytes = 18e6f;
+// The key blocks of a trajectory and what they are cut into (dense_parts()).  The partial sums lie by key, not by row: part for part the
+// dense keys' dk, then their dv, behind them the same of the response tokens where their blocks are cut.
 struct KeyParts {
   int prompt, beacons, tokens;       // keys: treated as dense-causal, complete windows' beacons, response rows that are no beacons
   int prompt_blocks, dense_blocks;
@@ -344,14 +334,7 @@ struct KeyParts {
     tokens = t.rows - prompt - beacons;
     prompt_blocks = (prompt + kDkvKeys - 1) / kDkvKeys;
     dense_blocks = prompt_blocks + (beacons + kDkvKeys - 1) / kDkvKeys;
-    const int blocks = min(max(dense_blocks, 1), kDkvAtOnce) * p.npairs, n = (kDkvAtOnce + blocks - 1) / blocks;
-    int most = p.splits;
-    if (p.most > p.splits) {         // (room for p.splits there always is: the tokens have p.band <= p.splits)
-      const int room = (p.splits * t.rows - (p.band > 1 ? p.band * tokens : 0)) / max(prompt + beacons, 1);
-      const int few = (int)(kPartBytes / (8.f * p.D * p.npairs * max(prompt + beacons, 1)));
-      most = max(most, min(min(p.most, min(room, few)), t.rows / kTileRows * p.g / 8));
-    }
-    parts = min(max(n, p.g > 1 ? 2 : 1), most);
+    parts = dense_parts(p.splits, p.most, p.band, p.npairs, p.g, p.D, t.rows, prompt + beacons, dense_blocks);
   }
   // first row of sum `of` of the dense keys (the tokens) of a trajectory; of: 2 * part + (0 for dk, 1 for dv)
   __device__ __forceinline__ int64_t dense_row(const BwdParams& p, int64_t off0, int of) const {
@@ -760,39 +743,6 @@ static bool joins(const BwdParams& p, const bc_shape* shape) {
   return blocks <= (p.npairs <= 4 ? 512 : 256);
 }
 
-// Partial sums the workspace has room for, of every row: what KeyParts chooses from.
-// A dense block streams all later rows of all heads, a chain of up to g * rows/32 tiles, and there are few of
-// them: they are cut until as many as run at once (three per CU) are there, taking one key in eight for dense
-// (ratios and prompt lengths are on the device).  Backward of 6 trajectories, 14/2 heads, d = 64, 12,966 rows: two
-// parts 523 us, six 300; one trajectory of 6631 rows, 24/8 heads: 597, three 372; three short trajectories: 118,
-// six 62; more parts than that cost work (16 trajectories of 8688 rows: two 2.70 ms, three 2.66, six 2.82; 8 of
-// 3389 rows, 32/8 heads: 2.37, 2.40, 2.55).  Parts of fewer than eight tiles are not worth their partial sums.
-constexpr int kMostSplits = 8, kMostParts = 16;
-static int dense_splits(const bc_shape* shape, int64_t total_rows) {
-  constexpr int64_t kMost = kMostSplits;
-  const int64_t blocks = total_rows * shape->Hkv / (8 * kDkvKeys) + 1;
-  const int64_t tiles = total_rows / shape->B * (shape->Hq / shape->Hkv) / kTileRows;      // of a chain
-  const int64_t n = (kDkvAtOnce + blocks - 1) / blocks, least = shape->Hq > shape->Hkv ? 2 : 1;
-  const int64_t most = tiles / 8 < kMost ? tiles / 8 : kMost;
-  return (int)(n < least || most < least ? least : n > most ? most : n);
-}
-
-// Workgroups that share a response block: a chain of about three tiles for each head of a group, which is what a launch of
-// a few trajectories takes where the chip is not full.  As many as run at once beside the dense blocks' parts, at least
-// two heads each.  Three trajectories of 336 to 795 rows, 12/2 heads, whole 69.3 us a pass, in three parts 67.1
-// (the dense blocks' chains are as long); three of 300 rows, 14/2 heads, d = 64, 56.9 and 50.2; of 380 rows (forward and gradients in one
-// graph), 12/2 heads 59.5 and 51.9, d = 64 45.9 and 40.0, but three of 830 rows 69.4 and 71.0.  Groups of fewer than six heads stay
-// whole: two trajectories of 216 rows, 4/1 heads, 44.5 and in two parts 44.9, called one by one.  In one graph groups of five gain as those of six do (two of
-// 270 rows, 5/1 heads 51.8 and 45.7, three of 830 64.6 and 65.1), groups of four half as much (43.0 and 40.1, 55.5 and 56.0).
-static int band_splits(const bc_shape* shape, int64_t total_rows, int splits) {
-  const int64_t pairs = (int64_t)shape->B * shape->Hkv, g = shape->Hq / shape->Hkv;
-  if (g < 6) return 1;
-  const int64_t blocks = total_rows * shape->Hkv / kDkvKeys;        // one in eight dense, as above
-  const int64_t n = (kDkvAtOnce - (blocks / 8 + 2 * pairs) * splits) / (blocks - blocks / 8 + pairs);
-  const int64_t most = g / 2 < splits ? g / 2 : splits;
-  return (int)(n < 1 ? 1 : n > most ? most : n);
-}
-
 // Floats of the workspace's first part (stat), rounded up so that the partials behind it start at 256 bytes:
 // they are stored and summed 16 bytes at a time, and an odd number of rows times heads would put them 8 off.
 static size_t stat_floats(const bc_shape* shape, int64_t total_rows) {
@@ -805,7 +755,7 @@ using namespace bc;
 
 extern "C" size_t bc_prefill_bwd_workspace_bytes(const bc_shape* shape, int64_t total_rows) {
   if (check_shape(shape) != BC_OK || total_rows < 1) return 0;
-  const int hs = dense_splits(shape, total_rows);
+  const int hs = dense_splits(shape->B, shape->Hq, shape->Hkv, total_rows);
   size_t bytes = stat_floats(shape, total_rows) * sizeof(float);
   if (hs > 1) bytes += (size_t)hs * 2 * total_rows * shape->Hkv * shape->d * sizeof(float);
   return bytes;
@@ -821,8 +771,8 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.dq = dq; p.dk = dk; p.dv = dv;
   p.stat = static_cast<float*>(workspace);
   p.part = p.stat + stat_floats(shape, total_rows);
-  p.splits = dense_splits(shape, total_rows);
-  p.most = p.splits == kMostSplits ? kMostParts : p.splits;       // (more parts only where the chip is not full)
+  p.splits = dense_splits(shape->B, shape->Hq, shape->Hkv, total_rows);
+  p.most = most_parts(p.splits);
   p.total_rows = total_rows;
   p.D = shape->d;
   p.Hq = shape->Hq; p.Hkv = shape->Hkv; p.g = shape->Hq / shape->Hkv;
@@ -834,16 +784,9 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.tiling = head_tiling(p.g);
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
-  p.band = band_splits(shape, total_rows, p.splits);
+  p.band = band_splits(shape->B, shape->Hq, shape->Hkv, total_rows, p.splits);
   const int key_blocks = (max_rows + kDkvKeys - 1) / kDkvKeys;
-  // Key blocks of a trajectory: at most `key_blocks` of response rows, and of prompt keys and gathered beacons, which are rows of it
-  // too, one more.  The parts of the latter together are at most two each, or as many workgroups as run at once and the last of each
-  // block's (see KeyParts).  A workgroup that finds no part costs 1 us in a thousand.
-  const int dense_blocks = key_blocks + 1;
-  const int64_t at_once = kDkvAtOnce / p.npairs + dense_blocks, all = (int64_t)dense_blocks * p.most;
-  const int64_t least = (int64_t)dense_blocks * (p.most < 2 ? p.most : 2);
-  const int64_t dense_parts = all < at_once ? all : at_once < least ? least : at_once;
-  const dim3 dkv_grid(p.pstride, (int)(dense_parts + (int64_t)key_blocks * p.band));
+  const dim3 dkv_grid(p.pstride, (int)dkv_grid_rows(p.npairs, p.most, p.band, key_blocks));
   const bool wide = rows_span_4gb(max_rows, shape), joined = joins(p, shape);
   if (shape->d == 128) launch_bwd<128>(p, joined, wide, dq_grid, dkv_grid, max_rows, hs);
   else launch_bwd<64>(p, joined, wide, dq_grid, dkv_grid, max_rows, hs);

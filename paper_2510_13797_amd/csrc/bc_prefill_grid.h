@@ -1,6 +1,7 @@
 // Which workgroup of the masked attention's kernels works on what, and where the hardware puts it.  Plain arithmetic without
 // memory, shared by the kernels, the calls that launch them and a host test that plays a grid through.
 #pragma once
+#include <cmath>
 #include <cstdint>
 
 #ifndef BC_HOST_DEVICE
@@ -53,6 +54,87 @@ inline int pair_stride(int npairs) { return npairs % 8 == 0 || npairs > 64 ? (np
 // 2067; 27 of which one has 956 rows, 32/8 heads: forward 31.8 and 27.0).
 BC_HOST_DEVICE int pair_in_turn(int at, int pstride, unsigned row) {
   return pstride % 16 == 0 ? (int)((at + 8u * row) % (unsigned)pstride) : at;
+}
+
+// ---------------------------------------------------------------------------
+// what the backward's key blocks are cut into
+// ---------------------------------------------------------------------------
+constexpr int kDkvKeys = 64;          // keys of a workgroup: two pairs of waves with 32 keys each
+constexpr int kDkvAtOnce = 3 * 256;   // workgroups that run at once
+constexpr int kMostSplits = 8, kMostParts = 16;
+
+// Partial sums the workspace has room for, of every row: what dense_parts() chooses from.
+// A dense block streams all later rows of all heads, a chain of up to g * rows/32 tiles, and there are few of
+// them: they are cut until as many as run at once (three per CU) are there, taking one key in eight for dense
+// (ratios and prompt lengths are on the device).  Backward of 6 trajectories, 14/2 heads, d = 64, 12,966 rows: two
+// parts 523 us, six 300; one trajectory of 6631 rows, 24/8 heads: 597, three 372; three short trajectories: 118,
+// six 62; more parts than that cost work (16 trajectories of 8688 rows: two 2.70 ms, three 2.66, six 2.82; 8 of
+// 3389 rows, 32/8 heads: 2.37, 2.40, 2.55).  Parts of fewer than eight tiles are not worth their partial sums.
+inline int dense_splits(int B, int Hq, int Hkv, int64_t total_rows) {
+  constexpr int64_t kMost = kMostSplits;
+  const int64_t blocks = total_rows * Hkv / (8 * kDkvKeys) + 1;
+  const int64_t tiles = total_rows / B * (Hq / Hkv) / kTileRows;      // of a chain
+  const int64_t n = (kDkvAtOnce + blocks - 1) / blocks, least = Hq > Hkv ? 2 : 1;
+  const int64_t most = tiles / 8 < kMost ? tiles / 8 : kMost;
+  return (int)(n < least || most < least ? least : n > most ? most : n);
+}
+
+// Workgroups that share a response block: a chain of about three tiles for each head of a group, which is what a launch of
+// a few trajectories takes where the chip is not full.  As many as run at once beside the dense blocks' parts, at least
+// two heads each.  Three trajectories of 336 to 795 rows, 12/2 heads, whole 69.3 us a pass, in three parts 67.1
+// (the dense blocks' chains are as long); three of 300 rows, 14/2 heads, d = 64, 56.9 and 50.2; of 380 rows (forward and gradients in one
+// graph), 12/2 heads 59.5 and 51.9, d = 64 45.9 and 40.0, but three of 830 rows 69.4 and 71.0.  Groups of fewer than six heads stay
+// whole: two trajectories of 216 rows, 4/1 heads, 44.5 and in two parts 44.9, called one by one.  In one graph groups of five gain as those of six do (two of
+// 270 rows, 5/1 heads 51.8 and 45.7, three of 830 64.6 and 65.1), groups of four half as much (43.0 and 40.1, 55.5 and 56.0).
+inline int band_splits(int B, int Hq, int Hkv, int64_t total_rows, int splits) {
+  const int64_t pairs = (int64_t)B * Hkv, g = Hq / Hkv;
+  if (g < 6) return 1;
+  const int64_t blocks = total_rows * Hkv / kDkvKeys;        // one in eight dense, as above
+  const int64_t n = (kDkvAtOnce - (blocks / 8 + 2 * pairs) * splits) / (blocks - blocks / 8 + pairs);
+  const int64_t most = g / 2 < splits ? g / 2 : splits;
+  return (int)(n < 1 ? 1 : n > most ? most : n);
+}
+
+// Most workgroups that share a dense key block: more than there is room for of every row only where the chip is not full.
+BC_HOST_DEVICE int most_parts(int splits) { return splits == kMostSplits ? kMostParts : splits; }
+
+// Parts of a trajectory's dense key blocks: as many as run at once if all trajectories are like this one, and two where the heads of a
+// group make the chain long.  One part stores its result directly.  (The host does not know how many keys are dense, and reckons with
+// one in eight.  Cut by that alone, 4 uncompressed trajectories of 2200 rows, 8/8 heads, had six parts of 1120 blocks and took
+// 376 us, 318 whole.)
+// A trajectory has room for `splits` sums of every row, and the fewer of its rows are dense the more parts fit, up to `most`.  The n-th part takes
+// some tiles / n^2 off the chain and costs one more sum of all dense keys: worth it up to kSumBytes for a tile, and for parts of kLeastTiles
+// tiles.  Both numbers from 600 batches of up to 48 trajectories, each with at most 8, 10, 12, 14 and 16 parts; of 150 others, the gradients of which take
+// 0.69 to 1.09 of the time with at most eight (mean 0.967).  By parts of eight tiles and 18 MB together, which is what one batch
+// had said, it was 0.70 to 1.21 (0.982): ten of 450 to 1153 rows, 4/1 heads, d = 64, 46.4 us with eight, 47.5 now, 52.5 so; one of 1229, 24/8 heads 52.9, 53.2
+// and 59.2.
+constexpr int kLeastTiles = 12;
+constexpr float kSumBytes = 0.5e6f;
+BC_HOST_DEVICE int dense_parts(int splits, int most, int band, int npairs, int g, int D, int rows, int dense_keys, int dense_blocks) {
+  const int some = dense_blocks < 1 ? 1 : dense_blocks > kDkvAtOnce ? kDkvAtOnce : dense_blocks, blocks = some * npairs;
+  const int n = (kDkvAtOnce + blocks - 1) / blocks, wanted = n < 2 && g > 1 ? 2 : n;
+  int fit = splits;                // (room for `splits` there always is: the tokens have band <= splits)
+  if (most > splits) {
+    const int keys = dense_keys < 1 ? 1 : dense_keys;
+    const int room = (splits * rows - (band > 1 ? band * (rows - dense_keys) : 0)) / keys;
+    const int tiles = rows / kTileRows * g, long_enough = tiles / kLeastTiles;
+    const int few = (int)sqrtf(kSumBytes * tiles / (8.f * D * npairs * keys));
+    int more = room < few ? room : few;
+    more = more < long_enough ? more : long_enough;
+    more = more < most ? more : most;
+    fit = fit < more ? more : fit;
+  }
+  return wanted < fit ? wanted : fit;
+}
+
+// Rows of the dkv grid.  Key blocks of a trajectory: at most `key_blocks` of response rows, and of prompt keys and gathered beacons,
+// which are rows of it too, one more.  The parts of the latter together are at most two each, or as many workgroups as run at once and
+// the last of each block's (dense_parts()).  A workgroup that finds no part costs 1 us in a thousand.
+inline int64_t dkv_grid_rows(int npairs, int most, int band, int key_blocks) {
+  const int dense_blocks = key_blocks + 1;
+  const int64_t at_once = kDkvAtOnce / npairs + dense_blocks, all = (int64_t)dense_blocks * most;
+  const int64_t least = (int64_t)dense_blocks * (most < 2 ? most : 2);
+  return (all < at_once ? all : at_once < least ? least : at_once) + (int64_t)key_blocks * band;
 }
 
 }  // namespace bc

@@ -494,10 +494,11 @@ def test_prefill_bwd_response_blocks_in_parts(dev, P, R, Hq, Hkv, d):
     test_prefill_bwd_key_blocks_and_their_parts_at_the_edges(dev, P, R, Hq, Hkv, d)
 
 
-@pytest.mark.parametrize("P,R,c,Hq,Hkv,d", [(5, 900, 32, 12, 2, 128), (130, 500, 1, 6, 1, 128), (60, 640, 0, 6, 1, 64), (64, 1100, 300, 8, 1, 64)])
+@pytest.mark.parametrize("P,R,c,Hq,Hkv,d", [(5, 900, 32, 12, 2, 128), (130, 500, 1, 6, 1, 128), (60, 640, 0, 6, 1, 64), (64, 1100, 300, 8, 1, 64),
+                                             (5, 1900, 32, 7, 1, 64), (5, 1400, 16, 8, 1, 128)])
 def test_prefill_bwd_as_many_parts_as_there_is_room_for(dev, P, R, c, Hq, Hkv, d):
-    # one trajectory on an idle chip: few dense keys (sixteen parts), two thirds and all of the rows dense, a last window that stays open;
-    # workspace and results hold NaN before the call
+    # one trajectory on an idle chip: few dense keys, two thirds and all of the rows dense, a last window that stays open, chains of 427 and 368
+    # tiles (sixteen parts); workspace and results hold NaN before the call
     import torch
     from paper_2510_13797_amd import bc
     pw = W.PrefillWorkload("pfb_room", 73, 1, Hq, Hkv, d, "bf16", np.array([P], np.int32), np.array([R], np.int32), np.array([c], np.int32))

@@ -3,6 +3,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -10,14 +11,23 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2510_13797_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def grids(tmp_path_factory):
+def model(tmp_path_factory):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         pytest.skip("no host compiler")
     exe = str(tmp_path_factory.mktemp("grid") / "prefill_grid_model")
     subprocess.check_call([cxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", exe, os.path.join(HERE, "prefill_grid_model.cpp")])
-    lines = subprocess.check_output([exe], timeout=300).decode().split("\n")
-    return [dict((k, int(v)) for k, v in (x.split("=") for x in l.split())) for l in lines if l]
+
+    def run(*args, lines=()):
+        text = "".join(" ".join(str(int(x)) for x in l) + "\n" for l in lines)
+        out = subprocess.run([exe, *args], input=text.encode(), stdout=subprocess.PIPE, timeout=300, check=True).stdout.decode()
+        return [dict((k, int(v)) for k, v in (x.split("=") for x in l.split())) for l in out.split("\n") if l]
+    return run
+
+
+@pytest.fixture(scope="module")
+def grids(model):
+    return model("pairs")
 
 
 def test_every_row_of_a_grid_has_every_pair_once(grids):
@@ -32,3 +42,37 @@ def test_a_pairs_workgroups_come_to_all_shader_engines(grids):
             assert g["engines"] == 4 and g["most"] <= 340, g
         else:                              # two pairs an XCD, one workgroup of a pair a row
             assert g["engines"] >= 2 and g["most"] <= 500, g
+
+
+def _trajectories(B, Hq, Hkv, d, rows, P, c):
+    return [(B, Hq, Hkv, d, sum(rows), max(rows), r, p, x) for r, p, x in zip(rows, P, c)]
+
+
+def test_parts_of_a_dense_key_block_fit_the_workspace_and_the_grid(model):
+    r = np.random.default_rng(20251013)
+    lines = []
+    for _ in range(4000):
+        g, Hkv, B = (int(x) for x in (r.integers(1, 9), r.choice([1, 2, 3, 8]), np.exp(r.uniform(0, np.log(130)))))
+        rows = np.exp(r.uniform(0, np.log(r.choice([60, 600, 9000])), B)).astype(np.int64)
+        lines += _trajectories(B, g * Hkv, Hkv, r.choice([64, 128]), rows, r.integers(0, 400, B), r.choice([0, 1, 2, 16, 32, 5000], B))
+    lines = [lines[i] for i in r.permutation(len(lines))[:60000]]
+    got = model(lines=lines)
+    assert len(got) == len(lines) and max(x["parts"] for x in got) == 16
+    for l, x in zip(lines, got):
+        assert 1 <= x["band"] <= x["splits"] and x["sums"] <= x["room"] and x["groups"] <= x["grid"], (l, x)
+
+
+def test_dense_key_blocks_have_more_than_eight_parts_only_where_each_saves_more_than_its_sums_cost(model):
+    # (with parts of eight tiles and up the first three were 5 to 9 % slower than with eight parts; the last is a third faster with sixteen)
+    for t in (_trajectories(10, 4, 1, 64, [450, 1153] * 5, [293] * 10, [32] * 10), _trajectories(1, 24, 8, 128, [1229], [110], [16]),
+              _trajectories(13, 16, 2, 128, [224, 551] * 6 + [400], [258] * 13, [16] * 13)):
+        assert all(x["parts"] <= 8 or x["parts"] * 12 <= x["tiles"] for x in model(lines=t))
+        assert max(x["parts"] for x in model(lines=t)) <= 12
+    assert [x["parts"] for x in model(lines=_trajectories(2, 7, 1, 64, [3745, 3961], [100, 100], [32, 32]))] == [16, 16]
+    r = np.random.default_rng(5)
+    got = model(lines=[_trajectories(*a, r.choice([64, 128]), [n] * a[0], [60] * a[0], [16] * a[0])[0]
+                       for a in [(1, 4, 1), (3, 12, 2), (6, 5, 1), (10, 4, 1), (2, 32, 8)] for n in r.integers(100, 6000, 200)])
+    more = [x for x in got if x["parts"] > 8]
+    assert len(more) > 100
+    for x in more:
+        assert x["parts"] * 12 <= x["tiles"] and x["parts"] ** 2 * x["bytes"] <= 0.5e6 * x["tiles"] * 1.0001, x
