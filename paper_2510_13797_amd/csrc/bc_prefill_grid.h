@@ -48,12 +48,14 @@ inline int pair_stride(int npairs) { return npairs % 8 == 0 || npairs > 64 ? (np
 // even number of pairs an XCD, a pair at the same place in every row of the grid has its workgroups on one engine or two, and
 // trajectories of different length or ratio then wait for the engine of the heaviest while the others stand idle (8 of 1482 to 5617 rows, ratios
 // of 2 to 32, 32/8 heads, forward with workspace: a third of the compute units idle, a call takes 487 us; 394 with the pairs of an XCD
-// changing places from row to row; 16 equal trajectories take what they took).  Two pairs an XCD with one head split come to two engines
-// either way, for every other even number it is four.  An odd number comes to all four in turn by itself, and changing places
+// changing places from row to row; 16 equal trajectories take what they took).  Two pairs an XCD change places every other row:
+// every row, a step of two workgroups and one back, they came to two engines again, and gradients in one launch of both kinds of workgroup
+// lost by it (eight of 26 to 2364 rows, 8/2 heads, 172 us in two launches, 185 in one, 134 now; two of 1058 and 4362, 32/8 heads, forward 82 and
+// 60).  An odd number comes to all four in turn by itself, and changing places
 // would undo that (130 trajectories, 129 of some 50 rows and one of 14,046, 5/1 heads, ratio 4: forward 590 us, 469 at the same place, gradients 2503 and
 // 2067; 27 of which one has 956 rows, 32/8 heads: forward 31.8 and 27.0).
 BC_HOST_DEVICE int pair_in_turn(int at, int pstride, unsigned row) {
-  return pstride % 16 == 0 ? (int)((at + 8u * row) % (unsigned)pstride) : at;
+  return pstride % 16 == 0 ? (int)((at + 8u * (pstride == 16 ? row / 2 : row)) % (unsigned)pstride) : at;
 }
 
 // ---------------------------------------------------------------------------

@@ -38,10 +38,8 @@ def test_a_pairs_workgroups_come_to_all_shader_engines(grids):
     for g in grids:
         if g["stride"] // 8 % 2:           # an odd number of pairs an XCD: one engine after the other
             assert g["run"] == 4, g
-        elif g["stride"] > 16 or g["splits"] > 1:
-            assert g["engines"] == 4 and g["most"] <= 340, g
-        else:                              # two pairs an XCD, one workgroup of a pair a row
-            assert g["engines"] >= 2 and g["most"] <= 500, g
+        else:
+            assert g["engines"] == 4 and g["most"] <= 340 and (g["run"] == 4 or (g["stride"], g["splits"]) != (16, 1)), g
 
 
 def _trajectories(B, Hq, Hkv, d, rows, P, c):
