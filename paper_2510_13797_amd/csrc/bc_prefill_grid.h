@@ -139,4 +139,27 @@ inline int64_t dkv_grid_rows(int npairs, int most, int band, int key_blocks) {
   return (all < at_once ? all : at_once < least ? least : at_once) + (int64_t)key_blocks * band;
 }
 
+// ---------------------------------------------------------------------------
+// the backward's launches
+// ---------------------------------------------------------------------------
+// Whether dq and dkv blocks go out in one launch: where the dq kernel's workgroups (of trajectories of the mean length) are no more than
+// the compute units, and for four pairs and fewer, whose dkv kernel does not fill the chip either, no more than run at once.  Otherwise the
+// chip has work for one kernel after the other, with three dkv workgroups a compute unit in place of two and none for Delta.  Forward and
+// gradients, us a pass, in two launches and in one, ratio 16, 4, 0 (those rows of a ratio that lie on the other side of the line in brackets):
+//   trajectories x tokens, heads   dq workgroups
+//   1 x 500, 12/2                     54, 60,  48    49.1 41.0 | 53.4  43.3 |  67.0  53.0
+//   1 x 500, 8/8                      40, 40,  32    46.2 39.2 | 51.2  39.4 |  62.8  45.2
+//   1 x 1000, 14/2, d = 64           136,156, 128    47.1 41.3 | 56.2  48.0 |  89.7  69.2
+//   6 x 384, 12/2                    252,288, 216    50.9 50.8 |(56.6  60.6)|  65.2  58.2
+//   4 x 600, 12/2                    240,288, 240    54.5 54.5 |(64.9  64.3)|  81.6  71.0
+//   2 x 500, 32/8                    272,304, 256   (54.7 57.1)|(67.0  68.3)|  83.8  78.0
+//   8 x 500, 12/2                    432,480, 384   (69.3 75.2)|(76.7  83.1)| (89.7  87.5)
+//   1 x 4000, 12/2 (two pairs)       402,468, 378     119  109 |  224   205 |   420   379
+//   2 x 2000, 12/2 (four)            408,468, 384    89.1 83.8 |  140   135 |   232   209
+inline bool in_one_launch(int B, int npairs, const HeadTiling& tiling, int64_t total_rows) {
+  const int64_t rows = kTileRows * tiling.row_blocks * (int64_t)B;
+  const int64_t blocks = (total_rows + rows - 1) / rows * npairs * tiling.splits;
+  return blocks <= (npairs <= 4 ? 512 : 256);
+}
+
 }  // namespace bc

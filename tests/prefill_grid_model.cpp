@@ -12,6 +12,7 @@
 //   tiles, bytes  of the chain of the longest dense block, and of one part's sums of all pairs
 //   sums, room    rows of partial sums, and of the trajectory's share of the workspace
 //   groups, grid  workgroups that have work in a column of the grid, and rows of it
+//   one           whether the dq kernel's workgroups go out in the same launch
 #include <cstdio>
 #include <cstring>
 #include <vector>
@@ -61,10 +62,11 @@ static void parts(const long long* a) {
   const auto blocks = [](int n) { return (n + kDkvKeys - 1) / kDkvKeys; };
   const int dense = blocks(prompt) + blocks(beacons);
   const int n = dense_parts(splits, most, band, B * Hkv, g, d, rows, keys, dense);
-  std::printf("splits=%d parts=%d band=%d tiles=%d bytes=%lld sums=%lld room=%lld groups=%d grid=%lld\n", splits, n, band, rows / kTileRows * g,
+  std::printf("splits=%d parts=%d band=%d tiles=%d bytes=%lld sums=%lld room=%lld groups=%d grid=%lld one=%d\n", splits, n, band, rows / kTileRows * g,
               8ll * d * B * Hkv * keys,
               (long long)(n > 1 ? n * keys : 0) + (band > 1 ? band * (rows - keys) : 0), splits > 1 ? (long long)splits * rows : 0,
-              dense * n + blocks(rows - prompt) * band, (long long)dkv_grid_rows(B * Hkv, most, band, blocks(max_rows)));
+              dense * n + blocks(rows - prompt) * band, (long long)dkv_grid_rows(B * Hkv, most, band, blocks(max_rows)),
+              (int)in_one_launch(B, B * Hkv, head_tiling(g), a[4]));
 }
 
 int main(int argc, char** argv) {

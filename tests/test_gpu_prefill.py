@@ -546,6 +546,43 @@ def test_prefill_bwd_in_one_launch_and_in_two(dev, P, R, c, Hq, Hkv, d):
         _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,B,longest", [
+    (14, 2, 64, 67, 300), (14, 2, 128, 16, 700), (7, 1, 128, 65, 200), (2, 1, 64, 130, 400), (9, 3, 128, 20, 700), (12, 4, 64, 13, 700), (25, 5, 64, 4, 1100),
+    (20, 4, 128, 7, 700), (2, 2, 64, 100, 700), (24, 8, 64, 3, 1100), (16, 8, 128, 9, 900)])
+def test_prefill_bwd_in_two_launches(dev, Hq, Hkv, d, B, longest):
+    # batches beyond the line for one launch, every kind of group and padded numbers of pairs (67, 65, 130 and 100 trajectories): one long trajectory,
+    # beside it one of no rows, of one and of 33, all others of up to a third; workspace and results hold NaN before the call
+    import torch
+    from paper_2510_13797_amd import bc
+    from test_prefill_grid import in_one_launch
+    r = np.random.default_rng([Hq, Hkv, d, B])
+    P, R, c = r.integers(0, 40, B), r.integers(1, longest // 3, B), r.choice([0, 1, 3, 16], B)
+    P[:2], R[:2], c[:2] = (17, 33), (longest, 0), (4, 5)
+    if B > 3:
+        P[2:4], R[2:4] = (0, 0), (0, 1)
+        P[-1], R[-1], c[-1] = 40, 170, 16
+    i32 = lambda x: x.astype(np.int32)
+    pw = W.PrefillWorkload("pfb_two", 83, B, Hq, Hkv, d, "bf16", i32(P), i32(R), i32(c))
+    qkv, dos = [pw.qkv(b) for b in range(B)], [pw.dout(b) for b in range(B)]
+    off = np.concatenate([[0], np.cumsum(pw.S)]).astype(np.int64)
+    total, most = int(off[-1]), int(pw.S.max())
+    assert not in_one_launch(B, Hq, Hkv, total)
+    q, k, v, do = (bc.to_device(np.concatenate(x), "bf16", dev) for x in (*zip(*qkv), dos))
+    out, lse = bc.prefill_attn(q, k, v, off, pw.P, pw.c, Hq, Hkv, d, pw.scale)
+    dq, dk, dv = (torch.full((total, h, d), float("nan"), device=dev) for h in (Hq, Hkv, Hkv))
+    shape = bc.bc_shape(B, Hq, Hkv, d, bc.BC_BF16, pw.scale)
+    ws = torch.full((bc.bc_prefill_bwd_workspace_bytes(shape, total) // 4,), float("nan"), device=dev)
+    tables = [torch.from_numpy(x).to(dev) for x in (off, pw.P, pw.c)]
+    st = bc.bc_prefill_attn_bwd(shape, *(t.data_ptr() for t in (q, k, v, out, lse, do, *tables)), most, total,
+                                *(t.data_ptr() for t in (dq, dk, dv, ws)), ws.numel() * 4, None)
+    assert st == bc.BC_OK
+    torch.cuda.synchronize()
+    dq, dk, dv = (x.cpu().numpy() for x in (dq, dk, dv))
+    for b in range(B):
+        if pw.S[b]:
+            _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_prefill_bwd_addresses_beyond_32_bits(dev, d):
     # as above for the gradients: 512 heads make rows of 128 or 64 KB, so a stated 4 GB of K rows needs

@@ -42,6 +42,25 @@ def test_a_pairs_workgroups_come_to_all_shader_engines(grids):
             assert g["engines"] == 4 and g["most"] <= 340 and (g["run"] == 4 or (g["stride"], g["splits"]) != (16, 1)), g
 
 
+def in_one_launch(B, Hq, Hkv, total_rows):
+    """Whether the gradients' two kinds of workgroup are one launch: the GPU tests say with it which side a case is on."""
+    g = Hq // Hkv
+    heads = 4 if g % 4 == 0 or g == 7 else 2 if g % 2 == 0 else 1
+    rows = 32 * (4 // heads) * B
+    return -(-total_rows // rows) * B * Hkv * -(-g // heads) <= (512 if B * Hkv <= 4 else 256)
+
+
+def test_the_side_of_the_line_that_the_gpu_tests_reckon_with(model):
+    r = np.random.default_rng(3)
+    cases = [(B, g * Hkv, Hkv, int(n)) for B in (1, 2, 4, 5, 16, 67, 130) for g in range(1, 9) for Hkv in (1, 2, 3, 8)
+             for n in [*r.integers(B, 700 * B, 20), 32 * B * 32, 32 * B * 32 + 1]]
+    got = [bool(x["one"]) for x in model(lines=[(B, Hq, Hkv, 64, n, n, n, 10, 4) for B, Hq, Hkv, n in cases])]
+    assert got == [in_one_launch(*c) for c in cases] and 500 < sum(got) < len(got) - 500
+    # the batches of the GPU test that lie on the line and one row beyond it
+    assert in_one_launch(4, 12, 2, 4 * 640) and not in_one_launch(4, 12, 2, 4 * 640 + 1)
+    assert in_one_launch(4, 8, 1, 4 * 2048) and not in_one_launch(4, 8, 1, 4 * 2048 + 1)
+
+
 def _trajectories(B, Hq, Hkv, d, rows, P, c):
     return [(B, Hq, Hkv, d, sum(rows), max(rows), r, p, x) for r, p, x in zip(rows, P, c)]
 
