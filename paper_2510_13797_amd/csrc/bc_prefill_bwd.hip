@@ -58,6 +58,7 @@ struct BwdParams {
   int64_t total_rows;
   int32_t Hq, Hkv, g;
   HeadTiling tiling;    // dq kernel
+  int32_t dq_rows;      // rows of its grid
   int32_t npairs;       // (trajectory, KV head) pairs
   int32_t pstride;      // see pair_stride()
   float scale;
@@ -645,13 +646,13 @@ __global__ __launch_bounds__(256) void prefill_bwd_delta_kernel(BwdParams p) {
   }
 }
 template <int D>
-__global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_joined_kernel(BwdParams p, int dq_rows) {
+__global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_joined_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>() > dkv_lds<D>() ? dq_lds<D>() : dkv_lds<D>()];
-  if ((int)blockIdx.y < dq_rows * p.tiling.splits) {
+  if ((int)blockIdx.y < p.dq_rows * p.tiling.splits) {
     const int by = blockIdx.y / p.tiling.splits;
-    dq_block<D, false, true>(p, lds, blockIdx.x, blockIdx.y - by * p.tiling.splits, by, dq_rows);
+    dq_block<D, false, true>(p, lds, blockIdx.x, blockIdx.y - by * p.tiling.splits, by, p.dq_rows);
   } else {
-    dkv_block<D>(p, lds, blockIdx.y - dq_rows * p.tiling.splits);
+    dkv_block<D>(p, lds, blockIdx.y - p.dq_rows * p.tiling.splits);
   }
 }
 
@@ -715,7 +716,7 @@ static void launch_bwd(const BwdParams& p, bool joined, bool wide, dim3 dq_grid,
     const int64_t n = ((int64_t)max_rows * p.Hq + kDeltaRows - 1) / kDeltaRows;
     prefill_bwd_delta_kernel<D><<<dim3(p.npairs / p.Hkv, (int)(n < 1024 ? n : 1024)), 256, 0, hs>>>(p);
     const dim3 grid(p.pstride, dq_grid.y * p.tiling.splits + dkv_grid.y);
-    prefill_bwd_joined_kernel<D><<<grid, kTileWaves * 64, 0, hs>>>(p, (int)dq_grid.y);
+    prefill_bwd_joined_kernel<D><<<grid, kTileWaves * 64, 0, hs>>>(p);
     return;
   }
   if (wide) prefill_bwd_dq_kernel<D, true><<<dq_grid, kTileWaves * 64, 0, hs>>>(p);
@@ -764,6 +765,7 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   p.tiling = head_tiling(p.g);
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
+  p.dq_rows = dq_grid.y;
   p.band = band_splits(shape->B, shape->Hq, shape->Hkv, total_rows, p.splits);
   const int key_blocks = (max_rows + kDkvKeys - 1) / kDkvKeys;
   const dim3 dkv_grid(p.pstride, (int)dkv_grid_rows(p.npairs, p.most, p.band, key_blocks));

@@ -316,6 +316,29 @@ def test_prefill_kernels_set_m0_in_front_of_every_load_to_lds(name, kernels, tmp
             assert not any(l.startswith(("scratch_", "buffer_")) for l in body), text[s][:80]
 
 
+def _arguments(text):
+    """Of every kernel: (offset, kind) of its arguments, from the metadata the compiler leaves behind the code."""
+    found, args = {}, []
+    for l in text[next(i for i, l in enumerate(text) if l.startswith("amdhsa.kernels:")):]:
+        m = re.match(r"(    | {6}- | {8})\.(offset|value_kind|name): +(\S+)$", l)
+        if l.startswith("    .args:"):
+            args = []
+        elif m and m.group(2) == "offset":
+            args.append([int(m.group(3)), None])
+        elif m and m.group(2) == "value_kind":
+            args[-1][1] = m.group(3)
+        elif m and m.group(1) == "    ":
+            found[m.group(3)] = [tuple(a) for a in args if not a[1].startswith("hidden_")]
+    return found
+
+
+@pytest.mark.parametrize("name,count", [("bc_prefill.hip", 8), ("bc_prefill_bwd.hip", 11)])
+def test_kernels_that_read_tables_of_their_arguments_have_one_argument(name, count, tmp_path):
+    # they find the tables at a fixed place behind the start of the argument segment, where their parameters lie
+    kernels = {k: a for k, a in _arguments(_assembly(name, tmp_path)).items() if "Params" in k}
+    assert len(kernels) == count and all(a == [(0, "by_value")] for a in kernels.values()), kernels
+
+
 def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
     text = _assembly("bc_decode.hip", tmp_path)
     starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc\d\ddecode_(lds|lds_cut|valu)_kernel\w+:", l)]
