@@ -264,16 +264,19 @@ def test_checker_flags_a_copy_of_an_inflight_register():
     assert got == ["s_waitcnt vmcnt(4)" + HAND, "landed v[62:65]" + HAND, "v_mov_b32_e32 v1, v62"]
 
 
+SET_M0 = r"s_mov_b32 m0, (s\d+|vcc_lo|vcc_hi)$"
+
+
 def check_m0(body):
     """M0 (the LDS address of a DMA load) is set by the hand-written sequence itself, right in front of
     every such load, and nothing else in the kernel touches it.  -> number of such loads"""
     n = 0
     for i, l in enumerate(body):
         if l.startswith("global_load_lds"):
-            assert body[i - 2].startswith("s_mov_b32 m0, s") and body[i - 1].startswith("s_nop"), body[i - 2:i + 1]
+            assert re.match(SET_M0, body[i - 2]) and body[i - 1].startswith("s_nop"), body[i - 2:i + 1]
             n += 1
         elif re.search(r"\bm0\b", l):
-            assert l.startswith("s_mov_b32 m0, s") and body[i + 2].startswith("global_load_lds"), body[i:i + 3]
+            assert re.match(SET_M0, l) and body[i + 2].startswith("global_load_lds"), body[i:i + 3]
     return n
 
 
@@ -292,17 +295,19 @@ def _assembly(name, tmp_path):
 
 def test_m0_check_flags_other_uses():
     load = ["s_mov_b32 m0, s4", "s_nop 0", "global_load_lds_dwordx4 v1, s[2:3]"]
-    assert check_m0(load + load) == 2
-    for bad in (load[1:], load[:1] + load[2:], ["s_mov_b32 m0, s4", "v_mov_b32_e32 v1, v2"] + load, ["s_add_i32 s3, m0, 1"] + load):
+    assert check_m0(load + load) == 2 and check_m0(["s_mov_b32 m0, vcc_lo"] + load[1:]) == 1
+    for bad in (load[1:], load[:1] + load[2:], ["s_mov_b32 m0, 0"] + load[1:], ["s_mov_b32 m0, s4", "v_mov_b32_e32 v1, v2"] + load, ["s_add_i32 s3, m0, 1"] + load):
         with pytest.raises(AssertionError):
             check_m0(["s_nop 0", "s_nop 0"] + bad + ["s_nop 0", "s_nop 0"])
 
 
-@pytest.mark.parametrize("name,kernels", [("bc_prefill.hip", {"prefill_kernel": 8}),
-                                          ("bc_prefill_bwd.hip", {"prefill_bwd_dq_kernel": 4, "prefill_bwd_dkv_kernel": 2})])
+# Instantiations, and workgroups of four waves that share a compute unit at d = 128 and 64: what the rules of the launches reckon with
+@pytest.mark.parametrize("name,kernels", [("bc_prefill.hip", {"prefill_kernel": (8, 3, 4)}),
+                                          ("bc_prefill_bwd.hip", {"prefill_bwd_dq_kernel": (4, 2, 3), "prefill_bwd_dkv_kernel": (2, 3, 4),
+                                                                  "prefill_bwd_joined_kernel": (2, 2, 3)})])
 def test_prefill_kernels_set_m0_in_front_of_every_load_to_lds(name, kernels, tmp_path):
     text = _assembly(name, tmp_path)
-    for kernel, count in kernels.items():
+    for kernel, (count, wide, narrow) in kernels.items():
         starts = [i for i, l in enumerate(text) if re.match(r"^_ZN2bc\d\d%s\w+:" % kernel, l)]
         assert len(starts) == count, (kernel, len(starts))
         for s in starts:
@@ -314,6 +319,8 @@ def test_prefill_kernels_set_m0_in_front_of_every_load_to_lds(name, kernels, tmp
             # no hand-written load has a destination register, and nothing of the tile loop lives in scratch
             assert all("load_lds" in l for l in marked if l.endswith(HAND) and l.startswith("global_load")), text[s][:80]
             assert not any(l.startswith(("scratch_", "buffer_")) for l in body), text[s][:80]
+            waves = next(int(x.group(1)) for x in (re.match(r"; Occupancy: (\d+)", l) for l in text[e:]) if x)
+            assert waves >= (wide if "ILi128E" in text[s] else narrow), (text[s][:80], waves)
 
 
 def _arguments(text):
