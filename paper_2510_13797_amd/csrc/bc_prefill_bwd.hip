@@ -493,7 +493,7 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
   kept_key[64] = last;
   kept_key[128] = !key_ok ? -1 : split >= 0 ? sum_at : jkey;
   constexpr int EARLY = D == 64 ? NJ : 0;       // column operands the keys' waves ask for in front of the second barrier
-  constexpr int SLOTS = 4 * NJ, PRE = KS < 8 ? KS : 8;        // matrix instructions of a column product; steps row operands are ahead
+  constexpr int SLOTS = 4 * NJ;                 // matrix instructions of a column product
 
   // The order of a pass is written out (step_fence(): nothing is moved across): LDS operands are asked for several instructions
   // ahead, and both kinds of wave have a loop of their own.  Forward and gradients, us a pass: one trajectory of 2100 rows 80.1 -> 77.2, one of
@@ -537,12 +537,11 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
           x = f32x16_t{0.f};
         }
 #pragma unroll
-        for (int i = 0; i < PRE; ++i) row_of(i);
+        for (int i = 0; i < KS; ++i) row_of(i);         // (all of them in front of the first product)
         step_fence();
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
           x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i], op[i], x, 0, 0, 0);
-          if (i + PRE < KS) row_of(i + PRE);
           if (!KEYS && i >= KS - 4) stats(i - KS + 4);
           if (KEYS && i >= KS - EARLY) c[i - KS + EARLY] = col_of(i - KS + EARLY);
           step_fence();
