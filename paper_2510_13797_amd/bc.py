@@ -503,10 +503,10 @@ class Runtime:
             active = self.mask(active)
         if out is None:
             out = self.out
-        st = _lib.bc_decode_step(_byref(self.shape), _byref(self.cache), k.data_ptr(), v.data_ptr(), q.data_ptr(),
-                                 out.data_ptr(), None if bk is None else bk.data_ptr(), None if bv is None else bv.data_ptr(),
-                                 None if active is None else active.data_ptr(), self.ws.data_ptr(), self.ws_bytes,
-                                 _stream_ptr())
+        st = (_lib or load()).bc_decode_step(_byref(self.shape), _byref(self.cache), k.data_ptr(), v.data_ptr(), q.data_ptr(),
+                                             out.data_ptr(), None if bk is None else bk.data_ptr(),
+                                             None if bv is None else bv.data_ptr(), None if active is None else active.data_ptr(),
+                                             self.ws.data_ptr(), self.ws_bytes, _stream_ptr())
         if st != BC_OK:
             _check(st)
         return out

@@ -85,3 +85,52 @@ def test_product_does_not_import_the_oracle():
         if f.endswith(".py"):
             src = open(os.path.join(ROOT, "oracle", f)).read()
             assert "paper_2510_13797_amd" not in src and "libbc" not in src, f
+
+
+def test_decode_step_hands_the_library_what_the_other_steps_do(monkeypatch):
+    # the call per token marshals its arguments by itself: the same as through bc_decode_step, also where the module has been loaded
+    # again since the object was made
+    import ctypes as C
+    import numpy as np
+    import torch
+    from paper_2510_13797_amd import bc
+    calls = []
+
+    class Library:
+        def bc_decode_step(self, *args):
+            calls.append([C.addressof(a._obj) if type(a).__name__ == "CArgObject" else a for a in args])
+            return bc.BC_OK
+
+    monkeypatch.setattr(bc, "load", lambda: Library())
+    monkeypatch.setattr(bc, "_stream_ptr", lambda: 7)
+    rt = bc.Runtime.__new__(bc.Runtime)
+    rt.torch, rt.device, rt.dtype, rt.ws_bytes = torch, torch.device("cpu"), "bf16", 40
+    rt.shape, rt.cache = bc.bc_shape(2, 4, 1, 64, bc.BC_BF16, 0.125), bc.bc_cache()
+    rt.out, rt.ws = torch.empty(2, 4, 64), torch.empty(40, dtype=torch.uint8)
+    k, v, bk, bv = (torch.zeros(2, 1, 64, dtype=torch.bfloat16) for _ in range(4))
+    q, out, active = torch.zeros(2, 4, 64, dtype=torch.bfloat16), torch.empty(2, 4, 64), torch.ones(2, dtype=torch.uint8)
+    p = bc._ptr
+    for lib in (Library(), None):
+        monkeypatch.setattr(bc, "_lib", lib)
+        for b in ((None, None), (bk, bv)):
+            for a in (None, active):
+                for o in (None, out):
+                    calls.clear()
+                    assert rt.decode_step(k, v, q, *b, a, o) is (rt.out if o is None else o)
+                    bc.bc_decode_step(rt.shape, rt.cache, p(k), p(v), p(q), p(rt.out if o is None else o), p(b[0]), p(b[1]), p(a), p(rt.ws), 40, 7)
+                    assert calls[0] == calls[1]
+        # host arrays are copied to the device first, beside tensors too
+        host = np.zeros((2, 1, 64), np.float32)
+        calls.clear()
+        rt.decode_step(host, v, q, host, bv, np.ones(2))
+        assert calls[0][3:5] == [v.data_ptr(), q.data_ptr()] and calls[0][7] == bv.data_ptr()
+        assert all(isinstance(x, int) for x in calls[0][2:10])
+    monkeypatch.setattr(Library, "bc_decode_step", lambda self, *args: bc.BC_ERR_ARG)
+    monkeypatch.setattr(bc, "_lib", Library())
+    monkeypatch.setattr(Library, "bc_status_str", lambda self, st: b"argument", raising=False)
+    try:
+        rt.decode_step(k, v, q)
+    except bc.BcError:
+        pass
+    else:
+        raise AssertionError("an error of the library has to be raised")
