@@ -59,6 +59,7 @@ struct PrefillParams {
   HeadTiling tiling;
   int32_t npairs;     // (trajectory, KV head) pairs
   int32_t pstride;    // pairs per head split in the grid, see pair_stride()
+  int32_t turn;       // see pair_turn()
   float qscale;       // softmax scale * log2(e)
   InlineTables tab;
 };
@@ -88,7 +89,7 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
   constexpr int OW = D / 2;                   // output columns that go through LDS at a time
   static_assert(LDS >= kTileWaves * 32 * OW * 4, "the output tiles fit the ring's LDS");
 
-  const int hh = blockIdx.x / p.pstride, pair = pair_in_turn(blockIdx.x - hh * p.pstride, p.pstride, blockIdx.y);
+  const int hh = blockIdx.x / p.pstride, pair = pair_in_turn(blockIdx.x - hh * p.pstride, p.pstride, p.turn, blockIdx.y);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
@@ -414,6 +415,7 @@ static int32_t prefill_forward(PrefillParams& p, const bc_shape* shape, const vo
   p.tiling = head_tiling(p.g);
   p.npairs = shape->Hkv * shape->B;
   p.pstride = pair_stride(p.npairs);
+  p.turn = pair_turn(p.pstride);
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const dim3 grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
   const bool wide = rows_span_4gb(max_rows, shape);

@@ -61,6 +61,7 @@ struct BwdParams {
   int32_t dq_rows;      // rows of its grid
   int32_t npairs;       // (trajectory, KV head) pairs
   int32_t pstride;      // see pair_stride()
+  int32_t turn;         // see pair_turn()
   float scale;
   float qscale;         // scale * log2(e)
   InlineTables tab;
@@ -104,7 +105,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, char* lds, int at_x
   static_assert(LOOK == 3, "the counts of begin_pass");
   static_assert(dq_lds<D>() >= kTileWaves * 32 * (D / 2) * 4, "the gradient tiles fit the ring's LDS");
 
-  const int pair = pair_in_turn(at_x, p.pstride, blockIdx.y);
+  const int pair = pair_in_turn(at_x, p.pstride, p.turn, blockIdx.y);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
@@ -360,7 +361,7 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
   static_assert(KEYS_AT >= OUT && KEYS_AT + kTileWaves * 768 == dkv_lds<D>(), "the gradient tiles fit");
   // grid: x = (trajectory, KV head), y = key block; the long dense blocks of every trajectory
   // are dispatched before any short one
-  const int pair = pair_in_turn(blockIdx.x, p.pstride, blockIdx.y);
+  const int pair = pair_in_turn(blockIdx.x, p.pstride, p.turn, blockIdx.y);
   if (pair >= p.npairs) return;
   const int kvh = pair % p.Hkv, b = pair / p.Hkv;
   const Trajectory traj = trajectory(p, b);
@@ -761,6 +762,7 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   hipStream_t hs = as_stream(stream);
   p.npairs = shape->B * shape->Hkv;
   p.pstride = pair_stride(p.npairs);
+  p.turn = pair_turn(p.pstride);
   p.tiling = head_tiling(p.g);
   const int rows_wg = kTileRows * p.tiling.row_blocks;
   const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);

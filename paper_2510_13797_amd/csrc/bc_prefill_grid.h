@@ -54,8 +54,10 @@ inline int pair_stride(int npairs) { return npairs % 8 == 0 || npairs > 64 ? (np
 // 60).  An odd number comes to all four in turn by itself, and changing places
 // would undo that (130 trajectories, 129 of some 50 rows and one of 14,046, 5/1 heads, ratio 4: forward 590 us, 469 at the same place, gradients 2503 and
 // 2067; 27 of which one has 956 rows, 32/8 heads: forward 31.8 and 27.0).
-BC_HOST_DEVICE int pair_in_turn(int at, int pstride, unsigned row) {
-  return pstride % 16 == 0 ? (int)((at + 8u * (pstride == 16 ? row / 2 : row)) % (unsigned)pstride) : at;
+// pair_turn(): eight times the places of a row, which the launch works out (chosen in the kernel: 383.4 us for that forward, 381.9 so, 381.2 before).
+inline int pair_turn(int pstride) { return pstride % 16 ? 0 : pstride == 16 ? 4 : 8; }
+BC_HOST_DEVICE int pair_in_turn(int at, int pstride, int turn, unsigned row) {
+  return turn ? (int)((at + (row * (unsigned)turn & ~7u)) % (unsigned)pstride) : at;
 }
 
 // ---------------------------------------------------------------------------

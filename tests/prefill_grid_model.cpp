@@ -31,7 +31,7 @@ static void pairs() {
       bool once = true;
       for (int y = 0; y < rows; ++y)
         for (int x = 0; x < splits * stride; ++x) {
-          const int pair = pair_in_turn(x % stride, stride, y);
+          const int pair = pair_in_turn(x % stride, stride, pair_turn(stride), y);
           const long long linear = (long long)y * splits * stride + x;
           if (pair < 0 || pair >= stride || (int)engines[pair].size() != y * splits + x / stride) { once = false; continue; }
           engines[pair].push_back((int)(linear / 8 % 4));
