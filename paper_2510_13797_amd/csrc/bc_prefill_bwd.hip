@@ -55,6 +55,7 @@ struct BwdParams {
   int32_t splits;       // rows of partial sums there is room for, per row, of dk and of dv
   int32_t most;         // most workgroups that share a dense key block
   int32_t band;         // workgroups that share a response block (see band_splits), at most `splits`
+  int32_t least;        // tiles of one of more than `splits` parts
   int64_t total_rows;
   int32_t Hq, Hkv, g;
   HeadTiling tiling;    // dq kernel
@@ -336,7 +337,7 @@ struct KeyParts {
     tokens = t.rows - prompt - beacons;
     prompt_blocks = (prompt + kDkvKeys - 1) / kDkvKeys;
     dense_blocks = prompt_blocks + (beacons + kDkvKeys - 1) / kDkvKeys;
-    parts = dense_parts(p.splits, p.most, p.band, p.npairs, p.g, p.D, t.rows, prompt + beacons, dense_blocks);
+    parts = dense_parts(p.splits, p.most, p.band, p.least, p.npairs, p.g, p.D, t.rows, prompt + beacons, dense_blocks);
   }
   // first row of sum `of` of the dense keys (the tokens) of a trajectory; of: 2 * part + (0 for dk, 1 for dv)
   __device__ __forceinline__ int64_t dense_row(const BwdParams& p, int64_t off0, int of) const {
@@ -768,6 +769,7 @@ static int32_t prefill_backward(BwdParams& p, const bc_shape* shape, const void*
   const dim3 dq_grid(p.tiling.splits * p.pstride, (max_rows + rows_wg - 1) / rows_wg);
   p.dq_rows = dq_grid.y;
   p.band = band_splits(shape->B, shape->Hq, shape->Hkv, total_rows, p.splits);
+  p.least = least_tiles(p.g, p.band);
   const int key_blocks = (max_rows + kDkvKeys - 1) / kDkvKeys;
   const dim3 dkv_grid(p.pstride, (int)dkv_grid_rows(p.npairs, p.most, p.band, key_blocks));
   const bool wide = rows_span_4gb(max_rows, shape), joined = in_one_launch(shape->B, p.npairs, p.tiling, total_rows);

@@ -107,22 +107,30 @@ BC_HOST_DEVICE int most_parts(int splits) { return splits == kMostSplits ? kMost
 // one in eight.  Cut by that alone, 4 uncompressed trajectories of 2200 rows, 8/8 heads, had six parts of 1120 blocks and took
 // 376 us, 318 whole.)
 // A trajectory has room for `splits` sums of every row, and the fewer of its rows are dense the more parts fit, up to `most`.  The n-th part takes
-// some tiles / n^2 off the chain and costs one more sum of all dense keys: worth it up to kSumBytes for a tile, and for parts of kLeastTiles
-// tiles.  Both numbers from 600 batches of up to 48 trajectories, each with at most 8, 10, 12, 14 and 16 parts; of 150 others, the gradients of which take
-// 0.69 to 1.09 of the time with at most eight (mean 0.967).  By parts of eight tiles and 18 MB together, which is what one batch
-// had said, it was 0.70 to 1.21 (0.982): ten of 450 to 1153 rows, 4/1 heads, d = 64, 46.4 us with eight, 47.5 now, 52.5 so; one of 1229, 24/8 heads 52.9, 53.2
-// and 59.2.
-constexpr int kLeastTiles = 12;
+// some tiles / n^2 off the chain and costs one more sum of all dense keys: worth it up to kSumBytes for a tile, and for parts of eight
+// tiles that are no shorter than a part of a response block (least_tiles()).  Both from 600 batches of up to 48 trajectories, each with at
+// most 8, 10, 12, 14 and 16 parts; of 234 others, the gradients of which take 0.68 to 1.10 of the time with at most eight
+// (mean 0.964).  By parts of eight tiles and 18 MB together, which is what one batch had said, it was 0.69 to 1.20 (0.987): ten of 450 to 1153 rows,
+// 4/1 heads, d = 64, 49.4 us with eight, 50.0 now, 52.6 so; one of 1229, 24/8 heads, 50.5, 50.4 and 57.1.  (The root and the quotient exactly, in front of
+// every workgroup's first load: 0.2 us of a small pass.)
 constexpr float kSumBytes = 0.5e6f;
-BC_HOST_DEVICE int dense_parts(int splits, int most, int band, int npairs, int g, int D, int rows, int dense_keys, int dense_blocks) {
+inline int least_tiles(int g, int band) { return 3 * ((g + band - 1) / band) > 8 ? 3 * ((g + band - 1) / band) : 8; }
+BC_HOST_DEVICE float approximate_root(float a, float b) {        // of a / b
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_sqrtf(a * __builtin_amdgcn_rcpf(b));
+#else
+  return sqrtf(a / b);
+#endif
+}
+BC_HOST_DEVICE int dense_parts(int splits, int most, int band, int least, int npairs, int g, int D, int rows, int dense_keys, int dense_blocks) {
   const int some = dense_blocks < 1 ? 1 : dense_blocks > kDkvAtOnce ? kDkvAtOnce : dense_blocks, blocks = some * npairs;
   const int n = (kDkvAtOnce + blocks - 1) / blocks, wanted = n < 2 && g > 1 ? 2 : n;
   int fit = splits;                // (room for `splits` there always is: the tokens have band <= splits)
   if (most > splits) {
     const int keys = dense_keys < 1 ? 1 : dense_keys;
     const int room = (splits * rows - (band > 1 ? band * (rows - dense_keys) : 0)) / keys;
-    const int tiles = rows / kTileRows * g, long_enough = tiles / kLeastTiles;
-    const int few = (int)sqrtf(kSumBytes * tiles / (8.f * D * npairs * keys));
+    const int tiles = rows / kTileRows * g, long_enough = tiles / least;
+    const int few = (int)approximate_root(kSumBytes * tiles, 8.f * D * npairs * keys);
     int more = room < few ? room : few;
     more = more < long_enough ? more : long_enough;
     more = more < most ? more : most;

@@ -61,7 +61,7 @@ static void parts(const long long* a) {
   const int prompt = c > 0 && P < rows ? P : rows, beacons = c > 0 ? (rows - prompt) / (c + 1) : 0, keys = prompt + beacons;
   const auto blocks = [](int n) { return (n + kDkvKeys - 1) / kDkvKeys; };
   const int dense = blocks(prompt) + blocks(beacons);
-  const int n = dense_parts(splits, most, band, B * Hkv, g, d, rows, keys, dense);
+  const int n = dense_parts(splits, most, band, least_tiles(g, band), B * Hkv, g, d, rows, keys, dense);
   std::printf("splits=%d parts=%d band=%d tiles=%d bytes=%lld sums=%lld room=%lld groups=%d grid=%lld one=%d\n", splits, n, band, rows / kTileRows * g,
               8ll * d * B * Hkv * keys,
               (long long)(n > 1 ? n * keys : 0) + (band > 1 ? band * (rows - keys) : 0), splits > 1 ? (long long)splits * rows : 0,
