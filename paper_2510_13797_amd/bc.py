@@ -490,7 +490,7 @@ class Runtime:
                                  1 if require_full_window else 0, _stream_ptr()))
 
     # A small step's kernel takes 5 us and its call took 7: tensors go to the library without a helper's frame for each of them
-    # (16 steps of 2 sequences of 32 to 176 rows, 4/1 heads, one by one: 115 -> 110 us).
+    # (16 steps of 2 sequences of 32 to 176 rows, 4/1 heads, one by one: 118 -> 110 us, where runs differ by as much).
     def decode_step(self, k, v, q, bk=None, bv=None, active=None, out=None):
         Tensor = self.torch.Tensor
         if not (isinstance(k, Tensor) and isinstance(v, Tensor) and isinstance(q, Tensor)):

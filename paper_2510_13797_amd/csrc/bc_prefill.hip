@@ -20,8 +20,9 @@
 // so that every row is written to HBM in bursts.  Head dimension 128 or 64 (a template parameter).
 //
 // What bounds it: the matrix cores under the card's power limit.  16 trajectories of 8688 rows, 12/2
-// heads, d = 128: 724 GFLOP of MFMA work are issued in 0.68 ms (1.06 PFLOP/s, 55 % of the cycles at
-// the 1.89 GHz the clock falls to; a library product of 16384^3 runs at 1.34 PFLOP/s here).  The form
+// heads, d = 128: 724 GFLOP of MFMA work are issued in 0.76 ms in a training pass, 0.81 in calls behind one
+// another and 0.68 in the fastest (0.96, 0.89 and 1.06 PFLOP/s; matrix pipe busy 61 % of the cycles at the 1.7 GHz the
+// clock falls to; a library product of 16384^3 runs at 1.34 PFLOP/s here).  The form
 // before this one, 16x16x32 MFMA with 16 rows of three heads per wave and two waves per SIMD, took
 // 0.80-0.85 ms.  Measured on the way, each against its neighbour in one session:
 //  - 32x32x16 instead of 16x16x32: half the operand reads per product, and vector work of other waves
@@ -307,7 +308,7 @@ __device__ __forceinline__ void prefill_rows(const PrefillParams& p, char* lds) 
 // EITHER: the form the conversion pass found V to fit, one of the two by a branch that is uniform over the launch.  (As two
 // launches, of which one left at its first instruction, with a third that cleared the verdict and a fourth that stored the tables, a
 // call took 30 us where its kernels' work is 10 to 15; now 19.  Large launches run at the power limit: 27,109 rows 489 us, both.
-// Both forms in one kernel keep 25 scalar registers in vector lanes, and at d = 64 four waves a SIMD where the half-precision form alone had five.  That
+// Both forms in one kernel keep 24 to 30 scalar registers in vector lanes, and at d = 64 four waves a SIMD where the half-precision form alone had five.  That
 // costs nothing that shows: read afresh in each form, without spills, 16 trajectories of 8688 rows, d = 64, 367 us and 363, 27,109 rows of 32/8 heads 287 and 287,
 // d = 128 484 and 486, three short ones 19.4 to 20.8 and 19.9.)
 template <int D, bool EITHER, bool WIDE>

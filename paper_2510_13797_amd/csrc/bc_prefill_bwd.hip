@@ -17,7 +17,7 @@
 //                response tokens  -> only the rows up to the end of their window (masked band)
 //              so the dense part of the work is spent on the ~P + S/(c+1) keys every row sees.
 //              A dense block is long (every later row x every head); it is cut into parts (see
-//              KeyParts), which write partial dK/dV to the workspace, and a third kernel adds
+//              dense_parts()), which write partial dK/dV to the workspace, and a third kernel adds
 //              them in a fixed order.  Response blocks are cut only where the chip is not full (band_splits)
 //              and store their result directly otherwise.
 //
@@ -27,11 +27,11 @@
 // (bc_prefill_tiles.h).
 //
 // What bounds both: the card's power limit on large launches, the chain of a tile's steps on small ones.  On 16 trajectories of 8688
-// rows (12/2 heads, d = 128) the dkv kernel issues 1458 GFLOP of MFMA work in 1.48 ms, the dq kernel 947 in 1.03 (under the profiler; both with the
-// matrix pipe half busy at 1.75 to 1.8 GHz; a loop of such products alone runs at 1.75 PFLOP/s and 1.75 GHz, with the operand reads and
+// rows (12/2 heads, d = 128) the dkv kernel issues 1458 GFLOP of MFMA work in 1.52 ms, the dq kernel 947 in 1.06 (averages under the profiler; both with the
+// matrix pipe 55 to 58 % busy at 1.75 to 1.8 GHz; a loop of such products alone runs at 1.75 PFLOP/s and 1.75 GHz, with the operand reads and
 // vector work of the dq kernel at 1.3): fewer cycles give a lower clock and half of what they should.  The forms before, 16x16x32
 // MFMA with 16 rows of two heads or 16 keys per wave and tiles read at half rate by bank conflicts, took 1.24 and 1.83 ms.
-// A forward and backward pass of that batch takes 3125 to 3170 us (cards differ by 3 %), of three trajectories of 336 to 795 rows 54.
+// A forward and backward pass of that batch takes 3100 to 3210 us (cards differ by 3 %), of three trajectories of 336 to 795 rows 52.
 #include "bc_prefill_tiles.h"
 
 namespace bc {
@@ -445,7 +445,7 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
   // the trajectory back to their own keys, start together (they are neighbours in dispatch order, on the same XCD) and so walk
   // the same rows at the same time: the later readers of a tile find it in the L2.  (Head by head and part behind part, blocks of different
   // length were soon at different heads: 16 trajectories of 8688 rows read 5.4 GB past the L2 and take 3218 us a
-  // pass, 3.9 GB and 3190 now.)
+  // pass, 3.7 GB and 3190 now.)
   const int ntile = (re - rs) / kTileRows + 1;       // row tiles per head
   const int stride = split >= 0 ? parts : 1, first = split >= 0 ? split : 0;
   const int count = (ntile * p.g - first + stride - 1) / stride;       // tiles of this workgroup
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(Bwd
 
 // Launches that leave the chip idle are a chain of kernels that each wait for the one before, and the dkv kernel waits for nothing but
 // Delta.  So Delta has a kernel of its own there, and the workgroups of both kernels go out together, dq first: three trajectories of 336 to
-// 795 rows, 12/2 heads, dq 18 and dkv 18 us become 6 and 26 under the profiler, a pass of forward and gradients 58.9 -> 54.0.  Delta's kernel is
+// 795 rows, 12/2 heads, dq 18 and dkv 18 us become 6 and 27 under the profiler, a pass of forward and gradients 58.9 -> 54.0.  Delta's kernel is
 // the first touch of `out`: with 64 rows a workgroup, four loads of a thread out at once, it takes 6.4 us, with 16 rows 6.2.
 constexpr int kDeltaRows = 16;        // rows of one head that a workgroup takes at a time: sixteen lanes a row
 template <int D>

@@ -64,7 +64,7 @@ BC_HOST_DEVICE int pair_in_turn(int at, int pstride, int turn, unsigned row) {
 // what the backward's key blocks are cut into
 // ---------------------------------------------------------------------------
 constexpr int kDkvKeys = 64;          // keys of a workgroup: two pairs of waves with 32 keys each
-constexpr int kDkvAtOnce = 3 * 256;   // workgroups that run at once
+constexpr int kDkvAtOnce = 3 * 256;   // workgroups that run at once at d = 128; at 64 it would be four a compute unit, which no rule here uses
 constexpr int kMostSplits = 8, kMostParts = 16;
 
 // Partial sums the workspace has room for, of every row: what dense_parts() chooses from.
@@ -154,8 +154,9 @@ inline int64_t dkv_grid_rows(int npairs, int most, int band, int key_blocks) {
 // ---------------------------------------------------------------------------
 // Whether dq and dkv blocks go out in one launch: where the dq kernel's workgroups (of trajectories of the mean length) are no more than
 // the compute units, and for four pairs and fewer, whose dkv kernel does not fill the chip either, no more than run at once.  Otherwise the
-// chip has work for one kernel after the other, with three dkv workgroups a compute unit in place of two and none for Delta.  Forward and
-// gradients, us a pass, in two launches and in one, ratio 16, 4, 0 (those rows of a ratio that lie on the other side of the line in brackets):
+// chip has work for one kernel after the other, with three dkv workgroups a compute unit in place of two (d = 64: four, three) and none
+// for Delta.  712 batches in one launch, most of them of one or two long trajectories beside short ones (which the mean does not tell), take 0.73
+// of the time of the gradients before there was one, the worst 1.04.  Forward and gradients, us a pass, in two launches and in one, ratio 16, 4, 0 (those rows of a ratio that lie on the other side of the line in brackets):
 //   trajectories x tokens, heads   dq workgroups
 //   1 x 500, 12/2                     54, 60,  48    49.1 41.0 | 53.4  43.3 |  67.0  53.0
 //   1 x 500, 8/8                      40, 40,  32    46.2 39.2 | 51.2  39.4 |  62.8  45.2
