@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
+#include <utility>
 
 #include "../../include/bc.h"
 
@@ -178,6 +180,30 @@ __device__ __forceinline__ float group_allreduce_sum(float x) {
   if (LPR >= 32) x += __shfl_xor(x, 16, 64);
   return x;
 }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  int y = __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xf, 0xf, true);
+  return fmaxf(x, __int_as_float(y));
+}
+template <int LPR>
+__device__ __forceinline__ float group_allreduce_max(float x) {
+  static_assert(LPR == 8 || LPR == 16, "lanes per row");
+  x = dpp_max<kDppXor1>(x);
+  x = dpp_max<kDppXor2>(x);
+  x = dpp_max<kDppHalfMirror>(x);
+  return LPR == 16 ? dpp_max<kDppMirror>(x) : x;
+}
+// Every lane gets lane K of its row of 16.
+template <int K>
+__device__ __forceinline__ float lane_of_row(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + K, 0xf, 0xf, true));
+}
+// f(0), f(1), ... f(N - 1), each with a number that is a constant
+template <int N, typename F, int... K>
+__device__ __forceinline__ void each_of(const F& f, std::integer_sequence<int, K...>) { (f(std::integral_constant<int, K>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void each_of(const F& f) { each_of<N>(f, std::make_integer_sequence<int, N>{}); }
 
 // All-reduce over the four 16-lane rows of a wave (lane l with l ^ 16 and l ^ 32) by the two
 // row-swap instructions of gfx950 instead of two LDS-routed shuffles.  permlane16_swap(x, x)

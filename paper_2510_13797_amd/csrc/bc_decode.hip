@@ -50,7 +50,7 @@ struct DecodeParams {
   const char* q;
   float* out;
   const uint8_t* active;
-  float* part;         // [pairs][max_chunks][Gp*D + kPartTail]: o, then running max (log2 units) and denominator
+  float* part;         // [pairs][max_chunks][Gp*D + kPartTail]: o, then (running max in log2 units, denominator) of every head
   int32_t* arrivals;   // chunks of a pair whose partial is written; zero between launches
   int64_t arrival_stride;     // from sequence to sequence (the pairs of a sequence are neighbours)
   // fused step (all nullable): append this token row first, evict with this beacon afterwards
@@ -77,6 +77,12 @@ struct DecodeParams {
   int32_t split_rows;  // shorter sequences stay whole
   float qscale;        // softmax scale * log2(e)
 };
+
+// Kernels that wait for one round trip after the other take the addresses of the tables as arguments of their own in front of the others, the
+// number of which (FILE_FLAGS) the hardware leaves in scalar registers: the tables are asked for by the first instructions (cut sequences: a step 0.1 us
+// shorter).  Where the first tiles are asked for before the tables are back it is no gain: they wait for the other arguments, and one counter serves both.
+#define BC_TABLE_ARGUMENTS const int32_t *tP, const int32_t *tnb, const int32_t *tw, const int32_t *tcap, const int32_t *tc, const int64_t *tbase
+constexpr int kTableArguments = 6 * 8;      // bytes
 
 struct PairInfo {
   int s, kvh, L, nchunks, chunk, row0, row_end;
@@ -134,9 +140,10 @@ __global__ __launch_bounds__(256) void sort_by_length_kernel(SortParams p) {
 // The kernel arguments span four 64-byte lines that the code below would touch one after the
 // other, each a miss of the scalar cache on the way to the first tile request: ask for all four
 // at once.
+template <int AT>
 __device__ __forceinline__ void touch_kernel_arguments() {
   typedef __attribute__((address_space(4))) const int const_int_t;
-  const_int_t* ka = (const_int_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  const_int_t* ka = (const_int_t*)__builtin_amdgcn_kernarg_segment_ptr() + AT / 4;
   static_assert(sizeof(DecodeParams) > 48 * 4, "the last line touched lies inside the arguments");
   const int a = ka[0], b = ka[16], c = ka[32], d = ka[48];
   asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d));
@@ -145,9 +152,11 @@ __device__ __forceinline__ void touch_kernel_arguments() {
 // The kernel arguments, to be read afresh: what only the end of a kernel needs holds no scalar registers before
 // (kept from the start, 38 of them went through vector lanes in front of the first tile requests: one sequence of
 // 1551 rows, 8 KV heads, 11.8 us a step instead of 10.8).
+template <int AT>
 __device__ __forceinline__ DecodeParams arguments_again() {
+  typedef __attribute__((address_space(4))) const char const_char_t;
   typedef __attribute__((address_space(4))) const DecodeParams const_params_t;
-  const_params_t* at = (const_params_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  const_params_t* at = (const_params_t*)((const_char_t*)__builtin_amdgcn_kernarg_segment_ptr() + AT);
   asm volatile("" : "+s"(at));
   return *(const DecodeParams*)at;
 }
@@ -156,10 +165,23 @@ __device__ __forceinline__ DecodeParams arguments_again() {
 // carries (KV head, slot, chunk) in its three dimensions, so that nothing has to be divided
 // before the tables can be requested; all of them are requested together.
 struct NoEarlyWork { __device__ __forceinline__ void operator()() const {} };
+// The six table entries travel through the scalar cache, requested by hand: their counter is not the vector loads' one, so work started in
+// the meantime (the first tile, when the caller has promised the slab geometry) does not have to be back before they are.
+struct TableEntries { int32_t P, nb, w, cap, c; int64_t base; };
+__device__ __forceinline__ void request_tables(const DecodeParams& p, int s, TableEntries& t) {
+  asm volatile("s_load_dword %0, %1, 0x0" : "=s"(t.P) : "s"(p.P + s) : "memory");
+  asm volatile("s_load_dword %0, %1, 0x0" : "=s"(t.nb) : "s"(p.nb + s) : "memory");
+  asm volatile("s_load_dword %0, %1, 0x0" : "=s"(t.w) : "s"(p.w + s) : "memory");
+  asm volatile("s_load_dword %0, %1, 0x0" : "=s"(t.cap) : "s"(p.cap + s) : "memory");
+  asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(t.base) : "s"(p.base + s) : "memory");
+  asm volatile("s_load_dword %0, %1, 0x0" : "=s"(t.c) : "s"(p.c + s) : "memory");
+}
+// early: the entries of sequence `slot`, requested before.
 template <typename F = NoEarlyWork>
 __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, int kvh, int chunk,
-                                              const F& while_tables_travel = F()) {
+                                              const F& while_tables_travel = F(), const TableEntries* early = nullptr) {
   PairInfo pi;
+  TableEntries t;
   int act, w;
   int s = slot;
   bool bad_order = false;
@@ -173,21 +195,13 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
   }
   pi.s = s;
   pi.kvh = kvh;
-  // The six table entries travel through the scalar cache, requested by hand: their counter is
-  // not the vector loads' one, so work started in the meantime (the first tile, when the caller
-  // has promised the slab geometry) does not have to be back before they are.
   {
-    int32_t tP, tnb, tw, tcap, tc;
-    int64_t tbase;
-    asm volatile("s_load_dword %0, %1, 0x0" : "=s"(tP) : "s"(p.P + pi.s) : "memory");
-    asm volatile("s_load_dword %0, %1, 0x0" : "=s"(tnb) : "s"(p.nb + pi.s) : "memory");
-    asm volatile("s_load_dword %0, %1, 0x0" : "=s"(tw) : "s"(p.w + pi.s) : "memory");
-    asm volatile("s_load_dword %0, %1, 0x0" : "=s"(tcap) : "s"(p.cap + pi.s) : "memory");
-    asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(tbase) : "s"(p.base + pi.s) : "memory");
-    asm volatile("s_load_dword %0, %1, 0x0" : "=s"(tc) : "s"(p.c + pi.s) : "memory");
+    // (with a dispatch order the sequence is another than the early request took it for)
+    if (early == nullptr || p.order) request_tables(p, pi.s, t);
+    else t = *early;
     while_tables_travel();
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(tP), "+s"(tnb), "+s"(tw), "+s"(tcap), "+s"(tbase), "+s"(tc) : : "memory");
-    pi.P = tP; pi.nb = tnb; w = tw; pi.cap = tcap; pi.base = tbase; pi.c = tc;
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(t.P), "+s"(t.nb), "+s"(t.w), "+s"(t.cap), "+s"(t.base), "+s"(t.c) : : "memory");
+    pi.P = t.P; pi.nb = t.nb; w = t.w; pi.cap = t.cap; pi.base = t.base; pi.c = t.c;
     // (the address of the kernel arguments keeps its registers up to here: the check of the generated code
     // tells these loads from the arguments' by them)
     asm volatile("" : : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
@@ -265,16 +279,16 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
 
 // The beacon entry of KV heads head0 .. head0 + heads - 1 goes to its slot behind the earlier beacons (the evicted
 // window's first row): by threads 0 .. threads - 1, once every reader of these heads' rows is done with them.  Four units
-// a thread are asked for before the first is stored.  FROM_LDS: the rows as request_beacon left them.
+// a thread are asked for before the first is stored.  FROM_LDS: the heads' K and V rows as request_beacon left them.
 constexpr int kBeaconBytes = 4096;
 template <int ROWB, bool FROM_LDS>
 __device__ __forceinline__ void store_beacon(const DecodeParams& p, const PairInfo& pi, int head0, int heads, int thread,
-                                             int threads, const char* lds_rows = nullptr) {
+                                             int threads, const char* lds_k = nullptr, const char* lds_v = nullptr) {
   constexpr int UPR = ROWB / 16;                   // 16-byte units per row
   const int n16 = heads * UPR;                     // 16-byte units of K (or of V)
   const int64_t src0 = (int64_t)(pi.s * p.Hkv + head0) * ROWB;
   auto unit = [&](int i) -> u32x4_t {
-    if constexpr (FROM_LDS) return *reinterpret_cast<const u32x4_t*>(lds_rows + (i << 4));
+    if constexpr (FROM_LDS) return *reinterpret_cast<const u32x4_t*>((i >= n16 ? lds_v - n16 * 16 : lds_k) + (i << 4));
     else return *reinterpret_cast<const u32x4_t*>((i >= n16 ? p.bv - n16 * 16 : p.bk) + src0 + (i << 4));
   };
   auto put = [&](int i, u32x4_t x) {
@@ -318,7 +332,7 @@ __device__ __forceinline__ void move_tables(const DecodeParams& p, const PairInf
 template <int ROWB>
 __device__ __forceinline__ void finish_step(const DecodeParams& p, const PairInfo& pi, int lane, const char* beacon = nullptr) {
   if (pi.evict_due) {
-    if (beacon != nullptr) store_beacon<ROWB, true>(p, pi, 0, p.Hkv, lane, 64, beacon);
+    if (beacon != nullptr) store_beacon<ROWB, true>(p, pi, 0, p.Hkv, lane, 64, beacon, beacon + p.Hkv * ROWB);
     else store_beacon<ROWB, false>(p, pi, 0, p.Hkv, lane, 64);
   }
   move_tables(p, pi, lane);
@@ -331,7 +345,7 @@ __device__ __forceinline__ void finish_step(const DecodeParams& p, const PairInf
 // therefore go past the caches in both directions (system scope: stores through to memory, loads from
 // it) and no cache has to be written back or invalidated: an agent-scope release in their place took 50 us.
 // A chunk's partial has its 128-byte lines to itself.
-constexpr int kPartTail = 32;        // floats behind the o rows: [Gp] maxima, [Gp] denominators, padding
+constexpr int kPartTail = 32;        // floats behind the o rows: [Gp] (maximum, denominator), padding
 
 __device__ __forceinline__ float* chunk_partial(const DecodeParams& p, const PairInfo& pi, int D, int chunk) {
   return p.part + ((int64_t)(pi.s * p.Hkv + pi.kvh) * p.max_chunks + chunk) * (p.Gp * D + kPartTail);
@@ -365,80 +379,103 @@ __device__ __forceinline__ bool last_arrival(const DecodeParams& p, const PairIn
 }
 
 // The fold, in chunk order (so results do not depend on which workgroup it is).  A second launch for it cost
-// 4.5 us and the gap between two dependent launches.
-template <int NT, int D>
-__device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairInfo& pi) {
-  const float* part = chunk_partial(p, pi, D, 0);
-  const int stride = p.Gp * D + kPartTail;
-  float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * D;
-  // up to sixteen chunks at a time: the loads of a batch are independent and in flight together (eight where the
-  // kernel would need more registers for it)
+// 4.5 us and the gap between two dependent launches.  What bounds it is one round trip to memory, and what the compiler puts in front: offsets
+// of 64 bits for all chunks, worked out before the first load and kept in vector lanes, with three loads and an exponential a chunk and lane and the
+// beacon's round trip ahead of it took 1.9 us from the last arrival to the end of the launch, 1.15 now (one sequence of 1551 rows, 32/8 heads, a step that evicts
+// 10.1 -> 8.7 us; 16 layers of 45 ragged sequences, 14/2 heads, d = 64, 169 -> 149).  A lane of each sixteen has the maximum and the denominator of one
+// chunk, and its weight goes round by DPP.  behind_loads: called when the first chunks' loads are out.
+template <int NT, int D, typename F>
+__device__ __forceinline__ void merge_chunks(const DecodeParams& p, const PairInfo& pi, const F& behind_loads) {
+  // sixteen chunks at a time, their loads in flight together (eight where the kernel would need more registers for it)
   constexpr int kBatch = NT > 256 ? 16 : 8;
-  for (int i = 2 * threadIdx.x; i < p.g * D; i += 2 * NT) {
-    const float* ml = part + p.Gp * D + i / D;
+  const char* part = reinterpret_cast<const char*>(chunk_partial(p, pi, D, 0));      // (scalar, with an offset per lane)
+  const uint32_t step = (uint32_t)(p.Gp * D + kPartTail) * 4u;
+  auto load = [&](uint32_t at) __attribute__((always_inline)) { return load_part2(reinterpret_cast<const float*>(part + at)); };
+  float* outp = p.out + (int64_t)(pi.s * p.Hq + pi.kvh * p.g) * D;
+  const int mine = threadIdx.x & (kBatch - 1);
+#pragma clang loop unroll(disable)
+  for (int i0 = 0; i0 < p.g * D; i0 += 2 * NT) {
+    const int i = i0 + 2 * threadIdx.x;
+    if (i >= p.g * D) continue;
+    uint32_t ml = (uint32_t)(p.Gp * D + 2 * (i / D)) * 4u, at = 4u * i;
     float mx = kNegBig, lsum = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int ch0 = 0; ch0 < pi.nchunks; ch0 += kBatch) {
-      float mv[kBatch], lv[kBatch];
+#pragma clang loop unroll(disable)
+    for (int n = pi.nchunks; n > 0; n -= kBatch) {       // chunks left
+      const uint64_t mlv = load(ml + (uint32_t)min(mine, n - 1) * step);
       uint64_t ov[kBatch];
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const int64_t at = (int64_t)min(ch0 + k, pi.nchunks - 1) * stride;
-        mv[k] = load_part(ml + at);
-        lv[k] = load_part(ml + at + p.Gp);
-        ov[k] = load_part2(part + at + i);
-      }
-      float bm = kNegBig;
+      for (int k0 = 0; k0 < kBatch; k0 += 4) {
+        if (k0 < n) {                                    // (a branch of the whole wave; behind the last chunk it repeats, with a weight of zero)
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        if (ch0 + k >= pi.nchunks) mv[k] = kNegBig;
-        bm = fmaxf(bm, mv[k]);
-      }
-      const float mn = fmaxf(mx, bm);
-      const float keep = fast_exp2(mx - mn);
-      lsum *= keep; o0 *= keep; o1 *= keep; mx = mn;
+          for (int k = k0; k < k0 + 4; ++k) ov[k] = load(at + (uint32_t)min(k, n - 1) * step);
+        } else {
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const float a = (ch0 + k < pi.nchunks) ? fast_exp2(mv[k] - mx) : 0.f;
-        lsum += lv[k] * a;
-        o0 += __uint_as_float((uint32_t)ov[k]) * a;
-        o1 += __uint_as_float((uint32_t)(ov[k] >> 32)) * a;
+          for (int k = k0; k < k0 + 4; ++k) ov[k] = 0;
+        }
       }
+      if (i0 == 0 && n == pi.nchunks) behind_loads();
+      const float m = mine < n ? __uint_as_float((uint32_t)mlv) : kNegBig;
+      const float mn = fmaxf(mx, group_allreduce_max<kBatch>(m));
+      const float keep = fast_exp2(mx - mn), a = mine < n ? fast_exp2(m - mn) : 0.f;
+      mx = mn;
+      lsum = lsum * keep + group_allreduce_sum<kBatch>(a * __uint_as_float((uint32_t)(mlv >> 32)));
+      o0 *= keep; o1 *= keep;
+      each_of<kBatch>([&](auto k) __attribute__((always_inline)) {
+        const float ak = lane_of_row<k>(a);
+        o0 = fmaf(__uint_as_float((uint32_t)ov[k]), ak, o0);
+        o1 = fmaf(__uint_as_float((uint32_t)(ov[k] >> 32)), ak, o1);
+      });
+      ml += kBatch * step; at += kBatch * step;
+      asm volatile("" : "+v"(ml), "+v"(at));             // (no addresses worked out for all passes in front of the first load)
     }
     *reinterpret_cast<float2*>(outp + i) = make_float2(o0 / lsum, o1 / lsum);
   }
 }
 
-// The end of a workgroup of a cut sequence.
+// The end of a workgroup of a cut sequence, in one place of its kernel for those with and without rows (the first of them brings the code into the
+// instruction cache).  beacon: the beacon rows of all heads in LDS, or null.
+struct Closing { PairInfo pi; const char* beacon; };
 template <int NT, int D, int ROWB>
-__device__ __forceinline__ void close_pair(const PairInfo& pi, int* s_arrived) {
+__device__ __forceinline__ void close_pair(const Closing& end, int* s_arrived) {
+  const PairInfo& pi = end.pi;
+  const char* beacon = end.beacon;
+  if (!last_arrival(arguments_again<kTableArguments>(), pi, s_arrived)) return;
+  // The pair's ticket goes out behind the loads of the partials, whose answers the wave would otherwise wait for it with.  (Its place as
+  // one of the lane's own: of what it takes for the wave's, the compiler makes a sum over lanes and looks at the answer at once.)
   int drawn = -1;
   {
-    const DecodeParams p = arguments_again();
-    if (!last_arrival(p, pi, s_arrived)) return;
-    if (pi.update && threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
-    // everyone who reads this KV head's rows has arrived: its beacon row need not wait for the sequence's last ticket
-    // (one sequence of 1551 rows, 32/8 heads: 10.3 -> 10.1 us)
-    if (pi.evict_due) store_beacon<ROWB, false>(p, pi, pi.kvh, 1, threadIdx.x, NT);
+    const DecodeParams p = arguments_again<kTableArguments>();
+    merge_chunks<NT, D>(p, pi, [&]() __attribute__((always_inline)) {
+      if (!pi.update || threadIdx.x != 0) return;
+      int at = pi.s * kTicketStride;
+      asm volatile("" : "+v"(at));
+      drawn = __hip_atomic_fetch_add(p.tickets + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
   }
-  merge_chunks<NT, D>(arguments_again(), pi);
-  if (!pi.update || threadIdx.x >= 64) return;
-  const DecodeParams p = arguments_again();
+  if (!pi.update) return;
+  const DecodeParams p = arguments_again<kTableArguments>();
+  // everyone who reads this KV head's rows has arrived: its beacon row need not wait for the sequence's last ticket
+  if (pi.evict_due) {
+    if (beacon != nullptr) store_beacon<ROWB, true>(p, pi, pi.kvh, 1, threadIdx.x, NT, beacon + pi.kvh * ROWB, beacon + (p.Hkv + pi.kvh) * ROWB);
+    else store_beacon<ROWB, false>(p, pi, pi.kvh, 1, threadIdx.x, NT);
+  }
+  if (threadIdx.x >= 64) return;
   if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, 0, pi.nchunks, p.max_chunks) - 1)
     move_tables(p, pi, threadIdx.x);
 }
-// The end of a workgroup without rows.  own: see tickets_due().
-template <int NT, int D, int ROWB>
-__device__ __forceinline__ void close_without_chunk(const PairInfo& pi, int own, int* s_arrived) {
+// The end of a workgroup without rows, but for what it does for a pair that is cut: true where close_pair() is its end.  own: see tickets_due().
+template <int ROWB>
+__device__ __forceinline__ bool close_without_chunk(const PairInfo& pi, int own) {
   const CloseBy move = closing_move(pi.update, false, pi.nchunks);
-  if (move == CloseBy::arrival) close_pair<NT, D, ROWB>(pi, s_arrived);
-  if (move != CloseBy::ticket) return;
+  if (move != CloseBy::ticket) return move == CloseBy::arrival;
   __syncthreads();                 // every wave has read the tables
-  if (threadIdx.x >= 64) return;
-  const DecodeParams p = arguments_again();
+  if (threadIdx.x >= 64) return false;
+  const DecodeParams p = arguments_again<kTableArguments>();
   int drawn = -1;
   if (threadIdx.x == 0) drawn = atomicAdd(p.tickets + pi.s * kTicketStride, 1);
   if (__builtin_amdgcn_readfirstlane(drawn) == tickets_due(p.Hkv, own, pi.nchunks, p.max_chunks) - 1)
     finish_step<ROWB>(p, pi, threadIdx.x);
+  return false;
 }
 
 // Epilogue of the plain-ALU kernel: s_m/s_l/s_acc hold one (m, l, o) per wave in LDS; merge them in wave order
@@ -471,8 +508,7 @@ __device__ __forceinline__ void merge_waves_and_store(const DecodeParams& p, con
       float* pml = po + p.Gp * D;
       store_part(po + i, o);
       if (x == 0) {
-        store_part(pml + h, mx);
-        store_part(pml + p.Gp + h, lsum);
+        store_part2(pml + 2 * h, mx, lsum);
       }
     }
   }
@@ -521,8 +557,7 @@ __device__ __forceinline__ void merge_waves_and_store4(const DecodeParams& p, co
       store_part2(po + h * D + x, o[0], o[1]);
       store_part2(po + h * D + x + 2, o[2], o[3]);
       if (x == 0) {
-        store_part(pml + h, mx);
-        store_part(pml + p.Gp + h, lsum);
+        store_part2(pml + 2 * h, mx, lsum);
       }
     }
   }
@@ -581,8 +616,9 @@ template <> __device__ __forceinline__ uint4 load16<true>(const char* p) { retur
 // CHUNKS: the plan cuts sequences into chunks.  A kernel of its own: with the fold compiled into the kernel of
 // whole sequences, 34 scalar registers of that spilled (200 pairs of 1000 rows: 20.6 us a step without, 21.2 with;
 // 320 of 1200: 45.2, 46.6).
+// True where close_pair() is still to come, with what it wants in `end`.
 template <int STREAM, int D, int VS, int NW, bool SHORT, bool CHUNKS>
-__device__ __forceinline__ void decode_lds(const DecodeParams& p) {
+__device__ __forceinline__ bool decode_lds(const DecodeParams& p, Closing* end) {
   static_assert(!CHUNKS || (VS == 1 && !SHORT), "the straight-line form and the V halves have whole sequences");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   constexpr bool KSTREAM = STREAM == 1, VSTREAM = STREAM >= 1;
@@ -599,12 +635,15 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   constexpr int NI = D / 32;               // MFMAs (k = 32) along the head dimension: 4 or 2
   constexpr int NJ = DV / 16;              // 16-column blocks of the output held here: 8 or 4
   constexpr int TILEB = kTileRows * ROWB;  // one K (or V) tile: 8 or 4 KB
-  touch_kernel_arguments();
+  constexpr int ARGS = CHUNKS ? kTableArguments : 0;      // where they lie
+  TableEntries tables;
+  if constexpr (CHUNKS) request_tables(p, (int)blockIdx.y, tables);
+  touch_kernel_arguments<ARGS>();
   // grid: (KV head, slot, chunk from the last or V half), see decode_grid().  VS = 2: the slots are padded so that a pair's two
   // workgroups are 8k apart in dispatch order (workgroups go to the XCDs in turn).
   const int vhalf = VS == 1 ? 0 : (int)blockIdx.z;
   const int slot = (int)blockIdx.y, kvh0 = (int)blockIdx.x;
-  if (VS != 1 && slot >= p.B) return;
+  if (VS != 1 && slot >= p.B) return false;
   // (the wave's number as a scalar: conditions on it become real branches, not lane masks)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r4 = lane / UPR, pos = lane & (UPR - 1);   // row within a 1 KB load, unit within the row
@@ -622,10 +661,17 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   auto request_query = [&](int s_) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      __attribute__((ext_vector_type(4))) uint32_t r = {0u, 0u, 0u, 0u};
-      if (n < p.g) {
-        const char* src = p.q + ((int64_t)(s_ * p.Hq + kvh0 * p.g + n) * D + 32 * i + 8 * kb) * 2;
-        asm volatile("global_load_dwordx4 %0, %1, off" : "+v"(r) : "v"(src) : "memory");
+      u32x4_t r;
+      if constexpr (CHUNKS) {
+        // (the columns behind the group's heads repeat the last one and are not looked at: shorter code than leaving their lanes out)
+        const char* src = p.q + ((int64_t)(s_ * p.Hq + kvh0 * p.g + min(n, p.g - 1)) * D + 32 * i + 8 * kb) * 2;
+        asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(r) : "v"(src) : "memory");
+      } else {
+        r = u32x4_t{0u, 0u, 0u, 0u};
+        if (n < p.g) {
+          const char* src = p.q + ((int64_t)(s_ * p.Hq + kvh0 * p.g + n) * D + 32 * i + 8 * kb) * 2;
+          asm volatile("global_load_dwordx4 %0, %1, off" : "+v"(r) : "v"(src) : "memory");
+        }
       }
       qb[i] = __builtin_bit_cast(bf16x8_t, r);
     }
@@ -686,7 +732,7 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
     for (int j = 0; j < VNDMA; ++j)
       load16_uncounted_s<VSTREAM>(vreg[j], (uint32_t)min(trow0 + VRPI * j + r4v, last_row) * ROWB + (posv << 4), vb_);
   };
-  if constexpr (SHORT) {            // the sequence is the slot: nothing here needs the tables
+  if constexpr (SHORT || CHUNKS) {      // no dispatch order, the sequence is the slot: nothing here needs the tables
     request_query(slot);
     request_new_row(slot);
   }
@@ -705,7 +751,8 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
       early_tile = true;
     }
   };
-  const PairInfo pi = VS == 1 && !SHORT ? pair_info(p, slot, kvh0, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0)
+  const PairInfo pi = VS == 1 && !SHORT ? pair_info(p, slot, kvh0, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0, NoEarlyWork(),
+                                                            CHUNKS ? &tables : nullptr)
                                         : pair_info(p, slot, kvh0, 0, request_early_tiles);
   // Tiles wave, wave + NW, ... of the chunk belong to this wave.
   const int ntiles = (pi.row_end - pi.row0 + kTileRows - 1) / kTileRows;
@@ -720,8 +767,11 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   }
   if (nothing_to_do) {
     wait_vmcnt<0>();
-    if constexpr (CHUNKS) close_without_chunk<NW * 64, D, ROWB>(pi, NW, reinterpret_cast<int*>(lds));
-    return;
+    if constexpr (CHUNKS) {
+      *end = Closing{pi, nullptr};
+      return close_without_chunk<ROWB>(pi, NW);
+    }
+    return false;
   }
   // rows the tile loads may touch: the resident rows that are already in the slab
   const int last_slab_row = max((pi.new_row >= 0 ? pi.new_row : pi.L) - 1, 0);
@@ -733,7 +783,7 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   const char* kbase = p.k_slab + stream_off;
   const char* vbase = p.v_slab + stream_off + vhalf * VROWB;
   const uint64_t kbase_s = (uint64_t)kbase, vbase_s = (uint64_t)vbase;      // (uniform: scalar registers)
-  if constexpr (!SHORT) {           // the sequence may come from the dispatch order: after the tables
+  if constexpr (!SHORT && !CHUNKS) {           // the sequence may come from the dispatch order: after the tables
     request_query(pi.s);
     request_new_row(pi.s);
   }
@@ -782,7 +832,7 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   // (the last wave has the fewest tiles; its loads have landed by the barrier in front of the merge)
   char* beacon = lds + NW * (TILEB + VTILEB);
   if (pi.evict_due && wave == NW - 1) {
-    const DecodeParams again = arguments_again();
+    const DecodeParams again = arguments_again<ARGS>();
     if (beacon_fits<ROWB>(again)) request_beacon<ROWB>(again, pi.s, lane, beacon);
   }
 
@@ -1008,26 +1058,32 @@ __device__ __forceinline__ void decode_lds(const DecodeParams& p) {
   merge_waves_and_store4<NW, DV, D, APITCH, CHUNKS>(p, pi, s_m, s_l, s_acc, WSTRIDE, vhalf * DV);
   if constexpr (CHUNKS) {
     if (pi.nchunks > 1) {
-      close_pair<NW * 64, D, ROWB>(pi, reinterpret_cast<int*>(lds));
-      return;
+      *end = Closing{pi, beacon_fits<ROWB>(arguments_again<ARGS>()) ? beacon : nullptr};
+      return true;
     }
   }
 
   // ---- the wave that drew the sequence's last ticket writes the beacon row and updates the tables
-  if (!pi.update) return;
+  if (!pi.update) return false;
   wait_vmcnt<0>();     // the ticket has arrived
   landed(ticket);
-  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, VS * NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, VS * NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return false;
   finish_step<ROWB>(p, pi, lane, beacon_fits<ROWB>(p) ? beacon : nullptr);
+  return false;
 }
 
 template <int STREAM, int D, int VS, int NW, bool SHORT = false>
 __global__ __launch_bounds__(NW * 64) void decode_lds_kernel(DecodeParams p) {
-  decode_lds<STREAM, D, VS, NW, SHORT, false>(p);
+  decode_lds<STREAM, D, VS, NW, SHORT, false>(p, nullptr);
 }
 template <int STREAM, int D, int NW>
-__global__ __launch_bounds__(NW * 64) void decode_lds_cut_kernel(DecodeParams p) {
-  decode_lds<STREAM, D, 1, NW, false, true>(p);
+__global__ __launch_bounds__(NW * 64) void decode_lds_cut_kernel(BC_TABLE_ARGUMENTS, DecodeParams p) {
+  p.P = tP; p.nb = tnb; p.w = tw; p.cap = tcap; p.c = tc; p.base = tbase;
+  p.order = nullptr;            // (see follows_order())
+  Closing end;
+  if (!decode_lds<STREAM, D, 1, NW, false, true>(p, &end)) return;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  close_pair<NW * 64, D, D * 2>(end, reinterpret_cast<int*>(lds));
 }
 
 // ---------------------------------------------------------------------------
@@ -1051,22 +1107,27 @@ constexpr int kValuWaves = 4;
 // large batches (12/2 heads, d = 128: 120 sequences of 760 rows 60.1 -> 33.7 us; 16/2 heads, 64 of 1500 rows 110 -> 38.4; 8/1
 // heads, 4 of 508 rows 17.5 -> 10.2).  Eight waves a workgroup: no difference, the load path is the same one.
 template <int D, int G, bool CHUNKS>
-__device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
+__device__ __forceinline__ bool decode_f32_rows(const DecodeParams& p, Closing* end) {
   constexpr int RB = D * 4;
   constexpr int SUB = 128 / D, ROWS = 16 * SUB;    // 16-row blocks of a tile, its rows
   constexpr int KI = D / 16, VJ = D / 64;          // 16-byte units per lane: of a K block's operand, of a row
   constexpr int NW = kValuWaves;
   typedef __attribute__((ext_vector_type(4))) float row16_t;
 
-  touch_kernel_arguments();
+  TableEntries tables;
+  request_tables(p, (int)blockIdx.y, tables);
+  touch_kernel_arguments<kTableArguments>();
   constexpr int APITCH = D + 4, WSTRIDE = G * APITCH + 2 * G + (2 * G) % 4;      // of the merge at the end, in floats
   constexpr int LDS = NW * (16 * SUB * RB > 4 * WSTRIDE ? 16 * SUB * RB : 4 * WSTRIDE);
   __shared__ __attribute__((aligned(1024))) char tiles[LDS];
-  const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0);
-  __shared__ int s_arrived;
+  const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0,
+                                NoEarlyWork(), &tables);
   if (!pi.live) {
-    if constexpr (CHUNKS) close_without_chunk<NW * 64, D, RB>(pi, NW, &s_arrived);
-    return;
+    if constexpr (CHUNKS) {
+      *end = Closing{pi, nullptr};
+      return close_without_chunk<RB>(pi, NW);
+    }
+    return false;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, kb = lane >> 4;
@@ -1268,21 +1329,22 @@ __device__ __forceinline__ void decode_f32_rows(const DecodeParams& p) {
   merge_waves_and_store4<NW, D, D, APITCH, CHUNKS, true>(p, pi, s_m, s_l, s_part, PITCH, 0);
   if constexpr (CHUNKS) {
     if (pi.nchunks > 1) {
-      close_pair<NW * 64, D, RB>(pi, &s_arrived);
-      return;
+      *end = Closing{pi, nullptr};
+      return true;
     }
   }
-  if (!pi.update) return;
+  if (!pi.update) return false;
   wait_vmcnt<0>();
   landed(ticket);
-  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, NW, 1, CHUNKS ? p.max_chunks : 1) - 1) return false;
   finish_step<RB>(p, pi, lane);
+  return false;
 }
 
 // The same on FMA instructions, for bf16 rows (BC_PLAN_PLAIN_ALU) and small fp32 groups (fma_is_faster).
 // CHUNKS: as for the matrix kernel.
 template <typename T, int D, int G, int U, bool CHUNKS>
-__device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
+__device__ __forceinline__ bool decode_alu_rows(const DecodeParams& p, Closing* end) {
   constexpr int ES = Elem<T>::size;
   constexpr int EPL = Elem<T>::per16;   // elements per lane per row
   constexpr int LPR = D / EPL;          // lanes per row
@@ -1290,12 +1352,17 @@ __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
   constexpr int RB = D * ES;            // row bytes
   constexpr int ROWS_PER_PASS = kValuWaves * RPI * U;
 
-  touch_kernel_arguments();
-  const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0);
-  __shared__ int s_arrived;
+  TableEntries tables;
+  request_tables(p, (int)blockIdx.y, tables);
+  touch_kernel_arguments<kTableArguments>();
+  const PairInfo pi = pair_info(p, (int)blockIdx.y, (int)blockIdx.x, CHUNKS ? p.max_chunks - 1 - (int)blockIdx.z : 0,
+                                NoEarlyWork(), &tables);
   if (!pi.live) {
-    if constexpr (CHUNKS) close_without_chunk<256, D, RB>(pi, 1, &s_arrived);
-    return;
+    if constexpr (CHUNKS) {
+      *end = Closing{pi, nullptr};
+      return close_without_chunk<RB>(pi, 1);
+    }
+    return false;
   }
   const int row_end = pi.row_end;
 
@@ -1463,22 +1530,31 @@ __device__ __forceinline__ void decode_alu_rows(const DecodeParams& p) {
   merge_waves_and_store<kValuWaves, D, CHUNKS>(p, pi, s_m, s_l, s_acc, G, G * D);
   if constexpr (CHUNKS) {
     if (pi.nchunks > 1) {
-      close_pair<256, D, RB>(pi, &s_arrived);
-      return;
+      *end = Closing{pi, nullptr};
+      return true;
     }
   }
-  if (!pi.update || wave != 0) return;
-  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, 1, 1, CHUNKS ? p.max_chunks : 1) - 1) return;
+  if (!pi.update || wave != 0) return false;
+  if (__builtin_amdgcn_readfirstlane(ticket) != tickets_due(p.Hkv, 1, 1, CHUNKS ? p.max_chunks : 1) - 1) return false;
   finish_step<RB>(p, pi, lane);
+  return false;
 }
 
 // Two workgroups of the matrix form share a compute unit.  (Groups of seven and eight used to be compiled for one, which only their FMA form
 // needs: see kLonePairs for what is left of that.)
 template <typename T, int D, int G, int U, bool CHUNKS, bool FMA = !std::is_same<T, float>::value>
 __global__ __launch_bounds__(256, FMA ? 1 : 2)
-void decode_valu_kernel(DecodeParams p) {
-  if constexpr (!FMA) decode_f32_rows<D, G, CHUNKS>(p);
-  else decode_alu_rows<T, D, G, U, CHUNKS>(p);
+void decode_valu_kernel(BC_TABLE_ARGUMENTS, DecodeParams p) {
+  p.P = tP; p.nb = tnb; p.w = tw; p.cap = tcap; p.c = tc; p.base = tbase;
+  if constexpr (CHUNKS) p.order = nullptr;            // (see follows_order())
+  Closing end;
+  bool closing;
+  if constexpr (!FMA) closing = decode_f32_rows<D, G, CHUNKS>(p, &end);
+  else closing = decode_alu_rows<T, D, G, U, CHUNKS>(p, &end);
+  if constexpr (CHUNKS) {
+    __shared__ int s_arrived;
+    if (closing) close_pair<256, D, D * Elem<T>::size>(end, &s_arrived);
+  }
 }
 
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -1659,12 +1735,12 @@ template <typename T, int D, int G>
 static void launch_valu_group(const DecodeParams& p, const DecodePlan& pl, dim3 grid, hipStream_t st) {
   if constexpr (std::is_same<T, float>::value && G <= 2) {
     if (pl.fma) {
-      decode_valu_kernel<T, D, G, 8, false, true><<<grid, 256, 0, st>>>(p);
+      decode_valu_kernel<T, D, G, 8, false, true><<<grid, 256, 0, st>>>(p.P, p.nb, p.w, p.cap, p.c, p.base, p);
       return;
     }
   }
-  if (p.max_chunks > 1) decode_valu_kernel<T, D, G, 8, true><<<grid, 256, 0, st>>>(p);
-  else decode_valu_kernel<T, D, G, 8, false><<<grid, 256, pl.lone_bytes, st>>>(p);
+  if (p.max_chunks > 1) decode_valu_kernel<T, D, G, 8, true><<<grid, 256, 0, st>>>(p.P, p.nb, p.w, p.cap, p.c, p.base, p);
+  else decode_valu_kernel<T, D, G, 8, false><<<grid, 256, pl.lone_bytes, st>>>(p.P, p.nb, p.w, p.cap, p.c, p.base, p);
 }
 template <typename T, int D>
 static void launch_valu(const DecodeParams& p, const DecodePlan& pl, dim3 grid, hipStream_t st) {
@@ -1681,13 +1757,14 @@ static void launch_valu(const DecodeParams& p, const DecodePlan& pl, dim3 grid, 
 // kernel's name as profilers print it.
 struct LdsLaunch {
   void (*fn)(DecodeParams);
+  void (*cut)(BC_TABLE_ARGUMENTS, DecodeParams);
   const char* name;
   dim3 grid;
   int threads;
   int lds_bytes;
 };
-#define BC_LDS_KERNEL(...) decode_lds_kernel<__VA_ARGS__>, "bc::decode_lds_kernel<" #__VA_ARGS__ ">"
-#define BC_LDS_CUT_KERNEL(...) decode_lds_cut_kernel<__VA_ARGS__>, "bc::decode_lds_cut_kernel<" #__VA_ARGS__ ">"
+#define BC_LDS_KERNEL(...) decode_lds_kernel<__VA_ARGS__>, nullptr, "bc::decode_lds_kernel<" #__VA_ARGS__ ">"
+#define BC_LDS_CUT_KERNEL(...) nullptr, decode_lds_cut_kernel<__VA_ARGS__>, "bc::decode_lds_cut_kernel<" #__VA_ARGS__ ">"
 
 static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, const DecodePlan& pl,
                                  bool ordered) {
@@ -1862,7 +1939,8 @@ static int32_t launch_attention(const bc_shape* shape, const bc_cache* cache, co
     const int32_t st = enable_big_lds();
     if (st != BC_OK) return st;
     const LdsLaunch k = pick_lds_kernel(shape, cache, pl, p.order != nullptr);
-    k.fn<<<k.grid, k.threads, k.lds_bytes, hs>>>(p);
+    if (k.cut) k.cut<<<k.grid, k.threads, k.lds_bytes, hs>>>(p.P, p.nb, p.w, p.cap, p.c, p.base, p);
+    else k.fn<<<k.grid, k.threads, k.lds_bytes, hs>>>(p);
   } else if (shape->kv_dtype == BC_BF16) {
     if (shape->d == 128) launch_valu<bf16_t, 128>(p, pl, grid, hs);
     else launch_valu<bf16_t, 64>(p, pl, grid, hs);

@@ -1012,6 +1012,21 @@ def test_long_sequences_get_a_chunk_for_every_512_rows(dev, B, Hq, Hkv, d, P, ch
     rollout(wl, rt, oc, G, range(1, G + 1), (G,), use_step_call=True)
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,dtype,chunk", [(8, 1, 128, "bf16", 512), (7, 1, 64, "bf16", 512), (10, 5, 128, "bf16", 128),
+                                                  (9, 9, 64, "bf16", 192), (8, 1, 128, "f32", 64), (3, 1, 64, "f32", 128)])
+def test_fold_of_every_number_of_chunks(dev, Hq, Hkv, d, dtype, chunk):
+    # the fold takes chunks by fours and by eights or sixteens; beacon rows from LDS (up to eight KV heads of d = 128) and from the caller's tensors
+    numbers = {1: (2, 3, 4, 5, 7, 8, 9, 12, 13, 16, 17, 18), 5: range(8, 15), 9: (5,)}[Hkv]
+    P = np.array([n * chunk - 5 for n in numbers], np.int32)
+    G = 6
+    wl = W.Workload("fold", 122, len(P), Hq, Hkv, d, dtype, P, np.full(len(P), G, np.int32), np.full(len(P), 2, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) > 4, text
+    rollout(wl, rt, oc, G, range(1, G + 1), (G,), use_step_call=True)
+    assert partials_written(rt)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,P", [(3, 6, 2, 128, (507, 509, 1100)), (3, 6, 2, 64, (827, 829, 1100)),
                                           (62, 4, 2, 128, (1019, 1021, 1100, 60))])
 def test_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, P):
