@@ -1561,6 +1561,7 @@ static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct DecodePlan {
   bool lds;           // LDS/MFMA kernel (bf16, d = 128) or the VALU kernel
+  bool eight_waves;   // cut plans of the LDS kernel: one workgroup of eight waves a compute unit (d = 64: two fit), or two of four (see pick_lds_kernel)
   bool fma;           // the latter on FMA instructions (bf16 always, fp32 by fma_is_faster())
   int lone_bytes;     // LDS that keeps its workgroups from sharing a compute unit, or none (see kLonePairs)
   int Gp;             // padded group size
@@ -1580,8 +1581,11 @@ struct DecodePlan {
 
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
 
-constexpr int kSplitMinCap = 960, kSplitMinRows = 512, kSplitMinRows64 = 832;
-constexpr int kFewPairs = 32;             // see make_plan
+// see make_plan
+constexpr int kSplitMinCap = 960, kSplitMinCapSome = 2 * kLdsWavesSplit * kTileRows + 1, kSplitMinRows = 320, kSplitMinRows64 = 384, kSplitMinRowsMany = 512;
+constexpr int kSplitAlone = 512, kSplitAlone64 = 832;
+constexpr int kFewPairs = 32, kFewPairsLong = 64;
+static int few_pairs(int d, int max_cap) { return d == 128 && max_cap >= 1024 ? kFewPairsLong : kFewPairs; }
 constexpr long kMostChunks = 64;
 constexpr int kChunkRowsMax = 512;    // rows a chunk of the matrix kernel need not go beyond: two passes of eight waves
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
@@ -1643,6 +1647,7 @@ constexpr int kLoneBytes = 52 << 10;      // with the tiles' 32 KB more than hal
 // alone: attention without a step.
 static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, int plan_bits, bool alone = false) {
   DecodePlan pl;
+  pl.eight_waves = true;
   const long npairs = (long)sh->B * sh->Hkv;
   pl.lds = sh->kv_dtype == BC_BF16 && !(plan_bits & BC_PLAN_PLAIN_ALU);
   if (pl.lds) {
@@ -1656,7 +1661,8 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
   }
   pl.chunk_rows = pl.lds ? std::min(kChunkRowsMax, std::max(2 * kTileRows, (max_cap + 15) / 16)) : pl.rows_per_pass;
   pl.split_rows = kSplitMinRows;
-  int split_cap = kSplitMinCap;         // capacity from which on the plan has chunks at all
+  // capacity from which on the plan has chunks at all
+  int split_cap = !alone && npairs >= 16 && npairs <= 48 ? kSplitMinCapSome : kSplitMinCap;
   if (!pl.lds) {
     // (a step reads its appended row behind the passes over the slab's)
     const int whole_passes = (npairs > kFewPairs || pl.Gp * sh->d >= 512 ? 1 : 2) + (alone ? 1 : 0);
@@ -1677,21 +1683,19 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // most sixteen, whose partials are folded in one round of loads, or one for every 512 rows (one sequence of
     // 150,256 rows, one KV head: sixteen 94 us, 64 38; 16,900 rows: 17.1, 15.5; 6000 rows, 8 KV heads: a chunk for
     // every 256 rows 15.7, every 512 14.8).  That many are 256 of the matrix kernel
-    // at d = 128 (128 KB of LDS each; at 48 pairs a step over 1500 rows takes 19.1 us with 288 workgroups, which
-    // make a second round, and 13.8 with 240), and 512 at d = 64 or with four waves (see pick_lds_kernel).  512 is
-    // the line from 33 pairs on: a ragged batch does not fill them, and its longest sequence sets the time (90 pairs
-    // of up to 2100 rows, cut in two by eight waves or in five by four: 31.5, 27.2 us; of equal length, 1500 rows:
-    // 19.0, 20.1); with up to 32 pairs eight waves and 256 are as fast or faster (16 pairs of 3000 rows: 12.0, 13.6;
-    // at 8 pairs 23 chunks take 12.2, sixteen 11.1).  (These before the grid went chunk by chunk, see decode_grid().)
-    // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster (d = 128, 8
-    // pairs, whole against cut: 700 rows 7.9, 9.2 us; 850: 8.9, 9.5; 1000: 9.4, 9.7; 2 pairs, 1000 rows: 9.25, 8.7);
-    // where the batch has longer sequences the shorter ones run in the tile loop, and are cut from 512 rows on
-    // (capacity 3000, d = 128, whole, cut: 8 pairs 10.8, 10.9 us at 520 rows, 11.7, 10.7 at 700; 64 pairs 13.5, 12.8 and
-    // 14.7, 13.1; 90 pairs 14.6, 14.4 and 15.1, 15.1).  With d = 64, or four chunks for a sequence at most, sequences of
-    // equal length are faster whole up to some 800 and 1000 rows (d = 64, 90 pairs: 9.8, 11.4 at 520, 11.1, 11.6 at 800,
-    // 12.1, 11.9 at 900; 120 pairs, d = 128: 15.7, 16.4 at 700, 18.8, 19.1 at 1000, 22.6, 22.5 at 1300), ragged batches cut
-    // (16 layers of 45 sequences, 14/2 heads, d = 64: 180 us from 832 rows on, 171 from 512); attention alone, which
-    // pays for its counters besides, cuts them later.
+    // at d = 128 (128 KB of LDS each; a second round of workgroups takes more than the cut saves), and 512 at d = 64 or with four waves (see
+    // pick_lds_kernel).  At d = 128 eight waves and 256 are faster with up to 64 pairs (us a step, four waves / eight; 48 pairs of 1500 rows 13.3 / 12.2,
+    // of 60 to 1500 11.3 / 10.5; 64 of 1500 14.0 / 12.6, of 60 to 1100 10.4 / 9.2, of 60 to 3000 16.8 / 16.0; 64 of 100 to 2000, eight pairs of each length, 11.9 / 12.0),
+    // beyond that a sequence has three chunks or two, of which a ragged batch's longest are too long (72 pairs of 100 to 2000 12.4 / 14.2; 96 15.5 / 17.2;
+    // of equal length, 1700 rows, 15.8 / 15.1 and 20.9 / 19.7).  With less than 1024 rows of capacity the line is at 32 pairs, where it used to be for all (40
+    // pairs of 60 to 980 9.4 / 7.9: they would gain too).  At d = 64 512 is the line from 33 pairs on (90 of up to 1900 rows 10.2, with 256 10.7).
+    // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster with few pairs (8 pairs, whole / cut: 600 rows 6.2 / 6.9,
+    // 750 7.2 / 7.1, 900 7.7 / 7.0) and with more than 48 (d = 128, 60 of 800 rows 9.7 / 10.5, 80 of 900 11.2 / 12.4; d = 64, 64 of 700 7.6 / 7.2); in between up to
+    // the rows that two tiles of each of twelve waves hold (16 pairs of 500 rows 5.9 / 6.7, 750 7.6 / 7.0, of 60 to 800 7.6 / 6.8; 32 of 750 8.9 / 7.8; 48 of 60 to 800
+    // 10.1 / 7.8, of 800 9.3 / 9.2).  Where the batch may have longer sequences the shorter ones run in the tile loop, and are cut from 320 rows on (whole, cut: 48 pairs of 400 rows,
+    // capacity 1600, 9.8 / 7.9; 64 of 400, capacity 1150, 9.1 / 7.8), with d = 64 from 384 (32 pairs of 340 6.1 / 6.2, 40 of 60 to 700 from 512, 384 and 320 rows on 6.9, 6.8
+    // and 6.9), with more than 64 pairs from 512 where d is 64 (90 ragged ones, 16 layers, from 512 149, from 384 152, from 320 154) or there are four
+    // chunks at most (120 pairs of 60 to 1500 rows, from 512 15.9, from 320 16.3); attention alone, which pays for its counters besides, cuts them later.
     // The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of 1 to 7 us (by group and d), against
     // some 2 us that a fold takes: cut from the second pass on, or from the third where a pass is short and the
     // batch is small, with up to 256 pairs.  256 workgroups run at once with groups of three or more (over 256
@@ -1700,9 +1704,9 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // fp32: lines in f32_split_rows().  More workgroups than 256 do not help there (40 pairs of 760 rows: 480 15.3, 240 13.5; 120 ragged
     // ones of 200 to 1200, d = 128, 29.2, 26.5; 128 pairs of 350, in four chunks and in two 16.3, 14.2) but for many pairs with
     // the shorter rows of d = 64 (100 pairs of up to 4400 rows: 26.4, and 34.0 with 256).
-    const bool eight_waves = npairs <= kFewPairs ||
-                             (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
-    const bool one_per_cu = pl.lds ? eight_waves
+    pl.eight_waves = npairs <= few_pairs(sh->d, max_cap) ||
+                     (sh->d == 128 && (plan_bits & (BC_PLAN_NO_SMALL_WORKGROUPS | BC_PLAN_CACHEABLE_LOADS)));
+    const bool one_per_cu = pl.lds ? pl.eight_waves
                             : sh->kv_dtype == BC_F32 ? npairs <= (sh->d == 64 ? 64 : 128) : pl.Gp >= 4;
     const long at_once = one_per_cu ? 256 : 512, most_pairs = pl.lds ? 127 : sh->kv_dtype == BC_F32 ? kF32MostPairs : 256;
     long chunks = 1;
@@ -1711,7 +1715,9 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
       const long by_rows = (max_cap + pl.chunk_rows - 1) / pl.chunk_rows, most = npairs < 128 ? kMostChunks : 4;
       if (chunks > by_rows) chunks = by_rows;
       if (chunks > most) chunks = most;
-      if (pl.lds && alone) pl.split_rows = chunks <= 4 ? 2 * kSplitMinRows : sh->d == 64 ? kSplitMinRows64 : kSplitMinRows;
+      if (pl.lds && !alone)
+        pl.split_rows = npairs > 64 && (sh->d == 64 || chunks <= 4) ? kSplitMinRowsMany : sh->d == 64 ? kSplitMinRows64 : kSplitMinRows;
+      if (pl.lds && alone) pl.split_rows = chunks <= 4 && npairs > 64 ? 2 * kSplitAlone : sh->d == 64 ? kSplitAlone64 : kSplitAlone;
     }
     pl.R = 0;                                        // spread evenly, decided per sequence
     pl.max_chunks = (int)chunks;
@@ -1811,7 +1817,7 @@ static LdsLaunch pick_lds_kernel(const bc_shape* shape, const bc_cache* cache, c
   const bool small = stream && !(cache->plan & BC_PLAN_NO_SMALL_WORKGROUPS);
   if (pl.max_chunks > 1) {
     if (shape->d == 128) {
-      if (small && pl.R == 0 && pairs > kFewPairs)
+      if (small && pl.R == 0 && !pl.eight_waves)
         return LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 4), grid, 4 * 64, lds_half};
       return stream ? LdsLaunch{BC_LDS_CUT_KERNEL(1, 128, 8), grid, kLdsWaves * 64, lds_full}
                     : LdsLaunch{BC_LDS_CUT_KERNEL(0, 128, 8), grid, kLdsWaves * 64, lds_full};
