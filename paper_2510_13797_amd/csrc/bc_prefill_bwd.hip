@@ -352,14 +352,19 @@ struct KeyParts {
 // forms dA, takes A through LDS, and adds Q^T.dS to dK: three of the six products each, and half of the
 // accumulators and key operands, so that three waves fit a SIMD where one wave per 32 keys (two times 64
 // accumulators and 64 operand registers) would leave room for one.
-template <int D> constexpr int dkv_lds() { return kDkvStages * (4 * kTileRows * D + 256) + 2 * 4096 + kTileWaves * 768; }
-template <int D>
+// JOINED: two workgroups a compute unit, whose registers and LDS let a pass work on two tiles.
+template <bool JOINED> constexpr int dkv_stages() { return JOINED ? kDkvStages + 1 : kDkvStages; }
+template <bool JOINED> constexpr int dkv_exchange() { return JOINED ? 2 * 8192 : 8192; }       // bytes in which A changes hands
+template <int D, bool JOINED> constexpr int dkv_lds() {
+  return dkv_stages<JOINED>() * (4 * kTileRows * D + 256) + dkv_exchange<JOINED>() + kTileWaves * 768;
+}
+template <int D, bool JOINED>
 __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by) {
-  constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB;
-  constexpr int RING = kDkvStages * 2 * TILE, STAT = RING, XCH = RING + kDkvStages * 256;
+  constexpr int ROWB = D * 2, KS = D / 16, NJ = D / 32, TILE = kTileRows * ROWB, STAGES = dkv_stages<JOINED>();
+  constexpr int RING = STAGES * 2 * TILE, STAT = RING, XCH = RING + STAGES * 256;
   constexpr int OUT = kTileWaves * 32 * (D / 2) * 4;
-  constexpr int KEYS_AT = XCH + 2 * 4096;
-  static_assert(KEYS_AT >= OUT && KEYS_AT + kTileWaves * 768 == dkv_lds<D>(), "the gradient tiles fit");
+  constexpr int KEYS_AT = XCH + dkv_exchange<JOINED>();
+  static_assert(KEYS_AT >= OUT && KEYS_AT + kTileWaves * 768 == dkv_lds<D, JOINED>(), "the gradient tiles fit");
   // grid: x = (trajectory, KV head), y = key block; the long dense blocks of every trajectory
   // are dispatched before any short one
   const int pair = pair_in_turn(blockIdx.x, p.pstride, p.turn, blockIdx.y);
@@ -488,7 +493,7 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
   const int roff[2] = {rows_tile + either_rows_offset(lane), rows_tile + (either_rows_offset(lane) ^ 128)};
   const int coff[2] = {cols_tile + either_cols_offset(lane, 0), cols_tile + either_cols_offset(lane, 1)};
   const int soff = STAT + (keys_role ? 128 : 0) + 16 * half;
-  f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds + XCH + kg * 4096) + lane;
+  f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds + XCH + kg * 4096) + lane;      // JOINED: 8 KB further on for every other tile
   // the lane's key, the last row it is seen from and where its sums go: in LDS, every register of the loop is in use
   int* kept_key = reinterpret_cast<int*>(lds + KEYS_AT + wave * 768) + lane;
   kept_key[0] = jkey;
@@ -594,8 +599,164 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
       }
     }
   };
-  if (keys_role) passes(std::true_type{});
-  else passes(std::false_type{});
+  // JOINED: a pass forms A or dA of tile `it` beside the column product of the tile before, with one barrier: A of a tile is taken in the pass
+  // behind the one that forms it.  What bounds a launch that leaves the chip idle is the chain of its longest parts: a pass of the keys' waves is some 2,000 cycles,
+  // 770 of them matrix instructions, the rest the operands' way through LDS, the split and the loads' issue.  Forward and gradients, in two steps with a
+  // barrier each (`passes`) and so: three trajectories of 336 to 795 rows 52.2 -> 50.9 us, one of 3100, 5/1 heads, 78.3 -> 74.9, two of 2128, 12/2 heads, 101.1 ->
+  // 98.9.  (In launches that fill the chip three workgroups a compute unit are better: 8 trajectories of 3200 rows, 8/8 heads, 383 and 404, 16 of 8688 3231 and 3313.)
+  struct TileAt { int64_t at; const float* stat; uint32_t row[2], stat_row; };
+  auto next_tile = [&]() BC_INLINE {                 // (behind the last place: one of the first row tile again)
+    const int h = kvh * p.g + next.h, row0 = rs + max(next.rt, 0) * kTileRows;
+    advance(next);
+    const int left = S - 1 - row0;                   // (rows that do not exist repeat the last one)
+    TileAt t;
+    t.at = (off0 + row0) * q_row_bytes + (int64_t)h * ROWB;
+    t.stat = p.stat + ((int64_t)h * p.total_rows + off0 + row0) * 2;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) t.row[u] = (uint32_t)min(tlane.row + 8 * u, left) * (uint32_t)q_row_bytes + tlane.in_row;
+    t.stat_row = (uint32_t)min(col, left) * 8u + half * 4u;
+    return t;
+  };
+  // By the keys' waves beside their column products.  (In front of the pass 51.3 us for the three trajectories, by all four waves 51.9.)
+  auto load_part = [&](const TileAt& t, int stage, int part) BC_INLINE {       // one of D / 16: 1 KB of Q or dO
+    const int which = part % 2, u = part / 2 % 2, n = part / 4;
+    lds_dma16_s<false>(t.row[u], (uint64_t)((which ? p.dout : p.q) + t.at + 128 * n),
+                       lds0 + stage * (2 * TILE) + (2 * kg + u) * 1024 + which * TILE + n * 4096);
+  };
+  auto load_stat = [&](const TileAt& t, int stage) BC_INLINE {
+    if (kg == 0) lds_dma4_s(t.stat_row, (uint64_t)t.stat, lds0 + STAT + stage * 256);
+  };
+  auto load_tile = [&](int stage) BC_INLINE {
+    const TileAt t = next_tile();
+#pragma unroll
+    for (int part = 0; part < D / 16; ++part) load_part(t, stage, part);
+    load_stat(t, stage);
+  };
+  auto joined_passes = [&](auto keys) BC_INLINE {
+    constexpr bool KEYS = decltype(keys)::value;
+    constexpr int PRE = 4;         // products that row operands are asked for ahead
+    Place now = next;
+    int stage = STAGES - 1;
+    if (KEYS && count > 0) load_tile(0);
+    bool busy_before = false;
+    float val[16];                 // A, or dA - Delta, of the tile before
+    const char* before = lds;
+    for (int it = 0; it <= count; ++it) {
+      stage = stage + 1 == STAGES ? 0 : stage + 1;
+      const char* tile = lds + stage * (2 * TILE);
+      const int row0 = rs + now.rt * kTileRows;
+      advance(now);
+      // tile `it` has landed, and everyone has finished pass it - 1, which was the last to look at tile it - 2
+      if constexpr (KEYS) wait_vmcnt<0>();
+      lds_barrier();
+      const int into = stage + 1 == STAGES ? 0 : stage + 1;      // of the next tile
+      const bool busy = it < count && row0 + kTileRows - 1 >= any_first && row0 <= any_last;
+      f32x4_t* put = xch + (it & 1) * 512;
+      const f32x4_t* got = xch + (~it & 1) * 512;
+      auto pass = [&](auto cur, auto prev) BC_INLINE {
+        constexpr bool CUR = decltype(cur)::value, PREV = decltype(prev)::value;
+        f32x16_t x;                // scores, or dA - Delta: the sums of dA start at -Delta
+        f32x4_t stat[4], a[4];     // log-sum-exp or -Delta of the lane's rows; A of the tile before
+        bf16x8_t r[KS], c[2 * NJ];
+        Parts y;
+        auto row_of = [&](int i) BC_INLINE { r[i] = *reinterpret_cast<const bf16x8_t*>(tile + roff[i & 1] + rows_read_imm<D>(i)); };
+        auto col_of = [&](int n) BC_INLINE { c[n] = cols_operand<D>(before + coff[n / NJ], n % NJ, n / NJ); };
+        TileAt to;
+        auto split = [&](int g) BC_INLINE {
+          if constexpr (KEYS) y.split(g, a[g / 2][2 * g % 4] * val[2 * g], a[g / 2][2 * g % 4 + 1] * val[2 * g + 1]);      // dS
+          else y.split(g, val[2 * g], val[2 * g + 1]);
+        };
+        if constexpr (CUR) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) stat[q] = *reinterpret_cast<const f32x4_t*>(lds + soff + stage * 256 + 32 * q);
+#pragma unroll
+          for (int i = 0; i < PRE; ++i) row_of(i);
+        }
+        if constexpr (KEYS && PREV) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) a[q] = got[64 * q];
+        }
+        if constexpr (CUR) {
+          if constexpr (KEYS) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = stat[e / 4][e % 4];
+          } else {
+            x = f32x16_t{0.f};
+          }
+        }
+        step_fence();
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+          if constexpr (CUR) {
+            x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r[i], op[i], x, 0, 0, 0);
+            if (i + PRE < KS) row_of(i + PRE);
+            if (KEYS && i == 0) to = next_tile();
+          }
+          if constexpr (PREV) {
+            if (i >= KS - NJ) col_of(i - KS + NJ);
+            // (what is asked for in front of the first product is there behind the second)
+#pragma unroll
+            for (int g = 0; g < 8; ++g)
+              if (i == KS / 4 + g * (KS - KS / 4) / 8) split(g);
+          }
+          step_fence();
+        }
+#pragma unroll
+        for (int m = 0; m < SLOTS; ++m) {
+          if constexpr (PREV) {
+            const int n = m / 2;
+            acc[n % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c[n], y.operand(m & 1, n / NJ), acc[n % NJ], 0, 0, 0);
+            if (m % 2 == 0 && n + NJ < 2 * NJ) col_of(n + NJ);
+          }
+          if constexpr (CUR && KEYS) {
+            if (m % 2 == 1) load_part(to, into, m / 2);
+            if (m == SLOTS - 1) load_stat(to, into);
+          }
+          if constexpr (CUR && !KEYS) {            // (the scores are there behind the second product)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if (m == 2 + e * (SLOTS - 3) / 15) {
+                val[e] = fast_exp2(fmaf(x[e], p.qscale, -stat[e / 4][e % 4]));
+                asm volatile("" : "+v"(val[e]));   // (worked out here and not behind the next barrier)
+              }
+          }
+          step_fence();
+        }
+        if constexpr (CUR && KEYS) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) val[e] = x[e];
+        }
+        if constexpr (CUR && !KEYS) {
+          if (row0 < all_first || row0 + kTileRows - 1 > all_last) {
+            const int from = kept_key[0] - row0, upto = kept_key[64] - row0;
+            const uint32_t mine = from >= 32 ? 0u : ~0u << max(from, 0);
+            const uint32_t past = upto < 0 ? 0u : upto >= 31 ? ~0u : (2u << upto) - 1u;
+            const uint32_t see = (mine & past) >> (4 * half);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) val[e] = keep_if_visible(val[e], see, e);
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) put[64 * q] = f32x4_t{val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
+        }
+      };
+      if (busy) {
+        if (busy_before) pass(std::true_type{}, std::true_type{});
+        else pass(std::true_type{}, std::false_type{});
+      } else {
+        if (KEYS && it + 1 < count) load_tile(into);
+        if (busy_before) pass(std::false_type{}, std::true_type{});
+      }
+      busy_before = busy;
+      before = tile;
+    }
+  };
+  if constexpr (JOINED) {
+    if (keys_role) joined_passes(std::true_type{});
+    else joined_passes(std::false_type{});
+  } else {
+    if (keys_role) passes(std::true_type{});
+    else passes(std::false_type{});
+  }
   lds_barrier();
 
   // every key row is owned by exactly one lane column of one block: plain stores
@@ -617,8 +778,8 @@ __device__ __forceinline__ void dkv_block(const BwdParams& p, char* lds, int by)
 
 template <int D>
 __global__ __launch_bounds__(kTileWaves * 64, 3) void prefill_bwd_dkv_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(1024))) char lds[dkv_lds<D>()];
-  dkv_block<D>(p, lds, blockIdx.y);
+  __shared__ __attribute__((aligned(1024))) char lds[dkv_lds<D, false>()];
+  dkv_block<D, false>(p, lds, blockIdx.y);
 }
 
 // Launches that leave the chip idle are a chain of kernels that each wait for the one before, and the dkv kernel waits for nothing but
@@ -648,12 +809,12 @@ __global__ __launch_bounds__(256) void prefill_bwd_delta_kernel(BwdParams p) {
 }
 template <int D>
 __global__ __launch_bounds__(kTileWaves * 64, 2) void prefill_bwd_joined_kernel(BwdParams p) {
-  __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>() > dkv_lds<D>() ? dq_lds<D>() : dkv_lds<D>()];
+  __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>() > dkv_lds<D, true>() ? dq_lds<D>() : dkv_lds<D, true>()];
   if ((int)blockIdx.y < p.dq_rows * p.tiling.splits) {
     const int by = blockIdx.y / p.tiling.splits;
     dq_block<D, false, true>(p, lds, blockIdx.x, blockIdx.y - by * p.tiling.splits, by, p.dq_rows);
   } else {
-    dkv_block<D>(p, lds, blockIdx.y - p.dq_rows * p.tiling.splits);
+    dkv_block<D, true>(p, lds, blockIdx.y - p.dq_rows * p.tiling.splits);
   }
 }
 
