@@ -282,7 +282,10 @@ __device__ __forceinline__ WindowStride window_stride(int c_table, int rows) {
   WindowStride ws;
   ws.c = min(c_table, 1 << 26);
   ws.stride = ws.c + 1;
-  ws.magic = ws.c > 0 ? (uint32_t)(0x100000000ull / (uint32_t)ws.stride) + 1u : 0u;
+  // floor(2^32 / stride) + 1, by a division of 32 bits (one of 64 is some 150 instructions in front of a workgroup's first load): 2^32 - 1 gives
+  // the same quotient but for powers of two
+  const uint32_t s = (uint32_t)max(ws.stride, 1);
+  ws.magic = ws.c > 0 ? 0xffffffffu / s + ((s & (s - 1)) == 0 ? 2u : 1u) : 0u;
   ws.exact = (uint64_t)(uint32_t)max(rows, 0) * (uint32_t)max(ws.stride, 1) < 0x100000000ull;
   return ws;
 }

@@ -149,6 +149,13 @@ inline int64_t dkv_grid_rows(int npairs, int most, int band, int key_blocks) {
   return (all < at_once ? all : at_once < least ? least : at_once) + (int64_t)key_blocks * band;
 }
 
+// The waves that add the parts up: keys a wave takes at a time where a key's row of dk (all KV heads) has less than 64 units of 16 bytes, slices
+// of 64 units where it has more.
+BC_HOST_DEVICE int reduce_keys(int per_row) { return per_row < 64 ? 64 / per_row : 1; }
+BC_HOST_DEVICE int reduce_slices(int per_row) { return per_row <= 64 ? 1 : (per_row + 63) / 64; }
+// Workgroups (of four waves) a trajectory at most.
+inline int reduce_blocks(int B) { return B <= 8 ? 1024 : B >= 64 ? 128 : 8192 / B; }
+
 // ---------------------------------------------------------------------------
 // the backward's launches
 // ---------------------------------------------------------------------------

@@ -546,6 +546,13 @@ def test_prefill_bwd_in_one_launch_and_in_two(dev, P, R, c, Hq, Hkv, d):
         _check_bwd(pw, qkv, dos, off, dq, dk, dv, b)
 
 
+@pytest.mark.parametrize("P,R,c,Hq,Hkv,d", [([60, 5], [2200, 40], [2, 0], 5, 5, 64), ([2100, 3], [300, 64], [16, 1], 5, 5, 128),
+                                            ([7, 130], [0, 900], [4, 1], 6, 1, 64)])
+def test_prefill_bwd_sums_of_parts_in_keys_and_slices(dev, P, R, c, Hq, Hkv, d):
+    # the sums' waves: two and three slices of a key's heads, more items than waves; four keys a wave; response rows with and without beacons among them
+    test_prefill_bwd_in_one_launch_and_in_two(dev, P, R, c, Hq, Hkv, d)
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,B,longest", [
     (14, 2, 64, 67, 300), (14, 2, 128, 16, 700), (7, 1, 128, 65, 200), (2, 1, 64, 130, 400), (9, 3, 128, 20, 700), (12, 4, 64, 13, 700), (25, 5, 64, 4, 1100),
     (20, 4, 128, 7, 700), (2, 2, 64, 100, 700), (24, 8, 64, 3, 1100), (16, 8, 128, 9, 900)])
