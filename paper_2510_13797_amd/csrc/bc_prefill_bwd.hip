@@ -790,20 +790,24 @@ constexpr int kDeltaRows = 16;        // rows of one head that a workgroup takes
 template <int D>
 __global__ __launch_bounds__(256) void prefill_bwd_delta_kernel(BwdParams p) {
   const Trajectory traj = trajectory(p, blockIdx.x);
-  const int64_t units = (int64_t)traj.rows * p.Hq;
+  // (in 32 bits: a joined launch has at most 65,536 rows of a head, see in_one_launch())
+  const uint32_t units = (uint32_t)traj.rows * (uint32_t)p.Hq, Hq = (uint32_t)p.Hq;
   const int lane = threadIdx.x & 15;
-  for (int64_t i = (int64_t)blockIdx.y * kDeltaRows + (threadIdx.x >> 4); i < units; i += (int64_t)gridDim.y * kDeltaRows) {
+  for (uint32_t i = blockIdx.y * kDeltaRows + (threadIdx.x >> 4); i < units; i += gridDim.y * kDeltaRows) {
     const int64_t at = traj.off0 * p.Hq + i;
     float4 o[D / 64];
     uint2 y[D / 64];
+    float lse2 = p.lse[at];
 #pragma unroll
     for (int t = 0; t < D / 64; ++t) {
       o[t] = *reinterpret_cast<const float4*>(p.out + at * D + 4 * lane + 64 * t);
       y[t] = *reinterpret_cast<const uint2*>(p.dout + (at * D + 4 * lane + 64 * t) * 2);
     }
-    const float lse2 = p.lse[at] * kLog2e, delta = row_dot<D>(o, y);
-    const int64_t row = i / p.Hq;
-    const int head = (int)(i - row * p.Hq);
+    const float delta = row_dot<D>(o, y);
+    // (asked for with the rest: used by two lanes of sixteen, it had been taken behind the sum and the branch, one more round trip)
+    asm volatile("" : "+v"(lse2));
+    lse2 *= kLog2e;
+    const uint32_t row = i / Hq, head = i - row * Hq;
     if (lane < 2) p.stat[((int64_t)head * p.total_rows + traj.off0 + row) * 2 + lane] = lane ? -delta : lse2;
   }
 }
