@@ -279,27 +279,35 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
 
 // The beacon entry of KV heads head0 .. head0 + heads - 1 goes to its slot behind the earlier beacons (the evicted
 // window's first row): by threads 0 .. threads - 1, once every reader of these heads' rows is done with them.  Four units
-// a thread are asked for before the first is stored.  FROM_LDS: the heads' K and V rows as request_beacon left them.
+// a thread are asked for before the first is stored.  FROM_LDS: from the heads' K and V rows as request_beacon left them, one of each at a time (in a loop of its
+// own: a step that evicts is 0.3 to 0.8 % shorter).
 constexpr int kBeaconBytes = 4096;
 template <int ROWB, bool FROM_LDS>
 __device__ __forceinline__ void store_beacon(const DecodeParams& p, const PairInfo& pi, int head0, int heads, int thread,
                                              int threads, const char* lds_k = nullptr, const char* lds_v = nullptr) {
   constexpr int UPR = ROWB / 16;                   // 16-byte units per row
   const int n16 = heads * UPR;                     // 16-byte units of K (or of V)
-  const int64_t src0 = (int64_t)(pi.s * p.Hkv + head0) * ROWB;
-  auto unit = [&](int i) -> u32x4_t {
-    if constexpr (FROM_LDS) return *reinterpret_cast<const u32x4_t*>((i >= n16 ? lds_v - n16 * 16 : lds_k) + (i << 4));
-    else return *reinterpret_cast<const u32x4_t*>((i >= n16 ? p.bv - n16 * 16 : p.bk) + src0 + (i << 4));
-  };
-  auto put = [&](int i, u32x4_t x) {
-    const int which = i >= n16, r = which ? i - n16 : i;
-    const int64_t at = (pi.base * p.Hkv + (int64_t)(head0 + r / UPR) * pi.cap + pi.P + pi.nb) * ROWB + ((r & (UPR - 1)) << 4);
-    if (i < 2 * n16) *reinterpret_cast<u32x4_t*>(const_cast<char*>(which ? p.v_slab : p.k_slab) + at) = x;
-  };
-  for (int i = thread; i < 2 * n16; i += 4 * threads) {
-    const int end = 2 * n16 - 1;
-    const u32x4_t a = unit(i), b = unit(min(i + threads, end)), c = unit(min(i + 2 * threads, end)), d = unit(min(i + 3 * threads, end));
-    put(i, a); put(i + threads, b); put(i + 2 * threads, c); put(i + 3 * threads, d);
+  const int64_t slot = (pi.base * p.Hkv + (int64_t)head0 * pi.cap + pi.P + pi.nb) * ROWB, head_bytes = (int64_t)pi.cap * ROWB;
+  auto place = [&](int i) { return slot + (int64_t)(i / UPR) * head_bytes + ((i & (UPR - 1)) << 4); };
+  if constexpr (FROM_LDS) {
+#pragma clang loop unroll(disable)
+    for (int i = thread; i < n16; i += threads) {
+      const u32x4_t k = *reinterpret_cast<const u32x4_t*>(lds_k + (i << 4)), v = *reinterpret_cast<const u32x4_t*>(lds_v + (i << 4));
+      *reinterpret_cast<u32x4_t*>(const_cast<char*>(p.k_slab) + place(i)) = k;
+      *reinterpret_cast<u32x4_t*>(const_cast<char*>(p.v_slab) + place(i)) = v;
+    }
+  } else {
+    const int64_t src0 = (int64_t)(pi.s * p.Hkv + head0) * ROWB;
+    auto unit = [&](int i) { return *reinterpret_cast<const u32x4_t*>((i >= n16 ? p.bv - n16 * 16 : p.bk) + src0 + (i << 4)); };
+    auto put = [&](int i, u32x4_t x) {
+      const int which = i >= n16;
+      if (i < 2 * n16) *reinterpret_cast<u32x4_t*>(const_cast<char*>(which ? p.v_slab : p.k_slab) + place(which ? i - n16 : i)) = x;
+    };
+    for (int i = thread; i < 2 * n16; i += 4 * threads) {
+      const int end = 2 * n16 - 1;
+      const u32x4_t a = unit(i), b = unit(min(i + threads, end)), c = unit(min(i + 2 * threads, end)), d = unit(min(i + 3 * threads, end));
+      put(i, a); put(i + threads, b); put(i + 2 * threads, c); put(i + 3 * threads, d);
+    }
   }
 }
 // The beacon rows of all KV heads into LDS (by one wave, uncounted loads), where they fit, for whoever turns out to
