@@ -61,16 +61,22 @@ class BcError(RuntimeError):
 
 
 _lib = None
-_byref = C.byref
+_call = None                  # the function of csrc/bc_call.cpp, with
+_call_lib = None              # the library whose entry point it calls, and
+_decode_step_at = None        # its address there
 
 
 def load():
     """Load libbc.so and declare the signatures; raises if the library or a symbol is missing."""
-    global _lib
+    global _lib, _call, _call_lib, _decode_step_at
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise BcError("libbc.so not built: run `python __graft_entry__.py` (hipcc, gfx950) first")
+    try:
+        from . import _bc_call
+    except ImportError as e:
+        raise BcError("_bc_call not built: run `python __graft_entry__.py` first (%s)" % e)
     lib = C.CDLL(LIB_PATH)
     for name in EXPORTS:
         if not hasattr(lib, name):
@@ -130,7 +136,9 @@ def load():
     lib.bc_topk_kl_loss_bwd.argtypes = [i64, i32, i32, vp, i32, vp, vp, vp, C.c_float, vp, vp]
     lib.bc_tables_to_host.restype = i32
     lib.bc_tables_to_host.argtypes = [sp, cp, vp, vp, vp, vp]
-    _lib = lib
+    _call = _bc_call.decode_step
+    _decode_step_at = C.cast(lib.bc_decode_step, C.c_void_p).value
+    _lib = _call_lib = lib
     return lib
 
 
@@ -503,10 +511,13 @@ class Runtime:
             active = self.mask(active)
         if out is None:
             out = self.out
-        st = (_lib or load()).bc_decode_step(_byref(self.shape), _byref(self.cache), k.data_ptr(), v.data_ptr(), q.data_ptr(),
-                                             out.data_ptr(), None if bk is None else bk.data_ptr(),
-                                             None if bv is None else bv.data_ptr(), None if active is None else active.data_ptr(),
-                                             self.ws.data_ptr(), self.ws_bytes, _stream_ptr())
+        lib = _lib or load()
+        if lib is _call_lib:
+            # (the conversions of a ctypes call of twelve arguments, eight of them data_ptr(): 2.1 us, so 0.9)
+            st = _call(_decode_step_at, self.shape, self.cache, k, v, q, out, bk, bv, active, self.ws, self.ws_bytes, _stream_ptr())
+        else:                 # another library in its place
+            st = lib.bc_decode_step(C.byref(self.shape), C.byref(self.cache), _ptr(k), _ptr(v), _ptr(q), _ptr(out), _ptr(bk), _ptr(bv),
+                                    _ptr(active), _ptr(self.ws), self.ws_bytes, _stream_ptr())
         if st != BC_OK:
             _check(st)
         return out
