@@ -865,11 +865,12 @@ __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
       const float* from = p.part + at * row_floats + 4 * unit;
       const int64_t next = (int64_t)plane * row_floats;
       f32x4_t sk = f32x4_t{0.f, 0.f, 0.f, 0.f}, sv = sk;
-      // eight parts on their way at a time, also of the last seven
-      for (int s0 = 0; s0 < sum; s0 += 8) {
-        f32x4_t xk[8], xv[8];
+      // two parts (large launches), or up to eight on their way at a time, also of the last seven
+      auto add = [&](int s0, auto count) BC_INLINE {
+        constexpr int N = decltype(count)::value;
+        f32x4_t xk[N], xv[N];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < N; ++e) {
           const float* x = from + 2 * min(s0 + e, sum - 1) * next;
           xk[e] = *reinterpret_cast<const f32x4_t*>(x);
           xv[e] = *reinterpret_cast<const f32x4_t*>(x + next);
@@ -878,10 +879,15 @@ __global__ __launch_bounds__(256) void prefill_bwd_reduce_kernel(BwdParams p) {
         // (a branch around an addition took the load behind it along: the parts came one by one)
         const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < N; ++e) {
           sk += s0 + e < sum ? xk[e] : zero;
           sv += s0 + e < sum ? xv[e] : zero;
         }
+      };
+      if (sum <= 2) {
+        add(0, std::integral_constant<int, 2>{});
+      } else {
+        for (int s0 = 0; s0 < sum; s0 += 8) add(s0, std::integral_constant<int, 8>{});
       }
       const int64_t to = (off0 + row) * row_floats + 4 * unit;
       *reinterpret_cast<f32x4_t*>(p.dk + to) = sk;

@@ -154,7 +154,7 @@ inline int64_t dkv_grid_rows(int npairs, int most, int band, int key_blocks) {
 BC_HOST_DEVICE int reduce_keys(int per_row) { return per_row < 64 ? 64 / per_row : 1; }
 BC_HOST_DEVICE int reduce_slices(int per_row) { return per_row <= 64 ? 1 : (per_row + 63) / 64; }
 // Workgroups (of four waves) a trajectory at most.
-inline int reduce_blocks(int B) { return B <= 8 ? 1024 : B >= 64 ? 128 : 8192 / B; }
+inline int reduce_blocks(int B) { return B <= 4 ? 1024 : B >= 32 ? 128 : 4096 / B; }
 
 // ---------------------------------------------------------------------------
 // the backward's launches
