@@ -1012,6 +1012,20 @@ def test_long_sequences_get_a_chunk_for_every_512_rows(dev, B, Hq, Hkv, d, P, ch
     rollout(wl, rt, oc, G, range(1, G + 1), (G,), use_step_call=True)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,P,chunks", [
+    (8, 4, 2, 128, (762, 30), 1), (8, 4, 2, 128, (763, 318), 13), (24, 4, 2, 64, (763, 381), 10), (49, 2, 1, 128, (763, 30), 1),      # 16 to 48 pairs: from 769 rows on
+    (32, 4, 2, 128, (1017, 318), 8), (32, 4, 2, 128, (1018, 318), 4), (65, 2, 1, 128, (1018, 510), 7)])      # eight waves from 1024 on, up to 64 pairs
+def test_plans_of_steps_at_their_lines(dev, B, Hq, Hkv, d, P, chunks):
+    # capacities and numbers of pairs on both sides of the plan's lines, short sequences that come to be cut in the rollout (320, 384 and 512 rows)
+    G = 7
+    P = np.resize(np.array(P, np.int32), B)
+    wl = W.Workload("lines", 126, B, Hq, Hkv, d, "bf16", P, np.full(B, G, np.int32), np.full(B, 3, np.int32))
+    rt, oc = make(wl, dev)
+    st, text = _bc().bc_decode_plan_describe(rt.shape, rt.cache)
+    assert st == 0 and int(text.split("chunks=")[1].split()[0]) == chunks, text
+    rollout(wl, rt, oc, G, range(1, G + 1), (3, G), use_step_call=True)
+
+
 @pytest.mark.parametrize("Hq,Hkv,d,dtype,chunk", [(8, 1, 128, "bf16", 512), (7, 1, 64, "bf16", 512), (10, 5, 128, "bf16", 128),
                                                   (9, 9, 64, "bf16", 192), (8, 1, 128, "f32", 64), (3, 1, 64, "f32", 128)])
 def test_fold_of_every_number_of_chunks(dev, Hq, Hkv, d, dtype, chunk):
