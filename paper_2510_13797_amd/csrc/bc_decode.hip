@@ -137,16 +137,16 @@ __global__ __launch_bounds__(256) void sort_by_length_kernel(SortParams p) {
   p.order[rank] = t;
 }
 
-// The kernel arguments span four 64-byte lines that the code below would touch one after the
-// other, each a miss of the scalar cache on the way to the first tile request: ask for all four
-// at once.
+// The kernel arguments span four 64-byte lines, five with AT bytes of table addresses in front, that the code below would touch one
+// after the other, each a miss of the scalar cache on the way to the first tile request: ask for all of them at once.
 template <int AT>
 __device__ __forceinline__ void touch_kernel_arguments() {
   typedef __attribute__((address_space(4))) const int const_int_t;
-  const_int_t* ka = (const_int_t*)__builtin_amdgcn_kernarg_segment_ptr() + AT / 4;
-  static_assert(sizeof(DecodeParams) > 48 * 4, "the last line touched lies inside the arguments");
-  const int a = ka[0], b = ka[16], c = ka[32], d = ka[48];
-  asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d));
+  const_int_t* ka = (const_int_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int kLines = (AT + (int)sizeof(DecodeParams) + 63) / 64;
+  static_assert(AT < 64 && (kLines == 4 || kLines == 5), "a load for every line of the arguments");
+  const int a = ka[AT / 4], b = ka[16], c = ka[32], d = ka[48], e = ka[16 * (kLines - 1)];
+  asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e));
 }
 
 // The kernel arguments, to be read afresh: what only the end of a kernel needs holds no scalar registers before

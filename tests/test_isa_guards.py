@@ -223,6 +223,35 @@ def reads_of_inflight_scalars(body):
     return found
 
 
+def argument_lines_asked_for_late(body):
+    """64-byte lines of the kernel arguments (s[0:1]) whose first load stands behind the first scalar wait: each is a miss of its own in
+    the chain in front of the first tile.  What stands in front of the aligned entry of a kernel with preloaded arguments is for firmware without preloading."""
+    entry = body.index(".p2align\t8") + 1 if ".p2align\t8" in body else 0
+    asked, late, waited = set(), [], False
+    for line in body[entry:]:
+        m = re.match(r"s_load_dword(?:x(\d+))? \S+ s\[0:1\], 0x([0-9a-f]+)$", line)
+        if m:
+            at, size = int(m.group(2), 16), 4 * int(m.group(1) or 1)
+            lines = set(range(at // 64, (at + size - 1) // 64 + 1))
+            late += [(n, line) for n in sorted(lines - asked) if waited]
+            asked |= lines
+        elif line.startswith("s_waitcnt") and "lgkmcnt" in line:
+            waited = True
+        elif re.match(r"s_\w+ (s[01]|s\[\d+:\d+\]),", line) and not line.startswith(("s_cmp", "s_bitcmp")):
+            first = [int(x) for x in re.findall(r"\d+", line.split(",")[0].split()[1])]
+            if first[0] <= 1:                  # the address is gone
+                break
+    return late
+
+
+def test_checker_flags_an_argument_line_behind_the_wait():
+    load = lambda at, n="": "s_load_dword%s s[8:9], s[0:1], 0x%x" % (n, at)
+    assert not argument_lines_asked_for_late([load(0), load(0x40), "s_waitcnt lgkmcnt(0)", load(0x20, "x8"), load(0x7c)])
+    assert argument_lines_asked_for_late([load(0), load(0x40), "s_waitcnt lgkmcnt(0)", load(0x60, "x16")]) == [(2, load(0x60, "x16"))]
+    assert argument_lines_asked_for_late([load(0x80), "s_waitcnt lgkmcnt(0)", ".p2align\t8", load(0), "s_waitcnt lgkmcnt(0)", load(0x80)])
+    assert not argument_lines_asked_for_late([load(0), "s_waitcnt lgkmcnt(0)", "s_add_u32 s0, s0, s2", load(0x80)])
+
+
 def test_checker_flags_a_copy_of_an_inflight_register():
     bad_s = ["s_load_dword s7, s[4:5], 0x0", "s_add_i32 s9, s7, 1", "s_waitcnt lgkmcnt(0)"]
     good_s = ["s_load_dword s7, s[4:5], 0x0", "s_add_i32 s9, s8, 1", "s_waitcnt lgkmcnt(0)",
@@ -370,6 +399,8 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
             one = m.group(1) != "f" and int(m.group(2)) >= 4
             waves = next(int(x.group(1)) for x in (re.match(r"; Occupancy: (\d+)", l) for l in text[e:]) if x)
             assert (waves == 1) if one else (waves >= 2), (text[s][:80], waves)
+        # the arguments' lines travel together
+        assert not argument_lines_asked_for_late(body), (text[s][:80], argument_lines_asked_for_late(body)[:3])
         # the six table entries of the prologue (both kernels)
         assert sum(1 for l in body if re.match(r"s_load_dword(x2)? \S+ s\[(?!0:1)\d+:\d+\], 0x0$", l)) >= 6, text[s][:80]
         assert not reads_of_inflight_scalars(body), (text[s][:80], reads_of_inflight_scalars(body)[:3])
