@@ -196,9 +196,17 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
   pi.s = s;
   pi.kvh = kvh;
   {
-    // (with a dispatch order the sequence is another than the early request took it for)
-    if (early == nullptr || p.order) request_tables(p, pi.s, t);
-    else t = *early;
+    if (early == nullptr) {
+      request_tables(p, pi.s, t);
+    } else if (p.order) {
+      // the sequence is another than the early request took it for, whose entries are on their way all the same: scalar loads return in any
+      // order, and their registers are not free before they have
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : : "s"(early->P), "s"(early->nb), "s"(early->w), "s"(early->cap), "s"(early->base), "s"(early->c) : "memory");
+      request_tables(p, pi.s, t);
+    } else {
+      t = *early;
+    }
     while_tables_travel();
     asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(t.P), "+s"(t.nb), "+s"(t.w), "+s"(t.cap), "+s"(t.base), "+s"(t.c) : : "memory");
     pi.P = t.P; pi.nb = t.nb; w = t.w; pi.cap = t.cap; pi.base = t.base; pi.c = t.c;

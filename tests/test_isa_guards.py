@@ -197,29 +197,36 @@ def reads_of_inflight_registers(body):
 
 def reads_of_inflight_scalars(body):
     """The same for the hand-written scalar table loads (s_load_dword[x2] ..., 0x0 from a pointer other
-    than the kernel-argument segment s[0:1]): reads of their destinations before the next
-    s_waitcnt lgkmcnt(0)."""
-    found, pending = [], set()
-    for line in body:
+    than the kernel-argument segment s[0:1]): instructions that touch their destinations before the next
+    s_waitcnt lgkmcnt(0), and loads into the registers of an earlier one without a wait of the source's own in
+    between (scalar loads return in any order, so that the earlier one may be the last to arrive; a wait that
+    the compiler placed for something else may be gone with its next version)."""
+    found, pending, unwaited = [], set(), set()
+    hand = [l.endswith(HAND) for l in body]
+    body = [l[:-len(HAND)] if l.endswith(HAND) else l for l in body]
+    for line, by_hand in zip(body, hand):
         op = line.split()[0]
-        if pending and "lgkmcnt(0)" in line:
+        if "lgkmcnt(0)" in line:
             pending = set()
+            if by_hand:
+                unwaited = set()
             continue
+        m = re.match(r"s_load_dword(x2)? (?:s(\d+)|s\[(\d+):(\d+)\]), s\[(\d+):\d+\], 0x0$", line)
         if pending and not op.endswith(":") and not op.startswith("."):
-            operands = line[len(op):].split(",")
-            whole = op.startswith(("s_cmp", "s_cbranch", "s_bitcmp", "global_", "ds_write", "v_cmp"))
-            reads = line[len(op):] if whole else ",".join(operands[1:])
-            used = set(int(x) for x in re.findall(r"\bs(\d+)\b", reads))
-            for m in re.finditer(r"s\[(\d+):(\d+)\]", reads):
-                used.update(range(int(m.group(1)), int(m.group(2)) + 1))
+            touched = line[len(op):] if not (m and by_hand) else line.split(",")[1]
+            used = set(int(x) for x in re.findall(r"\bs(\d+)\b", touched))
+            for x in re.finditer(r"s\[(\d+):(\d+)\]", touched):
+                used.update(range(int(x.group(1)), int(x.group(2)) + 1))
             if used & pending:
                 found.append(line)
-        m = re.match(r"s_load_dword(x2)? (?:s(\d+)|s\[(\d+):(\d+)\]), s\[(\d+):\d+\], 0x0$", line)
         if m and m.group(5) != "0":
-            if m.group(2) is not None:
-                pending.add(int(m.group(2)))
-            else:
-                pending.update(range(int(m.group(3)), int(m.group(4)) + 1))
+            first = int(m.group(2) or m.group(3))
+            regs = set(range(first, int(m.group(4) or first) + 1))
+            if by_hand and regs & unwaited:
+                found.append(line)
+            pending |= regs
+            if by_hand:
+                unwaited |= regs
     return found
 
 
@@ -257,6 +264,11 @@ def test_checker_flags_a_copy_of_an_inflight_register():
     good_s = ["s_load_dword s7, s[4:5], 0x0", "s_add_i32 s9, s8, 1", "s_waitcnt lgkmcnt(0)",
               "s_add_i32 s9, s7, 1"]
     assert reads_of_inflight_scalars(bad_s) and not reads_of_inflight_scalars(good_s)
+    assert reads_of_inflight_scalars([bad_s[0], "s_add_i32 s7, s8, 1", bad_s[2]])         # (written while it is out)
+    twice, wait = "s_load_dword s7, s[4:5], 0x0" + HAND, "s_waitcnt lgkmcnt(0)"
+    for between in ([], [wait], ["s_load_dword s9, s[4:5], 0x0" + HAND]):                 # (the compiler's wait is its own business)
+        assert reads_of_inflight_scalars([twice] + between + [twice])
+    assert not reads_of_inflight_scalars([twice, wait + HAND, twice, "s_add_i32 s9, s8, 1"])
     H = lambda lines: [l + HAND if l.startswith(("global_", "landed")) else l for l in lines]
     check = lambda lines: reads_of_inflight_registers(H(lines))
     bad = ["global_load_dwordx4 v[8:11], v[2:3], off", "v_mov_b32_e32 v20, v9", "s_waitcnt vmcnt(0)"]
@@ -403,7 +415,7 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
         assert not argument_lines_asked_for_late(body), (text[s][:80], argument_lines_asked_for_late(body)[:3])
         # the six table entries of the prologue (both kernels)
         assert sum(1 for l in body if re.match(r"s_load_dword(x2)? \S+ s\[(?!0:1)\d+:\d+\], 0x0$", l)) >= 6, text[s][:80]
-        assert not reads_of_inflight_scalars(body), (text[s][:80], reads_of_inflight_scalars(body)[:3])
+        assert not reads_of_inflight_scalars(marked), (text[s][:80], reads_of_inflight_scalars(marked)[:3])
 
 
 def test_fp32_decode_kernels_leave_the_ticket_alone_until_it_is_there(tmp_path):
