@@ -781,9 +781,15 @@ __device__ __forceinline__ bool decode_lds(const DecodeParams& p, Closing* end) 
       nothing_to_do = true;
     }
   }
+  auto query_landed = [&]() {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) landed(qb[i]);
+    landed(newrow_v);
+  };
   if (nothing_to_do) {
     wait_vmcnt<0>();
     if constexpr (CHUNKS) {
+      query_landed();          // (what is asked for before it is known to be wanted keeps its registers until it is there)
       *end = Closing{pi, nullptr};
       return close_without_chunk<ROWB>(pi, NW);
     }
@@ -826,11 +832,6 @@ __device__ __forceinline__ bool decode_lds(const DecodeParams& p, Closing* end) 
       const int vrow = VRPI * j + r4v;
       *reinterpret_cast<u32x4_t*>(wv + vrow * VROWB + ((posv ^ tile_swz<DV>(vrow)) << 4)) = vreg[j];
     }
-  };
-  auto query_landed = [&]() {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) landed(qb[i]);
-    landed(newrow_v);
   };
   auto k_regs_landed = [&]() {
 #pragma unroll

@@ -52,7 +52,7 @@ def _instructions(lines):
     return out
 
 
-def reads_of_inflight_registers(body):
+def reads_of_inflight_registers(body, by_marks=False):
     """(load line, offending line) pairs: instructions that touch (read or write) a destination
     register of a hand-written vector-memory load (one from an inline-assembly block, which the
     compiler neither sees nor waits for) before the place the source names as the point where the
@@ -69,7 +69,9 @@ def reads_of_inflight_registers(body):
         contradictory ways.
     States that differ are followed separately; every (instruction, state) pair is visited once.
     Whether the count of a partial wait is right is not checked here: that is the kernel's own
-    bookkeeping, which the parity tests exercise."""
+    bookkeeping, which the parity tests exercise.
+    by_marks: landing marks alone count.  A destination that no mark names on some path is free to the compiler
+    from the load on, whatever wait the source has there."""
     n = len(body)
     hand = [l.endswith(HAND) for l in body]
     body = [l[:-len(HAND)] if l.endswith(HAND) else l for l in body]
@@ -94,7 +96,7 @@ def reads_of_inflight_registers(body):
         if op == "s_endpgm":
             return []
         if op == "s_waitcnt":
-            if "vmcnt(0)" in line:
+            if "vmcnt(0)" in line and not by_marks:
                 out_regs = frozenset()
             return [(j, (out_regs, flags, vcc)) for j in nxt]
         if op == "landed":
@@ -275,6 +277,10 @@ def test_checker_flags_a_copy_of_an_inflight_register():
     good = ["global_load_dwordx4 v[8:11], v[2:3], off", "v_mov_b32_e32 v21, v20", "s_waitcnt vmcnt(0)",
             "ds_write_b128 v1, v[8:11]"]
     assert check(bad) and not check(good)
+    # a wait for everything does not keep a register that no mark names behind it
+    unnamed = ["global_load_dwordx4 v[8:11], v[2:3], off", "s_waitcnt vmcnt(0)", "v_mov_b32_e32 v9, v20"]
+    assert not check(unnamed) and reads_of_inflight_registers(H(unnamed), by_marks=True)
+    assert not reads_of_inflight_registers(H(unnamed[:2] + ["landed v[8:11]", unnamed[2]]), by_marks=True)
     assert not reads_of_inflight_registers(bad)          # a load the compiler knows about is its business
     # a partial wait covers what the landing marks behind it name, nothing else
     partial = ["global_load_dwordx4 v[8:11], v[2:3], off", "global_load_lds_dwordx4 v[4:5], off",
@@ -404,7 +410,7 @@ def test_decode_kernel_never_reads_a_register_whose_load_is_in_flight(tmp_path):
             for i in marks:
                 back = [l for l in body[max(0, i - 40):i] if not l.startswith("landed ")]
                 assert any(l.startswith("s_waitcnt vmcnt(") for l in back[-24:]), (text[s][:80], body[i])
-            assert not reads_of_inflight_registers(marked), (text[s][:80], reads_of_inflight_registers(marked)[:3])
+            assert not reads_of_inflight_registers(marked, by_marks=True), (text[s][:80], reads_of_inflight_registers(marked, by_marks=True)[:3])
         if "decode_valu_kernel" in text[s]:
             # the plan takes two workgroups of four waves per compute unit, one of the widest groups of bf16 rows
             m = re.search(r"decode_valu_kernelI(f|NS_6bf16_tE)Li\d+ELi(\d)E", text[s])
