@@ -6,7 +6,9 @@ Two layers, both argument marshalling only:
   * `Runtime`, which owns the torch tensors (slabs, tables, workspace) a cache needs
     and passes their addresses and torch's current stream to those functions.
 Every step of the path runs in the library's kernels; there is no fallback: loading
-fails loudly when libbc.so is missing.
+fails loudly when libbc.so is missing.  (Of the way to the library there is one: where
+the module of csrc/bc_call.cpp has not been built for this interpreter, the decode
+step's call goes through ctypes like all others.)
 """
 from __future__ import annotations
 
@@ -61,7 +63,7 @@ class BcError(RuntimeError):
 
 
 _lib = None
-_call = None                  # the function of csrc/bc_call.cpp, with
+_call = None                  # the function of csrc/bc_call.cpp (None where there is no such module), with
 _call_lib = None              # the library whose entry point it calls, and
 _decode_step_at = None        # its address there
 
@@ -73,10 +75,6 @@ def load():
         return _lib
     if not os.path.exists(LIB_PATH):
         raise BcError("libbc.so not built: run `python __graft_entry__.py` (hipcc, gfx950) first")
-    try:
-        from . import _bc_call
-    except ImportError as e:
-        raise BcError("_bc_call not built: run `python __graft_entry__.py` first (%s)" % e)
     lib = C.CDLL(LIB_PATH)
     for name in EXPORTS:
         if not hasattr(lib, name):
@@ -136,9 +134,14 @@ def load():
     lib.bc_topk_kl_loss_bwd.argtypes = [i64, i32, i32, vp, i32, vp, vp, vp, C.c_float, vp, vp]
     lib.bc_tables_to_host.restype = i32
     lib.bc_tables_to_host.argtypes = [sp, cp, vp, vp, vp, vp]
-    _call = _bc_call.decode_step
-    _decode_step_at = C.cast(lib.bc_decode_step, C.c_void_p).value
-    _lib = _call_lib = lib
+    _call = _call_lib = _decode_step_at = None
+    try:
+        from . import _bc_call
+    except ImportError:       # not built, or for another interpreter
+        pass
+    else:
+        _call, _call_lib, _decode_step_at = _bc_call.decode_step, lib, C.cast(lib.bc_decode_step, C.c_void_p).value
+    _lib = lib
     return lib
 
 
@@ -515,7 +518,7 @@ class Runtime:
         if lib is _call_lib:
             # (the conversions of a ctypes call of twelve arguments, eight of them data_ptr(): 2.1 us, so 0.9)
             st = _call(_decode_step_at, self.shape, self.cache, k, v, q, out, bk, bv, active, self.ws, self.ws_bytes, _stream_ptr())
-        else:                 # another library in its place
+        else:                 # no such module, or another library in its place
             st = lib.bc_decode_step(C.byref(self.shape), C.byref(self.cache), _ptr(k), _ptr(v), _ptr(q), _ptr(out), _ptr(bk), _ptr(bv),
                                     _ptr(active), _ptr(self.ws), self.ws_bytes, _stream_ptr())
         if st != BC_OK:
