@@ -1018,6 +1018,15 @@ __device__ __forceinline__ bool decode_lds(const DecodeParams& p, Closing* end) 
     if (wave >= ntiles) {
       wait_vmcnt<0>();          // the query loads, before their registers are reused
       query_landed();
+      if constexpr (CHUNKS) {
+        // One more round trip: where the query was asked for in front of the tables, the tickets of these waves came together with those of the
+        // workgroups without rows, and the waves with rows queued up behind them on the counter (steps of one sequence under a capacity of 1100 rows, with
+        // the query behind the tables, in front of them, and so: 130 rows, 32/8 heads, d = 64, 6.0, 6.9, 6.0 us; 100 rows, 64/16 heads, d = 128,
+        // 8.0, 9.1, 8.2; 60 rows, 32/8 heads, d = 128, 7.0, 6.25, 6.35; 1551 rows, cut, 9.3, 9.2, 9.3).
+        request_new_row(slot);
+        wait_vmcnt<0>();
+        landed(newrow_v);
+      }
       take_ticket();
     } else {
       for (int tile = wave;; tile += NW) {
