@@ -363,6 +363,10 @@ def test_prefill_kernels_set_m0_in_front_of_every_load_to_lds(name, kernels, tmp
             body = [l[:-len(HAND)] if l.endswith(HAND) else l for l in marked]
             # a tile of K (Q) and of V (dO) at least, from each of the places that ask for one
             assert check_m0(body) >= 4, text[s][:80]
+            # loops start where they are told to, not where the code in front of them happens to end
+            if name == "bc_prefill.hip":
+                loops = sum("Loop Header" in l for l in text[s:e])
+                assert loops >= 8 and sum(l.strip() == ".p2align\t4" for l in text[s:e]) >= loops // 2, text[s][:80]
             # no hand-written load has a destination register, and nothing of the tile loop lives in scratch
             assert all("load_lds" in l for l in marked if l.endswith(HAND) and l.startswith("global_load")), text[s][:80]
             assert not any(l.startswith(("scratch_", "buffer_")) for l in body), text[s][:80]
