@@ -1608,10 +1608,28 @@ struct DecodePlan {
 static int padded_group(int g) { return g <= 1 ? 1 : g <= 2 ? 2 : g <= 4 ? 4 : g <= 6 ? 6 : 8; }
 
 // see make_plan
-constexpr int kSplitMinCap = 960, kSplitMinCapSome = 2 * kLdsWavesSplit * kTileRows + 1, kSplitMinRows = 320, kSplitMinRows64 = 384, kSplitMinRowsMany = 512;
+constexpr int kSplitMinCap = 960, kSplitMinCapSome = 2 * kLdsWavesSplit * kTileRows + 1, kSplitMinCapSome64 = 912;
+constexpr int kSplitMinRows = 320, kSplitMinRows64 = 384, kSplitMinRowsMany = 512;
 constexpr int kSplitAlone = 512, kSplitAlone64 = 832;
 constexpr int kFewPairs = 32, kFewPairsLong = 64;
 static int few_pairs(int d, int max_cap) { return d == 128 && max_cap >= 1024 ? kFewPairsLong : kFewPairs; }
+// Capacity from which on a step's plan has chunks.  us a step, whole / cut, of sequences as long as the capacity lets them be ("r": ragged, from 60 rows on).
+// Fewer than 16 pairs, d = 128: 8 pairs (32/8 heads) of 600 rows 7.4 / 8.2, 750 8.1 / 8.5, 900 9.1 / 8.9, 14 (12/2) 8.0 / 8.1, 8.9 / 8.4, 10.1 / 8.6; d = 64: 6.6 / 7.5, 7.4 / 7.7,
+// 8.1 / 8.1 and 6.8 / 7.4, 7.5 / 7.5, 8.5 / 7.6.  (Few KV heads a sequence would be better off cut from 750 or 900 rows on.)
+// More than 48, d = 128: 64 of 700 11.1 / 11.4, of 930 13.2 / 12.6, r 12.2 / 10.8, 120 12.1 / 14.5, 15.5 / 17.0, r 13.3 / 14.0; d = 64: 64 8.9 / 8.6, 10.1 / 9.3, r 9.5 / 8.4, 120 9.4 /
+// 10.1, 10.7 / 11.0, r 9.9 / 9.4.  (Up to 64 pairs would be better off cut from 930 rows on, with d = 64 from 700.)
+// In between, d = 128: up to the rows that two tiles of each of twelve waves hold (24 of 780 11.0 / 8.9, of 930 12.3 / 9.2, r 11.8 / 8.5; 48 11.5 / 11.6, 12.8 / 12.0, r 12.0 / 10.9; 16 as
+// two sequences of eight heads 9.4 / 9.05, 10.0 / 9.4, as one of 16 9.98 / 10.10, 10.76 / 10.51).
+// d = 64: there up to 32 pairs of few KV heads a sequence (16 of 790 7.6 / 7.4, 24 7.9 / 7.6, 32 of four heads 7.9 / 7.8; three sequences of six 7.7 / 7.8, of eight 7.9 / 8.0, two of
+// eight 7.55 / 8.0: all chunks of a sequence are counted on one line of memory), and 48 (9.4 / 8.4: whole, they read past the caches, see kStreamMinWorkgroups).  The others up to the 28 tiles
+// with which a wave's fourth begins (40 of 790 8.05 / 8.25, 890 8.0 / 8.25, 905 8.8 / 8.3; two sequences of eight heads 7.6 / 8.1, 8.45 / 8.2 at 905), and 960 where a sequence has more KV
+// heads than twelve (16 in one sequence 7.6 / 9.3, at 935 8.5 / 9.5, in two 7.9 / 8.9 and 8.8 / 9.0; 32 in one 8.8 / 10.2, 9.9 / 10.4).
+static int split_capacity(const bc_shape* sh) {
+  const long npairs = (long)sh->B * sh->Hkv;
+  if (npairs < 16 || npairs > 48) return kSplitMinCap;
+  if (sh->d == 128 || npairs >= kStreamMinWorkgroups || (npairs <= 32 && sh->Hkv <= 5)) return kSplitMinCapSome;
+  return sh->Hkv <= 12 ? kSplitMinCapSome64 : kSplitMinCap;
+}
 constexpr long kMostChunks = 64;
 constexpr int kChunkRowsMax = 512;    // rows a chunk of the matrix kernel need not go beyond: two passes of eight waves
 constexpr int kPlanForSizing = -1;    // rows_override value: size the workspace (see below)
@@ -1688,7 +1706,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
   pl.chunk_rows = pl.lds ? std::min(kChunkRowsMax, std::max(2 * kTileRows, (max_cap + 15) / 16)) : pl.rows_per_pass;
   pl.split_rows = kSplitMinRows;
   // capacity from which on the plan has chunks at all
-  int split_cap = !alone && npairs >= 16 && npairs <= 48 ? kSplitMinCapSome : kSplitMinCap;
+  int split_cap = alone ? kSplitMinCap : split_capacity(sh);
   if (!pl.lds) {
     // (a step reads its appended row behind the passes over the slab's)
     const int whole_passes = (npairs > kFewPairs || pl.Gp * sh->d >= 512 ? 1 : 2) + (alone ? 1 : 0);
@@ -1715,10 +1733,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // beyond that a sequence has three chunks or two, of which a ragged batch's longest are too long (72 pairs of 100 to 2000 12.4 / 14.2; 96 15.5 / 17.2;
     // of equal length, 1700 rows, 15.8 / 15.1 and 20.9 / 19.7).  With less than 1024 rows of capacity the line is at 32 pairs, where it used to be for all (40
     // pairs of 60 to 980 9.4 / 7.9: they would gain too).  At d = 64 512 is the line from 33 pairs on (90 of up to 1900 rows 10.2, with 256 10.7).
-    // Up to 960 rows of capacity the whole-sequence forms of the matrix kernel are as fast or faster with few pairs (8 pairs, whole / cut: 600 rows 6.2 / 6.9,
-    // 750 7.2 / 7.1, 900 7.7 / 7.0) and with more than 48 (d = 128, 60 of 800 rows 9.7 / 10.5, 80 of 900 11.2 / 12.4; d = 64, 64 of 700 7.6 / 7.2); in between up to
-    // the rows that two tiles of each of twelve waves hold (16 pairs of 500 rows 5.9 / 6.7, 750 7.6 / 7.0, of 60 to 800 7.6 / 6.8; 32 of 750 8.9 / 7.8; 48 of 60 to 800
-    // 10.1 / 7.8, of 800 9.3 / 9.2).  Where the batch may have longer sequences the shorter ones run in the tile loop, and are cut from 320 rows on (whole, cut: 48 pairs of 400 rows,
+    // Up to split_capacity() rows of capacity all sequences stay whole.  Where the batch may have longer sequences the shorter ones run in the tile loop, and are cut from 320 rows on (whole, cut: 48 pairs of 400 rows,
     // capacity 1600, 9.8 / 7.9; 64 of 400, capacity 1150, 9.1 / 7.8), with d = 64 from 384 (32 pairs of 340 6.1 / 6.2, 40 of 60 to 700 from 512, 384 and 320 rows on 6.9, 6.8
     // and 6.9), with more than 64 pairs from 512 where d is 64 (90 ragged ones, 16 layers, from 512 149, from 384 152, from 320 154) or there are four
     // chunks at most (120 pairs of 60 to 1500 rows, from 512 15.9, from 320 16.3); attention alone, which pays for its counters besides, cuts them later.

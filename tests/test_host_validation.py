@@ -287,6 +287,18 @@ def test_batches_that_share_a_workspace_keep_their_counters(Hq, Hkv, d, dtype):
             assert not part or 128 * B2 <= (max(bytes1, bytes2) - part) // 256 * 256, (B1, B2)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,line", [
+    (15, 4, 1, 128, 960), (16, 4, 1, 128, 769), (1, 64, 16, 128, 769), (40, 4, 1, 128, 769), (24, 12, 2, 128, 769), (49, 4, 1, 128, 960),
+    (15, 4, 1, 64, 960), (16, 4, 1, 64, 769), (4, 16, 4, 64, 769), (5, 20, 5, 64, 769), (32, 4, 1, 64, 769), (8, 16, 4, 64, 769), (48, 4, 1, 64, 769), (6, 32, 8, 64, 769),
+    (3, 24, 6, 64, 912), (2, 32, 8, 64, 912), (4, 32, 8, 64, 912), (33, 4, 1, 64, 912), (20, 8, 2, 64, 912), (47, 4, 1, 64, 912), (4, 40, 10, 64, 912),
+    (1, 64, 16, 64, 960), (2, 64, 16, 64, 960), (1, 128, 32, 64, 960), (49, 4, 1, 64, 960)])
+def test_bf16_plans_have_chunks_from_their_line_on(B, Hq, Hkv, d, line):
+    # line: capacity from which on a step's plan has chunks.  d = 64: as before the cut came to be worth it only where few heads count on one line of memory
+    for cap, cut in ((line - 1, False), (line, True), (20000, True)):
+        st, text = bc.bc_decode_plan_describe(shape(B=B, Hq=Hq, Hkv=Hkv, d=d, dtype=bc.BC_BF16), cache(max_cap=cap))
+        assert st == 0 and (int(text.split("chunks=")[1].split()[0]) > 1) == cut, (cap, text)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,line", [(2, 8, 1, 128, 130), (1, 4, 1, 64, 258), (32, 4, 1, 64, 258), (33, 2, 1, 128, 130),
                                              (64, 1, 1, 64, 258), (64, 1, 1, 128, 130), (65, 2, 1, 128, 194), (48, 14, 2, 64, 258),
                                              (96, 1, 1, 128, 194), (97, 1, 1, 128, 258), (64, 12, 2, 64, 258), (64, 16, 2, 128, 258),
