@@ -1735,7 +1735,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // pairs of 60 to 980 9.4 / 7.9: they would gain too).  At d = 64 512 is the line from 33 pairs on (90 of up to 1900 rows 10.2, with 256 10.7).
     // Up to split_capacity() rows of capacity all sequences stay whole.  Where the batch may have longer sequences the shorter ones run in the tile loop, and are cut from 320 rows on (whole, cut: 48 pairs of 400 rows,
     // capacity 1600, 9.8 / 7.9; 64 of 400, capacity 1150, 9.1 / 7.8), with d = 64 from 384 (32 pairs of 340 6.1 / 6.2, 40 of 60 to 700 from 512, 384 and 320 rows on 6.9, 6.8
-    // and 6.9), with more than 64 pairs from 512 where d is 64 (90 ragged ones, 16 layers, from 512 149, from 384 152, from 320 154) or there are four
+    // and 6.9; 450 rows, four pairs 7.5 / 7.2, eight in one sequence 7.7 / 7.3) and one and two pairs from 512 (450 rows 6.4 / 6.8, 6.5 / 6.8), with more than 64 pairs from 512 where d is 64 (90 ragged ones, 16 layers, from 512 149, from 384 152, from 320 154) or there are four
     // chunks at most (120 pairs of 60 to 1500 rows, from 512 15.9, from 320 16.3); attention alone, which pays for its counters besides, cuts them later.
     // The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of 1 to 7 us (by group and d), against
     // some 2 us that a fold takes: cut from the second pass on, or from the third where a pass is short and the
@@ -1757,7 +1757,7 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
       if (chunks > by_rows) chunks = by_rows;
       if (chunks > most) chunks = most;
       if (pl.lds && !alone)
-        pl.split_rows = npairs > 64 && (sh->d == 64 || chunks <= 4) ? kSplitMinRowsMany : sh->d == 64 ? kSplitMinRows64 : kSplitMinRows;
+        pl.split_rows = npairs > 64 && (sh->d == 64 || chunks <= 4) ? kSplitMinRowsMany : sh->d == 128 ? kSplitMinRows : npairs <= 2 ? kSplitMinRowsMany : kSplitMinRows64;
       if (pl.lds && alone) pl.split_rows = chunks <= 4 && npairs > 64 ? 2 * kSplitAlone : sh->d == 64 ? kSplitAlone64 : kSplitAlone;
     }
     pl.R = 0;                                        // spread evenly, decided per sequence

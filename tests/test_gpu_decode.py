@@ -1041,6 +1041,15 @@ def test_fold_of_every_number_of_chunks(dev, Hq, Hkv, d, dtype, chunk):
     assert partials_written(rt)
 
 
+@pytest.mark.parametrize("B,Hkv,d,line", [(1, 1, 64, 512), (1, 2, 64, 512), (2, 1, 64, 512), (1, 3, 64, 384), (2, 2, 64, 384), (1, 1, 128, 320), (1, 2, 128, 320)])
+def test_rows_from_which_on_a_step_cuts_a_sequence(dev, B, Hkv, d, line):
+    for rows, cut in ((line - 1, False), (line, True)):
+        wl = W.Workload("line", 127, B, 2 * Hkv, Hkv, d, "bf16", np.full(B, rows - 1, np.int32), np.full(B, 1100 - rows, np.int32), np.full(B, 0, np.int32))
+        rt, oc = make(wl, dev)
+        rollout(wl, rt, oc, 1, (1,), (1,), use_step_call=True)
+        assert partials_written(rt) == cut, rows
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,P", [(3, 6, 2, 128, (507, 509, 1100)), (3, 6, 2, 64, (827, 829, 1100)),
                                           (62, 4, 2, 128, (1019, 1021, 1100, 60))])
 def test_sequences_come_to_their_cut_line(dev, B, Hq, Hkv, d, P):
