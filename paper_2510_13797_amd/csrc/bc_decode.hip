@@ -139,13 +139,14 @@ __global__ __launch_bounds__(256) void sort_by_length_kernel(SortParams p) {
 
 // The kernel arguments span four 64-byte lines, five with AT bytes of table addresses in front, that the code below would touch one
 // after the other, each a miss of the scalar cache on the way to the first tile request: ask for all of them at once.
-template <int AT>
+// LAST: the last line too (kernels that begin with the query's address ask for what it holds anyway; asked for twice, a step is 0.4 % longer).
+template <int AT, bool LAST = true>
 __device__ __forceinline__ void touch_kernel_arguments() {
   typedef __attribute__((address_space(4))) const int const_int_t;
   const_int_t* ka = (const_int_t*)__builtin_amdgcn_kernarg_segment_ptr();
   constexpr int kLines = (AT + (int)sizeof(DecodeParams) + 63) / 64;
   static_assert(AT < 64 && (kLines == 4 || kLines == 5), "a load for every line of the arguments");
-  const int a = ka[AT / 4], b = ka[16], c = ka[32], d = ka[48], e = ka[16 * (kLines - 1)];
+  const int a = ka[AT / 4], b = ka[16], c = ka[32], d = ka[kLines == 5 || LAST ? 48 : 32], e = ka[LAST ? 16 * (kLines - 1) : 32];
   asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e));
 }
 
@@ -654,7 +655,7 @@ __device__ __forceinline__ bool decode_lds(const DecodeParams& p, Closing* end) 
   constexpr int ARGS = CHUNKS ? kTableArguments : 0;      // where they lie
   TableEntries tables;
   if constexpr (CHUNKS) request_tables(p, (int)blockIdx.y, tables);
-  touch_kernel_arguments<ARGS>();
+  touch_kernel_arguments<ARGS, !CHUNKS>();
   // grid: (KV head, slot, chunk from the last or V half), see decode_grid().  VS = 2: the slots are padded so that a pair's two
   // workgroups are 8k apart in dispatch order (workgroups go to the XCDs in turn).
   const int vhalf = VS == 1 ? 0 : (int)blockIdx.z;
