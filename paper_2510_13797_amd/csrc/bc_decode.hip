@@ -1019,7 +1019,7 @@ __device__ __forceinline__ bool decode_lds(const DecodeParams& p, Closing* end) 
     if (wave >= ntiles) {
       wait_vmcnt<0>();          // the query loads, before their registers are reused
       query_landed();
-      if constexpr (CHUNKS) {
+      if (CHUNKS && pi.nchunks == 1) {         // (those of a cut sequence take none)
         // One more round trip: where the query was asked for in front of the tables, the tickets of these waves came together with those of the
         // workgroups without rows, and the waves with rows queued up behind them on the counter (steps of one sequence under a capacity of 1100 rows, with
         // the query behind the tables, in front of them, and so: 130 rows, 32/8 heads, d = 64, 6.0, 6.9, 6.0 us; 100 rows, 64/16 heads, d = 128,
