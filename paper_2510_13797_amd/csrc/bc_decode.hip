@@ -374,9 +374,6 @@ __device__ __forceinline__ void store_part2(float* a, float x, float y) {
   __hip_atomic_store(reinterpret_cast<uint64_t*>(a), (uint64_t)__float_as_uint(y) << 32 | __float_as_uint(x),
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__device__ __forceinline__ float load_part(const float* a) {
-  return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM));
-}
 __device__ __forceinline__ uint64_t load_part2(const float* a) {
   return __hip_atomic_load(reinterpret_cast<const uint64_t*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
