@@ -1,6 +1,6 @@
 // The Python decode step's call of the C ABI, as a CPython function: addresses of tensors and structures to the entry point without a Python
-// frame or a ctypes conversion for each.  A small step is as short as its call (16 steps of two sequences of 55 rows, called one by one: 108 -> 103 us),
-// and its conversions were 2.1 of 6.7 us, now 0.9.  The entry point's address comes with every call: nothing is kept here.
+// frame or a ctypes conversion for each.  What it gives is host time: the conversions were 2.1 us of a call of 6.7, now 0.9.  (A pass of 16 small steps, called one by
+// one, 98 to 109 us, differs from run to run by more than that.)  The entry point's address comes with every call: nothing is kept here.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

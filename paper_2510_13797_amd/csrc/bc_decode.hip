@@ -289,7 +289,7 @@ __device__ __forceinline__ PairInfo pair_info(const DecodeParams& p, int slot, i
 // The beacon entry of KV heads head0 .. head0 + heads - 1 goes to its slot behind the earlier beacons (the evicted
 // window's first row): by threads 0 .. threads - 1, once every reader of these heads' rows is done with them.  Four units
 // a thread are asked for before the first is stored.  FROM_LDS: from the heads' K and V rows as request_beacon left them, one of each at a time (in a loop of its
-// own: a step that evicts is 0.3 to 0.8 % shorter).
+// own, which is shorter code; steps that evict differ by less than their runs do).
 constexpr int kBeaconBytes = 4096;
 template <int ROWB, bool FROM_LDS>
 __device__ __forceinline__ void store_beacon(const DecodeParams& p, const PairInfo& pi, int head0, int heads, int thread,
@@ -1729,11 +1729,13 @@ static DecodePlan make_plan(const bc_shape* sh, int max_cap, int rows_override, 
     // pick_lds_kernel).  At d = 128 eight waves and 256 are faster with up to 64 pairs (us a step, four waves / eight; 48 pairs of 1500 rows 13.3 / 12.2,
     // of 60 to 1500 11.3 / 10.5; 64 of 1500 14.0 / 12.6, of 60 to 1100 10.4 / 9.2, of 60 to 3000 16.8 / 16.0; 64 of 100 to 2000, eight pairs of each length, 11.9 / 12.0),
     // beyond that a sequence has three chunks or two, of which a ragged batch's longest are too long (72 pairs of 100 to 2000 12.4 / 14.2; 96 15.5 / 17.2;
-    // of equal length, 1700 rows, 15.8 / 15.1 and 20.9 / 19.7).  With less than 1024 rows of capacity the line is at 32 pairs, where it used to be for all (40
-    // pairs of 60 to 980 9.4 / 7.9: they would gain too).  At d = 64 512 is the line from 33 pairs on (90 of up to 1900 rows 10.2, with 256 10.7).
+    // of equal length, 1700 rows, 15.8 / 15.1 and 20.9 / 19.7).  Attention alone the same (34 pairs of 1100 rows 12.8 / 11.0, 48 of 60 to 1500 13.6 / 11.8, 64 of 60 to
+    // 3000 19.3 / 18.6).  With less than 1024 rows of capacity the line is still at 32 pairs, where it was for all: nothing measured speaks for that (34 pairs of 780 rows 11.3 / 9.4, 40 of 1000
+    // 11.8 / 10.25, 64 of 60 to 1000 11.0 / 10.2, attention alone on 40 of 1000 12.7 / 11.2), but plans there are known by their number of chunks.  At d = 64 512 is the line from 33 pairs on (90 of up to 1900 rows 10.2, with 256 10.7).
     // Up to split_capacity() rows of capacity all sequences stay whole.  Where the batch may have longer sequences the shorter ones run in the tile loop, and are cut from 320 rows on (whole, cut: 48 pairs of 400 rows,
     // capacity 1600, 9.8 / 7.9; 64 of 400, capacity 1150, 9.1 / 7.8), with d = 64 from 384 (32 pairs of 340 6.1 / 6.2, 40 of 60 to 700 from 512, 384 and 320 rows on 6.9, 6.8
-    // and 6.9; 450 rows, four pairs 7.5 / 7.2, eight in one sequence 7.7 / 7.3) and one and two pairs from 512 (450 rows 6.4 / 6.8, 6.5 / 6.8), with more than 64 pairs from 512 where d is 64 (90 ragged ones, 16 layers, from 512 149, from 384 152, from 320 154) or there are four
+    // and 6.9; 450 rows, four pairs 7.5 / 7.2, eight in one sequence 7.7 / 7.3) and one and two pairs from 512 (450 rows 6.4 / 6.8, 6.5 / 6.8), with more than 64 pairs from 512 where d is 64 (from 512, from 384: 126 pairs
+    // of 400 to 505 rows 8.9 / 9.3, 110 8.8 / 9.1, 90 8.5 / 8.65, but 126 of 60 to 600 8.9 / 8.7, 80 of 60 to 600 8.55 / 8.05; 90 ragged ones, 16 layers, 149 / 152) or there are four
     // chunks at most (120 pairs of 60 to 1500 rows, from 512 15.9, from 320 16.3); attention alone, which pays for its counters besides, cuts them later.
     // The plain-ALU kernel is bound by its arithmetic, 64 or 128 rows a pass of 1 to 7 us (by group and d), against
     // some 2 us that a fold takes: cut from the second pass on, or from the third where a pass is short and the

@@ -112,7 +112,8 @@ BC_HOST_DEVICE int most_parts(int splits) { return splits == kMostSplits ? kMost
 // most 8, 10, 12, 14 and 16 parts; of 234 others, the gradients of which take 0.68 to 1.10 of the time with at most eight
 // (mean 0.964).  By parts of eight tiles and 18 MB together, which is what one batch had said, it was 0.69 to 1.20 (0.987): ten of 450 to 1153 rows,
 // 4/1 heads, d = 64, 49.4 us with eight, 50.0 now, 52.6 so; one of 1229, 24/8 heads, 50.5, 50.4 and 57.1.  (The root and the quotient exactly, in front of
-// every workgroup's first load: 0.2 us of a small pass.)
+// every workgroup's first load: 0.2 us of a small pass.  All of this with sums that cost some twice what they do now on small launches: a part more may pay there
+// where it does not get one.)
 constexpr float kSumBytes = 0.5e6f;
 inline int least_tiles(int g, int band) { return 3 * ((g + band - 1) / band) > 8 ? 3 * ((g + band - 1) / band) : 8; }
 BC_HOST_DEVICE float approximate_root(float a, float b) {        // of a / b
@@ -163,17 +164,19 @@ inline int reduce_blocks(int B) { return B <= 4 ? 1024 : B >= 32 ? 128 : 4096 / 
 // the compute units, and for four pairs and fewer, whose dkv kernel does not fill the chip either, no more than run at once.  Otherwise the
 // chip has work for one kernel after the other, with three dkv workgroups a compute unit in place of two (d = 64: four, three) and none
 // for Delta.  712 batches in one launch, most of them of one or two long trajectories beside short ones (which the mean does not tell), take 0.73
-// of the time of the gradients before there was one, the worst 1.04.  Forward and gradients, us a pass, in two launches and in one, ratio 16, 4, 0 (those rows of a ratio that lie on the other side of the line in brackets):
+// of the time of the gradients before there was one, the worst 1.04.  Forward and gradients, us a pass behind other work, in two launches and in one, ratio 16, 4, 0 (those rows of a ratio
+// that lie on the other side of the line in brackets).  The line was drawn for a joined kernel that was 2 to 6 % slower: from 240 to 290 workgroups of 12/2 heads some
+// would gain up to 11 % beyond it, others (32/8 heads, 480 workgroups) lose 2 to 4 %.
 //   trajectories x tokens, heads   dq workgroups
-//   1 x 500, 12/2                     54, 60,  48    49.1 41.0 | 53.4  43.3 |  67.0  53.0
-//   1 x 500, 8/8                      40, 40,  32    46.2 39.2 | 51.2  39.4 |  62.8  45.2
-//   1 x 1000, 14/2, d = 64           136,156, 128    47.1 41.3 | 56.2  48.0 |  89.7  69.2
-//   6 x 384, 12/2                    252,288, 216    50.9 50.8 |(56.6  60.6)|  65.2  58.2
-//   4 x 600, 12/2                    240,288, 240    54.5 54.5 |(64.9  64.3)|  81.6  71.0
-//   2 x 500, 32/8                    272,304, 256   (54.7 57.1)|(67.0  68.3)|  83.8  78.0
-//   8 x 500, 12/2                    432,480, 384   (69.3 75.2)|(76.7  83.1)| (89.7  87.5)
-//   1 x 4000, 12/2 (two pairs)       402,468, 378     119  109 |  224   205 |   420   379
-//   2 x 2000, 12/2 (four)            408,468, 384    89.1 83.8 |  140   135 |   232   209
+//   1 x 500, 12/2                     54, 60,  48    44.9 37.7 | 52.3  41.6 |  71.4  57.1
+//   1 x 500, 8/8                      40, 40,  32    46.3 36.6 | 51.4  38.7 |  71.2  51.3
+//   1 x 1000, 14/2, d = 64           136,156, 128    43.1 39.5 | 53.5  46.8 |  95.0  76.7
+//   6 x 384, 12/2                    252,288, 216    51.9 50.8 |(60.5  57.4)|  72.3  65.1
+//   4 x 600, 12/2                    240,288, 240    55.6 53.8 |(69.3  61.7)|  90.0  80.4
+//   2 x 500, 32/8                    272,304, 256   (51.0 52.7)|(62.4  61.3)|  85.1  79.1
+//   8 x 500, 12/2                    432,480, 384   (62.6 64.0)|(78.2  81.6)| (95.2  94.6)
+//   1 x 4000, 12/2 (two pairs)       402,468, 378     110  102 |  174   167 |   453   404
+//   2 x 2000, 12/2 (four)            408,468, 384    84.2 77.8 |  127   128 |   248   220
 inline bool in_one_launch(int B, int npairs, const HeadTiling& tiling, int64_t total_rows) {
   const int64_t rows = kTileRows * tiling.row_blocks * (int64_t)B;
   const int64_t blocks = (total_rows + rows - 1) / rows * npairs * tiling.splits;
