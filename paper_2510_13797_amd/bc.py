@@ -134,13 +134,15 @@ def load():
     lib.bc_topk_kl_loss_bwd.argtypes = [i64, i32, i32, vp, i32, vp, vp, vp, C.c_float, vp, vp]
     lib.bc_tables_to_host.restype = i32
     lib.bc_tables_to_host.argtypes = [sp, cp, vp, vp, vp, vp]
-    _call = _call_lib = _decode_step_at = None
+    call = at = None
     try:
         from . import _bc_call
     except ImportError:       # not built, or for another interpreter
         pass
     else:
-        _call, _call_lib, _decode_step_at = _bc_call.decode_step, lib, C.cast(lib.bc_decode_step, C.c_void_p).value
+        call, at = _bc_call.decode_step, C.cast(lib.bc_decode_step, C.c_void_p).value
+    # (another thread may be in a step already: nothing it uses is taken away)
+    _call, _decode_step_at, _call_lib = call, at, lib if call else None
     _lib = lib
     return lib
 
